@@ -178,6 +178,27 @@ sivf_status check_csr_args(sivf_ctx* ctx, const sivf_csr* X, const char* what) {
     return SIVF_OK;
 }
 
+// Run the device check on M and report what it found; *nonneg = no value is
+// negative.  Waits for the stream.
+sivf_status check_csr(sivf_ctx* ctx, const sivf_csr* M, const char* what, unsigned long long* flags, int* nonneg) {
+    const int f64 = M->val_dtype == SIVF_F64;
+    HIPCHK(ctx, validate_csr(M->row_ptr, M->col, M->val, f64, M->n_rows, M->n_cols, M->nnz, flags, ctx->stream));
+    unsigned long long h[4];
+    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    *nonneg = h[2] ? 0 : 1;
+    if (h[0] == 0 && h[3] == 0) return SIVF_OK;
+    HIPCHK(ctx, validate_csr_rows(M->row_ptr, M->col, M->val, f64, M->n_rows, M->n_cols, M->nnz, flags, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    const unsigned long long row = ~h[1];
+    if (h[0] & 1ull) return fail(ctx, SIVF_E_UNSORTED, "%s: row %llu has unsorted/duplicate columns or a decreasing row_ptr", what, row);
+    if (h[0] & 8ull) return fail(ctx, SIVF_E_UNSORTED, "%s: row_ptr[0] != 0 or row_ptr[n] != nnz", what);
+    if (h[0] & 2ull) return fail(ctx, SIVF_E_RANGE, "%s: row %llu has a column outside [0, %lld)", what, row, (long long)M->n_cols);
+    if (h[0] & 4ull) return fail(ctx, SIVF_E_NONFINITE, "%s: row %llu has a non-finite value", what, row);
+    return fail(ctx, SIVF_E_UNSORTED, "%s changed while it was being checked", what);
+}
+
 // Validate X on the device on every call that reads it.  Nothing is cached:
 // X may be edited in place between calls (same pointers, new contents), and
 // both the column range (used as an index by the walk) and the sign of the
@@ -185,33 +206,24 @@ sivf_status check_csr_args(sivf_ctx* ctx, const sivf_csr* X, const char* what) {
 // contents the kernels will read.  One coalesced pass over the nonzeros.
 sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, Work& w) {
     STCHK(check_csr_args(ctx, X, "X"));
-    const int f64 = X->val_dtype == SIVF_F64;
     unsigned long long* flags = nullptr;
     STCHK(w.get("vflags", 4, &flags));
-    unsigned long long init[3] = {0ull, ~0ull, 0ull};
-    HIPCHK(ctx, hipMemcpyAsync(flags, init, sizeof(init), hipMemcpyHostToDevice, ctx->stream));
-    if (X->n_rows > 0)
-        HIPCHK(ctx, validate_csr(X->row_ptr, X->col, X->val, f64, X->n_rows, X->n_cols, X->nnz, flags, ctx->stream));
-    unsigned long long h[3];
-    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     if (X->n_rows == 0) {
         int64_t rp0 = 0;
-        HIPCHK(ctx, hipMemcpy(&rp0, X->row_ptr, sizeof(int64_t), hipMemcpyDeviceToHost));
+        HIPCHK(ctx, hipMemcpyAsync(&rp0, X->row_ptr, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
         if (rp0 != 0 || X->nnz != 0) return fail(ctx, SIVF_E_UNSORTED, "X: empty matrix with row_ptr[0] != 0 or nnz != 0");
     }
-    if (h[0] & 1ull) return fail(ctx, SIVF_E_UNSORTED, "X: row %llu has unsorted/duplicate columns or a decreasing row_ptr", h[1]);
-    if (h[0] & 8ull) return fail(ctx, SIVF_E_UNSORTED, "X: row_ptr[0] != 0 or row_ptr[n] != nnz");
-    if (h[0] & 2ull) return fail(ctx, SIVF_E_RANGE, "X: row %llu has a column outside [0, %lld)", h[1], (long long)X->n_cols);
-    if (h[0] & 4ull) return fail(ctx, SIVF_E_NONFINITE, "X: row %llu has a non-finite value", h[1]);
+    int nonneg = 1;
+    STCHK(check_csr(ctx, X, "X", flags, &nonneg));
     out->n = X->n_rows;
     out->d = X->n_cols;
     out->nnz = X->nnz;
     out->rp = X->row_ptr;
     out->col = X->col;
     out->val = X->val;
-    out->f64 = f64;
-    out->nonneg = h[2] ? 0 : 1;
+    out->f64 = X->val_dtype == SIVF_F64;
+    out->nonneg = nonneg;
     return SIVF_OK;
 }
 
@@ -481,19 +493,12 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
     if (C->n_rows < 1 || C->n_rows > INT32_MAX) return fail(ctx, SIVF_E_SHAPE, "need 1 <= k <= 2^31-1");
     unsigned long long* flags = nullptr;
     STCHK(ws(ctx, "vflags", 4, &flags));
-    unsigned long long init[3] = {0ull, ~0ull, 0ull};
-    HIPCHK(ctx, hipMemcpyAsync(flags, init, sizeof(init), hipMemcpyHostToDevice, ctx->stream));
-    HIPCHK(ctx, validate_csr(C->row_ptr, C->col, C->val, 1, C->n_rows, C->n_cols, C->nnz, flags, ctx->stream));
-    unsigned long long h[3];
-    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    if (h[0] & 9ull) return fail(ctx, SIVF_E_UNSORTED, "centroids: row %llu unsorted or bad row_ptr", h[1]);
-    if (h[0] & 2ull) return fail(ctx, SIVF_E_RANGE, "centroids: column out of range in row %llu", h[1]);
-    if (h[0] & 4ull) return fail(ctx, SIVF_E_NONFINITE, "centroids: non-finite value in row %llu", h[1]);
+    int nonneg = 1;
+    STCHK(check_csr(ctx, C, "centroids", flags, &nonneg));
     const int32_t k = (int32_t)C->n_rows;
     sivf_ivf* f = nullptr;
     STCHK(new_file(ctx, k, C->n_cols, &f));
-    f->nonneg = h[2] ? 0 : 1;
+    f->nonneg = nonneg;
     sivf_status st = store_reserve(ctx, f, &f->cur, C->nnz);
     if (st == SIVF_OK) {
         hipError_t e = csr_to_store(C->row_ptr, C->col, (const double*)C->val, k, f->cur, ctx->stream);

@@ -151,9 +151,13 @@ hipError_t fill_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
 hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
-// validation: flags[0] |= error bits, flags[1] = min bad row, flags[2] = any negative
+// validation: fills flags[0..3] (cleared first): [0] error bits, [2] any
+// negative value, [3] descents inside rows; a matrix is valid iff [0] = [3] = 0
 hipError_t validate_csr(const int64_t* rp, const int32_t* col, const void* val, int f64, int64_t n,
                         int64_t d, int64_t nnz, unsigned long long* flags, hipStream_t s);
+// an invalid matrix again: flags[0] |= error bits by row, flags[1] = ~(smallest bad row)
+hipError_t validate_csr_rows(const int64_t* rp, const int32_t* col, const void* val, int f64, int64_t n,
+                             int64_t d, int64_t nnz, unsigned long long* flags, hipStream_t s);
 
 // flags[0] |= 1 if some a[i] is outside [0, k)
 hipError_t range_check_i32(const int32_t* a, int64_t n, int32_t k, unsigned long long* flags, hipStream_t s);

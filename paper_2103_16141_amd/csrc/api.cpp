@@ -108,6 +108,21 @@ sivf_status ws(sivf_ctx* ctx, const char* name, int64_t elems, T** out) {
     return SIVF_OK;
 }
 
+// The same, cleared when it is allocated (all of it: a later, larger request
+// may fit what was granted).
+template <typename T>
+sivf_status ws_zeroed(sivf_ctx* ctx, const char* name, int64_t elems, T** out) {
+    static_assert(sizeof(T) == 8, "cleared by 8-byte words");
+    auto it = ctx->ws.find(name);
+    void* before = it == ctx->ws.end() ? nullptr : it->second.first;
+    const size_t size = it == ctx->ws.end() ? 0 : it->second.second;
+    STCHK(ws(ctx, name, elems, out));
+    const auto& got = ctx->ws[name];
+    if (got.first != before || got.second != size)
+        HIPCHK(ctx, fill_u64((unsigned long long*)got.first, 0ull, (int64_t)(got.second / 8), ctx->stream));
+    return SIVF_OK;
+}
+
 // Workspace of one call, handed out buffer by buffer: the ctx's grow-only
 // named buffers (kCtx), consecutive 256-byte aligned pieces of a fixed device
 // block that is never allocated or freed here (kFixed), or no memory at all,
@@ -362,7 +377,8 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 
 // Structure f's current centroids by the flags in f->lam (Alg. 5 second half):
 // positions put the moving centroids first, then the file is built by position.
-sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f) {
+// norms: f->cnorm has yet to be computed (the update fills it).
+sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms) {
     const int64_t W64 = ivf_w64(f->k);
     const int64_t nseg2 = f->d * f->T * 2;
     IvfBuildWs w{};
@@ -436,7 +452,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f) {
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
     // norm bounds for the signed-data certificate: needed whenever the X of a
     // later call has a negative value, whatever the centroids' signs
-    HIPCHK(ctx, centroid_norms(f->cur, f->k, f->cnorm, ctx->stream));
+    if (norms) HIPCHK(ctx, centroid_norms(f->cur, f->k, f->cnorm, ctx->stream));
     return SIVF_OK;
 }
 
@@ -476,7 +492,7 @@ sivf_status init_impl(sivf_ctx* ctx, const Csr& Xc, int32_t k, const int32_t* in
         H(gather_rows(Xc, ids, k, f->cur, lens, ctx->stream, 1));
         H(fill_u8(f->lam, 0, k, ctx->stream));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f);
+    if (st == SIVF_OK) st = restructure(ctx, f, true);
     if (st == SIVF_OK) H(hipStreamSynchronize(ctx->stream));
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -507,7 +523,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
                        : fill_u8(f->lam, 0, k, ctx->stream);
         if (e != hipSuccess) st = fail(ctx, SIVF_E_HIP, "HIP error: %s", hipGetErrorString(e));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f);
+    if (st == SIVF_OK) st = restructure(ctx, f, true);
     if (st == SIVF_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, SIVF_E_HIP, "sync failed");
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -703,7 +719,7 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     hipStream_t s = ctx->stream;
     UpdateWs w{};
     w.nblk = std::max<int64_t>(1, (n + kObjBlock - 1) / kObjBlock);
-    w.nslots = ctx->n_cu * 8;
+    w.nslots = upd_fold_groups(ctx->n_cu);
     STCHK(ws(ctx, "u_hist", w.nblk * (int64_t)k, &w.hist));
     STCHK(ws(ctx, "u_ccount", k, &w.ccount));
     STCHK(ws(ctx, "u_cstart", k + 1, &w.cstart));
@@ -711,30 +727,30 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     STCHK(ws(ctx, "u_memnnz", k, &w.memnnz));
     STCHK(ws(ctx, "u_ub", k, &w.ub));
     STCHK(ws(ctx, "u_ubscan", k + 1, &w.ubscan));
-    STCHK(ws(ctx, "u_work", 1, &w.work));
+    STCHK(ws(ctx, "u_work", 3, &w.work));
+    STCHK(ws(ctx, "u_bigslot", k, &w.bigslot));
+    STCHK(ws(ctx, "u_bigc", kFoldBig, &w.bigc));
+    STCHK(ws(ctx, "u_bigr", kFoldBig, &w.bigr));
+    STCHK(ws(ctx, "u_splits", kFoldBig * (kFoldRanges + 1), &w.splits));
+    STCHK(ws(ctx, "u_jobs", kFoldBig * kFoldRanges, &w.jobs));
     STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(std::max<int64_t>(k, f->d * f->T * 2) + 1, n + 1)) + 8,
              &w.scan_ws));
-    {
-        // the dense accumulators must start zeroed; the kernel keeps them zero
-        auto it = ctx->ws.find("u_W");
-        const size_t need = (size_t)w.nslots * (size_t)Xc.d * sizeof(double);
-        bool fresh = it == ctx->ws.end() || it->second.second < need;
-        STCHK(ws(ctx, "u_W", (int64_t)w.nslots * Xc.d, &w.W));
-        if (fresh) HIPCHK(ctx, fill_f64(w.W, 0.0, (int64_t)w.nslots * Xc.d, s));
-    }
+    // the accumulators and their marks start zeroed; the kernel leaves them so
+    STCHK(ws_zeroed(ctx, "u_W", (int64_t)(w.nslots + kFoldBig) * Xc.d, &w.W));
+    STCHK(ws_zeroed(ctx, "u_touched", (int64_t)(w.nslots + kFoldBig) * ((Xc.d + 63) / 64), &w.touched));
     STCHK(check_assign(ctx, assign, n, k, "assign"));
     HIPCHK(ctx, hipEventRecord(ctx->ev[3], s));
     HIPCHK(ctx, upd_sort(assign, n, k, Xc.rp, w, s));
-    HIPCHK(ctx, upd_bounds(k, Xc.d, lambda, 1, f->cur, w, s));
+    HIPCHK(ctx, upd_bounds(k, Xc.d, Xc.nnz, lambda, 1, f->cur, w, s));
     int64_t total = 0;
     HIPCHK(ctx, hipMemcpyAsync(&total, w.ubscan + k, 8, hipMemcpyDeviceToHost, s));
     HIPCHK(ctx, hipStreamSynchronize(s));
     STCHK(store_reserve(ctx, f, &f->nxt, total));
-    HIPCHK(ctx, upd_segsum(Xc, k, lambda, 1, f->cur, f->nxt, w, s));
+    HIPCHK(ctx, upd_means(Xc, k, lambda, 1, f->cur, f->nxt, w, f->cnorm, s));
     std::swap(f->cur, f->nxt);
     HIPCHK(ctx, hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, s));
     f->nonneg = f->nonneg && Xc.nonneg;
-    STCHK(restructure(ctx, f));
+    STCHK(restructure(ctx, f, false));
     HIPCHK(ctx, hipEventRecord(ctx->ev[4], s));
     if (stats_host) {
         HIPCHK(ctx, hipStreamSynchronize(s));

@@ -232,6 +232,10 @@ hipError_t resume_own(const WalkArgs& a, const Store st, const int32_t* assign, 
                       double* own64, int64_t grid_waves, hipStream_t s);
 
 // update
+constexpr int kFoldTile = 4096;     // nonzeros a workgroup sorts and sums at a time
+constexpr int kFoldBigTiles = 8;    // clusters of at least as many tiles are cut into term ranges
+constexpr int kFoldRanges = 32;     // ranges of such a cluster, at most
+constexpr int kFoldBig = 1024;      // such clusters, at most (the others are summed whole)
 struct UpdateWs {
     int64_t* hist;      // [nblk * k] per object-block cluster counts -> offsets
     int64_t* ccount;    // [k] cluster sizes
@@ -240,17 +244,25 @@ struct UpdateWs {
     int64_t* memnnz;    // [k] sum of member row lengths
     int64_t* ub;        // [k] entry bound per cluster
     int64_t* ubscan;    // [k + 1] exclusive scan of ub
-    double* W;          // [nslots * d] dense FP64 accumulators, kept zero between uses
+    double* W;          // [(nslots + kFoldBig) * d] dense FP64 accumulators, kept zero between uses
+    unsigned long long* touched;  // [(nslots + kFoldBig) * ceil(d / 64)] terms of W in use, kept zero between uses
+    int32_t* bigslot;   // [k] number of a cluster cut into ranges, else -1
+    int32_t* bigc;      // [kFoldBig] its cluster
+    int32_t* bigr;      // [kFoldBig] its ranges
+    int32_t* splits;    // [kFoldBig * (kFoldRanges + 1)] their first terms
+    int32_t* jobs;      // [kFoldBig * kFoldRanges] number * kFoldRanges + range
     int64_t* scan_ws;
-    unsigned long long* work; // [1] work counter for seg_sum
-    int nslots;
+    unsigned long long* work; // [3] member sums: next job, clusters cut into ranges, their ranges
+    int nslots;         // workgroups of the member sums
     int64_t nblk;
 };
 constexpr int kObjBlock = 4096;
 hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, UpdateWs w, hipStream_t s);
-hipError_t upd_bounds(int32_t k, int64_t d, const uint8_t* lam, int allow_copy, const Store prev, UpdateWs w,
-                      hipStream_t s);
-hipError_t upd_segsum(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, const Store prev,
-                      Store next, UpdateWs w, hipStream_t s);
+hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
+                      UpdateWs w, hipStream_t s);
+int upd_fold_groups(int n_cu);   // workgroups (and accumulator rows) of the member sums
+// means and norms of every cluster into `next`, norm bounds into cnorm
+hipError_t upd_means(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, const Store prev, Store next,
+                     UpdateWs w, double* cnorm, hipStream_t s);
 
 }  // namespace sivf

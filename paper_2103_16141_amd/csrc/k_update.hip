@@ -5,17 +5,15 @@
 //    blocks, and an in-block bitonic sort of (cluster, local id) keys that
 //    gives each object its rank among same-cluster objects of its block.  The
 //    result lists every cluster's members in ascending object id.
-// 2. One wave per cluster (persistent waves, each with private dense FP64
-//    sums: term ids below kHotTerms in LDS, the rest in a row W of length d
-//    in HBM): w_t = sum of member values in ascending object id (sequential
-//    per term, exactly the reference fold), then in ascending term order
-//    q_t = w_t / |C_j|, s = s + q_t*q_t (sequential), support
-//    = {t : q_t != 0}; u_t = q_t / sqrt(s).  The sums are cleared as they are
-//    read, so they are zero again for the next cluster.  The member chain is
-//    the cost: each member ends with a wait for its stores, so every load is
-//    issued unconditionally and ahead of its use (see member_sums).
-//    Clusters with no members, or with unchanged members (flag 1), keep their
-//    previous centroid bitwise (it would be recomputed to the same bits).
+// 2. One workgroup per cluster sums its members' values term by term in
+//    ascending object id (k_upd_fold: tiles of nonzeros sorted by term in
+//    LDS), q_t = w_t / |C_j|, support = {t : q_t != 0}; then s = s + q_t*q_t
+//    sequentially in ascending term order and u_t = q_t / sqrt(s)
+//    (k_upd_norm).  Clusters with no members, or with unchanged members
+//    (flag 1), keep their previous centroid bitwise (it would be recomputed
+//    to the same bits).
+#include <algorithm>
+
 #include "internal.h"
 #include "wave.h"
 
@@ -111,232 +109,655 @@ hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, U
     return hipGetLastError();
 }
 
-__global__ void k_upd_bounds(int32_t k, int64_t d, const uint8_t* __restrict__ lam, int allow_copy, Store prev,
-                             const int64_t* __restrict__ ccount, const int64_t* __restrict__ memnnz,
-                             int64_t* __restrict__ ub) {
+// Entry bound per cluster, and the plan of the member sums: a cluster of at
+// least kFoldBigTiles tiles that holds more than 1 / kFoldBig of all nonzeros
+// (half a workgroup's share: fewer than kFoldBig clusters can) is cut into
+// term ranges that run side by side: up to kFoldRanges, at least 4 tiles and
+// about 8 nonzeros of a row each.
+__global__ void k_upd_bounds(int32_t k, int64_t d, int64_t nnz_all, const uint8_t* __restrict__ lam, int allow_copy,
+                             Store prev, UpdateWs w) {
     const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (j >= k) return;
-    const bool copy = ccount[j] == 0 || (allow_copy && lam[j]);
-    ub[j] = copy ? prev.nnz[j] : min(d, memnnz[j]);
+    const int64_t cnt = w.ccount[j], nnz = w.memnnz[j];
+    const bool copy = cnt == 0 || (allow_copy && lam[j]);
+    w.ub[j] = copy ? prev.nnz[j] : min(d, nnz);
+    int32_t slot = -1;
+    if (!copy && nnz >= (int64_t)kFoldBigTiles * kFoldTile && nnz > nnz_all / kFoldBig) {
+        const int64_t R = min(min((int64_t)kFoldRanges, nnz / (4 * kFoldTile)), nnz / (8 * cnt));
+        if (R >= 2) {
+            const unsigned long long b = atomicAdd(&w.work[1], 1ull);
+            if (b < (unsigned long long)kFoldBig) {
+                slot = (int32_t)b;
+                w.bigc[slot] = (int32_t)j;
+                w.bigr[slot] = (int32_t)R;
+                const unsigned long long at = atomicAdd(&w.work[2], (unsigned long long)R);
+                for (int r = 0; r < R; ++r) w.jobs[at + r] = slot * kFoldRanges + r;
+            }
+        }
+    }
+    w.bigslot[j] = slot;
 }
 
-hipError_t upd_bounds(int32_t k, int64_t d, const uint8_t* lam, int allow_copy, const Store prev, UpdateWs w,
-                      hipStream_t s) {
-    hipLaunchKernelGGL(k_upd_bounds, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, k, d, lam, allow_copy, prev,
-                       w.ccount, w.memnnz, w.ub);
-    hipError_t e = hipGetLastError();
+hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
+                      UpdateWs w, hipStream_t s) {
+    hipError_t e = fill_u64(w.work, 0ull, 3, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_upd_bounds, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, k, d, nnz, lam, allow_copy,
+                       prev, w);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     return exclusive_scan_i64(w.ub, w.ubscan, k, w.scan_ws, s);
 }
 
-// Sums of term ids below kHotTerms live in LDS (16 KB per wave), the rest in
-// the wave's HBM row: with term ids in decreasing frequency, as in the
-// Zipf-shaped corpora, most member nonzeros then update LDS, and the HBM row
-// takes only the rest.  (Any other term order gives the same sums.)
-constexpr int kHotTerms = 2048;
+// ---------------------------------------------------------------------------
+// Member sums.  The order of the additions is part of the result: w_t adds the
+// members' values in ascending object id.  Only additions to the same term are
+// ordered, so a workgroup takes kFoldTile nonzeros of a cluster's members at a
+// time (in member order), sorts them stably by term in LDS (radix passes of at
+// most 7 bits), and every run of one term is folded by a thread of its own, in
+// member order:
+//   * a cluster of at most kFoldTile nonzeros is done after one tile;
+//   * a longer one carries its sums from tile to tile in a dense FP64 row of
+//     the workgroup (d doubles), one read and one write per term and tile, and
+//     marks the terms it touched in a bitmap; the touched terms are emitted in
+//     ascending order at the end, the row and the bitmap are cleared as read.
+// What bounds it: the sort's LDS passes and their barriers.  Folding member by
+// member (a wave per cluster, each member waiting for the previous one's sums)
+// was bound by that chain, about 7 us a member: N = 1M, k = 1,000, D = 100,000
+// 14.7 -> 3.1 ms; N = 2M, k = 10,000, D = 140,000 19.7 -> 7.5 ms.
+// Cluster sizes are uneven (the largest of these has 14 times the mean), so
+// large clusters are cut into term ranges that run side by side (k_upd_split);
+// whole, the largest one alone held the kernel to 11 ms at N = 1M.
+// 4,096 nonzeros and 512 threads keep two workgroups on a CU (58 KB of LDS each
+// with FP32 values).
+constexpr int kFoldThreads = 512;
+constexpr int kFoldWaves = kFoldThreads / 64;
+constexpr int kFoldPer = kFoldTile / kFoldThreads;   // entries per thread: window i * 8 + wave, 64 wide
+constexpr int kFoldBits = 9;
+constexpr int kFoldBins = 1 << kFoldBits;              // one per thread
+static_assert(kFoldBins == kFoldThreads, "one bin per thread");
 
-// Ascending-term pass over a cluster's dense FP64 sums w: q_t = w_t / |C_j|,
-// s = s + q_t*q_t sequentially in ascending t, support {t : q_t != 0}
-// compacted into next[o ..), then u_t = q_t / sqrt(s).  The sums of four
-// 64-term chunks are loaded together; terms below kHotTerms are read from
-// the wave's LDS sums, the rest from its HBM row; both are zeroed as read.
-__device__ inline void term_pass(double* __restrict__ row, double* hot, int64_t d, int64_t cnt, int64_t o, int64_t j,
-                                 Store& next, int lane) {
-    const double dc = (double)cnt;
-    double ssq = 0.0;
-    int64_t eo = 0;
-    for (int64_t p0 = 0; p0 < d; p0 += 256) {
-        double wq[4];
+template <typename V>
+struct FoldLds {
+    uint32_t key[kFoldTile];         // terms by position (member order)
+    V val[kFoldTile + 4];            // values, by position, then in sorted order
+    uint16_t ia[kFoldTile + 8];      // positions in sorted order, double-buffered
+    uint16_t ib[kFoldTile + 8];
+    uint16_t cnt[kFoldWaves][kFoldBins];
+    uint16_t base[kFoldBins];
+    int64_t rb[kFoldThreads];        // first nonzero of each member of the tile
+    int32_t pre[kFoldThreads + 1];   // its position in the tile
+    int32_t wcnt[kFoldTile / 64];
+    int32_t wsum[kFoldWaves];
+    int64_t job;
+    int32_t nskip;
+};
+
+// exclusive block scan of one value per thread; *total: the sum
+__device__ inline int32_t fold_scan(int32_t v, int32_t* wsum, int32_t* total) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int32_t inc = wave_incl_scan_i32(v);
+    __syncthreads();   // wsum free
+    if (lane == 63) wsum[wid] = inc;
+    __syncthreads();
+    int32_t off = 0, tot = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t p = p0 + u * 64 + lane;
-            const double hv = hot[p < kHotTerms ? p : 0];
-            const double rv = row[p < d ? p : d - 1];
-            wq[u] = p >= d ? 0.0 : p < kHotTerms ? hv : rv;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t p = p0 + u * 64 + lane;
-            const double wv = wq[u];
-            const double qv = wv / dc;
-            const bool nz = qv != 0.0;
-            if (wv != 0.0) {
-                if (p < kHotTerms) hot[p] = 0.0;
-                else row[p] = 0.0;
-            }
-            unsigned long long m = ballot(nz);
-            if (!m) continue;
-            const double sq = qv * qv;
-            const int pos = lanes_below(m);
-            if (nz) {
-                next.term[o + eo + pos] = (int32_t)p;
-                next.val[o + eo + pos] = qv;
-            }
-            eo += __popcll(m);
-            while (m) {
-                const int l = __ffsll((long long)m) - 1;
-                ssq = ssq + bcast_f64(sq, l);
-                m &= m - 1;
-            }
-        }
+    for (int x = 0; x < kFoldWaves; ++x) {
+        const int32_t s = wsum[x];
+        if (x < wid) off += s;
+        tot += s;
     }
-    const double nr = sqrt(ssq);
-    for (int64_t p = lane; p < eo; p += 64) next.val[o + p] = next.val[o + p] / nr;
+    *total = tot;
+    return off + inc - v;
+}
+
+// Positions of the flagged entries among all flagged ones, in entry order:
+// entry (i, thread) is number i * kFoldThreads + threadIdx.x; mask[i] is the
+// wave's flag mask of window i.  base[i] + lanes_below(mask[i]) is the
+// position.  Returns the total.
+__device__ inline int32_t fold_compact(const unsigned long long (&mask)[kFoldPer], int32_t (&base)[kFoldPer],
+                                       int32_t* wcnt) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    __syncthreads();   // wcnt free
     if (lane == 0) {
-        next.start[j] = o;
-        next.nnz[j] = eo;
+#pragma unroll
+        for (int i = 0; i < kFoldPer; ++i) wcnt[i * kFoldWaves + wid] = __popcll(mask[i]);
     }
-    __threadfence_block();
+    __syncthreads();
+    static_assert(kFoldTile / 64 == 64, "one window count per lane");
+    const int32_t c = wcnt[lane];
+    const int32_t inc = wave_incl_scan_i32(c);
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) base[i] = __shfl(inc - c, i * kFoldWaves + wid, 64);
+    return __shfl(inc, 63, 64);
 }
 
-// Row chunks of 64 nonzeros a wave holds in registers per member (rows of up
-// to 256 nonzeros; the rest of a longer row is read chunk by chunk).
-constexpr int kRowPre = 4;
-
-typedef __attribute__((address_space(1))) double gdouble;   // global memory
-
-template <bool F64>
-__device__ inline double xval(const void* x, int64_t p) {
-    return F64 ? ((const double*)x)[p] : (double)((const float*)x)[p];
+// One stable counting pass over `ne` sorted positions: src order (nullptr:
+// identity) by (key >> shift) & mask into dst.
+template <typename V>
+__device__ inline void fold_radix(FoldLds<V>& L, const uint16_t* src, uint16_t* dst, int ne, int shift, int nbits) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const uint32_t dm = (1u << nbits) - 1u;
+    // each wave owns a contiguous part of the order, so ranks are stable
+    const int per = ((ne + kFoldThreads - 1) / kFoldThreads) * 64;
+    const int lo = wid * per, hi = min(ne, lo + per);
+    volatile uint16_t* cnt = L.cnt[wid];
+#pragma unroll
+    for (int b = 0; b < kFoldBins; b += 64) cnt[b + lane] = 0;
+    uint32_t rk[kFoldPer];   // digit << 16 | rank
+    uint16_t id[kFoldPer];
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) {
+        const int s = lo + i * 64 + lane;
+        const bool in = s < hi;
+        const int p = in ? (src ? src[s] : s) : 0;
+        id[i] = (uint16_t)p;
+        rk[i] = ((L.key[p] >> shift) & dm) << 16;
+    }
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) {
+        if (lo + i * 64 >= hi) break;   // wave-uniform
+        const bool in = lo + i * 64 + lane < hi;
+        const uint32_t dg = rk[i] >> 16;
+        unsigned long long m = ballot(in);
+        for (int b = 0; b < nbits; ++b) {
+            const unsigned long long v = ballot((dg >> b) & 1u);
+            m &= ((dg >> b) & 1u) ? v : ~v;
+        }
+        const uint32_t old = in ? cnt[dg] : 0u;
+        const int below = lanes_below(m);
+        rk[i] |= old + (uint32_t)below;
+        __builtin_amdgcn_wave_barrier();
+        if (in && below == 0) cnt[dg] = (uint16_t)(old + (uint32_t)__popcll(m));
+        __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // per digit: exclusive over waves, then over digits
+    uint32_t run = 0;
+#pragma unroll
+    for (int x = 0; x < kFoldWaves; ++x) {
+        const uint32_t c = L.cnt[x][threadIdx.x];
+        L.cnt[x][threadIdx.x] = (uint16_t)run;
+        run += c;
+    }
+    int32_t total;
+    L.base[threadIdx.x] = (uint16_t)fold_scan((int32_t)run, L.wsum, &total);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) {
+        if (lo + i * 64 + lane < hi) {
+            const uint32_t dg = rk[i] >> 16;
+            dst[L.base[dg] + L.cnt[wid][dg] + (rk[i] & 0xffffu)] = id[i];
+        }
+    }
+    __syncthreads();
 }
 
-// Member sums of cluster j (members q0 .. q1-1 of perm), ascending object id:
-// w_t = w_t + v for every nonzero (t, v) of each member row in turn.
-//
-// The sums are a chain: member q's additions must be visible before member
-// q+1's (the same term sits in different lanes of different rows), so each
-// member ends with a wait for its stores.  To keep that wait the only one,
-// every load is unconditional (clamped indices, masked results; a load
-// behind a condition makes the compiler wait for all outstanding loads) and
-// runs ahead of its use: the member id three members ahead, the row bounds
-// two ahead, the nonzeros one ahead, while member q's accumulators are read
-// (all loads before any store: a row's terms are distinct) and written.
-template <bool F64>
-__device__ inline void member_sums(const Csr& X, int64_t q0, int64_t q1, double* __restrict__ W, double* hot,
-                                   const UpdateWs& w, int lane) {
-    const int64_t qlast = q1 - 1;
-    const int64_t plast = X.nnz - 1;   // >= 0: the caller skips a matrix without nonzeros
-    auto perm_at = [&](int64_t q) -> int64_t { return (int64_t)w.perm[q < qlast ? q : qlast]; };
-    // stage state: member id of q+2 (bounds next), bounds of q+1 (row next), row of q
-    int64_t i2 = perm_at(q0 + 2);
-    int64_t b1, e1, b0, e0;
-    {
-        const int64_t i0 = perm_at(q0), i1 = perm_at(q0 + 1);
-        b0 = X.rp[i0];
-        e0 = X.rp[i0 + 1];
-        b1 = X.rp[i1];
-        e1 = X.rp[i1 + 1];
+// first entry in [lo, hi) of an ascending row whose column is >= t
+__device__ inline int64_t row_lower(const int32_t* __restrict__ col, int64_t lo, int64_t hi, int64_t t) {
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (col[mid] < t) lo = mid + 1;
+        else hi = mid;
     }
-    int32_t tc[kRowPre];
-    double vc[kRowPre];
-#pragma unroll
-    for (int c = 0; c < kRowPre; ++c) {
-        const int64_t p = b0 + c * 64 + lane;
-        const int64_t pc = p < plast ? p : plast;
-        const int32_t t = X.col[pc];
-        const double v = xval<F64>(X.val, pc);
-        tc[c] = p < e0 ? t : -1;
-        vc[c] = v;
-    }
-    gdouble* Wg = (gdouble*)W;
-    for (int64_t q = q0; q < q1; ++q) {
-        const bool has1 = q + 1 < q1;
-        // member q's accumulators first (the in-order load counter then lets
-        // the loads below stay in flight while these are awaited)
-        double gv[kRowPre], lv[kRowPre];
-#pragma unroll
-        for (int c = 0; c < kRowPre; ++c) {
-            gv[c] = Wg[tc[c] >= kHotTerms ? tc[c] : 0];
-            lv[c] = hot[tc[c] >= 0 && tc[c] < kHotTerms ? tc[c] : 0];
-        }
-        // member id of q+3, bounds of q+2, nonzeros of q+1
-        const int64_t i3 = perm_at(q + 3);
-        const int64_t b2 = X.rp[i2], e2 = X.rp[i2 + 1];
-        int32_t tn[kRowPre];
-        double vn[kRowPre];
-#pragma unroll
-        for (int c = 0; c < kRowPre; ++c) {
-            const int64_t p = b1 + c * 64 + lane;
-            const int64_t pc = p < plast ? p : plast;
-            const int32_t t = X.col[pc];
-            const double v = xval<F64>(X.val, pc);
-            tn[c] = has1 && p < e1 ? t : -1;
-            vn[c] = v;
-        }
-        // member q: every accumulator was read before any write (a row's
-        // terms are distinct)
-#pragma unroll
-        for (int c = 0; c < kRowPre; ++c) {
-            if (tc[c] >= kHotTerms) Wg[tc[c]] = gv[c] + vc[c];
-            else if (tc[c] >= 0) hot[tc[c]] = lv[c] + vc[c];
-        }
-        for (int64_t p = b0 + kRowPre * 64 + lane; p < e0; p += 64) {   // rows beyond 256 nonzeros
-            const int32_t t = X.col[p];
-            const double v = xval<F64>(X.val, p);
-            if (t >= kHotTerms) Wg[t] = Wg[t] + v;
-            else hot[t] = hot[t] + v;
-        }
-        // this member's sums must be visible to every lane before the next member
-        __threadfence_block();
-#pragma unroll
-        for (int c = 0; c < kRowPre; ++c) {
-            tc[c] = tn[c];
-            vc[c] = vn[c];
-        }
-        b0 = b1;
-        e0 = e1;
-        b1 = b2;
-        e1 = e2;
-        i2 = i3;
-    }
+    return lo;
 }
 
-// Cluster j's mean direction into next[o .. o + support): member sums, then
-// the ascending-term pass.
-__device__ inline void sum_normalize(const Csr& X, int64_t j, int64_t cnt, int64_t o, double* __restrict__ W,
-                                     double* hot, Store& next, const UpdateWs& w, int lane) {
-    const int64_t q0 = w.cstart[j], q1 = q0 + cnt;
-    if (X.nnz > 0) {
-        if (X.f64) member_sums<true>(X, q0, q1, W, hot, w, lane);
-        else member_sums<false>(X, q0, q1, W, hot, w, lane);
+// Stage the next nonzeros of up to kFoldThreads members: thread tid holds
+// member tid's nonzeros [b, b + len) (len 0: none; more than kFoldTile counts
+// as kFoldTile + 1).  Members are taken in order until kFoldTile nonzeros are
+// in; the last one may be taken in part.  Returns the nonzeros staged;
+// *ndone: members taken whole, *part: nonzeros taken of the next one.
+template <typename V, bool VALUES>
+__device__ inline int fold_stage(FoldLds<V>& L, const Csr& X, int64_t b, int32_t len, int* ndone, int* part) {
+    const int tid = threadIdx.x;
+    const V* __restrict__ xv = (const V*)X.val;
+    int32_t total;
+    const int32_t at = fold_scan(len, L.wsum, &total);
+    L.rb[tid] = b;
+    L.pre[tid] = at;
+    if (tid == 0) {
+        L.pre[kFoldThreads] = total;
+        L.nskip = 0;
     }
-    term_pass(W, hot, X.d, cnt, o, j, next, lane);
+    *ndone = __syncthreads_count(at + len <= kFoldTile);   // a prefix of the threads
+    if (tid == *ndone) L.nskip = max(0, kFoldTile - at);
+    const int ne = min(total, kFoldTile);
+    uint32_t t[kFoldPer];
+    V v[kFoldPer];
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) {
+        const int s = i * kFoldThreads + tid;
+        t[i] = 0u;
+        v[i] = (V)0;
+        if (s >= ne) continue;
+        // last member starting at or before s (empty ones before it share its start)
+        int lo = 0;
+#pragma unroll
+        for (int step = kFoldThreads / 2; step > 0; step >>= 1)
+            if (L.pre[lo + step] <= s) lo += step;
+        const int64_t p = L.rb[lo] + (s - L.pre[lo]);
+        t[i] = (uint32_t)X.col[p];
+        if (VALUES) v[i] = xv[p];
+    }
+#pragma unroll
+    for (int i = 0; i < kFoldPer; ++i) {
+        const int s = i * kFoldThreads + tid;
+        L.key[s] = t[i];
+        if (VALUES) L.val[s] = v[i];
+    }
+    __syncthreads();
+    *part = L.nskip;
+    return ne;
 }
 
-__global__ __launch_bounds__(256) void k_upd_segsum(Csr X, int32_t k, const uint8_t* __restrict__ lam, int allow_copy,
-                                                    Store prev, Store next, UpdateWs w) {
-    __shared__ double hot_all[4][kHotTerms];   // 64 KB: the four waves' LDS sums
-    const int lane = threadIdx.x & 63;
-    const int64_t gw = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    if (gw >= w.nslots) return;
-    double* __restrict__ W = w.W + gw * X.d;
-    double* hot = hot_all[threadIdx.x >> 6];
-    for (int i = lane; i < kHotTerms; i += 64) hot[i] = 0.0;   // kept zero by the term pass
-    for (int64_t j = wave_grab(w.work, 1ull); j < k; j = wave_grab(w.work, 1ull)) {
-        const int64_t cnt = w.ccount[j];
-        const int64_t o = w.ubscan[j];
-        if (cnt == 0 || (allow_copy && lam[j])) {
-            const int64_t ps = prev.start[j], m = prev.nnz[j];
-            for (int64_t p = lane; p < m; p += 64) {
-                next.term[o + p] = prev.term[ps + p];
-                next.val[o + p] = prev.val[ps + p];
+// Stable sort of the staged positions by term; returns the sorted order.
+template <typename V>
+__device__ inline const uint16_t* fold_sort(FoldLds<V>& L, int ne, int passes, int nbits) {
+    const uint16_t* cur = nullptr;
+    for (int ps = 0; ps < passes; ++ps) {
+        uint16_t* dst = (ps & 1) ? L.ib : L.ia;
+        fold_radix(L, cur, dst, ne, ps * nbits, nbits);
+        cur = dst;
+    }
+    return cur;
+}
+
+// The touched terms (bits) of the sums W in ascending order: q_t = w_t / dc
+// where not zero into next at o.  W and bits are left zero.  Returns the
+// entries written.  Every mark must be in memory, the whole workgroup calls.
+template <typename V>
+__device__ inline int64_t fold_emit(FoldLds<V>& L, double* W, unsigned long long* bits, int64_t d, double dc,
+                                    const Store& next, int64_t o) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int tid = threadIdx.x;
+    const int64_t nwords = (d + 63) / 64;
+    int64_t eo = 0;
+    for (int64_t wb = 0; wb < nwords; wb += kFoldThreads) {
+        unsigned long long word = 0;
+        if (wb + tid < nwords) word = atomicExch(&bits[wb + tid], 0ull);
+        int32_t total;
+        const int32_t at = fold_scan(__popcll(word), L.wsum, &total);
+        if (total == 0) continue;   // workgroup-uniform
+        // at most kFoldTile terms at a time: all words, or one wave's 64 words
+        const int nsub = total <= kFoldTile ? 1 : kFoldWaves;
+        for (int sub = 0; sub < nsub; ++sub) {
+            int32_t from = 0, n = total;
+            if (nsub > 1) {
+                for (int x = 0; x < sub; ++x) from += L.wsum[x];
+                n = L.wsum[sub];
             }
-            if (lane == 0) {
+            if (nsub == 1 || wid == sub) {
+                int p = at - from;
+                while (word) {
+                    L.key[p++] = (uint32_t)((wb + tid) * 64 + __builtin_ctzll(word));
+                    word &= word - 1;
+                }
+            }
+            __syncthreads();
+            uint32_t t[kFoldPer];
+            double acc[kFoldPer];
+            unsigned long long mask[kFoldPer];
+            int32_t base[kFoldPer];
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                const int e = i * kFoldThreads + tid;
+                t[i] = e < n ? L.key[e] : 0u;
+                acc[i] = e < n ? W[t[i]] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                const bool in = i * kFoldThreads + tid < n;
+                if (in) W[t[i]] = 0.0;
+                acc[i] = acc[i] / dc;
+                mask[i] = ballot(in && acc[i] != 0.0);
+            }
+            const int32_t got = fold_compact(mask, base, L.wcnt);
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                if ((mask[i] >> lane) & 1ull) {
+                    const int64_t to = o + eo + base[i] + lanes_below(mask[i]);
+                    next.term[to] = (int32_t)t[i];
+                    next.val[to] = acc[i];
+                }
+            }
+            eo += got;
+            __syncthreads();
+        }
+    }
+    return eo;
+}
+
+// Term ranges of the large clusters (k_upd_bounds lists them): the quantiles
+// of a sample of at most kFoldTile member nonzeros, so the ranges hold about
+// the same number of nonzeros whatever the terms' frequencies.
+template <typename V>
+__global__ __launch_bounds__(kFoldThreads) void k_upd_split(Csr X, UpdateWs w, int passes, int nbits) {
+    extern __shared__ __align__(16) unsigned char fold_smem[];
+    FoldLds<V>& L = *reinterpret_cast<FoldLds<V>*>(fold_smem);
+    const int tid = threadIdx.x;
+    const int nbig = min((int)w.work[1], kFoldBig);
+    for (int slot = blockIdx.x; slot < nbig; slot += gridDim.x) {
+        const int64_t j = w.bigc[slot], cnt = w.ccount[j];
+        const int R = w.bigr[slot];
+        // evenly spaced members, as many as fill a tile on average
+        const int64_t want = kFoldTile * cnt / max((int64_t)1, w.memnnz[j]);
+        const int nm = (int)max((int64_t)1, min(min((int64_t)kFoldThreads, cnt), want));
+        int64_t b = 0;
+        int32_t len = 0;
+        if (tid < nm) {
+            const int64_t i = w.perm[w.cstart[j] + tid * cnt / nm];
+            b = X.rp[i];
+            len = (int32_t)min((int64_t)kFoldTile + 1, X.rp[i + 1] - b);
+        }
+        int ndone, part;
+        const int ne = fold_stage<V, false>(L, X, b, len, &ndone, &part);
+        const uint16_t* cur = fold_sort(L, ne, passes, nbits);
+        if (tid <= R)
+            w.splits[slot * (kFoldRanges + 1) + tid] =
+                tid == 0 ? 0 : tid == R ? (int32_t)min(X.d, (int64_t)INT32_MAX)
+                                        : (ne ? (int32_t)L.key[cur[(int64_t)ne * tid / R]] : 0);
+        __syncthreads();
+    }
+}
+
+// Sums, means and supports of the recomputed clusters: q_t = w_t / |C_j| for
+// the terms with q_t != 0, ascending, into next at the cluster's offset (not
+// yet normalised; k_upd_norm follows).  Persistent workgroups take the ranges
+// of the large clusters first (their sums stay in the cluster's row for
+// k_upd_emit), then the other clusters whole.
+template <typename V>
+__global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_upd_fold(
+    Csr X, int32_t k, const uint8_t* __restrict__ lam, int allow_copy, Store next, UpdateWs w, int passes, int nbits) {
+    extern __shared__ __align__(16) unsigned char fold_smem[];
+    FoldLds<V>& L = *reinterpret_cast<FoldLds<V>*>(fold_smem);
+    const int lane = threadIdx.x & 63;
+    const int tid = threadIdx.x;
+    const int64_t nwords = (X.d + 63) / 64;
+    const int64_t njobs = min((int64_t)w.work[2], (int64_t)kFoldBig * kFoldRanges);
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) L.job = (int64_t)atomicAdd(w.work, 1ull);
+        __syncthreads();
+        const int64_t job = L.job;
+        if (job >= njobs + k) break;
+        int64_t j = job - njobs, row = blockIdx.x;   // the cluster, its row of sums
+        int64_t t0 = 0, t1 = X.d;                    // its range of terms
+        const bool ranged = job < njobs;
+        if (ranged) {
+            const int32_t code = w.jobs[job];
+            const int slot = code / kFoldRanges, r = code - slot * kFoldRanges;
+            j = w.bigc[slot];
+            row = w.nslots + slot;
+            t0 = w.splits[slot * (kFoldRanges + 1) + r];
+            t1 = w.splits[slot * (kFoldRanges + 1) + r + 1];
+            if (t0 >= t1) continue;
+        } else if (w.bigslot[j] >= 0) {
+            continue;
+        }
+        const int64_t cnt = w.ccount[j];
+        if (cnt == 0 || (allow_copy && lam[j])) continue;
+        double* W = w.W + row * X.d;
+        unsigned long long* bits = w.touched + row * nwords;
+        const double dc = (double)cnt;
+        const int64_t q0 = w.cstart[j], o = w.ubscan[j];
+        const bool single = !ranged && w.memnnz[j] <= kFoldTile && cnt <= kFoldThreads;
+        int64_t m0 = 0, skip = 0;   // next member, nonzeros of it already taken
+        bool first = true;
+        int64_t eo = 0;
+        // the nonzeros [mb, me) of member m0 + tid inside the range
+        int64_t mb = 0, me = 0;
+        auto fetch = [&]() {
+            mb = me = 0;
+            if (m0 + tid < cnt) {
+                const int64_t i = w.perm[q0 + m0 + tid];
+                me = X.rp[i + 1];
+                mb = X.rp[i];
+                if (ranged) {
+                    if (t1 < X.d) me = row_lower(X.col, mb, me, t1);
+                    if (t0 > 0) mb = row_lower(X.col, mb, me, t0);
+                }
+                if (tid == 0) mb += skip;
+            }
+        };
+        fetch();
+        while (m0 < cnt) {
+            int ndone, part;
+            const int ne = fold_stage<V, true>(L, X, mb, (int32_t)min((int64_t)kFoldTile + 1, me - mb), &ndone, &part);
+            // threads past the last member count as done
+            skip = ndone < kFoldThreads ? (ndone == 0 ? skip : 0) + part : 0;
+            m0 += ndone;
+            fetch();   // the next tile's members, ahead of this one's sort
+            if (ne == 0) continue;
+            const uint16_t* cur = fold_sort(L, ne, passes, nbits);
+            uint16_t* hp = cur == L.ia ? L.ib : L.ia;   // first sorted position of each run
+            // ---- runs of one term, their values moved into sorted order
+            unsigned long long mask[kFoldPer];
+            int32_t base[kFoldPer];
+            V sv[kFoldPer];
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                const int s = i * kFoldThreads + tid;
+                bool hd = false;
+                sv[i] = (V)0;
+                if (s < ne) {
+                    const int c = cur[s];
+                    hd = s == 0 || L.key[c] != L.key[cur[s - 1]];
+                    sv[i] = L.val[c];
+                }
+                mask[i] = ballot(hd);
+            }
+            const int nrun = fold_compact(mask, base, L.wcnt);   // its barriers end the reads of val
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                L.val[i * kFoldThreads + tid] = sv[i];
+                if ((mask[i] >> lane) & 1ull) hp[base[i] + lanes_below(mask[i])] = (uint16_t)(i * kFoldThreads + tid);
+            }
+            if (tid == 0) hp[nrun] = (uint16_t)ne;
+            __syncthreads();
+            // ---- fold every run onto the sum carried so far
+            uint32_t t[kFoldPer];
+            double acc[kFoldPer];
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                const int r = i * kFoldThreads + tid;
+                t[i] = r < nrun ? L.key[cur[hp[r]]] : 0u;
+                acc[i] = !first && r < nrun ? W[t[i]] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < kFoldPer; ++i) {
+                const int r = i * kFoldThreads + tid;
+                if (r >= nrun) continue;
+                const bool fresh = acc[i] == 0.0;
+                const int s1 = hp[r + 1];
+                double a = acc[i];
+                for (int s = hp[r]; s < s1; s += 4) {
+                    V x[4];   // reads past the run stay inside the tile's padding
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[u] = L.val[s + u];
+                    a = a + (double)x[0];
+#pragma unroll
+                    for (int u = 1; u < 4; ++u) {
+                        const double n = a + (double)x[u];
+                        a = s + u < s1 ? n : a;
+                    }
+                }
+                acc[i] = a;
+                if (!single) {
+                    W[t[i]] = a;
+                    if (fresh) atomicOr(&bits[t[i] >> 6], 1ull << (t[i] & 63));
+                }
+            }
+            first = false;
+            if (single) {
+                // ---- the only tile: emit from registers
+#pragma unroll
+                for (int i = 0; i < kFoldPer; ++i) {
+                    acc[i] = acc[i] / dc;
+                    mask[i] = ballot(i * kFoldThreads + tid < nrun && acc[i] != 0.0);
+                }
+                eo = fold_compact(mask, base, L.wcnt);
+#pragma unroll
+                for (int i = 0; i < kFoldPer; ++i) {
+                    if ((mask[i] >> lane) & 1ull) {
+                        const int64_t at = o + base[i] + lanes_below(mask[i]);
+                        next.term[at] = (int32_t)t[i];
+                        next.val[at] = acc[i];
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        if (ranged) continue;
+        if (!single) {
+            __threadfence();   // every mark in memory before the words are taken
+            __syncthreads();
+            eo = fold_emit(L, W, bits, X.d, dc, next, o);
+        }
+        if (tid == 0) {
+            next.start[j] = o;
+            next.nnz[j] = eo;
+        }
+    }
+}
+
+// the large clusters' entries, from their rows of sums
+__global__ __launch_bounds__(kFoldThreads) void k_upd_emit(int64_t d, Store next, UpdateWs w) {
+    __shared__ FoldLds<float> L;
+    const int nbig = min((int)w.work[1], kFoldBig);
+    for (int slot = blockIdx.x; slot < nbig; slot += gridDim.x) {
+        const int64_t j = w.bigc[slot], row = w.nslots + slot, o = w.ubscan[j];
+        __syncthreads();
+        const int64_t eo = fold_emit(L, w.W + row * d, w.touched + row * ((d + 63) / 64), d, (double)w.ccount[j], next, o);
+        if (threadIdx.x == 0) {
+            next.start[j] = o;
+            next.nnz[j] = eo;
+        }
+    }
+}
+
+// u_t = q_t / sqrt(s) with s = s + q_t * q_t sequentially in ascending t, or a
+// copy of the previous centroid for unchanged and empty clusters; and the
+// centroid's norm bound (as k_centroid_norms).  One workgroup per cluster: all
+// waves square kNormChunk values into LDS, the first wave folds the previous
+// chunk, every lane reading the same squares (16-byte broadcasts, 16 ahead).
+// Bound: the dependent FP64 additions of the longest centroid.  Against lane
+// reads of the squares out of registers: 0.98 -> 0.61 ms at N = 1M, k = 1,000.
+constexpr int kNormChunk = 1024;
+
+__global__ __launch_bounds__(256) void k_upd_norm(int32_t k, const uint8_t* __restrict__ lam, int allow_copy,
+                                                  Store prev, Store next, UpdateWs w, double* __restrict__ cnorm) {
+    __shared__ alignas(16) double sq[2][kNormChunk];
+    __shared__ double sh_nr;
+    __shared__ double sh_part[4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    for (int64_t j = blockIdx.x; j < k; j += gridDim.x) {
+        const bool copy = w.ccount[j] == 0 || (allow_copy && lam[j]);
+        int64_t o, m;
+        double part = 0.0;
+        if (copy) {
+            const int64_t ps = prev.start[j];
+            o = w.ubscan[j];
+            m = prev.nnz[j];
+            for (int64_t p = threadIdx.x; p < m; p += 256) {
+                const double u = prev.val[ps + p];
+                next.term[o + p] = prev.term[ps + p];
+                next.val[o + p] = u;
+                part = part + u * u;
+            }
+            if (threadIdx.x == 0) {
                 next.start[j] = o;
                 next.nnz[j] = m;
             }
         } else {
-            sum_normalize(X, j, cnt, o, W, hot, next, w, lane);
+            o = next.start[j];
+            m = next.nnz[j];
+            double s = 0.0;
+            int buf = 0;
+            for (int64_t p0 = 0; p0 < m + kNormChunk; p0 += kNormChunk, buf ^= 1) {
+                if (p0 < m) {
+#pragma unroll
+                    for (int u = 0; u < kNormChunk / 256; ++u) {
+                        const int64_t p = p0 + u * 256 + threadIdx.x;
+                        const double v = p < m ? next.val[o + p] : 0.0;   // + 0.0 leaves the sum as it is
+                        sq[buf][u * 256 + threadIdx.x] = v * v;
+                    }
+                }
+                if (wid == 0 && p0 > 0) {
+                    const double2* q = reinterpret_cast<const double2*>(sq[buf ^ 1]);
+                    const int n = (int)min((int64_t)kNormChunk, m - (p0 - kNormChunk));
+                    double2 x[8], y[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = q[u];
+                    for (int b = 0; b < n; b += 32) {
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) y[u] = q[b / 2 + 8 + u];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            s = s + x[u].x;
+                            s = s + x[u].y;
+                        }
+                        const int nb = b + 32 < kNormChunk ? b + 32 : 0;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) x[u] = q[nb / 2 + u];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            s = s + y[u].x;
+                            s = s + y[u].y;
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            if (threadIdx.x == 0) sh_nr = sqrt(s);
+            __syncthreads();
+            const double nr = sh_nr;
+            for (int64_t p = threadIdx.x; p < m; p += 256) {
+                const double u = next.val[o + p] / nr;
+                next.val[o + p] = u;
+                part = part + u * u;
+            }
         }
+        part = wave_sum_f64(part);
+        if (lane == 0) sh_part[wid] = part;
+        __syncthreads();
+        if (threadIdx.x == 0) cnorm[j] = centroid_norm_bound((sh_part[0] + sh_part[1]) + (sh_part[2] + sh_part[3]));
+        __syncthreads();
     }
 }
 
-hipError_t upd_segsum(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, const Store prev, Store next,
-                      UpdateWs w, hipStream_t s) {
-    hipError_t e = fill_u64(w.work, 0ull, 1, s);
+int upd_fold_groups(int n_cu) { return n_cu * 2; }
+
+template <typename V>
+static hipError_t upd_means_t(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, Store next,
+                              const UpdateWs& w, hipStream_t s) {
+    int bits = 1;
+    while (bits < 31 && ((int64_t)1 << bits) < X.d) ++bits;
+    const int passes = (bits + kFoldBits - 1) / kFoldBits, nbits = (bits + passes - 1) / passes;
+    const unsigned groups = (unsigned)w.nslots;
+    const size_t lds = sizeof(FoldLds<V>);
+    if (lds > 65536) {
+        for (const void* fn : {(const void*)k_upd_fold<V>, (const void*)k_upd_split<V>}) {
+            const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (X.nnz >= (int64_t)kFoldBigTiles * kFoldTile)
+        hipLaunchKernelGGL(k_upd_split<V>, dim3(kFoldBig), dim3(kFoldThreads), lds, s, X, w, passes, nbits);
+    hipLaunchKernelGGL(k_upd_fold<V>, dim3(groups), dim3(kFoldThreads), lds, s, X, k, lam, allow_copy, next, w, passes,
+                       nbits);
+    if (X.nnz >= (int64_t)kFoldBigTiles * kFoldTile)
+        hipLaunchKernelGGL(k_upd_emit, dim3(kFoldBig), dim3(kFoldThreads), 0, s, X.d, next, w);
+    return hipGetLastError();
+}
+
+hipError_t upd_means(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, const Store prev, Store next,
+                     UpdateWs w, double* cnorm, hipStream_t s) {
+    hipError_t e = X.f64 ? upd_means_t<double>(X, k, lam, allow_copy, next, w, s)
+                         : upd_means_t<float>(X, k, lam, allow_copy, next, w, s);
     if (e != hipSuccess) return e;
-    const int blocks = (w.nslots + 3) / 4;
-    hipLaunchKernelGGL(k_upd_segsum, dim3(blocks), dim3(256), 0, s, X, k, lam, allow_copy, prev, next, w);
+    hipLaunchKernelGGL(k_upd_norm, dim3((unsigned)std::min<int64_t>(k, 1 << 16)), dim3(256), 0, s, k, lam, allow_copy,
+                       prev, next, w, cnorm);
     return hipGetLastError();
 }
 

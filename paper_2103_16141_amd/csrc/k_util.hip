@@ -426,8 +426,7 @@ hipError_t store_export(const Store st, int32_t k, const int64_t* c_ptr, int32_t
     return hipGetLastError();
 }
 
-// cnorm[j] >= ||mu_j||_2: FP64 sum of squares (relative error <= nnz * 2^-53),
-// square root, then a 2^-30 relative margin.
+// cnorm[j] >= ||mu_j||_2 (the update computes its own while normalising).
 __global__ void k_centroid_norms(Store st, int32_t k, double* __restrict__ cnorm) {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
@@ -440,7 +439,7 @@ __global__ void k_centroid_norms(Store st, int32_t k, double* __restrict__ cnorm
             acc = acc + v * v;
         }
         acc = wave_sum_f64(acc);
-        if (lane == 0) cnorm[j] = sqrt(acc) * (1.0 + 0x1p-30) + 0x1p-1000;
+        if (lane == 0) cnorm[j] = centroid_norm_bound(acc);
     }
 }
 

@@ -85,6 +85,10 @@ __device__ inline int32_t wave_min_i32(int32_t v) {
     return v;
 }
 
+// A bound >= ||mu||_2 from the FP64 sum of squares acc (any order, relative
+// error <= nnz * 2^-53): square root, then a 2^-30 relative margin.
+__device__ inline double centroid_norm_bound(double acc) { return sqrt(acc) * (1.0 + 0x1p-30) + 0x1p-1000; }
+
 // bf16 storage <-> f32: the 16 high bits of an IEEE binary32.
 __device__ __host__ inline float bf16_to_f32(uint16_t b) {
     uint32_t u = (uint32_t)b << 16;

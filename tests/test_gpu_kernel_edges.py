@@ -65,3 +65,66 @@ def test_validation_of_long_and_short_rows_at_window_edges(dtype, shift):
         v[p] = -np.inf if p % 2 else np.nan
         name, msg = check(col, v)
         assert name == "SIVF_E_NONFINITE" and "row %d " % rows[p] in msg, p
+
+
+# ---------------------------------------------------------------- member sums
+def _rows_corpus(lens, d, dtype, seed, signed):
+    """Rows of the given lengths, terms spread over [0, d), unit norm; signed:
+    half the rows are the negated copy of the row before them."""
+    rng = np.random.default_rng(seed)
+    cols, vals = [], []
+    for i, m in enumerate(lens):
+        if signed and i % 2 and m == lens[i - 1]:
+            cols.append(cols[-1])
+            vals.append(-vals[-1])
+            continue
+        cols.append(np.sort(rng.choice(d, m, replace=False)).astype(np.int32))
+        v = np.exp(rng.standard_normal(m))
+        vals.append(v / np.sqrt((v * v).sum()) if m else v)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    return synth.Corpus(len(lens), d, rp, np.concatenate(cols).astype(np.int32), np.concatenate(vals).astype(dtype))
+
+
+# (row lengths, d): 4,096 nonzeros are summed at a time and 512 members enter a
+# tile; 2^7 and 2^14 terms are where the sort takes another pass
+_MEMBERS = {
+    "one tile exactly": ([64] * 64, 700),
+    "one nonzero over a tile": ([64] * 64 + [1], 700),
+    "512 short members": ([3] * 512, 128),
+    "513 short members": ([3] * 513, 129),
+    "rows longer than a tile": ([4095, 4096, 4097, 9000, 1], 16384),
+    "empty rows between and around": ([0, 0, 5, 0, 4100, 0, 0, 7, 0], 16385),
+    "every term touched, many tiles": ([900] * 40, 1000),
+    "a wide vocabulary": ([300] * 90, 150_001),
+    "one term": ([1] * 5000, 1),
+    # 8 tiles and more: term ranges side by side; the first has a term in every row
+    "cut into ranges": ([64] * 512, 600),
+    "just too small to cut": ([64] * 511 + [63], 600),
+    "more members than enter a tile, cut": ([40] * 1500 + [0, 700, 4099], 5000),
+}
+
+
+@pytest.mark.parametrize("name", list(_MEMBERS))
+@pytest.mark.parametrize("dtype,signed", [(np.float32, False), (np.float64, False), (np.float32, True)])
+def test_update_at_the_tile_edges_of_the_member_sums(name, dtype, signed):
+    # three clusters: the listed rows, one row, none; then the listed rows and
+    # the row swap a member so the accumulators are used again
+    from paper_2103_16141_amd.api import DeviceCsr
+    from tests.gpu_util import assert_centroids_equal, centroids_from_export
+    log("member sums: %s %s signed %d" % (name, np.dtype(dtype).name, signed))
+    lens, d = _MEMBERS[name]
+    lens = list(lens) + [min(d, 11)]
+    c = _rows_corpus(lens, d, dtype, len(name), signed)
+    X = DeviceCsr.from_corpus(c, device())
+    ids = [0, c.n - 1, min(1, c.n - 1)]
+    ctx = _ctx()
+    ivf = ctx.init_centroids(X, 3, ids)
+    ref = oracle.init_centroids(c, np.array(ids, np.int32))
+    lam = torch.zeros(3, dtype=torch.uint8, device=device())
+    a = np.zeros(c.n, np.int32)
+    a[-1] = 1
+    for step in range(3):
+        ctx.update(X, torch.from_numpy(a).to(device()), lam, ivf)
+        ref, _ = oracle.update(c, a, ref)
+        assert_centroids_equal(centroids_from_export(ivf.export(), 3, d), ref, "%s, step %d" % (name, step))
+        a[step] = 1 - a[step]

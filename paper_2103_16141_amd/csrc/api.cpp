@@ -1114,20 +1114,25 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     for (int64_t j = 0; j < nch; ++j) nnz_max = std::max(nnz_max, ho[(size_t)j + 1] - ho[(size_t)j]);
     float* dxp = nullptr;
     STCHK(ws(ctx, "soft_dxp", std::max<int64_t>(nnz_max, 1) * 8, &dxp));
-    int64_t *cnt = nullptr, *colptr = nullptr, *sws = nullptr;
-    int32_t *hist = nullptr, *xt_row = nullptr;
-    float* xt_val = nullptr;
+    int64_t *colptr = nullptr, *sws = nullptr;
+    const int32_t* xt_row = nullptr;
+    const float* xt_val = nullptr;
     DctWs dw{};
     if (dC_out) {
-        const int64_t nb = (n + 1023) / 1024;
         STCHK(ws(ctx, "soft_dCT", (int64_t)k * d, &dCT));
-        STCHK(ws(ctx, "csc_hist", std::max<int64_t>(nb * d, 1), &hist));
-        STCHK(ws(ctx, "csc_cnt", d, &cnt));
+        CscWs cw{};
+        for (int b = 0; b < 2; ++b) {
+            STCHK(ws(ctx, b ? "csc_key1" : "csc_key0", Xc.nnz, &cw.key[b]));
+            STCHK(ws(ctx, b ? "csc_row1" : "csc_row0", Xc.nnz, &cw.row[b]));
+            STCHK(ws(ctx, b ? "csc_val1" : "csc_val0", Xc.nnz, &cw.val[b]));
+        }
+        const int64_t table = csc_table_elems(Xc.nnz);
+        STCHK(ws(ctx, "csc_count", table, &cw.count));
+        STCHK(ws(ctx, "csc_start", table, &cw.start));
         STCHK(ws(ctx, "csc_ptr", d + 1, &colptr));
-        STCHK(ws(ctx, "csc_row", std::max<int64_t>(Xc.nnz, 1), &xt_row));
-        STCHK(ws(ctx, "csc_val", std::max<int64_t>(Xc.nnz, 1), &xt_val));
-        STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(d + 1, n + 1)) + 8, &sws));
-        HIPCHK(ctx, soft_csc(n, d, Xc.nnz, Xc.rp, Xc.col, (const float*)Xc.val, hist, cnt, colptr, sws, xt_row, xt_val, s));
+        STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(table, std::max<int64_t>(d + 1, n + 1))) + 8, &sws));
+        cw.scan_ws = sws;
+        HIPCHK(ctx, build_csc(n, d, Xc.nnz, Xc.rp, Xc.col, (const float*)Xc.val, cw, colptr, &xt_row, &xt_val, s));
         // ranges of at most 256 entries are summed whole; longer ones are cut
         // at row blocks: 512 rows for ranges of more than 2048 entries (hot
         // terms), 2048 rows for the rest (mid terms).  Every chunk's pieces

@@ -661,72 +661,6 @@ hipError_t soft_bwd_rows(int64_t c0, int64_t c1, int64_t p0, int64_t p1, const i
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- CSC of X (rows ascending per term)
-// hist[b][t] (b = block of kCscRows rows) by integer atomics, column scan over
-// blocks, then one wave per block walks its rows in order and places each
-// entry at colptr[t] + cursor[b][t]++ (terms inside a row are distinct; the
-// fence orders one row's cursor updates before the next row's).
-constexpr int kCscRows = 1024;
-
-__global__ void k_csc_hist(int64_t N, const int64_t* __restrict__ rp, const int32_t* __restrict__ col, int64_t d,
-                           int32_t* __restrict__ hist) {
-    const int64_t b = blockIdx.x;
-    const int64_t lo = b * kCscRows, hi = min(N, lo + kCscRows);
-    for (int64_t i = lo; i < hi; ++i)
-        for (int64_t p = rp[i] + threadIdx.x; p < rp[i + 1]; p += blockDim.x) atomicAdd(&hist[b * d + col[p]], 1);
-}
-
-__global__ void k_csc_colscan(int64_t nb, int64_t d, int32_t* __restrict__ hist, int64_t* __restrict__ cnt) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= d) return;
-    int64_t run = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        const int32_t h = hist[b * d + t];
-        hist[b * d + t] = (int32_t)run;
-        run += h;
-    }
-    cnt[t] = run;
-}
-
-__global__ __launch_bounds__(64) void k_csc_fill(int64_t N, const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                 const float* __restrict__ xv, int64_t d, int32_t* __restrict__ hist,
-                                                 const int64_t* __restrict__ colptr, int32_t* __restrict__ xt_row,
-                                                 float* __restrict__ xt_val) {
-    const int64_t b = blockIdx.x;
-    const int64_t lo = b * kCscRows, hi = min(N, lo + kCscRows);
-    int32_t* cur = hist + b * d;
-    for (int64_t i = lo; i < hi; ++i) {
-        for (int64_t p = rp[i] + threadIdx.x; p < rp[i + 1]; p += 64) {
-            const int32_t t = col[p];
-            const int32_t r = cur[t];
-            cur[t] = r + 1;
-            const int64_t pos = colptr[t] + r;
-            xt_row[pos] = (int32_t)i;
-            xt_val[pos] = xv[p];
-        }
-        __threadfence_block();
-    }
-}
-
-hipError_t soft_csc(int64_t N, int64_t d, int64_t nnz, const int64_t* rp, const int32_t* col, const float* xv,
-                    int32_t* hist, int64_t* cnt, int64_t* colptr, int64_t* scan_ws, int32_t* xt_row, float* xt_val,
-                    hipStream_t s) {
-    const int64_t nb = (N + kCscRows - 1) / kCscRows;
-    hipError_t e = hipSuccess;
-    e = fill_i32(hist, 0, nb * d, s);
-    if (e != hipSuccess) return e;
-    if (nb > 0) hipLaunchKernelGGL(k_csc_hist, dim3((unsigned)nb), dim3(256), 0, s, N, rp, col, d, hist);
-    hipLaunchKernelGGL(k_csc_colscan, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, nb, d, hist, cnt);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = exclusive_scan_i64(cnt, colptr, d, scan_ws, s);
-    if (e != hipSuccess) return e;
-    if (nb > 0)
-        hipLaunchKernelGGL(k_csc_fill, dim3((unsigned)nb), dim3(64), 0, s, N, rp, col, xv, d, hist, colptr, xt_row, xt_val);
-    (void)nnz;
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------- dC^T, term-major, one chunk of rows
 // dCT[t][:] (+)= sum over rows i in [c0, c1) containing t, ascending, of v_it * dS[i - c0][:].
 //

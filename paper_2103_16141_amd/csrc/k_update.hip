@@ -15,6 +15,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "tile_sort.h"
 #include "wave.h"
 
 #pragma clang fp contract(off)
@@ -170,12 +171,6 @@ hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int
 // whole, the largest one alone held the kernel to 11 ms at N = 1M.
 // 4,096 nonzeros and 512 threads keep two workgroups on a CU (58 KB of LDS each
 // with FP32 values).
-constexpr int kFoldThreads = 512;
-constexpr int kFoldWaves = kFoldThreads / 64;
-constexpr int kFoldPer = kFoldTile / kFoldThreads;   // entries per thread: window i * 8 + wave, 64 wide
-constexpr int kFoldBits = 9;
-constexpr int kFoldBins = 1 << kFoldBits;              // one per thread
-static_assert(kFoldBins == kFoldThreads, "one bin per thread");
 
 template <typename V>
 struct FoldLds {
@@ -183,33 +178,13 @@ struct FoldLds {
     V val[kFoldTile + 4];            // values, by position, then in sorted order
     uint16_t ia[kFoldTile + 8];      // positions in sorted order, double-buffered
     uint16_t ib[kFoldTile + 8];
-    uint16_t cnt[kFoldWaves][kFoldBins];
-    uint16_t base[kFoldBins];
+    TileSortLds s;
     int64_t rb[kFoldThreads];        // first nonzero of each member of the tile
     int32_t pre[kFoldThreads + 1];   // its position in the tile
     int32_t wcnt[kFoldTile / 64];
-    int32_t wsum[kFoldWaves];
     int64_t job;
     int32_t nskip;
 };
-
-// exclusive block scan of one value per thread; *total: the sum
-__device__ inline int32_t fold_scan(int32_t v, int32_t* wsum, int32_t* total) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int32_t inc = wave_incl_scan_i32(v);
-    __syncthreads();   // wsum free
-    if (lane == 63) wsum[wid] = inc;
-    __syncthreads();
-    int32_t off = 0, tot = 0;
-#pragma unroll
-    for (int x = 0; x < kFoldWaves; ++x) {
-        const int32_t s = wsum[x];
-        if (x < wid) off += s;
-        tot += s;
-    }
-    *total = tot;
-    return off + inc - v;
-}
 
 // Positions of the flagged entries among all flagged ones, in entry order:
 // entry (i, thread) is number i * kFoldThreads + threadIdx.x; mask[i] is the
@@ -232,67 +207,6 @@ __device__ inline int32_t fold_compact(const unsigned long long (&mask)[kFoldPer
     return __shfl(inc, 63, 64);
 }
 
-// One stable counting pass over `ne` sorted positions: src order (nullptr:
-// identity) by (key >> shift) & mask into dst.
-template <typename V>
-__device__ inline void fold_radix(FoldLds<V>& L, const uint16_t* src, uint16_t* dst, int ne, int shift, int nbits) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const uint32_t dm = (1u << nbits) - 1u;
-    // each wave owns a contiguous part of the order, so ranks are stable
-    const int per = ((ne + kFoldThreads - 1) / kFoldThreads) * 64;
-    const int lo = wid * per, hi = min(ne, lo + per);
-    volatile uint16_t* cnt = L.cnt[wid];
-#pragma unroll
-    for (int b = 0; b < kFoldBins; b += 64) cnt[b + lane] = 0;
-    uint32_t rk[kFoldPer];   // digit << 16 | rank
-    uint16_t id[kFoldPer];
-#pragma unroll
-    for (int i = 0; i < kFoldPer; ++i) {
-        const int s = lo + i * 64 + lane;
-        const bool in = s < hi;
-        const int p = in ? (src ? src[s] : s) : 0;
-        id[i] = (uint16_t)p;
-        rk[i] = ((L.key[p] >> shift) & dm) << 16;
-    }
-#pragma unroll
-    for (int i = 0; i < kFoldPer; ++i) {
-        if (lo + i * 64 >= hi) break;   // wave-uniform
-        const bool in = lo + i * 64 + lane < hi;
-        const uint32_t dg = rk[i] >> 16;
-        unsigned long long m = ballot(in);
-        for (int b = 0; b < nbits; ++b) {
-            const unsigned long long v = ballot((dg >> b) & 1u);
-            m &= ((dg >> b) & 1u) ? v : ~v;
-        }
-        const uint32_t old = in ? cnt[dg] : 0u;
-        const int below = lanes_below(m);
-        rk[i] |= old + (uint32_t)below;
-        __builtin_amdgcn_wave_barrier();
-        if (in && below == 0) cnt[dg] = (uint16_t)(old + (uint32_t)__popcll(m));
-        __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    // per digit: exclusive over waves, then over digits
-    uint32_t run = 0;
-#pragma unroll
-    for (int x = 0; x < kFoldWaves; ++x) {
-        const uint32_t c = L.cnt[x][threadIdx.x];
-        L.cnt[x][threadIdx.x] = (uint16_t)run;
-        run += c;
-    }
-    int32_t total;
-    L.base[threadIdx.x] = (uint16_t)fold_scan((int32_t)run, L.wsum, &total);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kFoldPer; ++i) {
-        if (lo + i * 64 + lane < hi) {
-            const uint32_t dg = rk[i] >> 16;
-            dst[L.base[dg] + L.cnt[wid][dg] + (rk[i] & 0xffffu)] = id[i];
-        }
-    }
-    __syncthreads();
-}
-
 // first entry in [lo, hi) of an ascending row whose column is >= t
 __device__ inline int64_t row_lower(const int32_t* __restrict__ col, int64_t lo, int64_t hi, int64_t t) {
     while (lo < hi) {
@@ -313,7 +227,7 @@ __device__ inline int fold_stage(FoldLds<V>& L, const Csr& X, int64_t b, int32_t
     const int tid = threadIdx.x;
     const V* __restrict__ xv = (const V*)X.val;
     int32_t total;
-    const int32_t at = fold_scan(len, L.wsum, &total);
+    const int32_t at = tile_scan(len, L.s.wsum, &total);
     L.rb[tid] = b;
     L.pre[tid] = at;
     if (tid == 0) {
@@ -357,7 +271,7 @@ __device__ inline const uint16_t* fold_sort(FoldLds<V>& L, int ne, int passes, i
     const uint16_t* cur = nullptr;
     for (int ps = 0; ps < passes; ++ps) {
         uint16_t* dst = (ps & 1) ? L.ib : L.ia;
-        fold_radix(L, cur, dst, ne, ps * nbits, nbits);
+        tile_radix(L.s, L.key, cur, dst, ne, ps * nbits, nbits);
         cur = dst;
     }
     return cur;
@@ -377,15 +291,15 @@ __device__ inline int64_t fold_emit(FoldLds<V>& L, double* W, unsigned long long
         unsigned long long word = 0;
         if (wb + tid < nwords) word = atomicExch(&bits[wb + tid], 0ull);
         int32_t total;
-        const int32_t at = fold_scan(__popcll(word), L.wsum, &total);
+        const int32_t at = tile_scan(__popcll(word), L.s.wsum, &total);
         if (total == 0) continue;   // workgroup-uniform
         // at most kFoldTile terms at a time: all words, or one wave's 64 words
         const int nsub = total <= kFoldTile ? 1 : kFoldWaves;
         for (int sub = 0; sub < nsub; ++sub) {
             int32_t from = 0, n = total;
             if (nsub > 1) {
-                for (int x = 0; x < sub; ++x) from += L.wsum[x];
-                n = L.wsum[sub];
+                for (int x = 0; x < sub; ++x) from += L.s.wsum[x];
+                n = L.s.wsum[sub];
             }
             if (nsub == 1 || wid == sub) {
                 int p = at - from;
@@ -731,9 +645,8 @@ int upd_fold_groups(int n_cu) { return n_cu * 2; }
 template <typename V>
 static hipError_t upd_means_t(const Csr& X, int32_t k, const uint8_t* lam, int allow_copy, Store next,
                               const UpdateWs& w, hipStream_t s) {
-    int bits = 1;
-    while (bits < 31 && ((int64_t)1 << bits) < X.d) ++bits;
-    const int passes = (bits + kFoldBits - 1) / kFoldBits, nbits = (bits + passes - 1) / passes;
+    int passes, nbits;
+    tile_sort_plan(X.d, &passes, &nbits);
     const unsigned groups = (unsigned)w.nslots;
     const size_t lds = sizeof(FoldLds<V>);
     if (lds > 65536) {

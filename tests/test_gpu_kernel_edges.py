@@ -128,3 +128,31 @@ def test_update_at_the_tile_edges_of_the_member_sums(name, dtype, signed):
         ref, _ = oracle.update(c, a, ref)
         assert_centroids_equal(centroids_from_export(ivf.export(), 3, d), ref, "%s, step %d" % (name, step))
         a[step] = 1 - a[step]
+
+
+# ---------------------------------------------------------------- soft form
+@pytest.mark.parametrize("n,d,lam", [(1, 5, 3), (40, 512, 60), (64, 513, 64), (300, 4096, 90), (200, 262_145, 50)])
+def test_soft_gradients_at_the_sort_edges_of_the_column_copy(n, d, lam):
+    # one, two and three sort passes (2^9, 2^18 columns), tiles of 4,096
+    # nonzeros with a remainder, and empty rows in a run; tolerances as in
+    # test_gpu_soft
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("column copy n=%d d=%d" % (n, d))
+    c = synth.make_corpus(n, d, lam, 1.0, np.float32, seed=n + d)
+    keep = np.ones(n, bool)
+    keep[n // 3:n // 2] = False
+    rows = np.repeat(keep, np.diff(c.row_ptr))
+    rp = np.concatenate([[0], np.cumsum(np.where(keep, np.diff(c.row_ptr), 0))]).astype(np.int64)
+    c = synth.Corpus(n, d, rp, np.ascontiguousarray(c.col[rows]), np.ascontiguousarray(c.val[rows]))
+    k = 7
+    C = np.abs(np.random.default_rng(d).standard_normal((k, d))).astype(np.float32)
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    X, Cg = DeviceCsr.from_corpus(c, device()), torch.from_numpy(C).to(device())
+    ctx = _ctx()
+    lse, _ = ctx.soft_assign_fwd(X, Cg, 0.05)
+    lse_ref = oracle.soft_forward(c, C.astype(np.float64), 0.05)
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=0, atol=5e-4)
+    dC, dX = ctx.soft_assign_bwd(X, Cg, 0.05, lse, 0.7)
+    dC_ref, dX_ref = oracle.soft_backward(c, C.astype(np.float64), 0.05, 0.7, lse_ref)
+    np.testing.assert_allclose(dC.cpu().numpy(), dC_ref, rtol=2e-3, atol=1e-7)
+    np.testing.assert_allclose(dX.cpu().numpy(), dX_ref, rtol=2e-3, atol=1e-9)

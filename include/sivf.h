@@ -314,12 +314,11 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
  *   whole), dC = dS^T X -> dC_out f32[k * d] (overwritten),
  *   dX_it = sum_j dS_ij C_jt on X's nonzeros -> dxval_out f32[nnz] (overwritten).
  * Either output may be NULL.  Deterministic (fixed summation order).
- * Workspace held by the ctx: C^T and dC^T (k * d floats each), X's column
- * copy (8 B per nonzero, built through 4 * d bytes of counts per 1024 rows),
- * dS for one chunk of rows (at most 256 MiB), dX partials (32 B per nonzero
- * of a chunk), and the dC pass's partial rows (k floats per piece of the
- * chunk with the most pieces, counted before the pass: about 130 MB at
- * N = 262,144, D = 100,000, k = 4,096). */
+ * Workspace held by the ctx: C^T and dC^T (k rounded up to 64 times d floats
+ * each), X's column copy (24 B per nonzero and 1 B of counts), dS for one chunk
+ * of rows (at most 512 MiB), dX partials (4 B per nonzero of a chunk and 64
+ * columns), and the dC pass's partial rows (k floats per 256 nonzeros of a
+ * chunk). */
 sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* C, int32_t k,
                                  float tau, const float* lse, float grad_loss, float* dC_out,
                                  float* dxval_out);

@@ -1063,16 +1063,20 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     Csr Xc;
     STCHK(validate(ctx, X, &Xc));
     if (Xc.f64) return fail(ctx, SIVF_E_UNSUPPORTED, "soft assignment takes SIVF_F32 object values");
-    float *CT = nullptr, *pmax = nullptr, *psum = nullptr;
+    const int64_t nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk;
+    float* CT = nullptr;
     double* loss = nullptr;
-    STCHK(ws(ctx, "soft_CT", (int64_t)k * Xc.d, &CT));
+    SoftFwdWs w{};
+    // rows per launch: the per-block partials of one launch take at most 512 MiB
+    w.rows = std::max<int64_t>(1, std::min<int64_t>(Xc.n, (int64_t)(64ll << 20) / nblk));
+    STCHK(ws(ctx, "soft_CT", nblk * kSoftBlk * Xc.d, &CT));
     STCHK(ws(ctx, "soft_loss", 1, &loss));
-    STCHK(ws(ctx, "soft_pmax", std::max<int64_t>(Xc.n, 1) * 8, &pmax));
-    STCHK(ws(ctx, "soft_psum", std::max<int64_t>(Xc.n, 1) * 8, &psum));
+    STCHK(ws(ctx, "soft_pmax", w.rows * nblk, &w.pmax));
+    STCHK(ws(ctx, "soft_psum", w.rows * nblk, &w.psum));
+    STCHK(ws(ctx, "soft_part", Xc.n / 256 + Xc.n / w.rows + 2, &w.part));
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, soft_transpose(C, CT, k, Xc.d, s));
-    HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, CT, k, tau, lse_out, loss, pmax, psum,
-                             ctx->n_cu, s));
+    HIPCHK(ctx, soft_pack(C, CT, k, Xc.d, s));
+    HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, CT, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
     if (loss_host) {
         HIPCHK(ctx, hipMemcpyAsync(loss_host, loss, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));
@@ -1094,32 +1098,37 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     if (!dC_out && !dxval_out) return SIVF_OK;
     const int64_t n = Xc.n, d = Xc.d;
     hipStream_t s = ctx->stream;
-    float *CT = nullptr, *dS = nullptr, *dxv = dxval_out, *dCT = nullptr;
-    STCHK(ws(ctx, "soft_CT", (int64_t)k * d, &CT));
-    // rows per chunk: dS of one chunk is at most 256 MiB
-    const int64_t rc = std::max<int64_t>(1, std::min<int64_t>(std::max<int64_t>(n, 1), (int64_t)(64ll << 20) / k));
-    STCHK(ws(ctx, "soft_dS", rc * (int64_t)k, &dS));
-    if (!dxv) STCHK(ws(ctx, "soft_dx", std::max<int64_t>(Xc.nnz, 1), &dxv));
-    HIPCHK(ctx, soft_transpose(C, CT, k, d, s));
-    // nonzero offsets of the row chunks: they size the per-group dX partials
-    // and bound the pieces of the dC pass
+    const int64_t nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk, kp = nblk * kSoftBlk;
+    float *CT = nullptr, *dS = nullptr, *dxp = nullptr, *dCT = nullptr;
+    STCHK(ws(ctx, "soft_CT", kp * d, &CT));
+    // rows per chunk: 24,576 rows of a 32-column dS block take 3 MB of an XCD's
+    // 4 MB L2 (backward at N = 262,144, k = 4,096 with 8,192 / 12,288 / 16,384 /
+    // 24,576 / 32,768 rows: 96 / 85 / 79 / 76 / 77 ms: smaller chunks read and
+    // write dC more often, larger ones miss L2); dS of a chunk is at most 512 MiB
+    const int64_t rc = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), (int64_t)24576, (int64_t)(128ll << 20) / kp}));
     const int64_t nch = std::max<int64_t>(1, (n + rc - 1) / rc);
-    int64_t* offs = nullptr;
-    STCHK(ws(ctx, "soft_offs", nch + 1, &offs));
-    HIPCHK(ctx, soft_chunk_offsets(Xc.rp, n, rc, nch, offs, s));
+    HIPCHK(ctx, soft_pack(C, CT, k, d, s));
+    // nonzero offsets of the row chunks: they size the per-block dX shares and
+    // the pieces of the dC pass
     std::vector<int64_t> ho((size_t)nch + 1);
-    HIPCHK(ctx, hipMemcpyAsync(ho.data(), offs, (size_t)(nch + 1) * 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(ctx, hipStreamSynchronize(s));
+    ho[(size_t)nch] = Xc.nnz;
+    if (nch > 1) {
+        int64_t* offs = nullptr;
+        STCHK(ws(ctx, "soft_offs", nch + 1, &offs));
+        HIPCHK(ctx, soft_chunk_offsets(Xc.rp, n, rc, nch, offs, s));
+        HIPCHK(ctx, hipMemcpyAsync(ho.data(), offs, (size_t)(nch + 1) * 8, hipMemcpyDeviceToHost, s));
+        HIPCHK(ctx, hipStreamSynchronize(s));
+    }
     int64_t nnz_max = 0;
     for (int64_t j = 0; j < nch; ++j) nnz_max = std::max(nnz_max, ho[(size_t)j + 1] - ho[(size_t)j]);
-    float* dxp = nullptr;
-    STCHK(ws(ctx, "soft_dxp", std::max<int64_t>(nnz_max, 1) * 8, &dxp));
-    int64_t *colptr = nullptr, *sws = nullptr;
+    if (dxval_out && nblk > 1) STCHK(ws(ctx, "soft_dxp", nnz_max * nblk, &dxp));
+    int64_t* colptr = nullptr;
     const int32_t* xt_row = nullptr;
     const float* xt_val = nullptr;
     DctWs dw{};
     if (dC_out) {
-        STCHK(ws(ctx, "soft_dCT", (int64_t)k * d, &dCT));
+        STCHK(ws(ctx, "soft_dS", rc * kp, &dS));
+        STCHK(ws(ctx, "soft_dCT", kp * d, &dCT));
         CscWs cw{};
         for (int b = 0; b < 2; ++b) {
             STCHK(ws(ctx, b ? "csc_key1" : "csc_key0", Xc.nnz, &cw.key[b]));
@@ -1130,52 +1139,34 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
         STCHK(ws(ctx, "csc_count", table, &cw.count));
         STCHK(ws(ctx, "csc_start", table, &cw.start));
         STCHK(ws(ctx, "csc_ptr", d + 1, &colptr));
-        STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(table, std::max<int64_t>(d + 1, n + 1))) + 8, &sws));
-        cw.scan_ws = sws;
+        STCHK(ws(ctx, "scan_ws", scan_ws_elems(table) + 8, &cw.scan_ws));
         HIPCHK(ctx, build_csc(n, d, Xc.nnz, Xc.rp, Xc.col, (const float*)Xc.val, cw, colptr, &xt_row, &xt_val, s));
-        // ranges of at most 256 entries are summed whole; longer ones are cut
-        // at row blocks: 512 rows for ranges of more than 2048 entries (hot
-        // terms), 2048 rows for the rest (mid terms).  Every chunk's pieces
-        // are counted first, and the partial rows are sized for the largest.
-        dw.piece = 256;
-        dw.hot_min = 2048;
-        dw.blk_rows = 512;
-        dw.mid_blk_rows = 2048;
+        // a range of more than kSoftPiece entries has less than one piece per
+        // kSoftPiece / 2 entries
+        dw.max_pieces = nnz_max / (kSoftPiece / 2);
+        STCHK(ws(ctx, "dct_next", d, &dw.next));
         STCHK(ws(ctx, "dct_lo", d, &dw.lo));
-        STCHK(ws(ctx, "dct_hi", d, &dw.hi));
-        STCHK(ws(ctx, "dct_np", d, &dw.np));
-        STCHK(ws(ctx, "dct_pstart", d + 1, &dw.pstart));
-        STCHK(ws(ctx, "dct_hflag", d, &dw.hflag));
-        STCHK(ws(ctx, "dct_hscan", d + 1, &dw.hscan));
-        STCHK(ws(ctx, "dct_hot", d, &dw.hot));
-        STCHK(ws(ctx, "dct_mflag", d, &dw.mflag));
-        STCHK(ws(ctx, "dct_mscan", d + 1, &dw.mscan));
+        STCHK(ws(ctx, "dct_len", d, &dw.len));
         STCHK(ws(ctx, "dct_mid", d, &dw.mid));
-        dw.scan_ws = sws;
-        int64_t* counts = nullptr;
-        STCHK(ws(ctx, "dct_counts", nch, &counts));
-        for (int64_t j = 0; j < nch; ++j)
-            HIPCHK(ctx, soft_dct_count(d, std::min(n, j * rc), std::min(n, (j + 1) * rc), colptr, xt_row, dw,
-                                       counts + j, s));
-        std::vector<int64_t> hc((size_t)nch);
-        HIPCHK(ctx, hipMemcpyAsync(hc.data(), counts, (size_t)nch * 8, hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipStreamSynchronize(s));
-        dw.max_pieces = 0;
-        for (int64_t j = 0; j < nch; ++j) dw.max_pieces = std::max(dw.max_pieces, hc[(size_t)j]);
-        STCHK(ws(ctx, "dct_item", std::max<int64_t>(dw.max_pieces, 1), &dw.item));
-        STCHK(ws(ctx, "dct_part", std::max<int64_t>(dw.max_pieces, 1) * (int64_t)k, &dw.part));
+        STCHK(ws(ctx, "dct_longt", d, &dw.longt));
+        STCHK(ws(ctx, "dct_longp", d, &dw.longp));
+        STCHK(ws(ctx, "dct_piece", dw.max_pieces, &dw.piece));
+        STCHK(ws(ctx, "dct_piece_len", dw.max_pieces, &dw.piece_len));
+        STCHK(ws(ctx, "dct_part", dw.max_pieces * kp, &dw.part));
+        STCHK(ws(ctx, "dct_count", nch * 4, &dw.count));
+        HIPCHK(ctx, fill_u64(dw.count, 0ull, nch * 4, s));
+        if (n == 0) HIPCHK(ctx, fill_i32((int32_t*)dC_out, 0, (int64_t)k * d, s));
     }
-    int first = 1;
-    for (int64_t c0 = 0, j = 0; c0 < n || first; c0 += rc, ++j) {
+    for (int64_t c0 = 0, j = 0; c0 < n; c0 += rc, ++j) {
         const int64_t c1 = std::min(n, c0 + rc);
-        if (c1 > c0)
-            HIPCHK(ctx, soft_bwd_rows(c0, c1, ho[(size_t)j], ho[(size_t)j + 1], Xc.rp, Xc.col, (const float*)Xc.val, CT,
-                                      k, tau, grad_loss, lse, dS, dxp, dxv, ctx->n_cu, s));
-        if (dC_out) HIPCHK(ctx, soft_dct(d, k, c0, c1, first, colptr, xt_row, xt_val, dS, dCT, dw, ctx->n_cu, s));
-        first = 0;
-        if (c1 >= n) break;
+        HIPCHK(ctx, soft_bwd_rows(c0, c1, ho[(size_t)j], ho[(size_t)j + 1], Xc.rp, Xc.col, (const float*)Xc.val, CT, d, k,
+                                  tau, grad_loss, lse, dS, dxp, dxval_out, ctx->n_cu, s));
+        if (dC_out) {
+            HIPCHK(ctx, soft_dct(d, k, c0, c1, j == 0, colptr, xt_row, xt_val, dS, dCT, dw, ctx->n_cu, s));
+            dw.count += 4;
+        }
     }
-    if (dC_out) HIPCHK(ctx, soft_transpose(dCT, dC_out, d, k, s));
+    if (dC_out && n > 0) HIPCHK(ctx, soft_unpack(dCT, dC_out, k, d, s));
     return SIVF_OK;
 }
 

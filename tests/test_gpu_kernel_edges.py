@@ -156,3 +156,67 @@ def test_soft_gradients_at_the_sort_edges_of_the_column_copy(n, d, lam):
     dC_ref, dX_ref = oracle.soft_backward(c, C.astype(np.float64), 0.05, 0.7, lse_ref)
     np.testing.assert_allclose(dC.cpu().numpy(), dC_ref, rtol=2e-3, atol=1e-7)
     np.testing.assert_allclose(dX.cpu().numpy(), dX_ref, rtol=2e-3, atol=1e-9)
+
+
+@pytest.mark.parametrize("k", [1, 31, 32, 33, 63, 64, 65, 128, 511, 512, 513, 577, 1100])
+def test_soft_blocks_of_columns_and_rows_of_every_length_class(k):
+    # columns come in blocks of 64 (C^T) and 32 (dS, dC), eight blocks at a time
+    # with XCDs sharing the last ones; rows of 0, 1, 15 .. 17, 63 .. 65, 112, 113,
+    # 127 .. 129, 200 terms take every register class and the gathered-twice
+    # path; terms of 1 .. 8, 9, 512, 513 and 1,400 entries every dC path
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("soft blocks k=%d" % k)
+    rng = np.random.default_rng(k)
+    classes = [0, 1, 15, 16, 17, 63, 64, 65, 112, 113, 127, 128, 129, 200]
+    d, n = 700, 1400
+    lens = np.resize(classes, n)
+    # term t < 12 in the first cut[t] rows that are long enough, the rest spread
+    cut = [1400, 513, 512, 9, 8, 7, 6, 5, 4, 3, 2, 1]
+    cols, used = [], np.zeros(12, int)
+    for i in range(n):
+        c = [t for t in range(12) if used[t] < cut[t]][:lens[i]]
+        used[c] += 1
+        rest = rng.choice(np.arange(12, d), lens[i] - len(c), replace=False)
+        cols.append(np.sort(np.concatenate([c, rest])).astype(np.int32))
+    assert list(used[1:]) == cut[1:]
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    v = np.exp(rng.standard_normal(rp[-1]))
+    v /= np.sqrt(np.repeat(np.add.reduceat(np.append(v * v, 0), rp[:-1]), lens))
+    c = synth.Corpus(n, d, rp, np.concatenate(cols), v.astype(np.float32))
+    C = np.abs(rng.standard_normal((k, d))).astype(np.float32)
+    C /= np.linalg.norm(C, axis=1, keepdims=True)
+    X, Cg = DeviceCsr.from_corpus(c, device()), torch.from_numpy(C).to(device())
+    ctx = _ctx()
+    lse, loss = ctx.soft_assign_fwd(X, Cg, 0.05)
+    lse_ref = oracle.soft_forward(c, C.astype(np.float64), 0.05)
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=0, atol=5e-4)
+    assert abs(loss + lse.double().sum().item()) <= 1e-9 * abs(loss)
+    dC, dX = ctx.soft_assign_bwd(X, Cg, 0.05, lse, 1.1)
+    dC_ref, dX_ref = oracle.soft_backward(c, C.astype(np.float64), 0.05, 1.1, lse_ref)
+    np.testing.assert_allclose(dC.cpu().numpy(), dC_ref, rtol=2e-3, atol=1e-7)
+    np.testing.assert_allclose(dX.cpu().numpy(), dX_ref, rtol=2e-3, atol=1e-9)
+    again = ctx.soft_assign_bwd(X, Cg, 0.05, lse, 1.1)
+    assert torch.equal(again[0], dC) and torch.equal(again[1], dX)
+    alone = ctx.soft_assign_bwd(X, Cg, 0.05, lse, 1.1, want_dc=False)
+    assert alone[0] is None and torch.equal(alone[1], dX)
+
+
+def test_soft_forward_keeps_infinities_to_their_own_terms():
+    # a -inf in one centroid's row of term 0 must not reach rows without that
+    # term, and a whole block of -inf similarities still leaves a finite lse
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("soft infinities")
+    rp = torch.tensor([0, 2, 3, 5], device=device())
+    col = torch.tensor([1, 2, 2, 0, 3], dtype=torch.int32, device=device())
+    val = torch.tensor([0.6, 0.8, 1.0, 0.6, 0.8], device=device())
+    C = torch.rand(130, 4, device=device())
+    C[64:128, 0] = -float("inf")
+    lse, _ = _ctx().soft_assign_fwd(DeviceCsr(rp, col, val, 4), C, 0.05)
+    X = torch.zeros(3, 4, dtype=torch.float64, device=device())
+    X[0, 1], X[0, 2], X[1, 2], X[2, 0], X[2, 3] = 0.6, 0.8, 1.0, 0.6, 0.8
+    S = torch.zeros(3, 130, dtype=torch.float64, device=device())
+    for t in range(4):   # term by term: 0 * inf must not appear
+        hit = X[:, t] != 0
+        S[hit] += X[hit, t:t + 1] * C[:, t].double()[None]
+    want = torch.logsumexp(S / 0.05, 1)
+    assert torch.isfinite(lse).all() and (lse.double() - want).abs().max() < 5e-4

@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 N_CU, CLOCK_GHZ = 256, 2.4   # MI355X compute units and peak engine clock
 POSTING_BYTES = {"fp32": 6, "bf16": 4}  # 2-byte centroid id + value
-WALK_KERNEL = "k_walk_fast<false, false>"   # FP32 postings, SIVF filter
+WALK_KERNEL = "k_walk_fast<false, false, false>"   # FP32 postings, SIVF filter
 # bytes the walk's L2 sends toward memory, from calibrated rocprofv3 --pmc
 # runs; used only while the kernel sources still hash the same
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "walk_8m_k10k_dram_traffic.md")

@@ -27,6 +27,8 @@
 // => the object is re-scored in FP64 over the survivors only (rescore_cand),
 // in the reference order; too many => over all eligible centroids through the
 // FP64 posting values (rescore_full).
+#include <algorithm>
+
 #include "internal.h"
 #include "wave.h"
 
@@ -365,9 +367,9 @@ __device__ double exact_rho(const WalkArgs& A, const Store& st, int64_t r0, int 
 // BF16 instantiations ask for 6 waves per SIMD (80 VGPRs): measured 6% faster
 // at N=8M, k=10k; the FP32 ones stay at the compiler's choice (5 waves),
 // where the cap's spills cost more than the extra wave gains.
-template <bool BF16, bool CB>
+template <bool BF16, bool CB, bool SHARE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 5))) void k_walk_fast(WalkArgs A, unsigned long long* __restrict__ work, int tb,
-                                                   int te) {
+                                                   int te, int share) {
     extern __shared__ float lds[];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int kts = A.kt + 64;   // tile plus one spare slot per lane
@@ -383,9 +385,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
     uint32_t lwords = 0;   // 4-byte words requested by this wave's vector loads (flushed at 2^31)
     uint32_t hwords = 0;   // of which words of 16-byte-per-lane loads (head rows, records)
     const uint32_t xb = 4u + (A.x_f64 ? 8u : 4u);   // one staged term: column + value
-    constexpr int kGrab = 8;
-    for (int64_t g0 = wave_grab(work, kGrab); g0 < A.n; g0 = wave_grab(work, kGrab)) {
-        const int64_t gend = min(g0 + kGrab, A.n);
+    // SHARE: a wave takes `share` objects by its number; else it grabs as many at a time
+    for (int64_t g0 = SHARE ? ((int64_t)blockIdx.x * kWalkWaves + wid) * share : wave_grab(work, share); g0 < A.n;
+         g0 = SHARE ? A.n : wave_grab(work, share)) {
+        const int64_t gend = min(g0 + share, A.n);
         for (int64_t i = g0; i < gend; ++i) {
             const int64_t r0 = A.rp[i];
             const int n = (int)(A.rp[i + 1] - r0);
@@ -470,7 +473,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
             if (lwords >= 0x80000000u) {   // wave-uniform; far below any one object's share
                 if (lane == 0) {
                     atomicAdd(&A.counters[10], 4ull * lwords);
-        atomicAdd(&A.counters[11], 4ull * hwords);
                     atomicAdd(&A.counters[11], 4ull * hwords);
                 }
                 lwords = 0;
@@ -756,13 +758,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
             }
         }
     }
+    // one set of counter updates per workgroup (the lists' LDS is free by now)
     macc = (unsigned long long)wave_sum_i64((int64_t)macc);
+    __syncthreads();
+    unsigned long long* tot = reinterpret_cast<unsigned long long*>(lds);
     if (lane == 0) {
-        atomicAdd(&A.counters[0], macc);
-        atomicAdd(&A.counters[10], 4ull * lwords);
-        atomicAdd(&A.counters[11], 4ull * hwords);
-        atomicAdd(&A.counters[3], icp_cnt);
-        if (rel_cnt) atomicAdd(&A.counters[7], rel_cnt);
+        const unsigned long long c[5] = {macc, 4ull * lwords, 4ull * hwords, icp_cnt, rel_cnt};
+        for (int q = 0; q < 5; ++q) tot[wid * 5 + q] = c[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        unsigned long long t = 0;
+        for (int w = 0; w < kWalkWaves; ++w) t += tot[w * 5 + threadIdx.x];
+        const int slot[5] = {0, 10, 11, 3, 7};
+        if (t) atomicAdd(&A.counters[slot[threadIdx.x]], t);
     }
 }
 
@@ -772,10 +781,15 @@ static size_t walk_lds_bytes(int kt) {
     return (size_t)kWalkWaves * ((size_t)kt + 64 + 2 * kCandCap + 2 * kTermCap) * sizeof(float);
 }
 
-// The four instantiations: posting precision x (SIVF | IVF-CBICP filter).
-static const void* walk_kernel(int bf16, int cb) {
-    return bf16 ? (cb ? (const void*)k_walk_fast<true, true> : (const void*)k_walk_fast<true, false>)
-                : (cb ? (const void*)k_walk_fast<false, true> : (const void*)k_walk_fast<false, false>);
+// The instantiations: posting precision x (SIVF | IVF-CBICP filter) x (objects
+// grabbed | shared out).
+template <bool BF16, bool CB>
+static const void* walk_kernel_s(int share) {
+    return share ? (const void*)k_walk_fast<BF16, CB, true> : (const void*)k_walk_fast<BF16, CB, false>;
+}
+static const void* walk_kernel(int bf16, int cb, int share) {
+    return bf16 ? (cb ? walk_kernel_s<true, true>(share) : walk_kernel_s<true, false>(share))
+                : (cb ? walk_kernel_s<false, true>(share) : walk_kernel_s<false, false>(share));
 }
 
 hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
@@ -783,20 +797,34 @@ hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, in
     const size_t lds = walk_lds_bytes(a.kt);
     int blocks = (grid_waves + kWalkWaves - 1) / kWalkWaves;
     if (blocks < 1) blocks = 1;
-    const void* fn = walk_kernel(pdt_bf16, a.cbicp);
+    // Many objects: a wave grabs them from the work counter, which evens out
+    // their costs, 8 at a time or at least four times (60,000 objects, BF16, one
+    // tile: 1.36 ms by twos, 1.64 by eights, 1.47 in equal shares).  Up to 8
+    // objects a wave the counter costs more than that (5,120 waves' turns on it
+    // take 50 us), so the waves take equal shares: 64 objects, k = 100, 260 (8
+    // waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects,
+    // k = 1,531, BF16 842 -> 346 us.
+    const int64_t waves = (int64_t)blocks * kWalkWaves;
+    const bool shared = a.n <= 8 * waves;
+    int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, a.n / (waves * 4)));
+    if (shared) {
+        share = (int)std::max<int64_t>(1, (a.n + waves - 1) / waves);
+        blocks = (int)((a.n + (int64_t)share * kWalkWaves - 1) / ((int64_t)share * kWalkWaves));
+    }
+    const void* fn = walk_kernel(pdt_bf16, a.cbicp, shared);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
     WalkArgs args = a;
-    void* params[] = {&args, &work, &tb, &te};
+    void* params[] = {&args, &work, &tb, &te, &share};
     return hipLaunchKernel(fn, dim3(blocks), dim3(64 * kWalkWaves), params, lds, s);
 }
 
 int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp) {
     const size_t lds = walk_lds_bytes(kt);
     int nb = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel(pdt_bf16, cbicp), 64 * kWalkWaves, lds);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel(pdt_bf16, cbicp, 0), 64 * kWalkWaves, lds);
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
 }

@@ -220,3 +220,39 @@ def test_soft_forward_keeps_infinities_to_their_own_terms():
         S[hit] += X[hit, t:t + 1] * C[:, t].double()[None]
     want = torch.logsumexp(S / 0.05, 1)
     assert torch.isfinite(lse).all() and (lse.double() - want).abs().max() < 5e-4
+
+
+# ---------------------------------------------------------------- walk
+@pytest.mark.parametrize("posting", ["fp32", "bf16"])
+@pytest.mark.parametrize("k", [60, 1500])
+def test_assignment_of_batches_on_both_sides_of_the_work_shares(posting, k):
+    # up to 8 objects a wave the objects are shared out, beyond that grabbed
+    # (5,120 FP32 and 6,144 BF16 waves; half and less with wide tiles): every
+    # batch must give what the first step gives for the same rows in one call
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("batches %s k=%d" % (posting, k))
+    c = synth.make_corpus(52_000, 900, 12, 1.1, np.float32, seed=k)
+    X = DeviceCsr.from_corpus(c, device())
+    ctx = _ctx(posting_dtype=posting)
+    ivf = ctx.init_centroids(X, k, synth.init_ids(c.n, k, 3))
+
+    def run(lo, hi):
+        a = torch.full((hi - lo,), -1, dtype=torch.int32, device=device())
+        own = torch.zeros(hi - lo, dtype=torch.float32, device=device())
+        lam = torch.zeros(k, dtype=torch.uint8, device=device())
+        b, e = int(c.row_ptr[lo]), int(c.row_ptr[hi])
+        rows = DeviceCsr(X.row_ptr[lo:hi + 1] - b, X.col[b:e].clone(), X.val[b:e].clone(), c.d)
+        return a, own, ctx.assign(rows, ivf, 1, a, own, lam)["multadds"]
+
+    a, own, m = run(0, c.n)
+    ref, _, _ = oracle.assign(c, oracle.init_centroids(c, synth.init_ids(c.n, k, 3)), rows=np.arange(0, c.n, 97))
+    assert np.array_equal(a.cpu().numpy()[::97], ref)
+    cuts = [0, 1, 4, 9, 5130, 5130 + 40_960, c.n]
+    total = 0
+    for lo, hi in zip(cuts[:-1], cuts[1:]):
+        pa, po, pm = run(lo, hi)
+        assert torch.equal(pa, a[lo:hi]) and torch.equal(po, own[lo:hi])
+        total += pm
+    assert total == m
+    pa, po, _ = run(0, 40_961)
+    assert torch.equal(pa, a[:40_961]) and torch.equal(po, own[:40_961])

@@ -8,12 +8,14 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <vector>
 
 #include "internal.h"
 #include "soft.h"
+#include "sort.h"
 
 using namespace sivf;
 
@@ -123,6 +125,21 @@ sivf_status ws_zeroed(sivf_ctx* ctx, const char* name, int64_t elems, T** out) {
     return SIVF_OK;
 }
 
+// Buffers of a sort of n entries ("<name>_..."); val: with values.
+template <typename V>
+sivf_status sort_ws(sivf_ctx* ctx, const std::string& name, int64_t n, bool val, SortWs<V>* w) {
+    for (int b = 0; b < 2; ++b) {
+        const std::string i = std::to_string(b);
+        STCHK(ws(ctx, (name + "_key" + i).c_str(), n, &w->key[b]));
+        STCHK(ws(ctx, (name + "_row" + i).c_str(), n, &w->row[b]));
+        if (val) STCHK(ws(ctx, (name + "_val" + i).c_str(), n, &w->val[b]));
+    }
+    const int64_t table = sort_table_elems(n);
+    STCHK(ws(ctx, (name + "_count").c_str(), table, &w->count));
+    STCHK(ws(ctx, (name + "_start").c_str(), table, &w->start));
+    return ws(ctx, (name + "_scan").c_str(), scan_ws_elems(table) + 8, &w->scan_ws);
+}
+
 // Workspace of one call, handed out buffer by buffer: the ctx's grow-only
 // named buffers (kCtx), consecutive 256-byte aligned pieces of a fixed device
 // block that is never allocated or freed here (kFixed), or no memory at all,
@@ -193,18 +210,36 @@ sivf_status check_csr_args(sivf_ctx* ctx, const sivf_csr* X, const char* what) {
     return SIVF_OK;
 }
 
-// Run the device check on M and report what it found; *nonneg = no value is
-// negative.  Waits for the stream.
-sivf_status check_csr(sivf_ctx* ctx, const sivf_csr* M, const char* what, unsigned long long* flags, int* nonneg) {
+// Assignments to check along with a matrix: every a[i] must lie in [0, k)
+// before it is used as an index on the device.
+struct Ids {
+    const int32_t* a;
+    int64_t n;
+    int32_t k;
+    const char* what;
+};
+
+// Run the device check on M and the id arrays (at most two) and report what it
+// found; *nonneg = no value of M is negative.  flags: 8 words.  Waits for the
+// stream once.
+sivf_status check_csr(sivf_ctx* ctx, const sivf_csr* M, const char* what, unsigned long long* flags, int* nonneg,
+                      std::initializer_list<Ids> ids = {}) {
     const int f64 = M->val_dtype == SIVF_F64;
+    unsigned long long* h = (unsigned long long*)ctx->pin;
     HIPCHK(ctx, validate_csr(M->row_ptr, M->col, M->val, f64, M->n_rows, M->n_cols, M->nnz, flags, ctx->stream));
-    unsigned long long h[4];
-    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
+    int q = 4;
+    for (const Ids& i : ids) HIPCHK(ctx, range_check_i32(i.a, i.n, i.k, flags + q++, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h, flags, 8 * sizeof(*h), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     *nonneg = h[2] ? 0 : 1;
-    if (h[0] == 0 && h[3] == 0) return SIVF_OK;
+    if (h[0] == 0 && h[3] == 0) {
+        q = 4;
+        for (const Ids& i : ids)
+            if (h[q++]) return fail(ctx, SIVF_E_RANGE, "%s has a value outside [0, %d)", i.what, i.k);
+        return SIVF_OK;
+    }
     HIPCHK(ctx, validate_csr_rows(M->row_ptr, M->col, M->val, f64, M->n_rows, M->n_cols, M->nnz, flags, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h, flags, 4 * sizeof(*h), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     const unsigned long long row = ~h[1];
     if (h[0] & 1ull) return fail(ctx, SIVF_E_UNSORTED, "%s: row %llu has unsorted/duplicate columns or a decreasing row_ptr", what, row);
@@ -219,18 +254,18 @@ sivf_status check_csr(sivf_ctx* ctx, const sivf_csr* M, const char* what, unsign
 // both the column range (used as an index by the walk) and the sign of the
 // values (which selects the certificate's error bound) must hold for the
 // contents the kernels will read.  One coalesced pass over the nonzeros.
-sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, Work& w) {
+sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, Work& w, std::initializer_list<Ids> ids = {}) {
     STCHK(check_csr_args(ctx, X, "X"));
     unsigned long long* flags = nullptr;
-    STCHK(w.get("vflags", 4, &flags));
+    STCHK(w.get("vflags", 8, &flags));
     if (X->n_rows == 0) {
-        int64_t rp0 = 0;
-        HIPCHK(ctx, hipMemcpyAsync(&rp0, X->row_ptr, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+        int64_t* rp0 = (int64_t*)ctx->pin;
+        HIPCHK(ctx, hipMemcpyAsync(rp0, X->row_ptr, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
         HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-        if (rp0 != 0 || X->nnz != 0) return fail(ctx, SIVF_E_UNSORTED, "X: empty matrix with row_ptr[0] != 0 or nnz != 0");
+        if (*rp0 != 0 || X->nnz != 0) return fail(ctx, SIVF_E_UNSORTED, "X: empty matrix with row_ptr[0] != 0 or nnz != 0");
     }
     int nonneg = 1;
-    STCHK(check_csr(ctx, X, "X", flags, &nonneg));
+    STCHK(check_csr(ctx, X, "X", flags, &nonneg, ids));
     out->n = X->n_rows;
     out->d = X->n_cols;
     out->nnz = X->nnz;
@@ -242,28 +277,9 @@ sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, Work& w) {
     return SIVF_OK;
 }
 
-sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out) {
+sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, std::initializer_list<Ids> ids = {}) {
     Work w{ctx};
-    return validate(ctx, X, out, w);
-}
-
-// Every a[i] must lie in [0, k) before it is used as an index on the device.
-sivf_status check_assign(sivf_ctx* ctx, const int32_t* a, int64_t n, int32_t k, const char* what, Work& w) {
-    unsigned long long* flags = nullptr;
-    STCHK(w.get("aflags", 2, &flags));
-    if (n <= 0) return SIVF_OK;
-    HIPCHK(ctx, fill_u64(flags, 0ull, 1, ctx->stream));
-    HIPCHK(ctx, range_check_i32(a, n, k, flags, ctx->stream));
-    unsigned long long h = 0;
-    HIPCHK(ctx, hipMemcpyAsync(&h, flags, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    if (h) return fail(ctx, SIVF_E_RANGE, "%s has a value outside [0, %d)", what, k);
-    return SIVF_OK;
-}
-
-sivf_status check_assign(sivf_ctx* ctx, const int32_t* a, int64_t n, int32_t k, const char* what) {
-    Work w{ctx};
-    return check_assign(ctx, a, n, k, what, w);
+    return validate(ctx, X, out, w, ids);
 }
 
 void choose_tiles(const sivf_ctx* ctx, int32_t k, int32_t* kt, int32_t* T) {
@@ -383,50 +399,33 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms) {
     const int64_t nseg2 = f->d * f->T * 2;
     IvfBuildWs w{};
     STCHK(ws(ctx, "ivf_bm", W64 * f->d, &w.bm));
-    STCHK(ws(ctx, "ivf_lbits", W64, &w.lbits));
     STCHK(ws(ctx, "ivf_pre0", W64 * f->d, &w.pre0));
     STCHK(ws(ctx, "ivf_pre1", W64 * f->d, &w.pre1));
     STCHK(ws(ctx, "ivf_cnt", nseg2, &w.cnt));
     STCHK(ws(ctx, "ivf_off", nseg2 + 1, &w.off));
-    STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(nseg2, f->k + 1)) + 8,
-             &w.scan_ws));
-    int64_t* pmv = nullptr;
-    int64_t* pmvpre = nullptr;
-    STCHK(ws(ctx, "ivf_mv", (int64_t)f->k, &pmv));
-    STCHK(ws(ctx, "ivf_mvpre", (int64_t)f->k + 1, &pmvpre));
-    HIPCHK(ctx, ivf_perm(f->lam, f->k, pmv, pmvpre, w.scan_ws, f->perm, f->iperm, ctx->stream));
-    int64_t nmv = 0;
-    HIPCHK(ctx, hipMemcpyAsync(&nmv, pmvpre + f->k, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    f->nmv = (int32_t)nmv;
-    HIPCHK(ctx, ivf_count(f->cur, f->k, f->d, f->kt, f->T, f->iperm, f->nmv, w, ctx->stream));
-    HIPCHK(ctx, ivf_offsets(f->d, f->T, w, f->seg, f->mid, ctx->stream));
-    // dense head rows: terms whose lists hold >= ceil(head_density * k) postings
-    int64_t* hflag = nullptr;
-    int64_t* hscan = nullptr;
-    int64_t H = 0;
-    if (f->head) {
-        const int64_t min_len = std::max<int64_t>(1, (int64_t)std::ceil((double)ctx->opt.head_density * f->k));
-        STCHK(ws(ctx, "head_flag", f->d + 1, &hflag));
-        STCHK(ws(ctx, "head_scan", f->d + 1, &hscan));
-        HIPCHK(ctx, head_flags(f->seg, f->d, f->T, min_len, hflag, ctx->stream));
-        HIPCHK(ctx, exclusive_scan_i64(hflag, hscan, f->d, w.scan_ws, ctx->stream));
-        HIPCHK(ctx, head_index(hflag, hscan, f->d, f->head, ctx->stream));
-        HIPCHK(ctx, hipMemcpyAsync(&H, hscan + f->d, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    }
-    int64_t P = 0, total = 0;
-    int64_t* cscan = nullptr;
+    STCHK(ws(ctx, "scan_ws", scan_ws_elems(nseg2) + 8, &w.scan_ws));
+    int64_t *cscan = nullptr, *meta = nullptr;
+    int32_t* hterm = nullptr;
     STCHK(ws(ctx, "ivf_cscan", (int64_t)f->k + 1, &cscan));
-    HIPCHK(ctx, exclusive_scan_i64(f->cur.nnz, cscan, f->k, w.scan_ws, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(&total, cscan + f->k, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(&P, f->seg + f->d * f->T, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    STCHK(ws(ctx, "ivf_meta", 4, &meta));
+    if (f->head) STCHK(ws(ctx, "head_term", f->d, &hterm));
+    HIPCHK(ctx, ivf_perm(f->lam, f->k, f->cur.nnz, f->perm, f->iperm, cscan, meta, ctx->stream));
+    HIPCHK(ctx, ivf_count(f->cur, f->k, f->d, f->kt, f->T, f->iperm, cscan, meta, w, ctx->stream));
+    // dense head rows: terms whose lists hold >= ceil(head_density * k) postings
+    const int64_t min_len = std::max<int64_t>(1, (int64_t)std::ceil((double)ctx->opt.head_density * f->k));
+    HIPCHK(ctx, ivf_offsets(f->d, f->T, w, min_len, f->seg, f->mid, f->head, hterm, meta, ctx->stream));
+    int64_t* h = (int64_t*)ctx->pin;
+    HIPCHK(ctx, hipMemcpyAsync(h, meta, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h + 3, f->seg + f->d * f->T, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    if (P != total)
-        return fail(ctx, SIVF_E_HIP, "internal: %lld postings for %lld centroid entries", (long long)P, (long long)total);
+    f->nmv = (int32_t)h[0];
+    const int64_t P = h[1], H = f->head ? h[2] : 0;
+    if (P != h[3])
+        return fail(ctx, SIVF_E_HIP, "internal: %lld postings for %lld centroid entries", (long long)h[3], (long long)P);
     STCHK(postings_reserve(ctx, f, P));
     f->P = P;
-    HIPCHK(ctx, ivf_fill(f->cur, f->k, f->d, f->kt, f->T, f->iperm, f->nmv, w, f->cid, f->v32, f->v16, f->v64,
-                         ctx->stream));
+    HIPCHK(ctx, ivf_fill(f->cur, f->k, f->d, f->kt, f->T, f->iperm, cscan, f->nmv, P, w, f->cid, f->v32, f->v16,
+                         f->v64, ctx->stream));
     f->H = 0;
     if (f->head && H > 0) {
         const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
@@ -445,8 +444,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms) {
             STCHK(dev_alloc(ctx, &f->hval, (size_t)(c * kpad * esz), &f->bytes));
             f->hcap = c;
         }
-        HIPCHK(ctx, head_fill(f->cur, f->k, f->head, f->iperm, kpad, f->kt, head_ktp(f->kt), H, f->pdt == SIVF_BF16,
-                              f->hval, ctx->stream));
+        HIPCHK(ctx, head_fill(hterm, f->seg, f->cid, f->v32, f->v16, f->T, head_ktp(f->kt), H, f->hval, ctx->stream));
         f->H = H;
     }
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
@@ -483,8 +481,9 @@ sivf_status init_impl(sivf_ctx* ctx, const Csr& Xc, int32_t k, const int32_t* in
         H(hipMemcpyAsync(ids, init_ids_host, (size_t)k * 4, hipMemcpyHostToDevice, ctx->stream));
         H(gather_rows(Xc, ids, k, f->cur, lens, ctx->stream, 0));
         H(exclusive_scan_i64(lens, scan, k, sws, ctx->stream));
-        H(hipMemcpyAsync(&total, scan + k, 8, hipMemcpyDeviceToHost, ctx->stream));
+        H(hipMemcpyAsync(ctx->pin, scan + k, 8, hipMemcpyDeviceToHost, ctx->stream));
         H(hipStreamSynchronize(ctx->stream));
+        total = *(const int64_t*)ctx->pin;
     }
     if (st == SIVF_OK) st = store_reserve(ctx, f, &f->cur, total);
     if (st == SIVF_OK) {
@@ -508,7 +507,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
     if (C->val_dtype != SIVF_F64) return fail(ctx, SIVF_E_INVALID, "centroid values must be SIVF_F64");
     if (C->n_rows < 1 || C->n_rows > INT32_MAX) return fail(ctx, SIVF_E_SHAPE, "need 1 <= k <= 2^31-1");
     unsigned long long* flags = nullptr;
-    STCHK(ws(ctx, "vflags", 4, &flags));
+    STCHK(ws(ctx, "vflags", 8, &flags));
     int nonneg = 1;
     STCHK(check_csr(ctx, C, "centroids", flags, &nonneg));
     const int32_t k = (int32_t)C->n_rows;
@@ -517,7 +516,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
     f->nonneg = nonneg;
     sivf_status st = store_reserve(ctx, f, &f->cur, C->nnz);
     if (st == SIVF_OK) {
-        hipError_t e = csr_to_store(C->row_ptr, C->col, (const double*)C->val, k, f->cur, ctx->stream);
+        hipError_t e = csr_to_store(C->row_ptr, C->col, (const double*)C->val, k, C->nnz, f->cur, ctx->stream);
         if (e == hipSuccess)
             e = lambda ? hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, ctx->stream)
                        : fill_u8(f->lam, 0, k, ctx->stream);
@@ -565,7 +564,7 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, int32_t k, int32_t
     STCHK(w.get("fobj", std::max<int64_t>(n, 1), &b->fobj));
     STCHK(w.get("changed", k, &b->changed));
     STCHK(w.get("obj_partial", b->nfin + 1, &b->obj_partial));
-    STCHK(w.get("objective", 2, &b->obj));
+    b->obj = (double*)(b->counters + 12);   // read back with the counters
     if (ctx->opt.exact_objective) STCHK(w.get("obj64_partial", b->nobj, &b->obj64_partial));
     const int64_t m = std::max<int64_t>(n, 1);
     if (b->launches > 1) {
@@ -584,6 +583,14 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, int32_t k, int32_t
     return SIVF_OK;
 }
 
+// Validates X and, where its shape fits the file, the ids in [0, k) with it
+// (nullptr: none).
+sivf_status validate_with_ids(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* f, const int32_t* ids, const char* what,
+                              Csr* out, Work& w) {
+    if (!ids || !X || X->n_cols != f->d) return validate(ctx, X, out, w);
+    return validate(ctx, X, out, w, {{ids, X->n_rows, f->k, what}});
+}
+
 // Assignment step r = iter (Alg. 4) of X against the file f.
 sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, int32_t iter, int32_t* assign_inout,
                         float* own_sim_inout, double* own64_inout, uint8_t* lambda_out, sivf_iter_stats* stats_host) {
@@ -592,7 +599,6 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     const int32_t k = f->k;
     const int relaxed = ctx->opt.filter_mode == SIVF_MODE_RELAXED;
     const int icp_on = iter >= 2 && ctx->opt.filter_mode != SIVF_MODE_IVF;
-    if (iter >= 2) STCHK(check_assign(ctx, assign_inout, n, k, "assign_inout (a^[r-1])", w));
     AssignBufs B;
     STCHK(assign_buffers(ctx, w, n, k, f->T, &B));
     const int64_t qcap = B.qcap;
@@ -680,10 +686,9 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     if (ctx->opt.exact_objective)
         HIPCHK(ctx, objective64(A, f->cur, assign_inout, obj64_partial, nobj, obj + 1, s));
     if (stats_host) {
-        unsigned long long c[12];
-        double o[2] = {0.0, 0.0};
-        HIPCHK(ctx, hipMemcpyAsync(c, counters, sizeof(c), hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipMemcpyAsync(o, obj, sizeof(o), hipMemcpyDeviceToHost, s));
+        const unsigned long long* c = (const unsigned long long*)ctx->pin;
+        const double* o = (const double*)(c + 12);
+        HIPCHK(ctx, hipMemcpyAsync(ctx->pin, counters, 14 * sizeof(*c), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));
         memset(stats_host, 0, sizeof(*stats_host));
         stats_host->iter = iter;
@@ -718,12 +723,9 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     const int32_t k = f->k;
     hipStream_t s = ctx->stream;
     UpdateWs w{};
-    w.nblk = std::max<int64_t>(1, (n + kObjBlock - 1) / kObjBlock);
     w.nslots = upd_fold_groups(ctx->n_cu);
-    STCHK(ws(ctx, "u_hist", w.nblk * (int64_t)k, &w.hist));
     STCHK(ws(ctx, "u_ccount", k, &w.ccount));
     STCHK(ws(ctx, "u_cstart", k + 1, &w.cstart));
-    STCHK(ws(ctx, "u_perm", std::max<int64_t>(n, 1), &w.perm));
     STCHK(ws(ctx, "u_memnnz", k, &w.memnnz));
     STCHK(ws(ctx, "u_ub", k, &w.ub));
     STCHK(ws(ctx, "u_ubscan", k + 1, &w.ubscan));
@@ -733,19 +735,28 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     STCHK(ws(ctx, "u_bigr", kFoldBig, &w.bigr));
     STCHK(ws(ctx, "u_splits", kFoldBig * (kFoldRanges + 1), &w.splits));
     STCHK(ws(ctx, "u_jobs", kFoldBig * kFoldRanges, &w.jobs));
-    STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(std::max<int64_t>(k, f->d * f->T * 2) + 1, n + 1)) + 8,
-             &w.scan_ws));
+    STCHK(ws(ctx, "u_scan", scan_ws_elems(k) + 8, &w.scan_ws));
+    SortWs<float> sw{};
+    STCHK(sort_ws(ctx, "u_sort", n, false, &sw));
     // the accumulators and their marks start zeroed; the kernel leaves them so
     STCHK(ws_zeroed(ctx, "u_W", (int64_t)(w.nslots + kFoldBig) * Xc.d, &w.W));
     STCHK(ws_zeroed(ctx, "u_touched", (int64_t)(w.nslots + kFoldBig) * ((Xc.d + 63) / 64), &w.touched));
-    STCHK(check_assign(ctx, assign, n, k, "assign"));
     HIPCHK(ctx, hipEventRecord(ctx->ev[3], s));
-    HIPCHK(ctx, upd_sort(assign, n, k, Xc.rp, w, s));
+    HIPCHK(ctx, upd_sort(assign, n, k, Xc.rp, sw, &w, s));
     HIPCHK(ctx, upd_bounds(k, Xc.d, Xc.nnz, lambda, 1, f->cur, w, s));
-    int64_t total = 0;
-    HIPCHK(ctx, hipMemcpyAsync(&total, w.ubscan + k, 8, hipMemcpyDeviceToHost, s));
-    HIPCHK(ctx, hipStreamSynchronize(s));
-    STCHK(store_reserve(ctx, f, &f->nxt, total));
+    // room for the new entries: the exact bound is on the device; where the
+    // largest it can be already fits or is small, the host need not wait for it
+    int64_t most = f->P + Xc.nnz;
+    if (f->d < most / k) most = f->d * k;
+    if (!f->nxt.term || f->nxt.cap < most) {
+        if (ctx->opt.workspace_cap_bytes != 0 || most > ((int64_t)4 << 20)) {
+            int64_t* total = (int64_t*)ctx->pin;
+            HIPCHK(ctx, hipMemcpyAsync(total, w.ubscan + k, 8, hipMemcpyDeviceToHost, s));
+            HIPCHK(ctx, hipStreamSynchronize(s));
+            most = *total;
+        }
+        STCHK(store_reserve(ctx, f, &f->nxt, most));
+    }
     HIPCHK(ctx, upd_means(Xc, k, lambda, 1, f->cur, f->nxt, w, f->cnorm, s));
     std::swap(f->cur, f->nxt);
     HIPCHK(ctx, hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, s));
@@ -810,11 +821,12 @@ sivf_status sivf_create(sivf_ctx** out, int device, void* hip_stream, const sivf
         delete ctx;
         return SIVF_E_HIP;
     }
-    for (auto& e : ctx->ev) {
-        if (hipEventCreate(&e) != hipSuccess) {
-            delete ctx;
-            return SIVF_E_HIP;
-        }
+    bool ok = hipHostMalloc(&ctx->pin, kPinBytes, hipHostMallocDefault) == hipSuccess;
+    for (auto& e : ctx->ev) ok = ok && hipEventCreate(&e) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        (void)sivf_destroy(ctx);
+        return SIVF_E_HIP;
     }
     *out = ctx;
     return SIVF_OK;
@@ -827,6 +839,7 @@ sivf_status sivf_destroy(sivf_ctx* ctx) {
     for (auto& kv : ctx->ws) (void)hipFree(kv.second.first);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     delete ctx;
     return SIVF_OK;
 }
@@ -909,8 +922,8 @@ sivf_status sivf_assign(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* f, int
         return fail(ctx, SIVF_E_INVALID, "the RELAXED filter needs own64_inout");
     if (iter < 1) return fail(ctx, SIVF_E_INVALID, "iter must be >= 1");
     Csr Xc;
-    STCHK(validate(ctx, X, &Xc));
     Work w{ctx};
+    STCHK(validate_with_ids(ctx, X, f, iter >= 2 ? assign_inout : nullptr, "assign_inout (a^[r-1])", &Xc, w));
     return assign_impl(ctx, w, Xc, f, iter, assign_inout, own_sim_inout, own64_inout, lambda_out, stats_host);
 }
 
@@ -927,8 +940,7 @@ sivf_status sivf_assign_noalloc(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf
     // the same requests as the run below, counted without memory
     Work m{ctx, Work::kMeasure};
     unsigned long long* flags = nullptr;
-    STCHK(m.get("vflags", 4, &flags));
-    if (iter >= 2) STCHK(m.get("aflags", 2, &flags));
+    STCHK(m.get("vflags", 8, &flags));
     AssignBufs B;
     STCHK(assign_buffers(ctx, m, X->n_rows, f->k, f->T, &B));
     if (m.used > kScratchBytes)
@@ -940,7 +952,7 @@ sivf_status sivf_assign_noalloc(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf
     if (!base) return fail(ctx, SIVF_E_HIP, "no scratch address for device %d", ctx->device);
     Work w{ctx, Work::kFixed, (char*)base, kScratchBytes};
     Csr Xc;
-    STCHK(validate(ctx, X, &Xc, w));
+    STCHK(validate_with_ids(ctx, X, f, iter >= 2 ? assign_inout : nullptr, "assign_inout (a^[r-1])", &Xc, w));
     return assign_impl(ctx, w, Xc, f, iter, assign_inout, own_sim_inout, own64_inout, lambda_out, stats_host);
 }
 
@@ -950,7 +962,8 @@ sivf_status sivf_update(sivf_ctx* ctx, const sivf_csr* X, const int32_t* assign,
     DevGuard g(ctx->device);
     if (!f || !assign || !lambda) return fail(ctx, SIVF_E_INVALID, "NULL argument");
     Csr Xc;
-    STCHK(validate(ctx, X, &Xc));
+    Work w{ctx};
+    STCHK(validate_with_ids(ctx, X, f, assign, "assign", &Xc, w));
     return update_impl(ctx, Xc, assign, lambda, f, stats_host);
 }
 
@@ -1009,16 +1022,21 @@ sivf_status sivf_resume(sivf_ctx* ctx, const sivf_csr* X, const sivf_csr* centro
     if (ctx->opt.filter_mode == SIVF_MODE_RELAXED && !own64_out)
         return fail(ctx, SIVF_E_INVALID, "the RELAXED filter needs own64_out");
     Csr Xc;
-    STCHK(validate(ctx, X, &Xc));
+    const int32_t k = (int32_t)std::min<int64_t>(centroids->n_rows, INT32_MAX);
+    if (X && X->n_cols == centroids->n_cols && k >= 1 && k <= X->n_rows) {
+        if (a_prev2)
+            STCHK(validate(ctx, X, &Xc, {{a_prev, X->n_rows, k, "a_prev"}, {a_prev2, X->n_rows, k, "a_prev2"}}));
+        else
+            STCHK(validate(ctx, X, &Xc, {{a_prev, X->n_rows, k, "a_prev"}}));
+    } else {
+        STCHK(validate(ctx, X, &Xc));
+    }
     if (centroids->n_cols != Xc.d)
         return fail(ctx, SIVF_E_SHAPE, "X has %lld columns, centroids %lld", (long long)Xc.d,
                     (long long)centroids->n_cols);
     if (centroids->n_rows < 1 || centroids->n_rows > Xc.n)
         return fail(ctx, SIVF_E_SHAPE, "need 1 <= k <= N (k=%lld, N=%lld)", (long long)centroids->n_rows,
                     (long long)Xc.n);
-    const int32_t k = (int32_t)centroids->n_rows;
-    STCHK(check_assign(ctx, a_prev, Xc.n, k, "a_prev"));
-    if (a_prev2) STCHK(check_assign(ctx, a_prev2, Xc.n, k, "a_prev2"));
     // lambda of the restart point: membership of every cluster unchanged
     // between the last two assignments (all 0 when only one exists)
     uint8_t *changed = nullptr, *lam = nullptr;
@@ -1078,8 +1096,9 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     HIPCHK(ctx, soft_pack(C, CT, k, Xc.d, s));
     HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, CT, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
     if (loss_host) {
-        HIPCHK(ctx, hipMemcpyAsync(loss_host, loss, sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->pin, loss, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));
+        *loss_host = *(const double*)ctx->pin;
     }
     return SIVF_OK;
 }
@@ -1129,18 +1148,19 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     if (dC_out) {
         STCHK(ws(ctx, "soft_dS", rc * kp, &dS));
         STCHK(ws(ctx, "soft_dCT", kp * d, &dCT));
-        CscWs cw{};
-        for (int b = 0; b < 2; ++b) {
-            STCHK(ws(ctx, b ? "csc_key1" : "csc_key0", Xc.nnz, &cw.key[b]));
-            STCHK(ws(ctx, b ? "csc_row1" : "csc_row0", Xc.nnz, &cw.row[b]));
-            STCHK(ws(ctx, b ? "csc_val1" : "csc_val0", Xc.nnz, &cw.val[b]));
-        }
-        const int64_t table = csc_table_elems(Xc.nnz);
-        STCHK(ws(ctx, "csc_count", table, &cw.count));
-        STCHK(ws(ctx, "csc_start", table, &cw.start));
+        SortWs<float> cw{};
+        STCHK(sort_ws(ctx, "soft", Xc.nnz, true, &cw));
         STCHK(ws(ctx, "csc_ptr", d + 1, &colptr));
-        STCHK(ws(ctx, "scan_ws", scan_ws_elems(table) + 8, &cw.scan_ws));
-        HIPCHK(ctx, build_csc(n, d, Xc.nnz, Xc.rp, Xc.col, (const float*)Xc.val, cw, colptr, &xt_row, &xt_val, s));
+        const int32_t* xt_col = nullptr;
+        SortIn<float> in{};
+        in.kind = kSortCsr;
+        in.n = Xc.nnz;
+        in.key = Xc.col;
+        in.val = (const float*)Xc.val;
+        in.rows = n;
+        in.rp = Xc.rp;
+        HIPCHK(ctx, sort_entries(in, d, cw, &xt_col, &xt_row, &xt_val, s));
+        HIPCHK(ctx, sort_starts(xt_col, Xc.nnz, d, colptr, s));
         // a range of more than kSoftPiece entries has less than one piece per
         // kSoftPiece / 2 entries
         dw.max_pieces = nnz_max / (kSoftPiece / 2);

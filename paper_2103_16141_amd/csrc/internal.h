@@ -19,6 +19,7 @@ static_assert(kTermCap % 64 == 0, "the walk reads staged terms a whole 64-term c
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request
 constexpr int kWalkWaves = 4;      // waves per workgroup in the walk kernels
 constexpr int kMaxTile = 4096;     // largest similarity tile (centroids) per wave
+constexpr size_t kPinBytes = 1024;
 
 // A device CSR that passed validation.
 struct Csr {
@@ -79,6 +80,7 @@ struct WalkArgs {
                                    // [7] relaxed-ICP objects [9] own64 queue length
                                    // [10] bytes requested by the walk's vector loads
                                    // [11] of which 16-byte-per-lane loads
+                                   // [12], [13] the two objectives (double)
                                    // [16 + launch] walk work counters
     int64_t qcap;           // capacity of the candidate queue
     // dense head rows (nullptr head: none)
@@ -137,6 +139,7 @@ struct sivf_ctx {
     size_t bytes_held = 0;
     std::map<std::string, std::pair<void*, size_t>> ws;  // grow-only named workspace
     hipEvent_t ev[8] = {};
+    void* pin = nullptr;   // kPinBytes of pinned host memory the calls read results through
 };
 
 namespace sivf {
@@ -151,7 +154,7 @@ hipError_t fill_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
 hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
-// validation: fills flags[0..3] (cleared first): [0] error bits, [2] any
+// validation: fills flags[0..3] of 8 words (all cleared first): [0] error bits, [2] any
 // negative value, [3] descents inside rows; a matrix is valid iff [0] = [3] = 0
 hipError_t validate_csr(const int64_t* rp, const int32_t* col, const void* val, int f64, int64_t n,
                         int64_t d, int64_t nnz, unsigned long long* flags, hipStream_t s);
@@ -159,20 +162,19 @@ hipError_t validate_csr(const int64_t* rp, const int32_t* col, const void* val, 
 hipError_t validate_csr_rows(const int64_t* rp, const int32_t* col, const void* val, int f64, int64_t n,
                              int64_t d, int64_t nnz, unsigned long long* flags, hipStream_t s);
 
-// flags[0] |= 1 if some a[i] is outside [0, k)
+// *flags |= 1 if some a[i] is outside [0, k)
 hipError_t range_check_i32(const int32_t* a, int64_t n, int32_t k, unsigned long long* flags, hipStream_t s);
 
 // centroid init: gather rows ids[j] of X into store (start must be exclusive scan of lengths)
 hipError_t gather_rows(const Csr& X, const int32_t* ids, int32_t k, Store st, int64_t* lens_out,
                        hipStream_t s, int phase);
 hipError_t centroid_norms(const Store st, int32_t k, double* cnorm, hipStream_t s);
-hipError_t csr_to_store(const int64_t* ptr, const int32_t* col, const double* val, int32_t k,
+hipError_t csr_to_store(const int64_t* ptr, const int32_t* col, const double* val, int32_t k, int64_t nnz,
                         Store st, hipStream_t s);
 
 // structured inverted file
 struct IvfBuildWs {
     unsigned long long* bm;     // [d * W64] centroid-presence bitmap per term
-    unsigned long long* lbits;  // [W64] flag bits
     uint16_t* pre0;             // [d * W64] moving-bit prefix within tile
     uint16_t* pre1;             // [d * W64] invariant-bit prefix within tile
     int64_t* cnt;               // [d * T * 2] (term, tile, part) counts
@@ -181,24 +183,25 @@ struct IvfBuildWs {
 };
 int64_t ivf_w64(int32_t k);
 // positions: moving centroids (flag 0) first, each group in ascending id;
-// mvpre[k] = number of moving centroids
-hipError_t ivf_perm(const uint8_t* lam, int32_t k, int64_t* mv, int64_t* mvpre, int64_t* scan_ws, int32_t* perm,
-                    int32_t* iperm, hipStream_t s);
+// cscan [k + 1]: exclusive scan of nnz; meta [3]: moving centroids, entries, 0
+hipError_t ivf_perm(const uint8_t* lam, int32_t k, const int64_t* nnz, int32_t* perm, int32_t* iperm, int64_t* cscan,
+                    int64_t* meta, hipStream_t s);
 hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,
-                     int32_t n_moving, IvfBuildWs w, hipStream_t s);
-hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t* seg, int32_t* mid, hipStream_t s);
+                     const int64_t* cscan, const int64_t* meta, IvfBuildWs w, hipStream_t s);
+// segment bounds; head rows for terms whose lists hold >= min_len postings
+// (head [d], hterm [rows], meta[2] = rows; head == nullptr: none)
+hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t min_len, int64_t* seg, int32_t* mid, int32_t* head,
+                       int32_t* hterm, int64_t* meta, hipStream_t s);
 hipError_t ivf_fill(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,
-                    int32_t n_moving, IvfBuildWs w, uint16_t* cid, float* v32, uint16_t* v16, double* v64,
-                    hipStream_t s);
-// dense head rows: flag[t] = 1 if term t's lists hold >= min_len postings
-hipError_t head_flags(const int64_t* seg, int64_t d, int32_t T, int64_t min_len, int64_t* flag, hipStream_t s);
+                    const int64_t* cscan, int32_t n_moving, int64_t P, IvfBuildWs w, uint16_t* cid, float* v32,
+                    uint16_t* v16, double* v64, hipStream_t s);
 hipError_t seg_records(const int64_t* seg, const int32_t* mid, const int32_t* head, int64_t d, int32_t T, uint4* rec,
                        hipStream_t s);
-hipError_t head_index(const int64_t* flag, const int64_t* scan, int64_t d, int32_t* head, hipStream_t s);
 // head-row slots per tile: kt rounded up to whole 512-centroid batches
 inline int32_t head_ktp(int32_t kt) { return (kt + 511) & ~511; }
-hipError_t head_fill(const Store st, int32_t k, const int32_t* head, const int32_t* iperm, int64_t kpad, int32_t kt,
-                     int32_t ktp, int64_t H, int pdt_bf16, void* hval, hipStream_t s);
+// the H head rows (v16 when not nullptr, else v32) from the filled lists
+hipError_t head_fill(const int32_t* hterm, const int64_t* seg, const uint16_t* cid, const float* v32,
+                     const uint16_t* v16, int32_t T, int32_t ktp, int64_t H, void* hval, hipStream_t s);
 hipError_t ivf_export(const sivf_ivf* f, int64_t* term_ptr, int32_t* split, int32_t* p_cid, double* p_val,
                       int64_t* ws_counts, int64_t* scan_ws, hipStream_t s);
 hipError_t store_export(const Store st, int32_t k, const int64_t* c_ptr, int32_t* c_col, double* c_val,
@@ -233,14 +236,13 @@ hipError_t resume_own(const WalkArgs& a, const Store st, const int32_t* assign, 
 
 // update
 constexpr int kFoldTile = 4096;     // nonzeros a workgroup sorts and sums at a time
-constexpr int kFoldBigTiles = 8;    // clusters of at least as many tiles are cut into term ranges
+constexpr int kFoldBigTiles = 2;    // clusters of at least as many tiles are cut into term ranges
 constexpr int kFoldRanges = 32;     // ranges of such a cluster, at most
 constexpr int kFoldBig = 1024;      // such clusters, at most (the others are summed whole)
 struct UpdateWs {
-    int64_t* hist;      // [nblk * k] per object-block cluster counts -> offsets
     int64_t* ccount;    // [k] cluster sizes
-    int64_t* cstart;    // [k + 1] exclusive scan of sizes
-    int32_t* perm;      // [n] objects sorted by cluster (ascending id inside)
+    int64_t* cstart;    // [k + 1] first member of each cluster in perm
+    const int32_t* perm;   // [n] objects sorted by cluster (ascending id inside)
     int64_t* memnnz;    // [k] sum of member row lengths
     int64_t* ub;        // [k] entry bound per cluster
     int64_t* ubscan;    // [k + 1] exclusive scan of ub
@@ -254,10 +256,12 @@ struct UpdateWs {
     int64_t* scan_ws;
     unsigned long long* work; // [3] member sums: next job, clusters cut into ranges, their ranges
     int nslots;         // workgroups of the member sums
-    int64_t nblk;
 };
-constexpr int kObjBlock = 4096;
-hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, UpdateWs w, hipStream_t s);
+template <typename V>
+struct SortWs;
+// sorts the objects (n > 0) by cluster: perm, cstart, ccount, memnnz of *w
+hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, const SortWs<float>& sw, UpdateWs* w,
+                    hipStream_t s);
 hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
                       UpdateWs w, hipStream_t s);
 int upd_fold_groups(int n_cu);   // workgroups (and accumulator rows) of the member sums

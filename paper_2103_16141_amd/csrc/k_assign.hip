@@ -1009,9 +1009,12 @@ hipError_t finalize_assign(int64_t n, int iter, const int32_t* a_new, const floa
     return hipGetLastError();
 }
 
-__global__ void k_finalize_lambda(int32_t k, int iter, const uint8_t* __restrict__ changed, uint8_t* __restrict__ lam,
-                                  unsigned long long* __restrict__ counters, const double* __restrict__ obj_partial,
-                                  int nblk, double* __restrict__ obj_out) {
+__global__ __launch_bounds__(256) void k_finalize_lambda(int32_t k, int iter, const uint8_t* __restrict__ changed,
+                                                         uint8_t* __restrict__ lam,
+                                                         unsigned long long* __restrict__ counters,
+                                                         const double* __restrict__ obj_partial, int nblk,
+                                                         double* __restrict__ obj_out) {
+    __shared__ double sh[4];
     const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     bool inv = false;
     if (j < k) {
@@ -1020,10 +1023,14 @@ __global__ void k_finalize_lambda(int32_t k, int iter, const uint8_t* __restrict
     }
     const int64_t c = wave_sum_i64(inv ? 1 : 0);
     if ((threadIdx.x & 63) == 0 && c) atomicAdd(&counters[6], (unsigned long long)c);
-    if (j == 0) {
+    if (blockIdx.x == 0) {
+        // a fixed order: every 256th partial sum, then a fixed tree
         double t = 0.0;
-        for (int b = 0; b < nblk; ++b) t = t + obj_partial[b];
-        *obj_out = t;
+        for (int b = threadIdx.x; b < nblk; b += 256) t = t + obj_partial[b];
+        t = wave_sum_f64(t);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = t;
+        __syncthreads();
+        if (threadIdx.x == 0) *obj_out = (sh[0] + sh[1]) + (sh[2] + sh[3]);
     }
 }
 

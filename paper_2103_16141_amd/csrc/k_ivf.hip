@@ -32,145 +32,213 @@ namespace sivf {
 int64_t ivf_w64(int32_t k) { return ((int64_t)k + 63) / 64; }
 
 // ---------------------------------------------------------------- positions
-__global__ void k_perm_flags(const uint8_t* __restrict__ lam, int32_t k, int64_t* __restrict__ mv) {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j < k) mv[j] = (lam && lam[j]) ? 0 : 1;
+// One workgroup: position of every centroid (moving ones first, each group in
+// ascending id), cscan = exclusive scan of the centroids' entry counts, and
+// meta[0] = moving centroids, meta[1] = entries, meta[2] = 0 (head rows so far).
+__global__ __launch_bounds__(1024) void k_ivf_perm(const uint8_t* __restrict__ lam, int32_t k,
+                                                   const int64_t* __restrict__ nnz, int32_t* __restrict__ perm,
+                                                   int32_t* __restrict__ iperm, int64_t* __restrict__ cscan,
+                                                   int64_t* __restrict__ meta) {
+    __shared__ int32_t sm[2][16];
+    __shared__ int64_t sn[2][16];
+    __shared__ int32_t stot[16];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int32_t moving = 0;
+    for (int64_t j = threadIdx.x; j < k; j += 1024) moving += lam[j] ? 0 : 1;
+    moving = (int32_t)wave_sum_i64(moving);
+    if (lane == 0) stot[wid] = moving;
+    __syncthreads();
+    int32_t nm = 0;
+    for (int w = 0; w < 16; ++w) nm += stot[w];
+    int32_t mcarry = 0;
+    int64_t ncarry = 0;
+    int buf = 0;
+    for (int64_t b = 0; b < k; b += 1024, buf ^= 1) {
+        const int64_t j = b + threadIdx.x;
+        const bool mv = j < k && !lam[j];
+        const int64_t n = j < k ? nnz[j] : 0;
+        const unsigned long long mm = ballot(mv);
+        const int64_t inc = wave_incl_scan_i64(n);
+        if (lane == 63) {
+            sm[buf][wid] = __popcll(mm);
+            sn[buf][wid] = inc;
+        }
+        __syncthreads();
+        int32_t before = mcarry + lanes_below(mm);
+        int64_t nb = ncarry + inc - n;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wid) {
+                before += sm[buf][w];
+                nb += sn[buf][w];
+            }
+            mcarry += sm[buf][w];
+            ncarry += sn[buf][w];
+        }
+        if (j < k) {
+            const int32_t q = mv ? before : nm + (int32_t)(j - before);
+            iperm[j] = q;
+            perm[q] = (int32_t)j;
+            cscan[j] = nb;
+        }
+    }
+    if (threadIdx.x == 0) {
+        cscan[k] = ncarry;
+        meta[0] = nm;
+        meta[1] = ncarry;
+        meta[2] = 0;
+    }
 }
 
-// mvpre = exclusive scan of the moving flags; n_moving = mvpre[k]
-__global__ void k_perm_fill(const uint8_t* __restrict__ lam, int32_t k, const int64_t* __restrict__ mvpre,
-                            int32_t* __restrict__ perm, int32_t* __restrict__ iperm) {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (j >= k) return;
-    const int64_t nm = mvpre[k];
-    const int64_t q = (lam && lam[j]) ? nm + (j - mvpre[j]) : mvpre[j];
-    iperm[j] = (int32_t)q;
-    perm[q] = (int32_t)j;
-}
-
-hipError_t ivf_perm(const uint8_t* lam, int32_t k, int64_t* mv, int64_t* mvpre, int64_t* scan_ws, int32_t* perm,
-                    int32_t* iperm, hipStream_t s) {
-    const unsigned blocks = (unsigned)(((int64_t)k + 255) / 256);
-    hipLaunchKernelGGL(k_perm_flags, dim3(blocks), dim3(256), 0, s, lam, k, mv);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = exclusive_scan_i64(mv, mvpre, k, scan_ws, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_perm_fill, dim3(blocks), dim3(256), 0, s, lam, k, mvpre, perm, iperm);
+hipError_t ivf_perm(const uint8_t* lam, int32_t k, const int64_t* nnz, int32_t* perm, int32_t* iperm, int64_t* cscan,
+                    int64_t* meta, hipStream_t s) {
+    hipLaunchKernelGGL(k_ivf_perm, dim3(1), dim3(1024), 0, s, lam, k, nnz, perm, iperm, cscan, meta);
     return hipGetLastError();
 }
 
-__global__ void k_ivf_bits(Store st, int32_t k, int64_t d, const int32_t* __restrict__ iperm,
-                           unsigned long long* __restrict__ bm) {
+// Calls f(centroid j, entry address) for the entries of all centroids in pieces
+// of kPiece consecutive ones per wave, wherever the centroids begin.  (A wave
+// per centroid left 1,000 waves with 30,000 entries each: presence bits 0.57,
+// file fill 2.07 ms at k = 1,000, D = 100,000; 0.25 and 1.14 in pieces.)
+constexpr int kPiece = 256;
+
+template <typename F>
+__device__ inline void each_entry(const Store& st, int32_t k, const int64_t* __restrict__ cscan, F f) {
     const int lane = threadIdx.x & 63;
+    const int64_t n = cscan[k], nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t j = wave; j < k; j += nw) {
-        const int64_t b = st.start[j], m = st.nnz[j];
-        const int64_t q = iperm[j];
-        unsigned long long* row = bm + (q >> 6) * d;
-        const unsigned long long bit = 1ull << (q & 63);
-        for (int64_t p = lane; p < m; p += 64) {
-            const int32_t t = st.term[b + p];
-            if (t >= 0 && t < d) atomicOr(&row[t], bit);
+    for (int64_t p0 = wave * kPiece; p0 < n; p0 += nw * kPiece) {
+        const int64_t p1 = min(n, p0 + kPiece);
+        int64_t lo = 0, hi = k - 1;   // last centroid starting at or before p0
+        while (lo < hi) {
+            const int64_t mid = (lo + hi + 1) >> 1;
+            if (cscan[mid] <= p0) lo = mid;
+            else hi = mid - 1;
+        }
+        for (int64_t j = lo; j < k && cscan[j] < p1; ++j) {
+            const int64_t a = max(p0, cscan[j]), e = min(p1, cscan[j + 1]), b = st.start[j] - cscan[j];
+            if (a < e) f(j, b + a, b + e, lane);
         }
     }
 }
 
-// invariant bits by position: positions n_moving .. k-1
-__global__ void k_lam_bits(int32_t k, int32_t n_moving, unsigned long long* __restrict__ lbits) {
-    int64_t w = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (w >= ((int64_t)k + 63) / 64) return;
-    unsigned long long m = 0;
-    for (int b = 0; b < 64; ++b) {
-        int64_t q = w * 64 + b;
-        if (q < k && q >= n_moving) m |= 1ull << b;
-    }
-    lbits[w] = m;
+__global__ __launch_bounds__(256) void k_ivf_bits(Store st, int32_t k, int64_t d, const int64_t* __restrict__ cscan,
+                                                  const int32_t* __restrict__ iperm,
+                                                  unsigned long long* __restrict__ bm) {
+    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int lane) {
+        const int64_t q = iperm[j];
+        unsigned long long* row = bm + (q >> 6) * d;
+        const unsigned long long bit = 1ull << (q & 63);
+        for (int64_t p = a + lane; p < e; p += 64) {
+            const int32_t t = st.term[p];
+            if (t >= 0 && t < d) atomicOr(&row[t], bit);
+        }
+    });
+}
+
+// the moving positions (below n_moving) among word w's 64
+__device__ inline unsigned long long moving_bits(int64_t w, int64_t n_moving) {
+    const int64_t left = n_moving - w * 64;
+    return left >= 64 ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
 }
 
 // One thread per (tile, term): per-word prefix counts inside the tile and the
 // segment's part sizes.
-__global__ void k_ivf_counts(const unsigned long long* __restrict__ bm, const unsigned long long* __restrict__ lbits,
+__global__ void k_ivf_counts(const unsigned long long* __restrict__ bm, const int64_t* __restrict__ meta,
                              int64_t d, int32_t kt, int32_t T, int64_t W64, uint16_t* __restrict__ pre0,
                              uint16_t* __restrict__ pre1, int64_t* __restrict__ cnt) {
     int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (idx >= d * T) return;
-    const int64_t tile = idx / d, t = idx - tile * d;
+    const int64_t tile = idx / d, t = idx - tile * d, nm = meta[0];
     const int64_t w0 = tile * (kt / 64);
     int64_t w1 = w0 + kt / 64;
     if (w1 > W64) w1 = W64;
     uint32_t c0 = 0, c1 = 0;
     for (int64_t w = w0; w < w1; ++w) {
-        unsigned long long m = bm[w * d + t];
-        unsigned long long lb = lbits[w];
+        const unsigned long long m = bm[w * d + t], mv = moving_bits(w, nm);
         pre0[w * d + t] = (uint16_t)c0;
         pre1[w * d + t] = (uint16_t)c1;
-        c0 += __popcll(m & ~lb);
-        c1 += __popcll(m & lb);
+        c0 += __popcll(m & mv);
+        c1 += __popcll(m & ~mv);
     }
     cnt[(t * T + tile) * 2 + 0] = c0;
     cnt[(t * T + tile) * 2 + 1] = c1;
 }
 
+static unsigned entry_grid(int64_t bound) {
+    return (unsigned)std::min<int64_t>(16384, std::max<int64_t>(1, (bound + 4 * kPiece - 1) / (4 * kPiece)));
+}
+
 hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,
-                     int32_t n_moving, IvfBuildWs w, hipStream_t s) {
+                     const int64_t* cscan, const int64_t* meta, IvfBuildWs w, hipStream_t s) {
     const int64_t W64 = ivf_w64(k);
     hipError_t e = fill_u64(w.bm, 0ull, W64 * d, s);
     if (e != hipSuccess) return e;
-    int64_t blocks = ((int64_t)k * 64 + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_ivf_bits, dim3((unsigned)blocks), dim3(256), 0, s, st, k, d, iperm, w.bm);
-    hipLaunchKernelGGL(k_lam_bits, dim3((unsigned)((W64 + 255) / 256)), dim3(256), 0, s, k, n_moving, w.lbits);
+    hipLaunchKernelGGL(k_ivf_bits, dim3(entry_grid(st.cap)), dim3(256), 0, s, st, k, d, cscan, iperm, w.bm);
     int64_t nt = d * T;
-    hipLaunchKernelGGL(k_ivf_counts, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.bm, w.lbits, d, kt, T,
-                       W64, w.pre0, w.pre1, w.cnt);
+    hipLaunchKernelGGL(k_ivf_counts, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.bm, meta, d, kt, T, W64,
+                       w.pre0, w.pre1, w.cnt);
     return hipGetLastError();
 }
 
-__global__ void k_ivf_seg(const int64_t* __restrict__ off, const int64_t* __restrict__ cnt, int64_t d, int32_t T,
-                          int64_t* __restrict__ seg, int32_t* __restrict__ mid) {
-    int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    int64_t nt = d * T;
+// Segment bounds, and the dense head rows: a term whose lists hold at least
+// min_len postings gets the next row (head[t], hterm[row]; the rows' order is
+// that of the atomics and changes no result).  head == nullptr: no rows.
+__global__ __launch_bounds__(256) void k_ivf_seg(const int64_t* __restrict__ off, const int64_t* __restrict__ cnt,
+                                                 int64_t d, int32_t T, int64_t min_len, int64_t* __restrict__ seg,
+                                                 int32_t* __restrict__ mid, int32_t* __restrict__ head,
+                                                 int32_t* __restrict__ hterm, int64_t* __restrict__ meta) {
+    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t nt = d * T;
     if (idx < nt) {
         seg[idx] = off[idx * 2];
         mid[idx] = (int32_t)cnt[idx * 2];
     } else if (idx == nt) {
         seg[nt] = off[nt * 2];
     }
+    if (!head) return;
+    const bool term = idx < d;
+    const bool hd = term && off[(idx + 1) * T * 2] - off[idx * T * 2] >= min_len;
+    const unsigned long long m = ballot(hd);
+    int64_t row = 0;
+    if (m) {
+        if (lanes_below(m) == 0 && hd) row = (int64_t)atomicAdd((unsigned long long*)&meta[2], (unsigned long long)__popcll(m));
+        row = bcast_i64(row, __builtin_ctzll(m)) + lanes_below(m);
+    }
+    if (term) head[idx] = hd ? (int32_t)row : -1;
+    if (hd) hterm[row] = (int32_t)idx;
 }
 
-hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t* seg, int32_t* mid, hipStream_t s) {
+hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t min_len, int64_t* seg, int32_t* mid, int32_t* head,
+                       int32_t* hterm, int64_t* meta, hipStream_t s) {
     const int64_t n = d * T * 2;
     hipError_t e = exclusive_scan_i64(w.cnt, w.off, n, w.scan_ws, s);
     if (e != hipSuccess) return e;
     int64_t nt = d * T + 1;
-    hipLaunchKernelGGL(k_ivf_seg, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.off, w.cnt, d, T, seg, mid);
+    hipLaunchKernelGGL(k_ivf_seg, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.off, w.cnt, d, T, min_len, seg,
+                       mid, head, hterm, meta);
     return hipGetLastError();
 }
 
-__global__ void k_ivf_fill(Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* __restrict__ iperm,
-                           int32_t n_moving,
-                           const unsigned long long* __restrict__ bm, const unsigned long long* __restrict__ lbits,
-                           const uint16_t* __restrict__ pre0, const uint16_t* __restrict__ pre1,
-                           const int64_t* __restrict__ off, uint16_t* __restrict__ cid, float* __restrict__ v32,
-                           uint16_t* __restrict__ v16, double* __restrict__ v64) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t j = wave; j < k; j += nw) {
+__global__ __launch_bounds__(256) void k_ivf_fill(Store st, int32_t k, int64_t d, int32_t kt, int32_t T,
+                                                  const int64_t* __restrict__ cscan,
+                                                  const int32_t* __restrict__ iperm, int32_t n_moving,
+                                                  const unsigned long long* __restrict__ bm,
+                                                  const uint16_t* __restrict__ pre0, const uint16_t* __restrict__ pre1,
+                                                  const int64_t* __restrict__ off, uint16_t* __restrict__ cid,
+                                                  float* __restrict__ v32, uint16_t* __restrict__ v16,
+                                                  double* __restrict__ v64) {
+    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int lane) {
         const int64_t q = iperm[j];
         const int part = q >= n_moving ? 1 : 0;
         const int64_t tile = q / kt, w = q >> 6;
-        const unsigned long long below = (1ull << (q & 63)) - 1ull;
-        const unsigned long long pm = part ? lbits[w] : ~lbits[w];
+        const unsigned long long mv = moving_bits(w, n_moving);
+        const unsigned long long pm = (part ? ~mv : mv) & ((1ull << (q & 63)) - 1ull);
         const uint16_t* pre = part ? pre1 : pre0;
         const uint16_t local = (uint16_t)(q - tile * kt);
-        const int64_t b = st.start[j], m = st.nnz[j];
-        for (int64_t p = lane; p < m; p += 64) {
-            const int64_t t = st.term[b + p];
-            const double u = st.val[b + p];
-            const int64_t rank = pre[w * d + t] + __popcll(bm[w * d + t] & pm & below);
+        for (int64_t p = a + lane; p < e; p += 64) {
+            const int64_t t = st.term[p];
+            const double u = st.val[p];
+            const int64_t rank = pre[w * d + t] + __popcll(bm[w * d + t] & pm);
             const int64_t pos = off[(t * T + tile) * 2 + part] + rank;
             cid[pos] = local;
             const float f = (float)u;  // round to nearest even
@@ -178,16 +246,14 @@ __global__ void k_ivf_fill(Store st, int32_t k, int64_t d, int32_t kt, int32_t T
             if (v16) v16[pos] = f32_to_bf16_rne(f);
             v64[pos] = u;
         }
-    }
+    });
 }
 
 hipError_t ivf_fill(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,
-                    int32_t n_moving, IvfBuildWs w, uint16_t* cid, float* v32, uint16_t* v16, double* v64,
-                    hipStream_t s) {
-    int64_t blocks = ((int64_t)k * 64 + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_ivf_fill, dim3((unsigned)blocks), dim3(256), 0, s, st, k, d, kt, T, iperm, n_moving, w.bm,
-                       w.lbits, w.pre0, w.pre1, w.off, cid, v32, v16, v64);
+                    const int64_t* cscan, int32_t n_moving, int64_t P, IvfBuildWs w, uint16_t* cid, float* v32,
+                    uint16_t* v16, double* v64, hipStream_t s) {
+    hipLaunchKernelGGL(k_ivf_fill, dim3(entry_grid(P)), dim3(256), 0, s, st, k, d, kt, T, cscan, iperm, n_moving, w.bm,
+                       w.pre0, w.pre1, w.off, cid, v32, v16, v64);
     return hipGetLastError();
 }
 
@@ -208,46 +274,33 @@ __device__ inline int32_t tile_slot(int32_t c, bool bf16) {
     return (c & ~511) + 8 * ((i & 255) >> 2) + 4 * (i >> 8) + (i & 3);
 }
 
-__device__ inline int64_t head_slot(int32_t j, int32_t kt, int32_t ktp, bool bf16) {
-    const int32_t tile = j / kt, jj = j - tile * kt;
-    return (int64_t)tile * ktp + tile_slot(jj, bf16);
-}
-__global__ void k_head_flags(const int64_t* __restrict__ seg, int64_t d, int32_t T, int64_t min_len,
-                             int64_t* __restrict__ flag) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= d) return;
-    flag[t] = (seg[(t + 1) * T] - seg[t * T] >= min_len) ? 1 : 0;
-}
-
-__global__ void k_head_index(const int64_t* __restrict__ flag, const int64_t* __restrict__ scan, int64_t d,
-                             int32_t* __restrict__ head) {
-    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= d) return;
-    head[t] = flag[t] ? (int32_t)scan[t] : -1;
-}
-
-__global__ void k_head_zero(uint32_t* __restrict__ w, int64_t nw) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nw; i += stride) w[i] = 0u;
-}
-
-// one wave per centroid: scatter its head-term values into the rows
-__global__ void k_head_scatter(Store st, int32_t k, const int32_t* __restrict__ head, const int32_t* __restrict__ iperm,
-                               int64_t kpad, int32_t kt, int32_t ktp, float* __restrict__ h32,
-                               uint16_t* __restrict__ h16) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    for (int64_t j = wave; j < k; j += nw) {
-        const int64_t b = st.start[j], m = st.nnz[j];
-        for (int64_t p = lane; p < m; p += 64) {
-            const int32_t r = head[st.term[b + p]];
-            if (r >= 0) {
-                const float f = (float)st.val[b + p];  // round to nearest even
-                if (h32) h32[r * kpad + head_slot(iperm[j], kt, ktp, false)] = f;
-                else h16[r * kpad + head_slot(iperm[j], kt, ktp, true)] = f32_to_bf16_rne(f);
-            }
-        }
+// One workgroup per (row, tile): the tile's postings of the row's term are
+// placed in LDS over zeros and the whole slice is written once, in order.
+// (Zeroing all rows and scattering the centroids' entries into them, one write
+// each: 0.74 ms at k = 1,000, D = 100,000; 0.015 now.)
+__global__ __launch_bounds__(256) void k_head_rows(const int32_t* __restrict__ hterm, const int64_t* __restrict__ seg,
+                                                   const uint16_t* __restrict__ cid, const float* __restrict__ v32,
+                                                   const uint16_t* __restrict__ v16, int32_t T, int32_t ktp,
+                                                   void* __restrict__ hval) {
+    __shared__ float slot[kMaxTile];
+    const int64_t r = blockIdx.x / T;
+    const int tile = (int)(blockIdx.x - r * T);
+    const int64_t t = hterm[r];
+    const int64_t lo = seg[t * T + tile], hi = seg[t * T + tile + 1];
+    for (int c = threadIdx.x; c < ktp; c += 256) slot[c] = 0.0f;
+    __syncthreads();
+    // slots hold the posting's bits: binary32, or bf16 in the low half
+    for (int64_t p = lo + threadIdx.x; p < hi; p += 256)
+        slot[tile_slot(cid[p], v16 != nullptr)] = v16 ? __uint_as_float(v16[p]) : v32[p];
+    __syncthreads();
+    const int64_t base = (r * T + tile) * ktp;
+    if (v16) {
+        uint32_t* out = (uint32_t*)hval + base / 2;
+        for (int c = threadIdx.x; c < ktp / 2; c += 256)
+            out[c] = __float_as_uint(slot[2 * c]) | (__float_as_uint(slot[2 * c + 1]) << 16);
+    } else {
+        float* out = (float*)hval + base;
+        for (int c = threadIdx.x; c < ktp; c += 256) out[c] = slot[c];
     }
 }
 
@@ -280,30 +333,15 @@ hipError_t seg_records(const int64_t* seg, const int32_t* mid, const int32_t* he
     return hipGetLastError();
 }
 
-hipError_t head_flags(const int64_t* seg, int64_t d, int32_t T, int64_t min_len, int64_t* flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_head_flags, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, seg, d, T, min_len, flag);
-    return hipGetLastError();
-}
-
-hipError_t head_index(const int64_t* flag, const int64_t* scan, int64_t d, int32_t* head, hipStream_t s) {
-    hipLaunchKernelGGL(k_head_index, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, flag, scan, d, head);
-    return hipGetLastError();
-}
-
-hipError_t head_fill(const Store st, int32_t k, const int32_t* head, const int32_t* iperm, int64_t kpad, int32_t kt,
-                     int32_t ktp, int64_t H, int pdt_bf16, void* hval, hipStream_t s) {
-    const int64_t bytes = H * kpad * (pdt_bf16 ? 2 : 4);
-    const int64_t nw = (bytes + 3) / 4;
-    if (nw == 0) return hipSuccess;
-    int64_t zb = (nw + 255) / 256;
-    if (zb > 65536) zb = 65536;
-    hipLaunchKernelGGL(k_head_zero, dim3((unsigned)zb), dim3(256), 0, s, (uint32_t*)hval, nw);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    int64_t blocks = ((int64_t)k * 64 + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    hipLaunchKernelGGL(k_head_scatter, dim3((unsigned)blocks), dim3(256), 0, s, st, k, head, iperm, kpad, kt, ktp,
-                       pdt_bf16 ? nullptr : (float*)hval, pdt_bf16 ? (uint16_t*)hval : nullptr);
+hipError_t head_fill(const int32_t* hterm, const int64_t* seg, const uint16_t* cid, const float* v32,
+                     const uint16_t* v16, int32_t T, int32_t ktp, int64_t H, void* hval, hipStream_t s) {
+    // at most 2^31 - 1 workgroups a launch
+    const int64_t most = ((int64_t)1 << 30) / T;
+    for (int64_t r = 0; r < H; r += most) {
+        const int64_t n = std::min(most, H - r);
+        void* to = v16 ? (void*)((uint16_t*)hval + r * T * ktp) : (void*)((float*)hval + r * T * ktp);
+        hipLaunchKernelGGL(k_head_rows, dim3((unsigned)(n * T)), dim3(256), 0, s, hterm + r, seg, cid, v32, v16, T, ktp, to);
+    }
     return hipGetLastError();
 }
 

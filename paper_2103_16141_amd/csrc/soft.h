@@ -26,21 +26,6 @@ hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const 
 hipError_t soft_bwd_rows(int64_t c0, int64_t c1, int64_t p0, int64_t p1, const int64_t* rp, const int32_t* col,
                          const float* xv, const float* CT, int64_t d, int32_t k, float tau, float grad,
                          const float* lse, float* dS, float* dxp, float* dxv, int n_cu, hipStream_t s);
-// workspace of the column copy: two buffers of nonzeros, the digit counts of
-// every tile and their scan (csc_table_elems each)
-struct CscWs {
-    int32_t* key[2];
-    int32_t* row[2];
-    float* val[2];
-    int64_t* count;
-    int64_t* start;
-    int64_t* scan_ws;
-};
-int64_t csc_table_elems(int64_t nnz);
-// column t's entries are (*rows, *vals)[colptr[t] .. colptr[t + 1]), rows
-// ascending; *rows and *vals point into w (nnz > 0)
-hipError_t build_csc(int64_t N, int64_t d, int64_t nnz, const int64_t* rp, const int32_t* col, const float* xv,
-                     CscWs w, int64_t* colptr, const int32_t** rows, const float** vals, hipStream_t s);
 // out[j] = rp[min(j * rc, n)] for j in [0, nch]: the nonzero offsets of the row chunks
 hipError_t soft_chunk_offsets(const int64_t* rp, int64_t n, int64_t rc, int64_t nch, int64_t* out, hipStream_t s);
 // workspace of the dC pass of one chunk of rows

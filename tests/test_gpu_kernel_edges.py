@@ -100,6 +100,8 @@ _MEMBERS = {
     # 8 tiles and more: term ranges side by side; the first has a term in every row
     "cut into ranges": ([64] * 512, 600),
     "just too small to cut": ([64] * 511 + [63], 600),
+    "two tiles exactly, cut": ([64] * 128, 600),
+    "two tiles less one, whole": ([64] * 127 + [63], 600),
     "more members than enter a tile, cut": ([40] * 1500 + [0, 700, 4099], 5000),
 }
 
@@ -256,3 +258,30 @@ def test_assignment_of_batches_on_both_sides_of_the_work_shares(posting, k):
     assert total == m
     pa, po, _ = run(0, 40_961)
     assert torch.equal(pa, a[:40_961]) and torch.equal(po, own[:40_961])
+
+
+# ---------------------------------------------------------------- structured file
+@pytest.mark.parametrize("k,d", [(1, 3), (63, 400), (64, 8191), (65, 8192), (1023, 8193), (1024, 300), (1025, 300),
+                                 (2049, 700), (17_000, 90)])
+@pytest.mark.parametrize("posting", ["fp32", "bf16"])
+def test_file_of_centroids_at_the_piece_and_scan_edges(k, d, posting):
+    # entries are handled 256 at a time wherever the centroids begin, positions
+    # 1,024 centroids at a time, scans of up to 16,384 elements in one
+    # workgroup; centroids of 0, 1, 255 .. 257 and all entries, random flags
+    log("file k=%d d=%d %s" % (k, d, posting))
+    rng = np.random.default_rng(k + d)
+    lens = np.minimum(np.resize([0, 1, 255, 256, 257, 7, 40, d], k), d)
+    if k > 2000:
+        lens = np.minimum(lens, 40)
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(d, m, replace=False)) for m in lens] + [np.zeros(0)]).astype(np.int32)
+    val = rng.standard_normal(len(col))
+    lam = (rng.random(k) < 0.4).astype(np.uint8)
+    ctx = _ctx(posting_dtype=posting)
+    ivf = ctx.build_centroid_ivf(*[torch.from_numpy(x).to(device()) for x in (ptr, col, val)], d,
+                                 torch.from_numpy(lam).to(device()))
+    ex = {m: t.cpu().numpy() for m, t in ivf.export().items()}
+    ref = oracle.build_ivf(oracle.Centroids(k, d, ptr, col, val), lam)
+    assert np.array_equal(ex["c_ptr"], ptr) and np.array_equal(ex["c_col"], col) and np.array_equal(ex["c_val"], val)
+    assert np.array_equal(ex["term_ptr"], ref.term_ptr) and np.array_equal(ex["split"], ref.split)
+    assert np.array_equal(ex["p_cid"], ref.cid) and np.array_equal(ex["p_val"], ref.val)

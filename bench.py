@@ -32,7 +32,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 N_CU, CLOCK_GHZ = 256, 2.4   # MI355X compute units and peak engine clock
 POSTING_BYTES = {"fp32": 6, "bf16": 4}  # 2-byte centroid id + value
-WALK_KERNEL = "k_walk_fast<false, false, false>"   # FP32 postings, SIVF filter
+# FP32 postings, SIVF filter, split walk; a launch is one of each per tile
+WALK_KERNEL = "k_walk_dense + k_walk_fast<false, false, false, true>"
 # bytes the walk's L2 sends toward memory, from calibrated rocprofv3 --pmc
 # runs; used only while the kernel sources still hash the same
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "walk_8m_k10k_dram_traffic.md")
@@ -386,7 +387,8 @@ def main():
     if not args.skip_cpu:
         cpu = cpu_baseline(corpus, ids, k, args.cpu_budget)
 
-    # the walk is one kernel launch per group of tiles_per_launch centroid tiles
+    # the walk is one launch per group of tiles_per_launch centroid tiles (and
+    # range of objects, where it is split)
     launches = s32["walk_launches"]
     launch_ms = s32["walk_s"] * 1e3 / launches
     # Roofline of the walk: the vector memory data path.  Its peak is what the

@@ -295,6 +295,28 @@ void choose_tiles(const sivf_ctx* ctx, int32_t k, int32_t* kt, int32_t* T) {
     *T = (k + want - 1) / want;
 }
 
+// The split walk reads the head rows faster than the plain one, but moves a sum
+// per object and slot through memory and takes three launches per range and
+// tile.  FP32 postings only (BF16 rows are half the bytes, and the plain walk
+// reads them faster: 500,000 objects, k = 10,000, 42 against 67 ms), not for
+// IVF-CBICP (it walks lists), not with a workspace cap (it needs up to 4 GiB) or
+// several tiles per launch.  It reads more rows than the plain walk, down to
+// 0.6 of head_density: 2,000,000 objects, k = 10,000, 228 ms at 1.0, 212 at
+// 0.6, 210 at 0.4; 1,000,000, k = 1,000, 14.2, 13.4 and 13.6.
+constexpr double kSplitDensity = 0.6;
+
+bool split_possible(const sivf_options& o) {
+    return o.posting_dtype == SIVF_F32 && o.filter_mode != SIVF_MODE_CBICP && o.workspace_cap_bytes == 0 &&
+           o.tiles_per_launch <= 1 && o.head_density > 0.0f;
+}
+
+// It needs rows and objects enough.  Rows (k = 10,000, 500,000 objects, plain
+// and split): 73 rows 41 and 51 ms, 1,219 rows 58 and 55; 2,000,000 objects,
+// 2,082 rows 242 and 212.  Rows x objects (k = 1,000): 11,000 rows with 8,192
+// objects 0.20 and 0.25 ms, 16,384 0.37 and 0.35, 1,000,000 19.3 and 12.9;
+// 1,800 rows with 65,536 objects 0.95 and 0.97, 131,072 1.80 and 1.70.
+bool split_pays(int64_t rows, int64_t objects) { return rows >= 1024 && objects >= (1 << 27) / rows; }
+
 // ---------------------------------------------------------------- file storage
 sivf_status store_reserve(sivf_ctx* ctx, sivf_ivf* f, Store* st, int64_t cap) {
     if (st->cap >= cap && st->term) return SIVF_OK;
@@ -337,6 +359,9 @@ sivf_status postings_reserve(sivf_ctx* ctx, sivf_ivf* f, int64_t P) {
     return SIVF_OK;
 }
 
+// meta, then tlen and srow of d terms
+size_t meta_bytes(int64_t d) { return kMeta * 8 + (size_t)d * 12; }
+
 void free_file(sivf_ctx* ctx, sivf_ivf* f) {
     if (!f) return;
     (void)hipStreamSynchronize(ctx->stream);
@@ -359,6 +384,8 @@ void free_file(sivf_ctx* ctx, sivf_ivf* f) {
     dev_free(ctx, f->lam, (size_t)f->k, &f->bytes);
     dev_free(ctx, f->cnorm, (size_t)f->k * 8, &f->bytes);
     dev_free(ctx, f->head, (size_t)f->d * 4, &f->bytes);
+    dev_free(ctx, f->sval, (size_t)f->scap * f->T * head_ktp(f->kt) * 4, &f->bytes);
+    dev_free(ctx, f->meta, meta_bytes(f->tlen ? f->d : 0), &f->bytes);
     dev_free(ctx, f->hval, (size_t)f->hcap * f->T * head_ktp(f->kt) * (f->pdt == SIVF_BF16 ? 2 : 4), &f->bytes);
     delete f;
 }
@@ -383,6 +410,12 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->lam, (size_t)k, &f->bytes);
     if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->cnorm, (size_t)k * 8, &f->bytes);
     if (st == SIVF_OK && ctx->opt.head_density > 0.0f) st = dev_alloc(ctx, (void**)&f->head, (size_t)d * 4, &f->bytes);
+    const int64_t td = split_possible(ctx->opt) ? d : 0;
+    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->meta, meta_bytes(td), &f->bytes);
+    if (st == SIVF_OK && td) {
+        f->tlen = (int2*)(f->meta + kMeta);
+        f->srow = (int32_t*)(f->tlen + d);
+    }
     if (st != SIVF_OK) {
         free_file(ctx, f);
         return st;
@@ -394,7 +427,10 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 // Structure f's current centroids by the flags in f->lam (Alg. 5 second half):
 // positions put the moving centroids first, then the file is built by position.
 // norms: f->cnorm has yet to be computed (the update fills it).
-sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms) {
+// objects: how many are likely to walk it.  The split walk's rows are made for
+// enough of them; a file built from given centroids gets none before its first
+// update (they take 0.17 ms of a 3.0 ms restart, and nobody may walk it so).
+sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, int64_t objects) {
     const int64_t W64 = ivf_w64(f->k);
     const int64_t nseg2 = f->d * f->T * 2;
     IvfBuildWs w{};
@@ -404,50 +440,70 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms) {
     STCHK(ws(ctx, "ivf_cnt", nseg2, &w.cnt));
     STCHK(ws(ctx, "ivf_off", nseg2 + 1, &w.off));
     STCHK(ws(ctx, "scan_ws", scan_ws_elems(nseg2) + 8, &w.scan_ws));
-    int64_t *cscan = nullptr, *meta = nullptr;
-    int32_t* hterm = nullptr;
+    int64_t *cscan = nullptr, *meta = f->meta;
+    int32_t *hterm = nullptr, *sterm = nullptr;
     STCHK(ws(ctx, "ivf_cscan", (int64_t)f->k + 1, &cscan));
-    STCHK(ws(ctx, "ivf_meta", 4, &meta));
     if (f->head) STCHK(ws(ctx, "head_term", f->d, &hterm));
+    if (f->srow) STCHK(ws(ctx, "split_term", f->d, &sterm));
     HIPCHK(ctx, ivf_perm(f->lam, f->k, f->cur.nnz, f->perm, f->iperm, cscan, meta, ctx->stream));
     HIPCHK(ctx, ivf_count(f->cur, f->k, f->d, f->kt, f->T, f->iperm, cscan, meta, w, ctx->stream));
-    // dense head rows: terms whose lists hold >= ceil(head_density * k) postings
+    // dense head rows: terms whose lists hold >= ceil(head_density * k) postings;
+    // sliced rows: down to kSplitDensity of that
     const int64_t min_len = std::max<int64_t>(1, (int64_t)std::ceil((double)ctx->opt.head_density * f->k));
-    HIPCHK(ctx, ivf_offsets(f->d, f->T, w, min_len, f->seg, f->mid, f->head, hterm, meta, ctx->stream));
+    const int64_t split_len =
+        std::max<int64_t>(1, (int64_t)std::ceil(kSplitDensity * (double)ctx->opt.head_density * f->k));
+    HIPCHK(ctx, ivf_offsets(f->d, f->T, w, min_len, f->seg, f->mid, f->head, hterm, split_len, f->tlen, f->srow, sterm,
+                            meta, ctx->stream));
     int64_t* h = (int64_t*)ctx->pin;
-    HIPCHK(ctx, hipMemcpyAsync(h, meta, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipMemcpyAsync(h + 3, f->seg + f->d * f->T, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h, meta, kMeta * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipMemcpyAsync(h + kMeta, f->seg + f->d * f->T, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     f->nmv = (int32_t)h[0];
-    const int64_t P = h[1], H = f->head ? h[2] : 0;
-    if (P != h[3])
-        return fail(ctx, SIVF_E_HIP, "internal: %lld postings for %lld centroid entries", (long long)h[3], (long long)P);
+    const int64_t P = h[1], P2 = h[kMeta], H = f->head ? h[2] : 0, SH = f->srow ? h[4] : 0;
+    if (P != P2)
+        return fail(ctx, SIVF_E_HIP, "internal: %lld postings for %lld centroid entries", (long long)P2, (long long)P);
     STCHK(postings_reserve(ctx, f, P));
     f->P = P;
     HIPCHK(ctx, ivf_fill(f->cur, f->k, f->d, f->kt, f->T, f->iperm, cscan, f->nmv, P, w, f->cid, f->v32, f->v16,
                          f->v64, ctx->stream));
     f->H = 0;
-    if (f->head && H > 0) {
-        const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
+    f->srows = 0;
+    const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
+    // room for n rows in one of the two row buffers
+    auto rows_reserve = [&](void** buf, int64_t* cap, int64_t n) -> sivf_status {
+        if (n <= *cap) return SIVF_OK;
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        dev_free(ctx, *buf, (size_t)(*cap * kpad * esz), &f->bytes);
+        *buf = nullptr;
+        *cap = 0;
+        const int64_t c = std::min<int64_t>(n + n / 8 + 16, std::min<int64_t>(f->d, kHeadMaxBytes / (kpad * esz)));
+        STCHK(dev_alloc(ctx, buf, (size_t)(c * kpad * esz), &f->bytes));
+        *cap = c;
+        return SIVF_OK;
+    };
+    if (H > 0) {
         // every row is addressed through a descriptor of its own, so the rows
         // together may exceed 4 GiB; kHeadMaxBytes only bounds the request
         if (H * kpad * esz > kHeadMaxBytes)
             return fail(ctx, SIVF_E_UNSUPPORTED,
                         "dense head rows would take %lld bytes (%lld rows), above %lld; raise head_density",
                         (long long)(H * kpad * esz), (long long)H, (long long)kHeadMaxBytes);
-        if (H > f->hcap) {
-            HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-            dev_free(ctx, f->hval, (size_t)(f->hcap * kpad * esz), &f->bytes);
-            f->hval = nullptr;
-            f->hcap = 0;
-            const int64_t c = std::min<int64_t>(H + H / 8 + 16, std::min<int64_t>(f->d, kHeadMaxBytes / (kpad * esz)));
-            STCHK(dev_alloc(ctx, &f->hval, (size_t)(c * kpad * esz), &f->bytes));
-            f->hcap = c;
-        }
+        STCHK(rows_reserve(&f->hval, &f->hcap, H));
         HIPCHK(ctx, head_fill(hterm, f->seg, f->cid, f->v32, f->v16, f->T, head_ktp(f->kt), H, f->hval, ctx->stream));
         f->H = H;
     }
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
+    // sliced rows, if a split walk is likely and there is room for them
+    if (split_pays(SH, objects) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
+        rows_reserve(&f->sval, &f->scap, SH) == SIVF_OK) {
+        uint32_t* wt = nullptr;
+        int32_t* sterm2 = nullptr;
+        STCHK(ws(ctx, "split_wt", SH, &wt));
+        STCHK(ws(ctx, "split_term2", SH, &sterm2));
+        HIPCHK(ctx, split_order(sterm, f->seg, f->T, f->v32, SH, wt, sterm2, f->srow, meta, ctx->stream));
+        HIPCHK(ctx, split_fill(sterm2, f->seg, f->cid, f->v32, f->T, head_ktp(f->kt), SH, f->sval, ctx->stream));
+        f->srows = SH;
+    }
     // norm bounds for the signed-data certificate: needed whenever the X of a
     // later call has a negative value, whatever the centroids' signs
     if (norms) HIPCHK(ctx, centroid_norms(f->cur, f->k, f->cnorm, ctx->stream));
@@ -491,7 +547,7 @@ sivf_status init_impl(sivf_ctx* ctx, const Csr& Xc, int32_t k, const int32_t* in
         H(gather_rows(Xc, ids, k, f->cur, lens, ctx->stream, 1));
         H(fill_u8(f->lam, 0, k, ctx->stream));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, Xc.n);
     if (st == SIVF_OK) H(hipStreamSynchronize(ctx->stream));
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -522,7 +578,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
                        : fill_u8(f->lam, 0, k, ctx->stream);
         if (e != hipSuccess) st = fail(ctx, SIVF_E_HIP, "HIP error: %s", hipGetErrorString(e));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, 0);
     if (st == SIVF_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, SIVF_E_HIP, "sync failed");
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -546,16 +602,50 @@ struct AssignBufs {
     uint8_t* st_rel = nullptr;
     int64_t qcap = 0;
     int nfin = 0, launches = 0, tpl = 0, nobj = 0;
+    // split walk: objects per range (0: not split) and ranges
+    int64_t range = 0, ranges = 1;
+    uint2* ent = nullptr;
+    int2* hc = nullptr;
+    uint8_t* flag = nullptr;
+    float* S = nullptr;
 };
 
-sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, int32_t k, int32_t T, AssignBufs* b) {
+// Decide whether the walk of Xc against f is split, and reserve what that needs.
+// A range's sums take at most 4 GiB (2,000,000 objects, k = 10,000: 210 ms;
+// with 1 GiB 215, with 256 MiB 270, its launches being short then).  Without
+// the memory the walk is not split.
+sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, AssignBufs* b) {
+    b->range = 0;
+    b->ranges = 1;
+    if (w.mode != Work::kCtx || !split_possible(ctx->opt) || !split_pays(f->srows, Xc.n)) return SIVF_OK;
+    const int64_t ktp = head_ktp(f->kt);
+    const int64_t range = std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp);
+    int64_t most = Xc.nnz, *m = nullptr;
+    if (range < Xc.n) {
+        STCHK(w.get("split_most", 1, &m));
+        HIPCHK(ctx, fill_i64(m, 0, 1, ctx->stream));
+        HIPCHK(ctx, range_nnz(Xc.rp, Xc.n, range, m, ctx->stream));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->pin, m, 8, hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        most = *(const int64_t*)ctx->pin;
+    }
+    if (w.get("split_ent", most, &b->ent) != SIVF_OK || w.get("split_hc", range, &b->hc) != SIVF_OK ||
+        w.get("split_flag", range, &b->flag) != SIVF_OK || w.get("split_S", range * ktp, &b->S) != SIVF_OK)
+        return SIVF_OK;
+    b->range = range;
+    b->ranges = (Xc.n + range - 1) / range;
+    return SIVF_OK;
+}
+
+sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, const sivf_ivf* f, AssignBufs* b) {
+    const int32_t k = f->k, T = f->T;
     const int relaxed = ctx->opt.filter_mode == SIVF_MODE_RELAXED;
     b->qcap = std::max<int64_t>(1024, n / 4);
     b->nfin = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (n + 4095) / 4096));
     b->tpl = std::min<int>(T, std::max<int>(1, ctx->opt.tiles_per_launch));
     b->launches = (T + b->tpl - 1) / b->tpl;
     b->nobj = ctx->n_cu * 16;   // workgroups of the exact objective (fixed: a fixed summation order)
-    STCHK(w.get("counters", 16 + b->launches, &b->counters));
+    STCHK(w.get("counters", 16 + b->launches * b->ranges, &b->counters));
     STCHK(w.get("a_new", n, &b->a_new));
     STCHK(w.get("own_new", n, &b->own_new));
     STCHK(w.get("qobj", b->qcap, &b->qobj));
@@ -566,7 +656,7 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, int32_t k, int32_t
     STCHK(w.get("obj_partial", b->nfin + 1, &b->obj_partial));
     b->obj = (double*)(b->counters + 12);   // read back with the counters
     if (ctx->opt.exact_objective) STCHK(w.get("obj64_partial", b->nobj, &b->obj64_partial));
-    const int64_t m = std::max<int64_t>(n, 1);
+    const int64_t m = std::max<int64_t>(b->range ? b->range : n, 1);
     if (b->launches > 1) {
         STCHK(w.get("st_theta", m, &b->st_theta));
         STCHK(w.get("st_best", m, &b->st_best));
@@ -576,8 +666,8 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, int32_t k, int32_t
         STCHK(w.get("st_cr", m * kCandCap, &b->st_cr));
     }
     if (relaxed) {
-        STCHK(w.get("own64_cur", m, &b->own64_cur));
-        STCHK(w.get("own64_queue", m, &b->own64_queue));
+        STCHK(w.get("own64_cur", std::max<int64_t>(n, 1), &b->own64_cur));
+        STCHK(w.get("own64_queue", std::max<int64_t>(n, 1), &b->own64_queue));
         if (b->launches > 1) STCHK(w.get("st_rel", m, &b->st_rel));
     }
     return SIVF_OK;
@@ -600,7 +690,8 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     const int relaxed = ctx->opt.filter_mode == SIVF_MODE_RELAXED;
     const int icp_on = iter >= 2 && ctx->opt.filter_mode != SIVF_MODE_IVF;
     AssignBufs B;
-    STCHK(assign_buffers(ctx, w, n, k, f->T, &B));
+    STCHK(split_setup(ctx, w, Xc, f, &B));
+    STCHK(assign_buffers(ctx, w, n, f, &B));
     const int64_t qcap = B.qcap;
     unsigned long long* counters = B.counters;
     int32_t *a_new = B.a_new, *qobj = B.qobj, *qcand = B.qcand, *qcnt = B.qcnt, *fobj = B.fobj;
@@ -662,14 +753,37 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     A.kpad = (int64_t)f->T * head_ktp(f->kt);
 
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, fill_u64(counters, 0ull, 16 + launches, s));
+    HIPCHK(ctx, fill_u64(counters, 0ull, 16 + launches * B.ranges, s));
     HIPCHK(ctx, fill_u8(changed, 0, k, s));
     HIPCHK(ctx, hipEventRecord(ctx->ev[0], s));
     if (n > 0) {
-        const int bpc = walk_blocks_per_cu(f->kt, f->pdt == SIVF_BF16, A.cbicp);
-        for (int l = 0; l < launches; ++l)
-            HIPCHK(ctx, walk_fast(A, f->pdt == SIVF_BF16, ctx->n_cu * bpc * kWalkWaves, l * tpl,
-                                  std::min(f->T, (l + 1) * tpl), counters + 16 + l, s));
+        const int bf16 = f->pdt == SIVF_BF16;
+        const int bpc = walk_blocks_per_cu(f->kt, bf16, A.cbicp, B.range > 0);
+        if (B.range) {
+            WalkArgs R = A;
+            R.srow = f->srow;
+            R.sval = f->sval;
+            R.srows = f->srows;
+            R.meta = f->meta;
+            R.tlen = f->tlen;
+            R.ent = B.ent;
+            R.hc = B.hc;
+            R.flag = B.flag;
+            R.S = B.S;
+            for (int64_t r = 0; r < B.ranges; ++r) {
+                R.c0 = r * B.range;
+                R.n = std::min(B.range, n - R.c0);
+                HIPCHK(ctx, walk_prep(R, ctx->n_cu, s));
+                for (int t = 0; t < f->T; ++t) {
+                    HIPCHK(ctx, walk_dense(R, t, ctx->n_cu, s));
+                    HIPCHK(ctx, walk_fast(R, bf16, ctx->n_cu * bpc * kWalkWaves, t, t + 1, counters + 16 + r * f->T + t, s));
+                }
+            }
+        } else {
+            for (int l = 0; l < launches; ++l)
+                HIPCHK(ctx, walk_fast(A, bf16, ctx->n_cu * bpc * kWalkWaves, l * tpl, std::min(f->T, (l + 1) * tpl),
+                                      counters + 16 + l, s));
+        }
     }
     HIPCHK(ctx, hipEventRecord(ctx->ev[1], s));
     if (n > 0) {
@@ -705,7 +819,7 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
         stats_host->relaxed_objects = (int64_t)c[7];
         stats_host->walk_bytes = (int64_t)c[10];
         stats_host->walk_wide_bytes = (int64_t)c[11];
-        stats_host->walk_launches = launches;
+        stats_host->walk_launches = (int32_t)(launches * B.ranges);
         float t = 0.0f;
         HIPCHK(ctx, hipEventElapsedTime(&t, ctx->ev[0], ctx->ev[1]));
         stats_host->t_walk_ms = t;
@@ -761,7 +875,7 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     std::swap(f->cur, f->nxt);
     HIPCHK(ctx, hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, s));
     f->nonneg = f->nonneg && Xc.nonneg;
-    STCHK(restructure(ctx, f, false));
+    STCHK(restructure(ctx, f, false, Xc.n));
     HIPCHK(ctx, hipEventRecord(ctx->ev[4], s));
     if (stats_host) {
         HIPCHK(ctx, hipStreamSynchronize(s));
@@ -942,7 +1056,7 @@ sivf_status sivf_assign_noalloc(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf
     unsigned long long* flags = nullptr;
     STCHK(m.get("vflags", 8, &flags));
     AssignBufs B;
-    STCHK(assign_buffers(ctx, m, X->n_rows, f->k, f->T, &B));
+    STCHK(assign_buffers(ctx, m, X->n_rows, f, &B));
     if (m.used > kScratchBytes)
         return fail(ctx, SIVF_E_UNSUPPORTED,
                     "sivf_assign_noalloc: %lld objects against %d centroids (%d launches) need %zu bytes of "

@@ -16,6 +16,11 @@ constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kCandCap = 32;       // candidate-list capacity per object in the fast pass
 constexpr int kTermCap = 128;      // object terms staged in LDS per wave by the fast pass (the rest read from X)
 static_assert(kTermCap % 64 == 0, "the walk reads staged terms a whole 64-term chunk at a time");
+constexpr int kSliceBytes = 256;   // of a sliced row: one block of 64 centroids
+constexpr int kSliceCols = 64;
+constexpr int kSplitHot = 608;     // sliced rows whose slices of a block fit a CU's LDS (and a row of zeros)
+constexpr int64_t kSplitMaxRows = 1 << 20;   // a block's slices stay well below 4 GiB
+constexpr int kMeta = 5;           // counts of a file on the device (sivf_ivf::meta)
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request
 constexpr int kWalkWaves = 4;      // waves per workgroup in the walk kernels
 constexpr int kMaxTile = 4096;     // largest similarity tile (centroids) per wave
@@ -87,6 +92,17 @@ struct WalkArgs {
     const int32_t* head;    // [d] row of each term, -1 if none
     const void* hval;       // [H * kpad] values in the posting dtype
     int64_t kpad;           // row length: T * head_ktp(kt) (each tile padded to 512 slots)
+    // split walk (S == nullptr: not used): objects c0 .. c0 + n - 1
+    int64_t c0;
+    const int32_t* srow;    // [d] sliced row of each term, -1 if none
+    const void* sval;       // [T * head_ktp(kt) / kSliceCols][srows] slices of kSliceBytes bytes
+    int64_t srows;
+    const int64_t* meta;    // [3]: rows whose slices go to LDS (rows 0 ..)
+    const int2* tlen;       // [d] postings of each term, and those of moving centroids
+    uint2* ent;             // [nonzeros of the range] (code, value) pairs per object
+    int2* hc;               // [n] LDS rows, other head rows of each object
+    uint8_t* flag;          // [n] bit 0: ICP branch, bit 1: relaxed branch
+    float* S;               // [n * head_ktp(kt)] head terms' sums of the current tile
     // relaxed ICP (filter mode RELAXED)
     Store st;                  // the current centroids (FP64 CSR) for exact similarities
     int relaxed;
@@ -94,6 +110,7 @@ struct WalkArgs {
     double* own64_cur;         // [n] exact rho to the previous centroid under the current centroids
     uint8_t* st_rel;           // [n] relaxed branch taken (kept between tile launches)
     // per-object running state between launches over successive tile ranges
+    // (indexed from c0)
     double* st_theta;       // [n] largest lower bound so far
     double* st_best;        // [n] best lower bound (diagnostic argmax)
     int32_t* st_bj;         // [n] its centroid
@@ -124,6 +141,12 @@ struct sivf_ivf {
     int32_t* head = nullptr;        // [d] dense head row of each term, -1 if none
     void* hval = nullptr;           // [hcap * kpad] dense head rows, posting dtype
     int64_t H = 0, hcap = 0;        // head rows in use / allocated
+    // the split walk's rows (allocated if a split walk may come)
+    int64_t* meta = nullptr;        // [kMeta] moving centroids, postings, head rows, rows read through LDS, sliced rows
+    int2* tlen = nullptr;           // [d] postings of each term, and those of moving centroids
+    int32_t* srow = nullptr;        // [d] sliced row of each term, -1 if none
+    void* sval = nullptr;           // [scap * kpad] sliced rows, FP32
+    int64_t srows = 0, scap = 0;    // sliced rows in use / allocated
     uint8_t* lam = nullptr;         // [k]
     double* cnorm = nullptr;        // [k]
     int nonneg = 1;
@@ -191,7 +214,15 @@ hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T
 // segment bounds; head rows for terms whose lists hold >= min_len postings
 // (head [d], hterm [rows], meta[2] = rows; head == nullptr: none)
 hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t min_len, int64_t* seg, int32_t* mid, int32_t* head,
-                       int32_t* hterm, int64_t* meta, hipStream_t s);
+                       int32_t* hterm, int64_t split_len, int2* tlen, int32_t* srow, int32_t* sterm, int64_t* meta,
+                       hipStream_t s);
+// sliced rows: renumbered with the heaviest (by the sum of |values|) first,
+// meta[3] = how many of them go to LDS, at most kSplitHot; then filled.  wt [H]
+// workspace, sterm [H] -> sterm2 [H].
+hipError_t split_order(const int32_t* sterm, const int64_t* seg, int32_t T, const float* v32, int64_t H, uint32_t* wt,
+                       int32_t* sterm2, int32_t* srow, int64_t* meta, hipStream_t s);
+hipError_t split_fill(const int32_t* sterm2, const int64_t* seg, const uint16_t* cid, const float* v32, int32_t T,
+                      int32_t ktp, int64_t H, void* sval, hipStream_t s);
 hipError_t ivf_fill(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,
                     const int64_t* cscan, int32_t n_moving, int64_t P, IvfBuildWs w, uint16_t* cid, float* v32,
                     uint16_t* v16, double* v64, hipStream_t s);
@@ -211,7 +242,13 @@ hipError_t store_export(const Store st, int32_t k, const int64_t* c_ptr, int32_t
 // walks tiles [tb, te) for every object; `work` is a zeroed grab counter
 hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
                      hipStream_t s);
-int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp);
+int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split);
+// split walk of a range of objects: prepare its terms, then per tile the head
+// terms' sums (walk_fast follows with a.S set)
+// *most = max(*most, nonzeros of a range of `range` rows)
+hipError_t range_nnz(const int64_t* rp, int64_t n, int64_t range, int64_t* most, hipStream_t s);
+hipError_t walk_prep(const WalkArgs& a, int n_cu, hipStream_t s);
+hipError_t walk_dense(const WalkArgs& a, int tile, int n_cu, hipStream_t s);
 hipError_t rescore_candidates(const WalkArgs& a, const Store st, int64_t grid_waves, hipStream_t s);
 // exact FP64 similarity of every object to its new centroid (relaxed ICP state)
 hipError_t own64_update(const WalkArgs& a, double* own64, int32_t* queue, int64_t grid_waves, hipStream_t s);

@@ -367,7 +367,10 @@ __device__ double exact_rho(const WalkArgs& A, const Store& st, int64_t r0, int 
 // BF16 instantiations ask for 6 waves per SIMD (80 VGPRs): measured 6% faster
 // at N=8M, k=10k; the FP32 ones stay at the compiler's choice (5 waves),
 // where the cap's spills cost more than the extra wave gains.
-template <bool BF16, bool CB, bool SHARE>
+// SPLIT: k_walk_prep has sorted the objects' terms and k_walk_dense has put the
+// head terms' sums of this tile into A.S; the wave starts from those and walks
+// the remaining terms' lists.
+template <bool BF16, bool CB, bool SHARE, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 5))) void k_walk_fast(WalkArgs A, unsigned long long* __restrict__ work, int tb,
                                                    int te, int share) {
     extern __shared__ float lds[];
@@ -379,7 +382,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
     float* cr = (float*)((int32_t*)(lds + kWalkWaves * kts) + kWalkWaves * kCandCap) + wid * kCandCap;
     int32_t* tt = (int32_t*)(lds + kWalkWaves * (kts + 2 * kCandCap)) + wid * kTermCap;
     float* tv = lds + kWalkWaves * (kts + 2 * kCandCap + kTermCap) + wid * kTermCap;
-    for (int jj = lane; jj < A.kt; jj += 64) sim[jj] = 0.0f;
+    if (!SPLIT)
+        for (int jj = lane; jj < A.kt; jj += 64) sim[jj] = 0.0f;
 
     unsigned long long macc = 0, icp_cnt = 0, rel_cnt = 0;
     uint32_t lwords = 0;   // 4-byte words requested by this wave's vector loads (flushed at 2^31)
@@ -389,32 +393,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
     for (int64_t g0 = SHARE ? ((int64_t)blockIdx.x * kWalkWaves + wid) * share : wave_grab(work, share); g0 < A.n;
          g0 = SHARE ? A.n : wave_grab(work, share)) {
         const int64_t gend = min(g0 + share, A.n);
-        for (int64_t i = g0; i < gend; ++i) {
+        for (int64_t o = g0; o < gend; ++o) {   // o: the object's number in this launch's range
+            const int64_t i = SPLIT ? A.c0 + o : o;
             const int64_t r0 = A.rp[i];
             const int n = (int)(A.rp[i + 1] - r0);
+            int nl = n;                          // terms to walk here, in `ent` if SPLIT
+            const uint2* ent = nullptr;
             int32_t a_old = -1;
-            bool icp = false;
+            bool icp = false, rel = false;
             float own_old = 0.0f;
-            if (A.icp_on) {
-                a_old = A.a_prev[i];
-                icp = A.lam[a_old] != 0;
-                own_old = A.own_prev[i];
-            }
-            if (tb == 0) icp_cnt += icp ? 1 : 0;
-            // relaxed ICP: own cluster moved, but the exact similarity to the
-            // own centroid did not decrease -> moving centroids only
-            bool rel = false;
-            if (A.relaxed && A.icp_on && !icp) {
-                if (tb == 0) {
-                    const double rn = exact_rho(A, A.st, r0, n, a_old);
-                    rel = rn >= A.own64_prev[i];
-                    if (lane == 0) {
-                        A.own64_cur[i] = rn;
-                        if (te < A.T) A.st_rel[i] = rel ? 1 : 0;
+            if (SPLIT) {
+                const int2 hc = A.hc[o];
+                const uint32_t fl = A.flag[o];
+                nl = n - hc.x - hc.y;
+                ent = A.ent + (r0 - A.rp[A.c0]) + hc.x + hc.y;
+                icp = (fl & 1u) != 0;
+                rel = (fl & 2u) != 0;
+                if (icp && tb == 0) {
+                    a_old = A.a_prev[i];
+                    own_old = A.own_prev[i];
+                }
+            } else {
+                if (A.icp_on) {
+                    a_old = A.a_prev[i];
+                    icp = A.lam[a_old] != 0;
+                    own_old = A.own_prev[i];
+                }
+                if (tb == 0) icp_cnt += icp ? 1 : 0;
+                // relaxed ICP: own cluster moved, but the exact similarity to the
+                // own centroid did not decrease -> moving centroids only
+                if (A.relaxed && A.icp_on && !icp) {
+                    if (tb == 0) {
+                        const double rn = exact_rho(A, A.st, r0, n, a_old);
+                        rel = rn >= A.own64_prev[i];
+                        if (lane == 0) {
+                            A.own64_cur[i] = rn;
+                            if (te < A.T) A.st_rel[o] = rel ? 1 : 0;
+                        }
+                        rel_cnt += rel ? 1 : 0;
+                    } else {
+                        rel = A.st_rel[o] != 0;
                     }
-                    rel_cnt += rel ? 1 : 0;
-                } else {
-                    rel = A.st_rel[i] != 0;
                 }
             }
             const bool filt = icp || rel;   // compare moving centroids only
@@ -441,13 +460,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
             int ccount = 0;             // > kCandCap once the list has overflowed
             if (tb > 0) {
                 // resume after the tiles of earlier launches
-                theta = A.st_theta[i];
-                best_lo = A.st_best[i];
-                best_j = A.st_bj[i];
-                ccount = A.st_cnt[i];
+                theta = A.st_theta[o];
+                best_lo = A.st_best[o];
+                best_j = A.st_bj[o];
+                ccount = A.st_cnt[o];
                 if (lane < min(ccount, kCandCap)) {
-                    cj[lane] = A.st_cj[i * kCandCap + lane];
-                    cr[lane] = A.st_cr[i * kCandCap + lane];
+                    cj[lane] = A.st_cj[o * kCandCap + lane];
+                    cr[lane] = A.st_cr[o * kCandCap + lane];
                 }
             } else if (icp) {
                 double r = (double)own_old;
@@ -464,12 +483,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
 
             // Stage the object's first kTermCap terms and values in LDS once
             // (each lane later reads only the entries it wrote itself).
-            for (int h = lane; h < min(n, kTermCap); h += 64) {
+            for (int h = lane; h < min(nl, kTermCap); h += 64) {
+                if (SPLIT) {
+                    const uint2 e = ent[h];
+                    tt[h] = (int32_t)e.x;
+                    tv[h] = __uint_as_float(e.y);
+                    continue;
+                }
                 const int32_t t = A.col[r0 + h];
                 tt[h] = t;
                 tv[h] = load_xval(A.xval, A.x_f64, r0 + h);
             }
-            lwords += (uint32_t)min(n, kTermCap) * (xb / 4);
+            lwords += (uint32_t)min(nl, kTermCap) * (xb / 4);
             if (lwords >= 0x80000000u) {   // wave-uniform; far below any one object's share
                 if (lane == 0) {
                     atomicAdd(&A.counters[10], 4ull * lwords);
@@ -480,7 +505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
             }
             // Work is a sequence of (tile, term chunk) pairs, tile-major; an
             // empty row still has one pair per tile so every tile is closed.
-            const int nch = max(1, (n + 63) >> 6);
+            const int nch = max(1, (nl + 63) >> 6);
             const int npairs = (te_obj - tb) * nch;
             // segment record and object value of pair pi, issued one pair ahead
             // of their use and decoded only there: every lane loads (terms past
@@ -494,13 +519,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 const int tl = tb + rel;
                 const int hb = (pi - rel * nch) * 64;
                 const int h = hb + lane;
-                nin = h < n;
+                nin = h < nl;
                 int32_t t;
                 float xv;
                 if (hb < kTermCap) {   // staged terms (hb + lane < kTermCap)
                     t = tt[hb + lane];
                     xv = tv[hb + lane];
-                } else {               // rows longer than kTermCap: n > hb
+                } else if (SPLIT) {    // more terms than kTermCap: nl > hb
+                    const uint2 e = ent[min(h, nl - 1)];
+                    t = (int32_t)e.x;
+                    xv = __uint_as_float(e.y);
+                } else {
                     const int64_t hc = r0 + min(h, n - 1);
                     t = A.col[hc];
                     xv = load_xval(A.xval, A.x_f64, hc);
@@ -521,7 +550,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 // dense batches cover [0, dlim); the tile range the walk may
                 // have touched, and the epilogue clears, is [0, ew)
                 const int32_t dlim = front_only ? elim : A.kt;
-                const int32_t ew = front_only ? min(width, (elim + 511) & ~511) : width;
+                const int32_t ew = SPLIT ? elim : front_only ? min(width, (elim + 511) & ~511) : width;
                 const uint4 rr = nrec;
                 const bool in = nin;
                 const float v = nv;
@@ -531,7 +560,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 const int64_t e = s0 + (in ? (front_only ? mv : (int32_t)(rr.z & 0xffffu)) : 0);
                 const int32_t hr = in ? (int32_t)rr.w : -1;
                 const int h = ch * 64 + lane;
-                if (in) macc += test_flag ? (unsigned long long)mv : (unsigned long long)(e - s0);
+                if (in && !SPLIT) macc += test_flag ? (unsigned long long)mv : (unsigned long long)(e - s0);
+                if (SPLIT && ch == 0) {
+                    // the tile starts from the head terms' sums (only the eligible
+                    // prefix is read or written below)
+                    const float4* src = reinterpret_cast<const float4*>(A.S + o * (int64_t)ktp);
+                    float4* dst = reinterpret_cast<float4*>(sim);
+                    for (int q = lane; 4 * q < elim; q += 64) dst[q] = src[q];
+                    lwords += (uint32_t)(elim + 3);
+                    hwords += (uint32_t)(elim + 3);
+                }
                 // ---- walk the non-empty lists of this chunk in ascending term
                 // order, kBatch postings per batch (a batch never spans two
                 // lists); the next batch's loads are in flight while the
@@ -544,16 +582,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 // 1024-centroid group summed in registers, one merge into
                 // the tile per chunk
                 int hrow = -1;
-                const bool use_head = A.head && !(filt && CB);
+                const bool use_head = !SPLIT && A.head && !(filt && CB);
                 if (use_head && h < n) hrow = hr;
-                const unsigned long long dl = ballot(hrow >= 0);
+                const unsigned long long dl = SPLIT ? 0ull : ballot(hrow >= 0);
                 if (dl) {
                     const uint32_t w = head_terms<BF16>(A, sim, dl, hrow, v, tile, ktp, dlim, lane);
                     lwords += w;
                     hwords += w;
                 }
                 // ---- other terms: structured lists
-                unsigned long long live = ballot(h < n && e > s0 && hrow < 0);
+                unsigned long long live = ballot(h < nl && e > s0 && hrow < 0);
                 if (live) {
                     // current list seen from a base aligned to 8 postings:
                     // positions [lo, hi) relative to the base are the list's
@@ -689,7 +727,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                         int32_t jc = 0;   // the centroid id, once needed
                         if (jj < ew) {
                             r32 = sim[jj];
-                            sim[jj] = 0.0f;
+                            if (!SPLIT) sim[jj] = 0.0f;
                             if (r32 >= rlow && jj < elim) {
                                 jc = A.perm[base + jj];
                                 const double r = (double)r32;
@@ -712,14 +750,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
             if (te < A.T) {
                 // later tiles follow in another launch: keep the running state
                 if (lane == 0) {
-                    A.st_theta[i] = theta;
-                    A.st_best[i] = best_lo;
-                    A.st_bj[i] = best_j;
-                    A.st_cnt[i] = ccount;
+                    A.st_theta[o] = theta;
+                    A.st_best[o] = best_lo;
+                    A.st_bj[o] = best_j;
+                    A.st_cnt[o] = ccount;
                 }
                 if (lane < min(ccount, kCandCap)) {
-                    A.st_cj[i * kCandCap + lane] = cj[lane];
-                    A.st_cr[i * kCandCap + lane] = cr[lane];
+                    A.st_cj[o * kCandCap + lane] = cj[lane];
+                    A.st_cr[o * kCandCap + lane] = cr[lane];
                 }
             } else if (!A.certify) {
                 // ---- decision
@@ -782,14 +820,15 @@ static size_t walk_lds_bytes(int kt) {
 }
 
 // The instantiations: posting precision x (SIVF | IVF-CBICP filter) x (objects
-// grabbed | shared out).
-template <bool BF16, bool CB>
-static const void* walk_kernel_s(int share) {
-    return share ? (const void*)k_walk_fast<BF16, CB, true> : (const void*)k_walk_fast<BF16, CB, false>;
+// grabbed | shared out), and the split walk's lists (FP32, no IVF-CBICP).
+template <bool BF16, bool CB, bool SPLIT>
+static const void* walk_kernel_s(bool share) {
+    return share ? (const void*)k_walk_fast<BF16, CB, true, SPLIT> : (const void*)k_walk_fast<BF16, CB, false, SPLIT>;
 }
-static const void* walk_kernel(int bf16, int cb, int share) {
-    return bf16 ? (cb ? walk_kernel_s<true, true>(share) : walk_kernel_s<true, false>(share))
-                : (cb ? walk_kernel_s<false, true>(share) : walk_kernel_s<false, false>(share));
+static const void* walk_kernel(int bf16, int cb, bool share, bool split) {
+    if (split) return walk_kernel_s<false, false, true>(share);
+    return bf16 ? (cb ? walk_kernel_s<true, true, false>(share) : walk_kernel_s<true, false, false>(share))
+                : (cb ? walk_kernel_s<false, true, false>(share) : walk_kernel_s<false, false, false>(share));
 }
 
 hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
@@ -811,7 +850,7 @@ hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, in
         share = (int)std::max<int64_t>(1, (a.n + waves - 1) / waves);
         blocks = (int)((a.n + (int64_t)share * kWalkWaves - 1) / ((int64_t)share * kWalkWaves));
     }
-    const void* fn = walk_kernel(pdt_bf16, a.cbicp, shared);
+    const void* fn = walk_kernel(pdt_bf16, a.cbicp, shared, a.S != nullptr);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -821,12 +860,266 @@ hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, in
     return hipLaunchKernel(fn, dim3(blocks), dim3(64 * kWalkWaves), params, lds, s);
 }
 
-int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp) {
+int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split) {
     const size_t lds = walk_lds_bytes(kt);
     int nb = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel(pdt_bf16, cbicp, 0), 64 * kWalkWaves, lds);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, walk_kernel(pdt_bf16, cbicp, false, split), 64 * kWalkWaves, lds);
     if (e != hipSuccess || nb < 1) nb = 1;
     return nb;
+}
+
+// ---------------------------------------------------------------------------
+// split walk
+// ---------------------------------------------------------------------------
+// Where most of an object's mult-adds fall on FP32 head rows, one wave per
+// object spends its time on L1 misses: the rows of unrelated objects share
+// little in 32 KB, and a tile's rows (7 MB and more) do not fit an XCD's L2.
+// So for larger batches the rows are read by a kernel of its own, in slices of
+// 256 bytes that do fit: a block of 64 centroids at a time per XCD (a tile of
+// 1024 is 16 blocks over 8 XCDs), all objects, with the slices of the heaviest
+// rows in LDS.  k_walk_prep sorts every object's terms by where their values
+// come from, k_walk_dense leaves the head terms' sums in A.S, and the list walk
+// starts from them.  1,000,000 objects, k = 1,000: 20.7 ms as one kernel, 13.4
+// (prep 1.5, dense 7.4, lists 4.5) now; 2,000,000, k = 10,000: 242 and 212 ms.
+
+// One wave per object of the range: its terms as (code, value) pairs, rows of
+// LDS slices first (code: byte offset of the slice in a block), then the other
+// head rows, then the terms with lists only (code: the term), each in ascending
+// term order; their counts; the filter decision; the object's mult-adds.
+__global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
+    __shared__ unsigned long long sh[4][4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t nw = (int64_t)gridDim.x * 4;
+    const int nhot = (int)A.meta[3];
+    const int64_t p0 = A.rp[A.c0];
+    unsigned long long macc = 0, icp_cnt = 0, rel_cnt = 0, terms = 0;
+    for (int64_t o = (int64_t)blockIdx.x * 4 + wid; o < A.n; o += nw) {
+        const int64_t i = A.c0 + o, r0 = A.rp[i];
+        const int n = (int)(A.rp[i + 1] - r0);
+        bool icp = false, rel = false;
+        if (A.icp_on) {
+            const int32_t a_old = A.a_prev[i];
+            icp = A.lam[a_old] != 0;
+            if (A.relaxed && !icp) {
+                const double rn = exact_rho(A, A.st, r0, n, a_old);
+                rel = rn >= A.own64_prev[i];
+                if (lane == 0) A.own64_cur[i] = rn;
+            }
+        }
+        icp_cnt += icp ? 1 : 0;
+        rel_cnt += rel ? 1 : 0;
+        terms += (unsigned long long)n;
+        int nh = 0, nc = 0;
+        for (int h0 = 0; h0 < n; h0 += 64) {
+            const int h = h0 + lane;
+            const int32_t row = h < n ? A.srow[A.col[r0 + h]] : -1;
+            nh += __popcll(ballot(row >= 0 && row < nhot));
+            nc += __popcll(ballot(row >= nhot));
+        }
+        uint2* out = A.ent + (r0 - p0);
+        int ah = 0, ac = nh, at = nh + nc;
+        for (int h0 = 0; h0 < n; h0 += 64) {
+            const int h = h0 + lane;
+            const bool in = h < n;
+            int32_t t = 0, row = -1;
+            float v = 0.0f;
+            if (in) {
+                t = A.col[r0 + h];
+                v = load_xval(A.xval, A.x_f64, r0 + h);
+                row = A.srow[t];
+                const int2 len = A.tlen[t];
+                macc += (unsigned long long)(icp || rel ? len.y : len.x);
+            }
+            const bool hot = in && row >= 0 && row < nhot, cold = in && row >= nhot, tail = in && row < 0;
+            const unsigned long long mh = ballot(hot), mc = ballot(cold), mt = ballot(tail);
+            const int pos = hot ? ah + lanes_below(mh) : cold ? ac + lanes_below(mc) : at + lanes_below(mt);
+            if (in) out[pos] = make_uint2(row >= 0 ? (uint32_t)row * kSliceBytes : (uint32_t)t, __float_as_uint(v));
+            ah += __popcll(mh);
+            ac += __popcll(mc);
+            at += __popcll(mt);
+        }
+        if (lane == 0) {
+            A.hc[o] = make_int2(nh, nc);
+            A.flag[o] = (uint8_t)((icp ? 1 : 0) | (rel ? 2 : 0));
+        }
+    }
+    macc = (unsigned long long)wave_sum_i64((int64_t)macc);
+    if (lane == 0) {
+        sh[wid][0] = macc;
+        sh[wid][1] = icp_cnt;
+        sh[wid][2] = rel_cnt;
+        sh[wid][3] = terms * (A.x_f64 ? 32 : 28);   // bytes loaded: column and row twice, value, lengths
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const unsigned long long t = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
+        const int slot[4] = {0, 3, 7, 10};
+        if (t) atomicAdd(&A.counters[slot[threadIdx.x]], t);
+    }
+}
+
+// The head terms' sums of one tile.  A workgroup of 16 waves holds a block's
+// slices of the heaviest rows in LDS and takes four objects per wave, one per
+// 16-lane DPP row: a term's code and value reach the row's lanes by a broadcast,
+// each lane adds 16 bytes of the slice (4 centroids), terms in the order of the
+// pairs.  Slices are 256 bytes apart, so the 16 lanes of a DPP row read each LDS
+// bank once.  Bound by LDS reads (4 bytes a mult-add: 8 cycles for a wave's
+// read, 32 with four SIMDs) and vector instructions (7 per step, 28 cycles),
+// about even; the other rows' slices come from L2 meanwhile.
+constexpr int kDenseThreads = 1024;
+constexpr uint32_t kOutside = 0xffffff00u;
+
+template <int S>
+__device__ inline uint32_t drow_bcast(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + S, 0xf, 0xf, true);
+}
+
+__device__ inline void dense_fma(float4& acc, const u32x4& u, float x) {
+    fma4(acc, x, __uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w));
+}
+
+// steps 4 G .. 4 G + 3 of the 16 pairs e held by each DPP row
+template <int G>
+__device__ inline void dense_hot4(float4& acc, const char* panel, const uint2& e, uint32_t q16) {
+    u32x4 u[4];
+    u[0] = *reinterpret_cast<const u32x4*>(panel + (drow_bcast<4 * G + 0>(e.x) | q16));
+    u[1] = *reinterpret_cast<const u32x4*>(panel + (drow_bcast<4 * G + 1>(e.x) | q16));
+    u[2] = *reinterpret_cast<const u32x4*>(panel + (drow_bcast<4 * G + 2>(e.x) | q16));
+    u[3] = *reinterpret_cast<const u32x4*>(panel + (drow_bcast<4 * G + 3>(e.x) | q16));
+    dense_fma(acc, u[0], __uint_as_float(drow_bcast<4 * G + 0>(e.y)));
+    dense_fma(acc, u[1], __uint_as_float(drow_bcast<4 * G + 1>(e.y)));
+    dense_fma(acc, u[2], __uint_as_float(drow_bcast<4 * G + 2>(e.y)));
+    dense_fma(acc, u[3], __uint_as_float(drow_bcast<4 * G + 3>(e.y)));
+}
+template <int G>
+__device__ inline void dense_cold_load4(u32x4* u, __amdgpu_buffer_rsrc_t r, const uint2& e, uint32_t q16) {
+    u[4 * G + 0] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 0>(e.x) | q16, 0, 0);
+    u[4 * G + 1] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 1>(e.x) | q16, 0, 0);
+    u[4 * G + 2] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 2>(e.x) | q16, 0, 0);
+    u[4 * G + 3] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 3>(e.x) | q16, 0, 0);
+}
+template <int G>
+__device__ inline void dense_cold_fma4(float4& acc, const u32x4* u, const uint2& e) {
+    dense_fma(acc, u[4 * G + 0], __uint_as_float(drow_bcast<4 * G + 0>(e.y)));
+    dense_fma(acc, u[4 * G + 1], __uint_as_float(drow_bcast<4 * G + 1>(e.y)));
+    dense_fma(acc, u[4 * G + 2], __uint_as_float(drow_bcast<4 * G + 2>(e.y)));
+    dense_fma(acc, u[4 * G + 3], __uint_as_float(drow_bcast<4 * G + 3>(e.y)));
+}
+
+// over the four DPP rows (v is the same in a row's lanes)
+__device__ inline int rows_max(int v) {
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+__global__ __launch_bounds__(kDenseThreads) void k_walk_dense(WalkArgs A, int tile) {
+    extern __shared__ u32x4 dense_panel[];
+    const int lane = threadIdx.x & 63, q = lane & 15, sub = lane >> 4;
+    const uint32_t q16 = 16u * q;
+    const int ktp = (A.kt + 511) & ~511, nbt = ktp / kSliceCols;
+    const int nhot = (int)A.meta[3];
+    const uint32_t zero = (uint32_t)nhot * kSliceBytes;   // the panel's row of zeros
+    const int base = tile * A.kt, width = min(A.kt, A.k - base);
+    const int used = (width + kSliceCols - 1) / kSliceCols;
+    const int64_t groups = (A.n + 3) / 4, p0 = A.rp[A.c0];
+    const char* panel = reinterpret_cast<const char*>(dense_panel);
+    uint32_t loads = 0;   // this wave's vector loads, in KB requested
+    for (int64_t ph = 0; ph * kXcds < used; ++ph) {
+        const Share sh = phase_share(ph, used);
+        const char* src = (const char*)A.sval + ((int64_t)tile * nbt + sh.blk) * A.srows * kSliceBytes;
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), (short)0, (int)(uint32_t)(A.srows * kSliceBytes), 0x00020000);
+        __syncthreads();
+        for (int e = threadIdx.x; e < nhot * 16; e += kDenseThreads) dense_panel[e] = reinterpret_cast<const u32x4*>(src)[e];
+        if (threadIdx.x < 16) dense_panel[nhot * 16 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+        loads += (uint32_t)(nhot / 64 + 1);
+        const bool moving = base + sh.blk * kSliceCols < A.nmv;   // some centroid of the block moved
+        for (int64_t g = sh.first; g < groups; g += sh.step) {
+            const int64_t o = 4 * g + sub;
+            int2 hc = make_int2(0, 0);
+            int64_t off = 0;
+            bool write = o < A.n;
+            if (write) {
+                hc = A.hc[o];
+                off = A.rp[A.c0 + o] - p0;
+                if (A.flag[o] != 0 && !moving) {   // compares moving centroids only
+                    write = false;
+                    hc = make_int2(0, 0);
+                }
+            }
+            const uint2* ent = A.ent + off;
+            const int mh = rows_max(hc.x), mc = rows_max(hc.y);
+            // lanes past the object's terms: zeros, from the panel or past the buffer
+            // (whose size is below kOutside: at most kSplitMaxRows rows)
+            auto hot_at = [&](int h) { return h + q < hc.x ? ent[h + q] : make_uint2(zero, 0u); };
+            auto cold_at = [&](int h) { return h + q < hc.y ? ent[hc.x + h + q] : make_uint2(kOutside, 0u); };
+            float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            uint2 c = cold_at(0), e = hot_at(0);
+            for (int h = 0; h < mc || h < mh; h += 16) {
+                // this round's cold slices in flight while the panel's are added
+                u32x4 u[16];
+                const uint2 cn = cold_at(h + 16), en = hot_at(h + 16);
+                loads += 1;
+                if (h < mc) {
+                    dense_cold_load4<0>(u, rsrc, c, q16);
+                    if (h + 4 < mc) dense_cold_load4<1>(u, rsrc, c, q16);
+                    if (h + 8 < mc) dense_cold_load4<2>(u, rsrc, c, q16);
+                    if (h + 12 < mc) dense_cold_load4<3>(u, rsrc, c, q16);
+                    loads += (uint32_t)(min(16, mc - h) + 3) & ~3u;
+                }
+                if (h < mh) {
+                    dense_hot4<0>(acc, panel, e, q16);
+                    if (h + 4 < mh) dense_hot4<1>(acc, panel, e, q16);
+                    if (h + 8 < mh) dense_hot4<2>(acc, panel, e, q16);
+                    if (h + 12 < mh) dense_hot4<3>(acc, panel, e, q16);
+                }
+                if (h < mc) {
+                    dense_cold_fma4<0>(acc, u, c);
+                    if (h + 4 < mc) dense_cold_fma4<1>(acc, u, c);
+                    if (h + 8 < mc) dense_cold_fma4<2>(acc, u, c);
+                    if (h + 12 < mc) dense_cold_fma4<3>(acc, u, c);
+                }
+                c = cn;
+                e = en;
+            }
+            if (write) *reinterpret_cast<float4*>(A.S + o * (int64_t)ktp + sh.blk * kSliceCols + 4 * q) = acc;
+        }
+    }
+    if (lane == 0 && loads) {
+        atomicAdd(&A.counters[10], 1024ull * loads);
+        atomicAdd(&A.counters[11], 1024ull * loads);
+    }
+}
+
+// *most = max(*most, the nonzeros of one of the ranges of `range` rows)
+__global__ void k_range_nnz(const int64_t* __restrict__ rp, int64_t n, int64_t range, int64_t* __restrict__ most) {
+    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (r * range >= n) return;
+    const int64_t c = rp[min(n, (r + 1) * range)] - rp[r * range];
+    atomicMax((unsigned long long*)most, (unsigned long long)c);
+}
+
+hipError_t range_nnz(const int64_t* rp, int64_t n, int64_t range, int64_t* most, hipStream_t s) {
+    const int64_t ranges = (n + range - 1) / range;
+    hipLaunchKernelGGL(k_range_nnz, dim3((unsigned)((ranges + 255) / 256)), dim3(256), 0, s, rp, n, range, most);
+    return hipGetLastError();
+}
+
+hipError_t walk_prep(const WalkArgs& a, int n_cu, hipStream_t s) {
+    const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((a.n + 3) / 4, (int64_t)n_cu * 8));
+    hipLaunchKernelGGL(k_walk_prep, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t walk_dense(const WalkArgs& a, int tile, int n_cu, hipStream_t s) {
+    const size_t lds = (size_t)(kSplitHot + 1) * kSliceBytes;
+    hipError_t e = hipFuncSetAttribute((const void*)k_walk_dense, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    // one workgroup per CU (its LDS), a multiple of the XCDs
+    const unsigned grid = (unsigned)((n_cu + kXcds - 1) / kXcds * kXcds);
+    hipLaunchKernelGGL(k_walk_dense, dim3(grid), dim3(kDenseThreads), lds, s, a, tile);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void k_rescore_cand(WalkArgs A, Store st) {

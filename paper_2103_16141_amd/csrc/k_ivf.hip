@@ -86,6 +86,7 @@ __global__ __launch_bounds__(1024) void k_ivf_perm(const uint8_t* __restrict__ l
         meta[0] = nm;
         meta[1] = ncarry;
         meta[2] = 0;
+        meta[4] = 0;
     }
 }
 
@@ -186,7 +187,9 @@ hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T
 __global__ __launch_bounds__(256) void k_ivf_seg(const int64_t* __restrict__ off, const int64_t* __restrict__ cnt,
                                                  int64_t d, int32_t T, int64_t min_len, int64_t* __restrict__ seg,
                                                  int32_t* __restrict__ mid, int32_t* __restrict__ head,
-                                                 int32_t* __restrict__ hterm, int64_t* __restrict__ meta) {
+                                                 int32_t* __restrict__ hterm, int64_t split_len,
+                                                 int2* __restrict__ tlen, int32_t* __restrict__ srow,
+                                                 int32_t* __restrict__ sterm, int64_t* __restrict__ meta) {
     const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t nt = d * T;
     if (idx < nt) {
@@ -197,25 +200,42 @@ __global__ __launch_bounds__(256) void k_ivf_seg(const int64_t* __restrict__ off
     }
     if (!head) return;
     const bool term = idx < d;
-    const bool hd = term && off[(idx + 1) * T * 2] - off[idx * T * 2] >= min_len;
-    const unsigned long long m = ballot(hd);
-    int64_t row = 0;
-    if (m) {
-        if (lanes_below(m) == 0 && hd) row = (int64_t)atomicAdd((unsigned long long*)&meta[2], (unsigned long long)__popcll(m));
-        row = bcast_i64(row, __builtin_ctzll(m)) + lanes_below(m);
-    }
+    const int64_t len = term ? off[(idx + 1) * T * 2] - off[idx * T * 2] : 0;
+    // the next row of a list for each lane whose term gets one
+    auto take = [&](bool has, int64_t* count) -> int64_t {
+        const unsigned long long m = ballot(has);
+        int64_t row = 0;
+        if (m) {
+            if (lanes_below(m) == 0 && has) row = (int64_t)atomicAdd((unsigned long long*)count, (unsigned long long)__popcll(m));
+            row = bcast_i64(row, __builtin_ctzll(m)) + lanes_below(m);
+        }
+        return row;
+    };
+    const bool hd = term && len >= min_len;
+    const int64_t row = take(hd, &meta[2]);
     if (term) head[idx] = hd ? (int32_t)row : -1;
     if (hd) hterm[row] = (int32_t)idx;
+    if (!srow) return;
+    const bool sl = term && len >= split_len;
+    const int64_t q = take(sl, &meta[4]);
+    if (term) {
+        int64_t mv = 0;
+        for (int32_t tile = 0; tile < T; ++tile) mv += cnt[(idx * T + tile) * 2];
+        tlen[idx] = make_int2((int)len, (int)mv);
+        srow[idx] = sl ? (int32_t)q : -1;
+    }
+    if (sl) sterm[q] = (int32_t)idx;
 }
 
 hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t min_len, int64_t* seg, int32_t* mid, int32_t* head,
-                       int32_t* hterm, int64_t* meta, hipStream_t s) {
+                       int32_t* hterm, int64_t split_len, int2* tlen, int32_t* srow, int32_t* sterm, int64_t* meta,
+                       hipStream_t s) {
     const int64_t n = d * T * 2;
     hipError_t e = exclusive_scan_i64(w.cnt, w.off, n, w.scan_ws, s);
     if (e != hipSuccess) return e;
     int64_t nt = d * T + 1;
     hipLaunchKernelGGL(k_ivf_seg, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.off, w.cnt, d, T, min_len, seg,
-                       mid, head, hterm, meta);
+                       mid, head, hterm, split_len, tlen, srow, sterm, meta);
     return hipGetLastError();
 }
 
@@ -342,6 +362,112 @@ hipError_t head_fill(const int32_t* hterm, const int64_t* seg, const uint16_t* c
         void* to = v16 ? (void*)((uint16_t*)hval + r * T * ktp) : (void*)((float*)hval + r * T * ktp);
         hipLaunchKernelGGL(k_head_rows, dim3((unsigned)(n * T)), dim3(256), 0, s, hterm + r, seg, cid, v32, v16, T, ktp, to);
     }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- sliced rows
+// The split walk's rows: like dense head rows (FP32), but stored by blocks of
+// 64 slots, [tile][block][row], 256-byte slices, so that a pass over one block
+// reads one contiguous array of slices, whatever rows it needs.
+
+// sum of |values| of each row's postings (a fixed order), as ordered bits
+__global__ __launch_bounds__(256) void k_split_weight(const int32_t* __restrict__ sterm, const int64_t* __restrict__ seg,
+                                                     int32_t T, const float* __restrict__ v32, int64_t H,
+                                                     uint32_t* __restrict__ wt) {
+    const int lane = threadIdx.x & 63;
+    const int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
+    if (r >= H) return;
+    const int64_t t = sterm[r], lo = seg[t * T], hi = seg[(t + 1) * T];
+    float acc = 0.0f;
+    for (int64_t p = lo + lane; p < hi; p += 64) acc = acc + fabsf(v32[p]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) acc = acc + __shfl_xor(acc, o, 64);
+    if (lane == 0) wt[r] = __float_as_uint(acc);
+}
+
+// One workgroup: the largest set {weight >= x} of at most kSplitHot rows (the
+// same on every run), numbered first.  The numbers inside the two groups come
+// from atomics; they change no result.
+__global__ __launch_bounds__(1024) void k_split_order(const uint32_t* __restrict__ wt, const int32_t* __restrict__ sterm,
+                                                     int64_t H, int32_t* __restrict__ sterm2, int32_t* __restrict__ srow,
+                                                     int64_t* __restrict__ meta) {
+    __shared__ uint32_t hist[256];
+    __shared__ uint32_t prefix, left, nh, nc;
+    if (threadIdx.x == 0) {
+        prefix = 0;
+        left = kSplitHot;   // rank of the row sought among those with the prefix
+        nh = nc = 0;
+    }
+    // the kSplitHot-th largest weight, byte by byte
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+        __syncthreads();
+        const uint32_t pf = prefix;
+        for (int64_t r = threadIdx.x; r < H; r += 1024)
+            if (shift == 24 || (wt[r] >> (shift + 8)) == pf) atomicAdd(&hist[(wt[r] >> shift) & 255u], 1u);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t b = 255, before = 0;
+            while (b > 0 && before + hist[b] < left) before += hist[b--];
+            left -= before;
+            prefix = (pf << 8) | b;
+        }
+        __syncthreads();
+    }
+    // rows at least as heavy: kept if they all fit, else only the heavier ones
+    const uint32_t y = prefix;
+    uint32_t ge = 0;
+    for (int64_t r = threadIdx.x; r < H; r += 1024) ge += wt[r] >= y ? 1u : 0u;
+    ge = (uint32_t)wave_sum_i64(ge);
+    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[0], ge);
+    __syncthreads();
+    const bool ties = hist[0] <= (uint32_t)kSplitHot;
+    uint32_t hot = 0;
+    for (int64_t r = threadIdx.x; r < H; r += 1024) hot += (wt[r] > y || (ties && wt[r] == y)) ? 1u : 0u;
+    hot = (uint32_t)wave_sum_i64(hot);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[1], hot);
+    __syncthreads();
+    hot = hist[1];
+    for (int64_t r = threadIdx.x; r < H; r += 1024) {
+        const bool h = wt[r] > y || (ties && wt[r] == y);
+        const uint32_t q = h ? atomicAdd(&nh, 1u) : hot + atomicAdd(&nc, 1u);
+        sterm2[q] = sterm[r];
+        srow[sterm[r]] = (int32_t)q;
+    }
+    if (threadIdx.x == 0) meta[3] = hot;
+}
+
+hipError_t split_order(const int32_t* sterm, const int64_t* seg, int32_t T, const float* v32, int64_t H, uint32_t* wt, int32_t* sterm2, int32_t* srow, int64_t* meta,
+                      hipStream_t s) {
+    hipLaunchKernelGGL(k_split_weight, dim3((unsigned)((H + 3) / 4)), dim3(256), 0, s, sterm, seg, T, v32, H, wt);
+    hipLaunchKernelGGL(k_split_order, dim3(1), dim3(1024), 0, s, wt, sterm, H, sterm2, srow, meta);
+    return hipGetLastError();
+}
+
+// As k_head_rows: one workgroup per (row, tile).
+__global__ __launch_bounds__(256) void k_split_rows(const int32_t* __restrict__ sterm, const int64_t* __restrict__ seg,
+                                                    const uint16_t* __restrict__ cid, const float* __restrict__ v32,
+                                                    int32_t T, int32_t ktp, int64_t H, float* __restrict__ sval) {
+    __shared__ float slot[kMaxTile];
+    const int64_t r = blockIdx.x / T;
+    const int tile = (int)(blockIdx.x - r * T);
+    const int64_t t = sterm[r];
+    const int64_t lo = seg[t * T + tile], hi = seg[t * T + tile + 1];
+    for (int c = threadIdx.x; c < ktp; c += 256) slot[c] = 0.0f;
+    __syncthreads();
+    for (int64_t p = lo + threadIdx.x; p < hi; p += 256) slot[cid[p]] = v32[p];
+    __syncthreads();
+    const int64_t b0 = (int64_t)tile * (ktp / kSliceCols);
+    for (int c = threadIdx.x; c < ktp; c += 256)
+        sval[((b0 + c / kSliceCols) * H + r) * kSliceCols + c % kSliceCols] = slot[c];
+}
+
+hipError_t split_fill(const int32_t* sterm2, const int64_t* seg, const uint16_t* cid, const float* v32, int32_t T,
+                      int32_t ktp, int64_t H, void* sval, hipStream_t s) {
+    hipLaunchKernelGGL(k_split_rows, dim3((unsigned)(H * T)), dim3(256), 0, s, sterm2, seg, cid, v32, T, ktp, H,
+                       (float*)sval);
     return hipGetLastError();
 }
 

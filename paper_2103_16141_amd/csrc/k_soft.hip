@@ -34,7 +34,6 @@ namespace sivf {
 
 constexpr int kBlk = kSoftBlk;   // columns of a C^T block (one 256-byte slice per term)
 constexpr int kSub = kSoftSub;   // columns of a dS / dC^T block (128-byte slices)
-constexpr int kXcds = 8;
 
 // ---------------------------------------------------------------- block layouts
 // out[b][t][c] = C[64 b + c][t] (0 past the last centroid), 64x64 tiles via LDS
@@ -82,22 +81,6 @@ hipError_t soft_unpack(const float* dCT, float* dC, int64_t k, int64_t d, hipStr
 }
 
 // ---------------------------------------------------------------- work split
-// Blocks run in phases of up to 8, one block per XCD; in a phase with fewer
-// blocks than XCDs, XCDs share a block and split its rows.  A wave takes items
-// first, first + step, ... of block `blk`.
-struct Share {
-    int64_t blk, first, step;
-};
-
-__device__ inline Share phase_share(int64_t phase, int64_t nblk) {
-    const int x = blockIdx.x % kXcds;
-    const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x / kXcds) * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    const int64_t waves = (int64_t)(gridDim.x / kXcds) * (blockDim.x >> 6);
-    const int nb = (int)min((int64_t)kXcds, nblk - phase * kXcds);
-    const int b = x % nb, sharers = (kXcds - 1 - b) / nb + 1;
-    return {phase * kXcds + b, wave * sharers + x / nb, waves * sharers};
-}
-
 // workgroups (a multiple of 8) for `items` wave-sized items per block
 static unsigned share_grid(const void* fn, int64_t items, int64_t nblk, int threads, int n_cu) {
     int nb = 0;

@@ -88,6 +88,24 @@ __device__ inline int32_t wave_min_i32(int32_t v) {
 // error <= nnz * 2^-53): square root, then a 2^-30 relative margin.
 __device__ inline double centroid_norm_bound(double acc) { return sqrt(acc) * (1.0 + 0x1p-30) + 0x1p-1000; }
 
+constexpr int kXcds = 8;   // workgroup b runs on XCD b mod 8
+
+// Blocks run in phases of up to 8, one block per XCD; in a phase with fewer
+// blocks than XCDs, XCDs share a block and split its rows.  A wave takes items
+// first, first + step, ... of block `blk`.
+struct Share {
+    int64_t blk, first, step;
+};
+
+__device__ inline Share phase_share(int64_t phase, int64_t nblk) {
+    const int x = blockIdx.x % kXcds;
+    const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x / kXcds) * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    const int64_t waves = (int64_t)(gridDim.x / kXcds) * (blockDim.x >> 6);
+    const int nb = (int)min((int64_t)kXcds, nblk - phase * kXcds);
+    const int b = x % nb, sharers = (kXcds - 1 - b) / nb + 1;
+    return {phase * kXcds + b, wave * sharers + x / nb, waves * sharers};
+}
+
 // bf16 storage <-> f32: the 16 high bits of an IEEE binary32.
 __device__ __host__ inline float bf16_to_f32(uint16_t b) {
     uint32_t u = (uint32_t)b << 16;

@@ -285,3 +285,90 @@ def test_file_of_centroids_at_the_piece_and_scan_edges(k, d, posting):
     assert np.array_equal(ex["c_ptr"], ptr) and np.array_equal(ex["c_col"], col) and np.array_equal(ex["c_val"], val)
     assert np.array_equal(ex["term_ptr"], ref.term_ptr) and np.array_equal(ex["split"], ref.split)
     assert np.array_equal(ex["p_cid"], ref.cid) and np.array_equal(ex["p_val"], ref.val)
+
+
+# ---------------------------------------------------------------- split walk
+def _striped(n, d, lam, seed, dtype, signed=False, empty=False):
+    """n unit rows of lam terms, one from each of lam stripes of the d terms
+    (the first terms of a stripe more often); rows 0, 7, 14, .. empty if asked."""
+    from paper_2103_16141_amd.api import DeviceCsr
+    g = torch.Generator(device=device()).manual_seed(seed)
+    w = d // lam
+    u = torch.rand(n, lam, device=device(), generator=g)
+    col = (u * u * w).int().clamp_(max=w - 1) + torch.arange(lam, device=device(), dtype=torch.int32) * w
+    v = torch.rand(n, lam, device=device(), generator=g, dtype=dtype) + 0.05
+    if signed:
+        v *= torch.where(torch.rand(n, lam, device=device(), generator=g) < 0.3, -1.0, 1.0).to(dtype)
+    v /= torch.linalg.vector_norm(v.double(), dim=1, keepdim=True).to(dtype)
+    lens = torch.full((n,), lam, device=device(), dtype=torch.int64)
+    if empty:
+        lens[::7] = 0
+        keep = lens > 0
+        col, v = col[keep], v[keep]
+    rp = torch.cat([torch.zeros(1, device=device(), dtype=torch.int64), lens.cumsum(0)])
+    return DeviceCsr(rp, col.reshape(-1).contiguous(), v.reshape(-1).contiguous(), d)
+
+
+@pytest.mark.parametrize("n,d,lam,k,kt,mode,dtype,signed,empty", [
+    (90_003, 1_600, 40, 70, 64, "sivf", torch.float32, False, False),    # two tiles, the last of 6 centroids
+    (90_001, 1_600, 20, 130, 0, "relaxed", torch.float64, False, True),  # three blocks, the last of 2
+    (70_002, 2_400, 150, 64, 0, "sivf", torch.float32, True, False),     # rows over two chunks, signed values
+    (70_000, 2_400, 8, 600, 0, "ivf", torch.float32, False, False),      # two phases of blocks; no filter
+    (2_200_001, 1_100, 5, 12, 0, "sivf", torch.float32, False, False),   # two ranges of objects
+])
+def test_split_walk_equals_the_plain_walk(n, d, lam, k, kt, mode, dtype, signed, empty):
+    # rows x objects put the walk past the split's line; a workspace cap (far
+    # above what is used) keeps it plain.  Assignments, own similarities and
+    # counts are those of the plain walk, and the assignments the argmax in FP64
+    log("split walk n %d d %d lam %d k %d" % (n, d, lam, k))
+    X = _striped(n, d, lam, 5, dtype, signed, empty)
+    ids = np.random.default_rng(7).choice(n, k, replace=False).astype(np.int32)
+    opts = dict(k_tile=kt, filter_mode=mode, head_density=0.02)
+    split, plain = _ctx(**opts), _ctx(workspace_cap_bytes=1 << 40, **opts)
+    fs, fp = split.init_centroids(X, k, ids), plain.init_centroids(X, k, ids)
+    state = [(split, fs), (plain, fp)]
+    dev = device()
+    a = torch.zeros(n, dtype=torch.int32, device=dev)
+    own = torch.zeros(n, dtype=torch.float32, device=dev)
+    own64 = torch.zeros(n, dtype=torch.float64, device=dev) if mode == "relaxed" else None
+    lam_ = torch.zeros(k, dtype=torch.uint8, device=dev)
+    was_split = False
+    for r in (1, 2, 3, 4):
+        out = []
+        for ctx, f in state:
+            a1, own1, l1 = a.clone(), own.clone(), lam_.clone()
+            e1 = None if own64 is None else own64.clone()
+            st = ctx.assign(X, f, r, a1, own1, l1, own64=e1)
+            out.append((a1, own1, l1, e1, st))
+        (a1, o1, l1, e1, s1), (a2, o2, l2, e2, s2) = out
+        assert torch.equal(a1, a2) and torch.equal(l1, l2)
+        if own64 is not None:
+            assert torch.equal(e1, e2)
+        for key in ("multadds", "moved", "icp_objects", "n_invariant", "relaxed_objects", "head_rows"):
+            assert s1[key] == s2[key], key
+        was_split |= s1["walk_bytes"] != s2["walk_bytes"]
+        # own similarities: two FP32 sums of at most lam products of a unit row
+        # and a unit column, each within lam * 2^-24 of the exact value, or the
+        # FP64 value rounded
+        assert float((o1.double() - o2.double()).abs().max()) <= 2 * (lam + 1) * 2.0 ** -24
+        a, own, own64 = a1, o1, e1
+        if r in (1, 4):
+            c = fs.centroids()
+            C = torch.zeros(k, d, dtype=torch.float64, device=dev)
+            C[torch.repeat_interleave(torch.arange(k, device=dev), c.row_ptr.diff()), c.col.long()] = c.val.double()
+            for lo in range(0, n, 50_000):
+                hi = min(n, lo + 50_000)
+                b, e = int(X.row_ptr[lo]), int(X.row_ptr[hi])
+                D = torch.zeros(hi - lo, d, dtype=torch.float64, device=dev)
+                rows = torch.repeat_interleave(torch.arange(hi - lo, device=dev), X.row_ptr[lo:hi + 1].diff())
+                D[rows, X.col[b:e].long()] = X.val[b:e].double()
+                S = D @ C.T
+                mine = S.gather(1, a[lo:hi].long()[:, None])[:, 0]
+                assert float((S.max(1).values - mine).max()) <= 1e-12
+        lam_ = l1
+        for ctx, f in state:
+            ctx.update(X, a, lam_, f)
+    assert was_split
+    for ctx, f in state:
+        f.free()
+        ctx.close()

@@ -282,13 +282,25 @@ sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, std::initialize
     return validate(ctx, X, out, w, ids);
 }
 
-void choose_tiles(const sivf_ctx* ctx, int32_t k, int32_t* kt, int32_t* T) {
+// Tiles of k centroids holding an estimated `postings` over d terms.  Every
+// tile repeats an object's work per term and its scan, so the widest is the best
+// as long as its rows stay in cache; wider than 2048 costs occupancy (LDS).
+// FP32, walk in ms with 1024 and 2048: 60,000 objects, k = 1,531 1.14 and 0.71
+// (one tile for two); 400,000, k = 20,000 84.4 and 68.9; 5,000,000, k = 10,000
+// 536 and 500 (2560: 10 - 15% more).  BF16 files, half the bytes, pay the
+// scattered access to a wider tile sooner: sparse (the seed objects: 62.5 and
+// 51.7) 2048; up to 3% dense, or in at most two tiles, 1536 (k = 10,000, 2%
+// dense: 86.2 with 1024, 86.0 with 1536, 88.8 with 2048; k = 1,500, 12% dense
+// 19.7 and 15.4); denser 1024 (5,000,000 objects, 6% dense: 439, 460, 490).
+void choose_tiles(const sivf_ctx* ctx, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
     int32_t want = ctx->opt.k_tile;
     if (want <= 0) {
-        // widest tile measured fastest at N = 8M, k = 10k (tile-major walk, both dtypes)
-        const int32_t kmax = 1024;
-        int32_t t = (k + kmax - 1) / kmax;
-        int32_t w = (k + t - 1) / t;
+        const double density = postings / ((double)k * (double)d);
+        int32_t kmax = kTileWide;
+        if (ctx->opt.posting_dtype == SIVF_BF16 && density > 0.003)
+            kmax = density < 0.033 || k <= 2 * kTileMid ? kTileMid : kTileNarrow;
+        const int32_t t = (k + kmax - 1) / kmax;
+        const int32_t w = (k + t - 1) / t;
         want = ((w + 63) / 64) * 64;
     }
     *kt = want;
@@ -372,9 +384,9 @@ void free_file(sivf_ctx* ctx, sivf_ivf* f) {
         dev_free(ctx, st->term, (size_t)st->cap * 4, &f->bytes);
         dev_free(ctx, st->val, (size_t)st->cap * 8, &f->bytes);
     }
-    dev_free(ctx, f->seg, (size_t)(f->d * f->T + 1) * 8, &f->bytes);
-    dev_free(ctx, f->mid, (size_t)(f->d * f->T) * 4, &f->bytes);
-    dev_free(ctx, f->rec, (size_t)(f->d * f->T) * 16, &f->bytes);
+    dev_free(ctx, f->seg, (size_t)(f->d * f->Tcap + 1) * 8, &f->bytes);
+    dev_free(ctx, f->mid, (size_t)(f->d * f->Tcap) * 4, &f->bytes);
+    dev_free(ctx, f->rec, (size_t)(f->d * f->Tcap) * 16, &f->bytes);
     dev_free(ctx, f->perm, (size_t)f->k * 4, &f->bytes);
     dev_free(ctx, f->iperm, (size_t)f->k * 4, &f->bytes);
     dev_free(ctx, f->cid, (size_t)f->pcap * 2, &f->bytes);
@@ -384,9 +396,9 @@ void free_file(sivf_ctx* ctx, sivf_ivf* f) {
     dev_free(ctx, f->lam, (size_t)f->k, &f->bytes);
     dev_free(ctx, f->cnorm, (size_t)f->k * 8, &f->bytes);
     dev_free(ctx, f->head, (size_t)f->d * 4, &f->bytes);
-    dev_free(ctx, f->sval, (size_t)f->scap * f->T * head_ktp(f->kt) * 4, &f->bytes);
+    dev_free(ctx, f->sval, (size_t)f->scap * 4, &f->bytes);
     dev_free(ctx, f->meta, meta_bytes(f->tlen ? f->d : 0), &f->bytes);
-    dev_free(ctx, f->hval, (size_t)f->hcap * f->T * head_ktp(f->kt) * (f->pdt == SIVF_BF16 ? 2 : 4), &f->bytes);
+    dev_free(ctx, f->hval, (size_t)f->hcap * (f->pdt == SIVF_BF16 ? 2 : 4), &f->bytes);
     delete f;
 }
 
@@ -396,15 +408,17 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     f->k = k;
     f->d = d;
     f->pdt = ctx->opt.posting_dtype;
-    choose_tiles(ctx, k, &f->kt, &f->T);
+    // arrays for the most tiles the file may come to have
+    choose_tiles(ctx, k, INFINITY, d, &f->kt, &f->T);
+    f->Tcap = f->T;
     sivf_status st = SIVF_OK;
     for (Store* s : {&f->cur, &f->nxt}) {
         if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&s->start, (size_t)k * 8, &f->bytes);
         if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&s->nnz, (size_t)k * 8, &f->bytes);
     }
-    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->seg, (size_t)(d * f->T + 1) * 8, &f->bytes);
-    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->mid, (size_t)(d * f->T) * 4, &f->bytes);
-    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->rec, (size_t)(d * f->T) * 16, &f->bytes);
+    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->seg, (size_t)(d * f->Tcap + 1) * 8, &f->bytes);
+    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->mid, (size_t)(d * f->Tcap) * 4, &f->bytes);
+    if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->rec, (size_t)(d * f->Tcap) * 16, &f->bytes);
     if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->perm, (size_t)k * 4, &f->bytes);
     if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->iperm, (size_t)k * 4, &f->bytes);
     if (st == SIVF_OK) st = dev_alloc(ctx, (void**)&f->lam, (size_t)k, &f->bytes);
@@ -427,10 +441,11 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 // Structure f's current centroids by the flags in f->lam (Alg. 5 second half):
 // positions put the moving centroids first, then the file is built by position.
 // norms: f->cnorm has yet to be computed (the update fills it).
-// objects: how many are likely to walk it.  The split walk's rows are made for
+// postings: an estimate of their entries.  objects: how many are likely to walk it.  The split walk's rows are made for
 // enough of them; a file built from given centroids gets none before its first
 // update (they take 0.17 ms of a 3.0 ms restart, and nobody may walk it so).
-sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, int64_t objects) {
+sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, int64_t objects) {
+    choose_tiles(ctx, f->k, postings, f->d, &f->kt, &f->T);
     const int64_t W64 = ivf_w64(f->k);
     const int64_t nseg2 = f->d * f->T * 2;
     IvfBuildWs w{};
@@ -469,15 +484,15 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, int64_t objects)
     f->H = 0;
     f->srows = 0;
     const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
-    // room for n rows in one of the two row buffers
+    // room for n rows in one of the two row buffers (cap: in values)
     auto rows_reserve = [&](void** buf, int64_t* cap, int64_t n) -> sivf_status {
-        if (n <= *cap) return SIVF_OK;
+        if (n * kpad <= *cap) return SIVF_OK;
         HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-        dev_free(ctx, *buf, (size_t)(*cap * kpad * esz), &f->bytes);
+        dev_free(ctx, *buf, (size_t)(*cap * esz), &f->bytes);
         *buf = nullptr;
         *cap = 0;
-        const int64_t c = std::min<int64_t>(n + n / 8 + 16, std::min<int64_t>(f->d, kHeadMaxBytes / (kpad * esz)));
-        STCHK(dev_alloc(ctx, buf, (size_t)(c * kpad * esz), &f->bytes));
+        const int64_t c = std::min<int64_t>(n + n / 8 + 16, std::min<int64_t>(f->d, kHeadMaxBytes / (kpad * esz))) * kpad;
+        STCHK(dev_alloc(ctx, buf, (size_t)(c * esz), &f->bytes));
         *cap = c;
         return SIVF_OK;
     };
@@ -547,7 +562,7 @@ sivf_status init_impl(sivf_ctx* ctx, const Csr& Xc, int32_t k, const int32_t* in
         H(gather_rows(Xc, ids, k, f->cur, lens, ctx->stream, 1));
         H(fill_u8(f->lam, 0, k, ctx->stream));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true, Xc.n);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, 0.0, Xc.n);
     if (st == SIVF_OK) H(hipStreamSynchronize(ctx->stream));
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -578,7 +593,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
                        : fill_u8(f->lam, 0, k, ctx->stream);
         if (e != hipSuccess) st = fail(ctx, SIVF_E_HIP, "HIP error: %s", hipGetErrorString(e));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true, 0);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, (double)C->nnz, 0);
     if (st == SIVF_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, SIVF_E_HIP, "sync failed");
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -875,7 +890,8 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     std::swap(f->cur, f->nxt);
     HIPCHK(ctx, hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, s));
     f->nonneg = f->nonneg && Xc.nonneg;
-    STCHK(restructure(ctx, f, false, Xc.n));
+    // (a cluster's members share terms: a quarter to two thirds of their nonzeros remain)
+    STCHK(restructure(ctx, f, false, Xc.nnz / 3.0, Xc.n));
     HIPCHK(ctx, hipEventRecord(ctx->ev[4], s));
     if (stats_host) {
         HIPCHK(ctx, hipStreamSynchronize(s));

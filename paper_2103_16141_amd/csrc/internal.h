@@ -23,6 +23,7 @@ constexpr int64_t kSplitMaxRows = 1 << 20;   // a block's slices stay well below
 constexpr int kMeta = 5;           // counts of a file on the device (sivf_ivf::meta)
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request
 constexpr int kWalkWaves = 4;      // waves per workgroup in the walk kernels
+constexpr int kTileWide = 2048, kTileMid = 1536, kTileNarrow = 1024;   // automatic tile widths
 constexpr int kMaxTile = 4096;     // largest similarity tile (centroids) per wave
 constexpr size_t kPinBytes = 1024;
 
@@ -124,7 +125,7 @@ struct WalkArgs {
 struct sivf_ivf {
     int32_t k = 0;
     int64_t d = 0;
-    int32_t kt = 0, T = 0;
+    int32_t kt = 0, T = 0, Tcap = 0;   // tile width, tiles, tiles that seg, mid and rec have room for
     sivf_dtype pdt = SIVF_F32;
     sivf::Store cur, nxt;           // current centroids, and the buffer the next update writes
     int64_t* seg = nullptr;         // [d*T + 1]
@@ -139,14 +140,14 @@ struct sivf_ivf {
     double* v64 = nullptr;          // [pcap] FP64 values (exact re-score over whole lists)
     int64_t P = 0, pcap = 0;
     int32_t* head = nullptr;        // [d] dense head row of each term, -1 if none
-    void* hval = nullptr;           // [hcap * kpad] dense head rows, posting dtype
-    int64_t H = 0, hcap = 0;        // head rows in use / allocated
+    void* hval = nullptr;           // [hcap] dense head rows of kpad values, posting dtype
+    int64_t H = 0, hcap = 0;        // head rows in use / values allocated
     // the split walk's rows (allocated if a split walk may come)
     int64_t* meta = nullptr;        // [kMeta] moving centroids, postings, head rows, rows read through LDS, sliced rows
     int2* tlen = nullptr;           // [d] postings of each term, and those of moving centroids
     int32_t* srow = nullptr;        // [d] sliced row of each term, -1 if none
-    void* sval = nullptr;           // [scap * kpad] sliced rows, FP32
-    int64_t srows = 0, scap = 0;    // sliced rows in use / allocated
+    void* sval = nullptr;           // [scap] sliced rows of kpad values, FP32
+    int64_t srows = 0, scap = 0;    // sliced rows in use / values allocated
     uint8_t* lam = nullptr;         // [k]
     double* cnorm = nullptr;        // [k]
     int nonneg = 1;

@@ -372,3 +372,43 @@ def test_split_walk_equals_the_plain_walk(n, d, lam, k, kt, mode, dtype, signed,
     for ctx, f in state:
         f.free()
         ctx.close()
+
+
+# ---------------------------------------------------------------- tile widths
+@pytest.mark.parametrize("posting,k,d,widths", [
+    ("fp32", 2_048, 2_000, (2_048, 2_048)),
+    ("fp32", 2_049, 2_000, (1_088, 1_088)),
+    ("bf16", 1_025, 400, (1_088, 1_088)),     # one tile however dense
+    ("bf16", 2_048, 400, (2_048, 1_024)),     # two after the first update
+    ("bf16", 3_100, 500, (1_600, 832)),       # 2 -> 4 tiles
+    ("bf16", 3_100, 5_000, (1_600, 1_088)),   # 2 -> 3 tiles
+])
+def test_automatic_tiles_follow_the_file(posting, k, d, widths):
+    # tile widths are chosen when a file is built: the trajectory is that of
+    # fixed tiles of 512, whatever they are
+    log("tiles %s k %d d %d" % (posting, k, d))
+    n, lam = 2 * k + 3, 50
+    X = _striped(n, d, lam, 3, torch.float32)
+    ids = np.random.default_rng(1).choice(n, k, replace=False).astype(np.int32)
+    state = []
+    for kt in (0, 512):
+        ctx = _ctx(posting_dtype=posting, k_tile=kt)
+        f = ctx.init_centroids(X, k, ids)
+        state.append([ctx, f, torch.zeros(n, dtype=torch.int32, device=device()),
+                      torch.zeros(n, dtype=torch.float32, device=device()),
+                      torch.zeros(k, dtype=torch.uint8, device=device())])
+    for r in (1, 2, 3):
+        assert state[0][1].sizes()["k_tile"] == widths[0 if r == 1 else 1]
+        stats = [ctx.assign(X, f, r, a, own, lam_) for ctx, f, a, own, lam_ in state]
+        (_, _, a1, _, l1), (_, _, a2, _, l2) = state
+        assert torch.equal(a1, a2) and torch.equal(l1, l2)
+        for key in ("multadds", "moved", "icp_objects", "n_invariant"):
+            assert stats[0][key] == stats[1][key], key
+        for ctx, f, a, own, lam_ in state:
+            ctx.update(X, a, lam_, f)
+    p1, p2 = state[0][1].export(), state[1][1].export()
+    for m in p1:
+        assert torch.equal(p1[m], p2[m]), m
+    for ctx, f, *_ in state:
+        f.free()
+        ctx.close()

@@ -322,12 +322,19 @@ bool split_possible(const sivf_options& o) {
            o.tiles_per_launch <= 1 && o.head_density > 0.0f;
 }
 
-// It needs rows and objects enough.  Rows (k = 10,000, 500,000 objects, plain
-// and split): 73 rows 41 and 51 ms, 1,219 rows 58 and 55; 2,000,000 objects,
-// 2,082 rows 242 and 212.  Rows x objects (k = 1,000): 11,000 rows with 8,192
-// objects 0.20 and 0.25 ms, 16,384 0.37 and 0.35, 1,000,000 19.3 and 12.9;
-// 1,800 rows with 65,536 objects 0.95 and 0.97, 131,072 1.80 and 1.70.
-bool split_pays(int64_t rows, int64_t objects) { return rows >= 1024 && objects >= (1 << 27) / rows; }
+// What it saves and costs per object and centroid grows with the sliced terms
+// per object (h): about (h - 38) 0.1 ps, and 0.13 ms a tile are lost.  Plain and
+// split, ms: k = 10,000: h = 21 65.1 and 76.8 (1,000,000 objects), 34 8.8 and 9.1
+// (100,000), 42 27.3 and 25.6 (300,000), 52 100.6 and 87.5 (1,000,000); k = 4,000,
+// 100,000 objects, h = 76 6.4 and 5.4; k = 1,000, h = 84: 16,384 objects 0.37 and
+// 0.35, 1,000,000 19.1 and 13.1; k = 300, h = 48, 60,000 0.49 and 0.66, h = 58,
+// 400,000 2.10 and 2.04.  Few rows stay in L2 anyway (37 rows, h = 41: 18.2 and
+// 18.9; 270 rows, h = 42 27.3 and 25.6).
+constexpr int64_t kSplitMinRows = 128;
+bool split_pays(double h, int64_t objects, const sivf_ivf* f) {
+    return (h - 38.0) * (double)objects * (double)f->k >= 1e9 * f->T;
+}
+
 
 // ---------------------------------------------------------------- file storage
 sivf_status store_reserve(sivf_ctx* ctx, sivf_ivf* f, Store* st, int64_t cap) {
@@ -441,10 +448,10 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 // Structure f's current centroids by the flags in f->lam (Alg. 5 second half):
 // positions put the moving centroids first, then the file is built by position.
 // norms: f->cnorm has yet to be computed (the update fills it).
-// postings: an estimate of their entries.  objects: how many are likely to walk it.  The split walk's rows are made for
-// enough of them; a file built from given centroids gets none before its first
+// postings: an estimate of their entries.  X: objects likely to walk it
+// (nullptr: unknown); the split walk's rows are made if it pays for them.  A file built from given centroids gets none before its first
 // update (they take 0.17 ms of a 3.0 ms restart, and nobody may walk it so).
-sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, int64_t objects) {
+sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, const Csr* X) {
     choose_tiles(ctx, f->k, postings, f->d, &f->kt, &f->T);
     const int64_t W64 = ivf_w64(f->k);
     const int64_t nseg2 = f->d * f->T * 2;
@@ -469,6 +476,8 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
         std::max<int64_t>(1, (int64_t)std::ceil(kSplitDensity * (double)ctx->opt.head_density * f->k));
     HIPCHK(ctx, ivf_offsets(f->d, f->T, w, min_len, f->seg, f->mid, f->head, hterm, split_len, f->tlen, f->srow, sterm,
                             meta, ctx->stream));
+    const bool split = X && f->srow && X->n > 0 && X->nnz > 0;
+    if (split) HIPCHK(ctx, split_sample(X->col, X->nnz, f->srow, meta, ctx->stream));
     int64_t* h = (int64_t*)ctx->pin;
     HIPCHK(ctx, hipMemcpyAsync(h, meta, kMeta * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipMemcpyAsync(h + kMeta, f->seg + f->d * f->T, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
@@ -483,6 +492,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
                          f->v64, ctx->stream));
     f->H = 0;
     f->srows = 0;
+    f->sfrac = split && h[6] > 0 ? (double)h[5] / (double)h[6] : 0.0;
     const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
     // room for n rows in one of the two row buffers (cap: in values)
     auto rows_reserve = [&](void** buf, int64_t* cap, int64_t n) -> sivf_status {
@@ -508,8 +518,8 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
         f->H = H;
     }
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
-    // sliced rows, if a split walk is likely and there is room for them
-    if (split_pays(SH, objects) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
+    // sliced rows, if a split walk pays and there is room for them
+    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
         rows_reserve(&f->sval, &f->scap, SH) == SIVF_OK) {
         uint32_t* wt = nullptr;
         int32_t* sterm2 = nullptr;
@@ -562,7 +572,7 @@ sivf_status init_impl(sivf_ctx* ctx, const Csr& Xc, int32_t k, const int32_t* in
         H(gather_rows(Xc, ids, k, f->cur, lens, ctx->stream, 1));
         H(fill_u8(f->lam, 0, k, ctx->stream));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true, 0.0, Xc.n);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, 0.0, &Xc);
     if (st == SIVF_OK) H(hipStreamSynchronize(ctx->stream));
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -593,7 +603,7 @@ sivf_status build_impl(sivf_ctx* ctx, const sivf_csr* C, const uint8_t* lambda, 
                        : fill_u8(f->lam, 0, k, ctx->stream);
         if (e != hipSuccess) st = fail(ctx, SIVF_E_HIP, "HIP error: %s", hipGetErrorString(e));
     }
-    if (st == SIVF_OK) st = restructure(ctx, f, true, (double)C->nnz, 0);
+    if (st == SIVF_OK) st = restructure(ctx, f, true, (double)C->nnz, nullptr);
     if (st == SIVF_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) st = fail(ctx, SIVF_E_HIP, "sync failed");
     if (st != SIVF_OK) {
         free_file(ctx, f);
@@ -620,8 +630,8 @@ struct AssignBufs {
     // split walk: objects per range (0: not split) and ranges
     int64_t range = 0, ranges = 1;
     uint2* ent = nullptr;
-    int2* hc = nullptr;
-    uint8_t* flag = nullptr;
+    int64_t npairs = 0;
+    uint2* hdr = nullptr;
     float* S = nullptr;
 };
 
@@ -632,21 +642,29 @@ struct AssignBufs {
 sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, AssignBufs* b) {
     b->range = 0;
     b->ranges = 1;
-    if (w.mode != Work::kCtx || !split_possible(ctx->opt) || !split_pays(f->srows, Xc.n)) return SIVF_OK;
+    if (w.mode != Work::kCtx || !split_possible(ctx->opt) || f->srows == 0 || Xc.n == 0) return SIVF_OK;
+    const double h = f->sfrac * Xc.nnz / Xc.n;
+    if (!split_pays(h, Xc.n, f)) return SIVF_OK;
     const int64_t ktp = head_ktp(f->kt);
-    const int64_t range = std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp);
-    int64_t most = Xc.nnz, *m = nullptr;
-    if (range < Xc.n) {
-        STCHK(w.get("split_most", 1, &m));
-        HIPCHK(ctx, fill_i64(m, 0, 1, ctx->stream));
-        HIPCHK(ctx, range_nnz(Xc.rp, Xc.n, range, m, ctx->stream));
-        HIPCHK(ctx, hipMemcpyAsync(ctx->pin, m, 8, hipMemcpyDeviceToHost, ctx->stream));
-        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-        most = *(const int64_t*)ctx->pin;
+    int64_t range = std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp), pairs = 0, *most = nullptr;
+    STCHK(w.get("split_most", 1, &most));
+    for (;; range = (range + 1) / 2) {
+        if (!split_pays(h, range, f)) return SIVF_OK;   // very long rows
+        int64_t nnz = Xc.nnz;
+        if (range < Xc.n) {
+            HIPCHK(ctx, fill_i64(most, 0, 1, ctx->stream));
+            HIPCHK(ctx, range_nnz(Xc.rp, Xc.n, range, most, ctx->stream));
+            HIPCHK(ctx, hipMemcpyAsync(ctx->pin, most, 8, hipMemcpyDeviceToHost, ctx->stream));
+            HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+            nnz = *(const int64_t*)ctx->pin;
+        }
+        pairs = split_pairs(nnz, range);
+        if (pairs <= kSplitMaxPairs) break;
     }
-    if (w.get("split_ent", most, &b->ent) != SIVF_OK || w.get("split_hc", range, &b->hc) != SIVF_OK ||
-        w.get("split_flag", range, &b->flag) != SIVF_OK || w.get("split_S", range * ktp, &b->S) != SIVF_OK)
+    if (w.get("split_ent", pairs, &b->ent) != SIVF_OK || w.get("split_hdr", range, &b->hdr) != SIVF_OK ||
+        w.get("split_S", range * ktp, &b->S) != SIVF_OK)
         return SIVF_OK;
+    b->npairs = pairs;
     b->range = range;
     b->ranges = (Xc.n + range - 1) / range;
     return SIVF_OK;
@@ -782,8 +800,8 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
             R.meta = f->meta;
             R.tlen = f->tlen;
             R.ent = B.ent;
-            R.hc = B.hc;
-            R.flag = B.flag;
+            R.npairs = B.npairs;
+            R.hdr = B.hdr;
             R.S = B.S;
             for (int64_t r = 0; r < B.ranges; ++r) {
                 R.c0 = r * B.range;
@@ -891,7 +909,7 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     HIPCHK(ctx, hipMemcpyAsync(f->lam, lambda, (size_t)k, hipMemcpyDeviceToDevice, s));
     f->nonneg = f->nonneg && Xc.nonneg;
     // (a cluster's members share terms: a quarter to two thirds of their nonzeros remain)
-    STCHK(restructure(ctx, f, false, Xc.nnz / 3.0, Xc.n));
+    STCHK(restructure(ctx, f, false, Xc.nnz / 3.0, &Xc));
     HIPCHK(ctx, hipEventRecord(ctx->ev[4], s));
     if (stats_host) {
         HIPCHK(ctx, hipStreamSynchronize(s));

@@ -19,8 +19,11 @@ static_assert(kTermCap % 64 == 0, "the walk reads staged terms a whole 64-term c
 constexpr int kSliceBytes = 256;   // of a sliced row: one block of 64 centroids
 constexpr int kSliceCols = 64;
 constexpr int kSplitHot = 608;     // sliced rows whose slices of a block fit a CU's LDS (and a row of zeros)
-constexpr int64_t kSplitMaxRows = 1 << 20;   // a block's slices stay well below 4 GiB
-constexpr int kMeta = 5;           // counts of a file on the device (sivf_ivf::meta)
+// pairs of a range: two chunks of fill, then every object's, filled up twice
+inline int64_t split_pairs(int64_t nnz, int64_t objects) { return 32 + nnz + 32 * objects; }
+constexpr int64_t kSplitMaxPairs = (1 << 29) - 1;   // of a range: less than 4 GiB
+constexpr int64_t kSplitMaxRows = (1 << 20) - 1;   // 20 bits; a block's slices stay well below 4 GiB
+constexpr int kMeta = 7;           // counts of a file on the device (sivf_ivf::meta)
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request
 constexpr int kWalkWaves = 4;      // waves per workgroup in the walk kernels
 constexpr int kTileWide = 2048, kTileMid = 1536, kTileNarrow = 1024;   // automatic tile widths
@@ -100,9 +103,9 @@ struct WalkArgs {
     int64_t srows;
     const int64_t* meta;    // [3]: rows whose slices go to LDS (rows 0 ..)
     const int2* tlen;       // [d] postings of each term, and those of moving centroids
-    uint2* ent;             // [nonzeros of the range] (code, value) pairs per object
-    int2* hc;               // [n] LDS rows, other head rows of each object
-    uint8_t* flag;          // [n] bit 0: ICP branch, bit 1: relaxed branch
+    uint2* ent;             // [npairs] (code, value) pairs of the range's objects
+    int64_t npairs;
+    uint2* hdr;             // [n] an object's first pair; other sliced rows << 12 | LDS rows << 2 | 2: relaxed | 1: ICP
     float* S;               // [n * head_ktp(kt)] head terms' sums of the current tile
     // relaxed ICP (filter mode RELAXED)
     Store st;                  // the current centroids (FP64 CSR) for exact similarities
@@ -143,11 +146,13 @@ struct sivf_ivf {
     void* hval = nullptr;           // [hcap] dense head rows of kpad values, posting dtype
     int64_t H = 0, hcap = 0;        // head rows in use / values allocated
     // the split walk's rows (allocated if a split walk may come)
-    int64_t* meta = nullptr;        // [kMeta] moving centroids, postings, head rows, rows read through LDS, sliced rows
+    int64_t* meta = nullptr;        // [kMeta] moving centroids, postings, head rows, rows read through LDS, sliced rows,
+                                    // sampled nonzeros of sliced terms, sampled nonzeros
     int2* tlen = nullptr;           // [d] postings of each term, and those of moving centroids
     int32_t* srow = nullptr;        // [d] sliced row of each term, -1 if none
     void* sval = nullptr;           // [scap] sliced rows of kpad values, FP32
     int64_t srows = 0, scap = 0;    // sliced rows in use / values allocated
+    double sfrac = 0.0;             // fraction of the objects' nonzeros in sliced terms (a sample)
     uint8_t* lam = nullptr;         // [k]
     double* cnorm = nullptr;        // [k]
     int nonneg = 1;
@@ -217,6 +222,9 @@ hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T
 hipError_t ivf_offsets(int64_t d, int32_t T, IvfBuildWs w, int64_t min_len, int64_t* seg, int32_t* mid, int32_t* head,
                        int32_t* hterm, int64_t split_len, int2* tlen, int32_t* srow, int32_t* sterm, int64_t* meta,
                        hipStream_t s);
+// meta[6] += nonzeros sampled (at most 65,536, evenly spaced), meta[5] += those
+// whose term has a sliced row
+hipError_t split_sample(const int32_t* col, int64_t nnz, const int32_t* srow, int64_t* meta, hipStream_t s);
 // sliced rows: renumbered with the heaviest (by the sum of |values|) first,
 // meta[3] = how many of them go to LDS, at most kSplitHot; then filled.  wt [H]
 // workspace, sterm [H] -> sterm2 [H].

@@ -87,6 +87,8 @@ __global__ __launch_bounds__(1024) void k_ivf_perm(const uint8_t* __restrict__ l
         meta[1] = ncarry;
         meta[2] = 0;
         meta[4] = 0;
+        meta[5] = 0;
+        meta[6] = 0;
     }
 }
 
@@ -369,6 +371,33 @@ hipError_t head_fill(const int32_t* hterm, const int64_t* seg, const uint16_t* c
 // The split walk's rows: like dense head rows (FP32), but stored by blocks of
 // 64 slots, [tile][block][row], 256-byte slices, so that a pass over one block
 // reads one contiguous array of slices, whatever rows it needs.
+
+// 1024 runs of 64 nonzeros
+__global__ __launch_bounds__(256) void k_split_sample(const int32_t* __restrict__ col, int64_t nnz,
+                                                      const int32_t* __restrict__ srow, int64_t* __restrict__ meta) {
+    __shared__ int sh[4][2];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int has = 0, all = 0;
+    for (int q = 0; q < 4; ++q) {
+        const int64_t run = (blockIdx.x * 4 + wid) * 4 + q, p = run * (nnz / 1024) + lane;
+        const bool in = p < nnz;
+        all += __popcll(ballot(in));
+        has += __popcll(ballot(in && srow[col[in ? p : 0]] >= 0));
+    }
+    if (lane == 0) {
+        sh[wid][0] = has;
+        sh[wid][1] = all;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        atomicAdd((unsigned long long*)&meta[5 + threadIdx.x],
+                  (unsigned long long)(sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x]));
+}
+
+hipError_t split_sample(const int32_t* col, int64_t nnz, const int32_t* srow, int64_t* meta, hipStream_t s) {
+    hipLaunchKernelGGL(k_split_sample, dim3(64), dim3(256), 0, s, col, nnz, srow, meta);
+    return hipGetLastError();
+}
 
 // sum of |values| of each row's postings (a fixed order), as ordered bits
 __global__ __launch_bounds__(256) void k_split_weight(const int32_t* __restrict__ sterm, const int64_t* __restrict__ seg,

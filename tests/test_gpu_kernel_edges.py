@@ -310,15 +310,15 @@ def _striped(n, d, lam, seed, dtype, signed=False, empty=False):
 
 
 @pytest.mark.parametrize("n,d,lam,k,kt,mode,dtype,signed,empty", [
-    (90_003, 1_600, 40, 70, 64, "sivf", torch.float32, False, False),    # two tiles, the last of 6 centroids
-    (90_001, 1_600, 20, 130, 0, "relaxed", torch.float64, False, True),  # three blocks, the last of 2
-    (70_002, 2_400, 150, 64, 0, "sivf", torch.float32, True, False),     # rows over two chunks, signed values
-    (70_000, 2_400, 8, 600, 0, "ivf", torch.float32, False, False),      # two phases of blocks; no filter
-    (2_200_001, 1_100, 5, 12, 0, "sivf", torch.float32, False, False),   # two ranges of objects
+    (500_003, 1_600, 100, 70, 64, "sivf", torch.float32, False, False),   # two tiles, the last of 6 centroids
+    (300_001, 1_600, 80, 130, 0, "relaxed", torch.float64, False, True),  # three blocks, the last of 2; empty rows
+    (150_002, 2_400, 150, 64, 0, "sivf", torch.float32, True, False),     # rows over two chunks, signed values
+    (100_000, 2_400, 60, 600, 0, "ivf", torch.float32, False, False),     # ten blocks over eight parts; no filter
+    (2_200_001, 1_120, 80, 12, 0, "sivf", torch.float32, False, False),   # two ranges of objects
 ])
 def test_split_walk_equals_the_plain_walk(n, d, lam, k, kt, mode, dtype, signed, empty):
-    # rows x objects put the walk past the split's line; a workspace cap (far
-    # above what is used) keeps it plain.  Assignments, own similarities and
+    # sliced terms x objects x centroids put the walk past the split's line; a
+    # workspace cap (far above what is used) keeps it plain.  Assignments, own similarities and
     # counts are those of the plain walk, and the assignments the argmax in FP64
     log("split walk n %d d %d lam %d k %d" % (n, d, lam, k))
     X = _striped(n, d, lam, 5, dtype, signed, empty)

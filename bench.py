@@ -38,7 +38,7 @@ WALK_KERNEL = "k_walk_dense + k_walk_fast<false, false, false, true>"
 # runs; used only while the kernel sources still hash the same
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "walk_8m_k10k_dram_traffic.md")
 WALK_SOURCES = ["paper_2103_16141_amd/csrc/k_assign.hip", "paper_2103_16141_amd/csrc/internal.h",
-                "paper_2103_16141_amd/csrc/wave.h"]
+                "paper_2103_16141_amd/csrc/slices.h", "paper_2103_16141_amd/csrc/wave.h"]
 
 
 def walk_source_hash():

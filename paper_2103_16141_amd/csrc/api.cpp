@@ -1235,6 +1235,19 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     SoftFwdWs w{};
     // rows per launch: the per-block partials of one launch take at most 512 MiB
     w.rows = std::max<int64_t>(1, std::min<int64_t>(Xc.n, (int64_t)(64ll << 20) / nblk));
+    // the commonest terms in LDS: fewer rows per launch; without a workspace cap,
+    // and only if there is memory
+    const int64_t lds_rows = ctx->opt.workspace_cap_bytes == 0 ? soft_lds_rows(Xc.n, Xc.nnz, Xc.d, k) : 0;
+    if (lds_rows > 0) {
+        const int64_t rows = std::min(lds_rows, w.rows);
+        w.nnz = Xc.nnz;
+        if (ws(ctx, "soft_hdr", rows, &w.hdr) == SIVF_OK && ws(ctx, "soft_count", Xc.d, &w.count) == SIVF_OK &&
+            ws(ctx, "soft_slot", Xc.d, &w.slot) == SIVF_OK && ws(ctx, "soft_hot", kSplitHot + 1, &w.term) == SIVF_OK &&
+            ws(ctx, "soft_ent", split_pairs(Xc.nnz, rows), &w.ent) == SIVF_OK) {
+            w.nhot = w.term + kSplitHot;
+            w.rows = rows;
+        }
+    }
     STCHK(ws(ctx, "soft_CT", nblk * kSoftBlk * Xc.d, &CT));
     STCHK(ws(ctx, "soft_loss", 1, &loss));
     STCHK(ws(ctx, "soft_pmax", w.rows * nblk, &w.pmax));

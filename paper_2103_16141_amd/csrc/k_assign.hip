@@ -30,6 +30,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "slices.h"
 #include "wave.h"
 
 #pragma clang fp contract(off)
@@ -367,10 +368,6 @@ __device__ double exact_rho(const WalkArgs& A, const Store& st, int64_t r0, int 
 // BF16 instantiations ask for 6 waves per SIMD (80 VGPRs): measured 6% faster
 // at N=8M, k=10k; the FP32 ones stay at the compiler's choice (5 waves),
 // where the cap's spills cost more than the extra wave gains.
-__device__ inline int hdr_hot(const uint2& hd) { return (int)((hd.y >> 2) & 1023u); }
-__device__ inline int hdr_cold(const uint2& hd) { return (int)(hd.y >> 12); }
-__device__ inline int chunks16(int n) { return (n + 15) >> 4; }
-
 // SPLIT: k_walk_prep has sorted the objects' terms and k_walk_dense has put the
 // head terms' sums of this tile into A.S; the wave starts from those and walks
 // the remaining terms' lists.
@@ -886,8 +883,6 @@ int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split) {
 // (prep 1.5, dense 8.7, lists 3.5) now; 2,000,000, k = 10,000: 231 and 185 ms
 // (2.7, 104, 78).
 
-constexpr uint32_t kOutside = 0xffffff00u;
-
 // One wave per object of the range: its terms as (code, value) pairs, rows of
 // LDS slices first (code: byte offset of the slice in a block), then the other
 // sliced rows, then the terms with lists only (code: the term), each in ascending
@@ -975,222 +970,38 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
     }
 }
 
-// The head terms' sums of one tile.  A workgroup of 16 waves holds a block's
-// slices of the heaviest rows in LDS and takes four objects per wave, one per
-// 16-lane DPP row: a term's code and value reach the row's lanes by a broadcast,
-// each lane adds 16 bytes of the slice (4 centroids), terms in the order of the
-// pairs.  Slices are 256 bytes apart, so the 16 lanes of a DPP row read each LDS
-// bank once.  Bound by vector instructions (5 a step, 20 cycles, 4 waves per
-// SIMD: 65% of the time at k = 10,000; LDS reads 30%) and by the return path of
-// the other rows' slices, which come from L2 (busy 89%).  Pairs in chunks of 16,
-// fetched a group ahead, multiply-adds that broadcast by themselves, and all XCDs
-// on the same objects: 569,413 objects, k = 8,482 46.6 -> 43.2 ms (whole walk).
-constexpr int kDenseThreads = 1024;
-
-template <int S>
-__device__ inline uint32_t drow_bcast(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + S, 0xf, 0xf, true);
-}
-
-// acc += v[4 G + i] * u[i], i = 0 .. 3, v broadcast within each DPP row by the
-// multiply-add itself (compiled from a broadcast and four fmaf it takes a move
-// more per step).  A DPP operand may not be written by the two instructions
-// before: hence the s_nop.
-template <int G>
-__device__ inline void dense_fma4(float4& acc, float v, const u32x4 (&u)[4]) {
-#define STEP(S, A, B, C, D)                                                          \
-    "v_fmac_f32_dpp %0, %4, " A " row_newbcast:" S " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp %1, %4, " B " row_newbcast:" S " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp %2, %4, " C " row_newbcast:" S " row_mask:0xf bank_mask:0xf\n\t" \
-    "v_fmac_f32_dpp %3, %4, " D " row_newbcast:" S " row_mask:0xf bank_mask:0xf\n\t"
-#define FOUR(S0, S1, S2, S3)                                                                                     \
-    asm("s_nop 1\n\t" STEP(S0, "%5", "%6", "%7", "%8") STEP(S1, "%9", "%10", "%11", "%12")                       \
-            STEP(S2, "%13", "%14", "%15", "%16") STEP(S3, "%17", "%18", "%19", "%20")                            \
-        : "+v"(acc.x), "+v"(acc.y), "+v"(acc.z), "+v"(acc.w)                                                     \
-        : "v"(v), "v"(u[0].x), "v"(u[0].y), "v"(u[0].z), "v"(u[0].w), "v"(u[1].x), "v"(u[1].y), "v"(u[1].z),     \
-          "v"(u[1].w), "v"(u[2].x), "v"(u[2].y), "v"(u[2].z), "v"(u[2].w), "v"(u[3].x), "v"(u[3].y), "v"(u[3].z), \
-          "v"(u[3].w))
-    if (G == 0) FOUR("0", "1", "2", "3");
-    if (G == 1) FOUR("4", "5", "6", "7");
-    if (G == 2) FOUR("8", "9", "10", "11");
-    if (G == 3) FOUR("12", "13", "14", "15");
-#undef FOUR
-#undef STEP
-}
-
-typedef __attribute__((address_space(3))) const u32x4* lds_u32x4;
-
-// steps 4 G .. 4 G + 3 of the 16 pairs e held by each DPP row: slices in LDS
-// (panel16: the panel's address + 16 q) or in memory
-template <int G>
-__device__ inline void dense_hot_load4(u32x4 (&u)[4], uint32_t panel16, const uint2& e) {
-    u[0] = *(lds_u32x4)(drow_bcast<4 * G + 0>(e.x) + panel16);
-    u[1] = *(lds_u32x4)(drow_bcast<4 * G + 1>(e.x) + panel16);
-    u[2] = *(lds_u32x4)(drow_bcast<4 * G + 2>(e.x) + panel16);
-    u[3] = *(lds_u32x4)(drow_bcast<4 * G + 3>(e.x) + panel16);
-}
-template <int G>
-__device__ inline void dense_cold_load4(u32x4 (&u)[4], __amdgpu_buffer_rsrc_t r, const uint2& e, uint32_t q16) {
-    u[0] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 0>(e.x) | q16, 0, 0);
-    u[1] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 1>(e.x) | q16, 0, 0);
-    u[2] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 2>(e.x) | q16, 0, 0);
-    u[3] = __builtin_amdgcn_raw_buffer_load_b128(r, drow_bcast<4 * G + 3>(e.x) | q16, 0, 0);
-}
-
-// over the four DPP rows (v is the same in a row's lanes)
-__device__ inline int rows_max(int v) {
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
-
-// A lane's place in a list of pairs: byte offset of its pair in the next chunk of
-// 16, and the chunks left; then chunks of fill.
-struct DenseList {
-    uint32_t at;
-    int left;
-};
-
-// Pairs are loaded through a descriptor of all pairs (less than 4 GiB), whether
-// or not the list has any left: a load that may not happen would make the
-// compiler wait for all before it.
-__device__ inline uint2 next_pairs(__amdgpu_buffer_rsrc_t ents, DenseList& l, uint32_t fill) {
-    const uint32_t at = l.left > 0 ? l.at : fill;
-    l.at += 128;
-    l.left -= 1;
-    const auto v = __builtin_amdgcn_raw_buffer_load_b64(ents, at, 0, 0);
-    return make_uint2(v[0], v[1]);
-}
-
-// 16 pairs of the LDS rows (e) and CQ groups of four of the others (c) of a
-// wave's objects: the latter's slices and the next pairs are in flight while
-// the former are added.  mh, mc: steps left.
-template <int CQ>
-__device__ inline void dense_round(float4& acc, uint2& c, uint2& e, int mh, int mc, __amdgpu_buffer_rsrc_t ents, DenseList& lc,
-                                   DenseList& lh, uint32_t panel16, __amdgpu_buffer_rsrc_t rsrc, uint32_t q16,
-                                   uint32_t q8) {
-    u32x4 u0[4], u1[4], u2[4], u3[4], a[4];
-    uint2 cn = c, en = e;
-    if (CQ == 4 && mc > 16) cn = next_pairs(ents, lc, 128 + q8);
-    if (mh > 16) en = next_pairs(ents, lh, q8);
-    __builtin_amdgcn_sched_barrier(0);
-    if (CQ > 0) dense_cold_load4<0>(u0, rsrc, c, q16);
-    if (CQ > 1) dense_cold_load4<1>(u1, rsrc, c, q16);
-    if (CQ > 2) dense_cold_load4<2>(u2, rsrc, c, q16);
-    if (CQ > 3) dense_cold_load4<3>(u3, rsrc, c, q16);
-    __builtin_amdgcn_sched_barrier(0);
-    const float ev = __uint_as_float(e.y), cv = __uint_as_float(c.y);
-    if (0 < mh) {
-        dense_hot_load4<0>(a, panel16, e);
-        dense_fma4<0>(acc, ev, a);
-    }
-    if (4 < mh) {
-        dense_hot_load4<1>(a, panel16, e);
-        dense_fma4<1>(acc, ev, a);
-    }
-    if (8 < mh) {
-        dense_hot_load4<2>(a, panel16, e);
-        dense_fma4<2>(acc, ev, a);
-    }
-    if (12 < mh) {
-        dense_hot_load4<3>(a, panel16, e);
-        dense_fma4<3>(acc, ev, a);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (CQ > 0) dense_fma4<0>(acc, cv, u0);
-    if (CQ > 1) dense_fma4<1>(acc, cv, u1);
-    if (CQ > 2) dense_fma4<2>(acc, cv, u2);
-    if (CQ > 3) dense_fma4<3>(acc, cv, u3);
-    c = cn;
-    e = en;
-}
-
+// The head terms' sums of one tile (dense_groups).  Bound by vector instructions
+// (5 a step, 20 cycles, 4 waves per SIMD: 65% of the time at k = 10,000; LDS
+// reads 30%) and by the return path of the other rows' slices, which come from
+// L2 (busy 89%).  Pairs in chunks of 16, fetched a group ahead, multiply-adds
+// that broadcast by themselves, and all XCDs on the same objects: 569,413
+// objects, k = 8,482 46.6 -> 43.2 ms (whole walk).
 __global__ __launch_bounds__(kDenseThreads) void k_walk_dense(WalkArgs A, int tile) {
-    extern __shared__ u32x4 dense_panel[];
+    extern __shared__ u32x4 panel[];
     const int lane = threadIdx.x & 63, q = lane & 15, sub = lane >> 4;
-    const uint32_t q16 = 16u * q, q8 = 8u * q;
-    const uint32_t panel16 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(char*)dense_panel + q16;
     const int ktp = (A.kt + 511) & ~511, nbt = ktp / kSliceCols;
     const int nhot = (int)A.meta[3];
     const int base = tile * A.kt, width = min(A.kt, A.k - base);
-    const int used = (width + kSliceCols - 1) / kSliceCols;
     const int n = (int)A.n, groups = (n + 3) / 4;   // a range: at most 2^21 objects
-    const __amdgpu_buffer_rsrc_t ents =
-        __builtin_amdgcn_make_buffer_rsrc(A.ent, (short)0, (int)(uint32_t)(A.npairs * sizeof(uint2)), 0x00020000);
+    const __amdgpu_buffer_rsrc_t ents = bytes_rsrc(A.ent, (uint32_t)(A.npairs * sizeof(uint2)));
     uint32_t loads = 0;   // this wave's vector loads, in KB requested
-    // eight blocks at a time, one per XCD, over the same objects (their pairs are
-    // then read from memory once); of the rest's (block, group) pairs, block-major,
-    // an XCD takes an eighth
-    // (at most 2^31 pairs: 64 blocks, 4 GiB of sums)
-    const int xcd = blockIdx.x % kXcds, whole = used / kXcds * kXcds, rest = (used - whole) * groups;
-    const int wave = (blockIdx.x / kXcds) * (kDenseThreads / 64) +
-                         __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int step = (gridDim.x / kXcds) * (kDenseThreads / 64);
-    const int mine = (int)((int64_t)xcd * rest / kXcds);
-    const int end = whole / kXcds * groups + (int)((int64_t)(xcd + 1) * rest / kXcds) - mine;
-    for (int at = 0; at < end;) {
-        int blk = at / groups, g0 = at - blk * groups;
-        if (blk < whole / kXcds) {
-            blk = blk * kXcds + xcd;
-        } else {
-            const int r = mine + at - whole / kXcds * groups;
-            blk = r / groups;
-            g0 = r - blk * groups;
-            blk += whole;
-        }
-        const int g1 = min(groups, g0 + end - at);
-        at += g1 - g0;
+    each_block((width + kSliceCols - 1) / kSliceCols, groups, [&](int blk, int g0, int g1) {
         const char* src = (const char*)A.sval + ((int64_t)tile * nbt + blk) * A.srows * kSliceBytes;
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char*>(src), (short)0, (int)(uint32_t)(A.srows * kSliceBytes), 0x00020000);
         __syncthreads();
-        for (int e = threadIdx.x; e < nhot * 16; e += kDenseThreads) dense_panel[e] = reinterpret_cast<const u32x4*>(src)[e];
-        if (threadIdx.x < 16) dense_panel[nhot * 16 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+        for (int e = threadIdx.x; e < nhot * 16; e += kDenseThreads) panel[e] = reinterpret_cast<const u32x4*>(src)[e];
+        if (threadIdx.x < 16) panel[nhot * 16 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
         __syncthreads();
         loads += (uint32_t)(nhot / 64 + 1);
         const bool moving = base + blk * kSliceCols < A.nmv;   // some centroid of the block moved
-        const int first = g0 + wave;
-        if (first >= g1) continue;
-        auto header = [&](int g) { return A.hdr[min(4 * g + sub, n - 1)]; };
-        // a set flag: the object compares moving centroids only
-        auto wanted = [&](int g, const uint2& hd) { return 4 * g + sub < n && ((hd.y & 3u) == 0 || moving); };
-        // headers are fetched two groups ahead, first pairs one
-        uint2 hd = header(first);
-        int nh = 0, nc = 0;
-        DenseList lh, lc;
-        auto lists = [&](bool want, int& h, int& c) {
-            h = want ? hdr_hot(hd) : 0;
-            c = want ? hdr_cold(hd) : 0;
-            lh = DenseList{hd.x * 8 + q8, chunks16(h)};
-            lc = DenseList{lh.at + 128 * lh.left, chunks16(c)};
-        };
-        bool write = wanted(first, hd);
-        lists(write, nh, nc);
-        uint2 c = next_pairs(ents, lc, 128 + q8), e = next_pairs(ents, lh, q8);
-        hd = header(first + step);
-        for (int g = first; g < g1; g += step) {
-            const int mh = rows_max(nh), mc = rows_max(nc);
-            const bool nwrite = wanted(g + step, hd);
-            DenseList mlh = lh, mlc = lc;
-            lists(nwrite, nh, nc);
-            const uint2 cn = next_pairs(ents, lc, 128 + q8), en = next_pairs(ents, lh, q8);
-            hd = header(g + 2 * step);
-            float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            for (int h = 0; h < mc || h < mh; h += 16) {
-                const int cq = min(4, max(0, mc - h + 3) >> 2);
-                loads += 1 + 4u * cq;
-                if (cq == 0) dense_round<0>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
-                else if (cq == 1) dense_round<1>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
-                else if (cq == 2) dense_round<2>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
-                else if (cq == 3) dense_round<3>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
-                else dense_round<4>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
-            }
-            if (write)
-                *reinterpret_cast<float4*>(A.S + (int64_t)(4 * g + sub) * ktp + blk * kSliceCols + 4 * q) = acc;
-            write = nwrite;
-            c = cn;
-            e = en;
-        }
-    }
+        dense_groups<1>(
+            g0, g1, ents, panel, bytes_rsrc(src, (uint32_t)(A.srows * kSliceBytes)), loads,
+            [&](int g) { return A.hdr[min(4 * g + sub, n - 1)]; },
+            // a set flag: the object compares moving centroids only
+            [&](int g, const uint2& hd) { return 4 * g + sub < n && ((hd.y & 3u) == 0 || moving); },
+            [&](int g, const float4& acc, bool want) {
+                if (want) *reinterpret_cast<float4*>(A.S + (int64_t)(4 * g + sub) * ktp + blk * kSliceCols + 4 * q) = acc;
+            });
+    });
     if (lane == 0 && loads) {
         atomicAdd(&A.counters[10], 1024ull * loads);
         atomicAdd(&A.counters[11], 1024ull * loads);

@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "slices.h"
 #include "wave.h"
 
 namespace sivf {
@@ -414,57 +415,36 @@ __global__ __launch_bounds__(256) void k_split_weight(const int32_t* __restrict_
     if (lane == 0) wt[r] = __float_as_uint(acc);
 }
 
-// One workgroup: the largest set {weight >= x} of at most kSplitHot rows (the
-// same on every run), numbered first.  The numbers inside the two groups come
-// from atomics; they change no result.
+// One workgroup: the heaviest rows that fit LDS, numbered first.  The numbers
+// inside the two groups come from atomics; they change no result.
 __global__ __launch_bounds__(1024) void k_split_order(const uint32_t* __restrict__ wt, const int32_t* __restrict__ sterm,
-                                                     int64_t H, int32_t* __restrict__ sterm2, int32_t* __restrict__ srow,
-                                                     int64_t* __restrict__ meta) {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t prefix, left, nh, nc;
-    if (threadIdx.x == 0) {
-        prefix = 0;
-        left = kSplitHot;   // rank of the row sought among those with the prefix
-        nh = nc = 0;
-    }
-    // the kSplitHot-th largest weight, byte by byte
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-        __syncthreads();
-        const uint32_t pf = prefix;
-        for (int64_t r = threadIdx.x; r < H; r += 1024)
-            if (shift == 24 || (wt[r] >> (shift + 8)) == pf) atomicAdd(&hist[(wt[r] >> shift) & 255u], 1u);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t b = 255, before = 0;
-            while (b > 0 && before + hist[b] < left) before += hist[b--];
-            left -= before;
-            prefix = (pf << 8) | b;
-        }
-        __syncthreads();
-    }
-    // rows at least as heavy: kept if they all fit, else only the heavier ones
-    const uint32_t y = prefix;
-    uint32_t ge = 0;
-    for (int64_t r = threadIdx.x; r < H; r += 1024) ge += wt[r] >= y ? 1u : 0u;
-    ge = (uint32_t)wave_sum_i64(ge);
-    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[0], ge);
-    __syncthreads();
-    const bool ties = hist[0] <= (uint32_t)kSplitHot;
+                                                      int64_t H, int32_t* __restrict__ sterm2, int32_t* __restrict__ srow,
+                                                      int64_t* __restrict__ meta) {
+    __shared__ uint32_t sh[258];
+    __shared__ uint32_t count, nh, nc;
+    if (threadIdx.x == 0) count = nh = nc = 0;
+    const uint32_t x = top_weights(wt, H, kSplitHot, sh);
     uint32_t hot = 0;
-    for (int64_t r = threadIdx.x; r < H; r += 1024) hot += (wt[r] > y || (ties && wt[r] == y)) ? 1u : 0u;
+    each_weight(wt, H, [&](uint32_t v, int64_t) { hot += v >= x ? 1u : 0u; });
     hot = (uint32_t)wave_sum_i64(hot);
-    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[1], hot);
+    if ((threadIdx.x & 63) == 0) atomicAdd(&count, hot);
     __syncthreads();
-    hot = hist[1];
-    for (int64_t r = threadIdx.x; r < H; r += 1024) {
-        const bool h = wt[r] > y || (ties && wt[r] == y);
-        const uint32_t q = h ? atomicAdd(&nh, 1u) : hot + atomicAdd(&nc, 1u);
-        sterm2[q] = sterm[r];
-        srow[sterm[r]] = (int32_t)q;
-    }
+    hot = count;
+    // a wave takes its lanes' numbers at once
+    auto take = [&](bool has, uint32_t* c) -> uint32_t {
+        const unsigned long long m = ballot(has);
+        uint32_t at = 0;
+        if (m && (threadIdx.x & 63) == 0) at = atomicAdd(c, (uint32_t)__popcll(m));
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)at) + lanes_below(m);
+    };
+    each_weight(wt, H, [&](uint32_t v, int64_t r) {
+        const bool h = r < H && v >= x, c = r < H && v < x;
+        const uint32_t qh = take(h, &nh), qc = hot + take(c, &nc);
+        if (!h && !c) return;
+        const int32_t t = sterm[r];
+        sterm2[h ? qh : qc] = t;
+        srow[t] = (int32_t)(h ? qh : qc);
+    });
     if (threadIdx.x == 0) meta[3] = hot;
 }
 

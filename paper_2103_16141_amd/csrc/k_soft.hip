@@ -27,6 +27,7 @@
 #include <utility>
 
 #include "internal.h"
+#include "slices.h"
 #include "soft.h"
 #include "wave.h"
 
@@ -324,24 +325,171 @@ __global__ __launch_bounds__(1024) void k_soft_loss(const double* __restrict__ p
     if (threadIdx.x == 0) *out = -sh[0];
 }
 
+// ---------------------------------------------------------------- forward, the commonest terms in LDS
+// Larger calls read the slices of the 608 commonest terms (56% of the nonzeros
+// at Zipf 1.1, D = 100,000) from LDS: the gather's L1 misses were all of its
+// time, and those slices were most of its L2 hits.  Which terms they are is
+// counted on a sample of the nonzeros; any choice gives the same sums up to
+// their order.  N = 262,144, D = 100,000, 100 terms a row, k = 4,096: 27.5 ->
+// 16.5 ms (0.3 of it choosing and sorting the terms); at N = 20,011, k = 1,021
+// (kSoftLdsWork / 2.4) 0.36 -> 0.37.
+
+// counts of terms in 1024 runs of 64 nonzeros
+__global__ __launch_bounds__(256) void k_soft_sample(const int32_t* __restrict__ col, int64_t nnz,
+                                                     uint32_t* __restrict__ count) {
+    const int64_t p = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (nnz / 1024) + (threadIdx.x & 63);
+    if (p < nnz) atomicAdd(&count[col[p]], 1u);
+}
+
+// one workgroup: the commonest terms' slots (slot[t], -1: none; term[slot]; *nhot)
+__global__ __launch_bounds__(1024) void k_soft_hot(const uint32_t* __restrict__ count, int64_t d,
+                                                   int32_t* __restrict__ slot, int32_t* __restrict__ term,
+                                                   int32_t* __restrict__ nhot) {
+    __shared__ uint32_t sh[258];
+    __shared__ uint32_t nh;
+    if (threadIdx.x == 0) nh = 0;
+    const uint32_t x = top_weights(count, d, kSplitHot, sh);
+    each_weight(count, d, [&](uint32_t v, int64_t t) {
+        if (t >= d) return;
+        int32_t q = -1;
+        if (v >= x) {
+            q = (int32_t)atomicAdd(&nh, 1u);
+            term[q] = (int32_t)t;
+        }
+        slot[t] = q;
+    });
+    __syncthreads();
+    if (threadIdx.x == 0) *nhot = (int32_t)nh;
+}
+
+// A wave per row of the chunk: its pairs and header (slices.h), the slot's or the
+// term's slice as code.  Row o's pairs start at 32 + (nonzeros before it) + 32 o.
+__global__ __launch_bounds__(256) void k_soft_prep(int64_t c0, int64_t n, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ col, const float* __restrict__ xv,
+                                                   const int32_t* __restrict__ slot, const int32_t* __restrict__ nhot,
+                                                   uint2* __restrict__ ent, uint2* __restrict__ hdr) {
+    const int lane = threadIdx.x & 63;
+    const int64_t p0 = rp[c0];
+    const uint2 fill_hot = make_uint2((uint32_t)*nhot * kSliceBytes, 0u), fill_cold = make_uint2(kOutside, 0u);
+    if (blockIdx.x == 0 && threadIdx.x < 32) ent[threadIdx.x] = threadIdx.x < 16 ? fill_hot : fill_cold;
+    for (int64_t o = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); o < n; o += (int64_t)gridDim.x * 4) {
+        const int64_t r0 = rp[c0 + o];
+        const int m = (int)(rp[c0 + o + 1] - r0);
+        int nh = 0;
+        for (int h = lane; h - lane < m; h += 64) nh += __popcll(ballot(h < m && slot[col[r0 + min(h, m - 1)]] >= 0));
+        const int nc = m - nh, ph = 16 * chunks16(nh), pc = 16 * chunks16(nc);
+        const int64_t to = 32 + (r0 - p0) + 32 * o;
+        uint2* out = ent + to;
+        if (lane < 16) {
+            if (nh + lane < ph) out[nh + lane] = fill_hot;
+            if (nc + lane < pc) out[ph + nc + lane] = fill_cold;
+        }
+        int ah = 0, ac = ph;
+        for (int h0 = 0; h0 < m; h0 += 64) {
+            const int h = h0 + lane;
+            const int32_t t = h < m ? col[r0 + h] : 0, q = h < m ? slot[t] : -1;
+            const unsigned long long mh = ballot(q >= 0), mc = ballot(h < m && q < 0);
+            if (h < m)
+                out[q >= 0 ? ah + lanes_below(mh) : ac + lanes_below(mc)] =
+                    make_uint2((uint32_t)(q >= 0 ? q : t) * kSliceBytes, __float_as_uint(xv[r0 + h]));
+            ah += __popcll(mh);
+            ac += __popcll(mc);
+        }
+        if (lane == 0) hdr[o] = make_uint2((uint32_t)to, ((uint32_t)nc << 12) | ((uint32_t)nh << 2));
+    }
+}
+
+// k_soft_fwd's results for a chunk of rows, four rows to a wave (dense_groups).
+// Four partial sums: dX, which takes exp of S from here and S from the backward,
+// is off by 1.3e-6 of its largest value with one, 0.8e-6 with four.
+__global__ __launch_bounds__(kDenseThreads) void k_soft_fwd_lds(int n, const uint2* __restrict__ ent, uint32_t npairs,
+                                                                const uint2* __restrict__ hdr,
+                                                                const int32_t* __restrict__ term,
+                                                                const int32_t* __restrict__ nhot,
+                                                                const float* __restrict__ CT, int64_t d, int32_t k,
+                                                                float inv_tau, float* __restrict__ pmax,
+                                                                float* __restrict__ psum) {
+    extern __shared__ u32x4 panel[];
+    const int q = threadIdx.x & 15, sub = (threadIdx.x & 63) >> 4, nh = *nhot;
+    const __amdgpu_buffer_rsrc_t ents = bytes_rsrc(ent, npairs * (uint32_t)sizeof(uint2));
+    uint32_t loads = 0;
+    each_block((k + kBlk - 1) / kBlk, (n + 3) / 4, [&](int blk, int g0, int g1) {
+        const char* src = (const char*)(CT + (int64_t)blk * d * kBlk);
+        __syncthreads();
+        for (int e = threadIdx.x; e < nh * 16; e += kDenseThreads)
+            panel[e] = *reinterpret_cast<const u32x4*>(src + (int64_t)term[e >> 4] * kSliceBytes + 16 * (e & 15));
+        if (threadIdx.x < 16) panel[nh * 16 + threadIdx.x] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+        const int cols = k - blk * kBlk - 4 * q;   // of the lane's four, those that exist
+        dense_groups<4>(
+            g0, g1, ents, panel, bytes_rsrc(src, (uint32_t)(d * kSliceBytes)), loads,
+            [&](int g) { return hdr[min(4 * g + sub, n - 1)]; }, [&](int g, const uint2&) { return 4 * g + sub < n; },
+            [&](int g, const float4& acc, bool want) {
+                const float x0 = cols > 0 ? acc.x * inv_tau : -INFINITY, x1 = cols > 1 ? acc.y * inv_tau : -INFINITY;
+                const float x2 = cols > 2 ? acc.z * inv_tau : -INFINITY, x3 = cols > 3 ? acc.w * inv_tau : -INFINITY;
+                float mx = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
+                mx = fmaxf(mx, dpp<0x128>(mx));
+                mx = fmaxf(mx, dpp<0x124>(mx));
+                mx = fmaxf(mx, dpp<0x122>(mx));
+                mx = fmaxf(mx, dpp<0x121>(mx));
+                const float b = mx == -INFINITY ? 0.0f : mx;
+                float z = (cols > 0 ? expf(x0 - b) : 0.0f) + (cols > 1 ? expf(x1 - b) : 0.0f);
+                z = z + ((cols > 2 ? expf(x2 - b) : 0.0f) + (cols > 3 ? expf(x3 - b) : 0.0f));
+                z = z + dpp<0x128>(z);
+                z = z + dpp<0x124>(z);
+                z = z + dpp<0x122>(z);
+                z = z + dpp<0x121>(z);
+                if (want && q == 0) {
+                    pmax[(int64_t)blk * n + 4 * g + sub] = mx;
+                    psum[(int64_t)blk * n + 4 * g + sub] = z;
+                }
+            });
+    });
+}
+
 // 32-bit slice offsets reach every term of a block (and one past is outside)
 static bool narrow_offsets(int64_t d) { return d * (kBlk * 4) <= (int64_t)0xffffff00u; }
+
+int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k) {
+    constexpr int64_t kRows = 65536;
+    // headers hold 20 bits of a row's nonzeros
+    if (nnz * (int64_t)k < kSoftLdsWork || !narrow_offsets(d) || d >= (1 << 20) ||
+        split_pairs(nnz, kRows) > kSplitMaxPairs)
+        return 0;
+    return std::min(N, kRows);
+}
 
 hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* CT, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s) {
     const int64_t nblk = ((int64_t)k + kBlk - 1) / kBlk;
     const bool narrow = narrow_offsets(d);
     const void* fn = narrow ? (const void*)k_soft_fwd<uint32_t> : (const void*)k_soft_fwd<uint64_t>;
+    constexpr size_t lds = (size_t)(kSplitHot + 1) * kSliceBytes;
+    if (w.ent) {
+        hipError_t e = hipFuncSetAttribute((const void*)k_soft_fwd_lds, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e == hipSuccess) e = fill_i32((int32_t*)w.count, 0, d, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_soft_sample, dim3(256), dim3(256), 0, s, col, w.nnz, w.count);
+        hipLaunchKernelGGL(k_soft_hot, dim3(1), dim3(1024), 0, s, w.count, d, w.slot, w.term, w.nhot);
+    }
     int64_t parts = 0;
     for (int64_t c0 = 0; c0 < N; c0 += w.rows) {
         const int64_t c1 = std::min(N, c0 + w.rows), n = c1 - c0;
         const unsigned grid = share_grid(fn, n, nblk, 256, n_cu);
-        if (narrow)
+        if (w.ent) {
+            const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + 3) / 4, (int64_t)n_cu * 8));
+            hipLaunchKernelGGL(k_soft_prep, dim3((unsigned)blocks), dim3(256), 0, s, c0, n, rp, col, xv, w.slot, w.nhot,
+                               w.ent, w.hdr);
+            hipLaunchKernelGGL(k_soft_fwd_lds, dim3((unsigned)((n_cu + kXcds - 1) / kXcds * kXcds)), dim3(kDenseThreads), lds,
+                               s, (int)n, w.ent, (uint32_t)split_pairs(w.nnz, w.rows), w.hdr, w.term, w.nhot, CT, d, k,
+                               1.0f / tau, w.pmax, w.psum);
+        } else if (narrow) {
             hipLaunchKernelGGL(k_soft_fwd<uint32_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, CT, d, k,
                                1.0f / tau, w.pmax, w.psum);
-        else
+        } else {
             hipLaunchKernelGGL(k_soft_fwd<uint64_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, CT, d, k,
                                1.0f / tau, w.pmax, w.psum);
+        }
         const int64_t wgs = (n + 255) / 256;
         hipLaunchKernelGGL(k_soft_lse, dim3((unsigned)wgs), dim3(256), 0, s, n, nblk, w.pmax, w.psum, lse + c0,
                            w.part + parts);

@@ -7,6 +7,7 @@ namespace sivf {
 
 constexpr int kSoftBlk = 64;     // columns of a C^T block
 constexpr int kSoftSub = 32;     // columns of a dS / dC^T block
+constexpr int64_t kSoftLdsWork = 1ll << 32;   // nonzeros x k from which the forward uses LDS
 constexpr int kSoftPiece = 512;  // CSC entries a wave sums at most
 
 // C (k x d) -> blocks [ceil(k / 64)][d][64] of C^T, zero past column k
@@ -18,7 +19,15 @@ struct SoftFwdWs {
     float* pmax;     // [ceil(k / 64) * rows] max of S / tau per (block, row)
     float* psum;     // [ceil(k / 64) * rows] sum of exp(S / tau - max)
     double* part;    // partial sums of lse: one per 256 rows of every launch
+    // with the commonest terms in LDS (ent == nullptr: not)
+    int64_t nnz;
+    uint2* ent;      // [split_pairs(nnz, rows)] pairs of a launch's rows
+    uint2* hdr;      // [rows]
+    uint32_t* count; // [d] sampled nonzeros of each term
+    int32_t *slot, *term, *nhot;   // [d], [kSplitHot], [1]
 };
+// rows per launch with the commonest terms in LDS, or 0: not so
+int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k);
 hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* CT, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s);
 // rows [c0, c1) whose nonzeros are [p0, p1).  dS: blocks [2 ceil(k / 64)][c1 - c0][32]

@@ -412,3 +412,52 @@ def test_automatic_tiles_follow_the_file(posting, k, d, widths):
     for ctx, f, *_ in state:
         f.free()
         ctx.close()
+
+
+@pytest.mark.parametrize("n,d,k", [
+    (91_003, 800, 641),    # more terms than LDS holds; 11 blocks over 8 XCDs
+    (22_001, 600, 2_701),  # every term in LDS
+    (235_001, 800, 250),   # four launches of rows; 4 blocks
+])
+def test_soft_forward_with_common_terms_in_lds(n, d, k):
+    # rows of 0 .. 300 terms: no chunk, chunks filled up, several; four rows of
+    # different lengths to a wave.  S is a sum of at most 300 products of unit
+    # vectors' entries (302 * 2^-24), divided by tau, and exp and log add 1e-5
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("soft forward in LDS n %d d %d k %d" % (n, d, k))
+    rng = np.random.default_rng(k)
+    lens = torch.from_numpy(rng.permutation(np.resize([0, 1, 15, 16, 17, 63, 64, 65, 200, 300], n))).to(device())
+    g = torch.Generator(device=device()).manual_seed(k)
+    cols = []
+    for lo in range(0, n, 10_000):
+        m = lens[lo:lo + 10_000]
+        # m distinct terms of each row, early terms more often: the m smallest of weighted draws
+        w = torch.rand(m.numel(), d, device=device(), generator=g) * torch.linspace(0.2, 1.0, d, device=device())
+        take = torch.zeros(m.numel(), d, dtype=torch.bool, device=device())
+        take.scatter_(1, w.argsort(1), torch.arange(d, device=device())[None, :] < m[:, None])
+        cols.append(take.nonzero()[:, 1].int())
+    col = torch.cat(cols)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64, device=device()), lens.cumsum(0)])
+    v = torch.rand(col.numel(), device=device(), generator=g) + 0.1
+    row = torch.repeat_interleave(torch.arange(n, device=device()), lens)
+    ss = torch.zeros(n, device=device(), dtype=torch.float64).index_add_(0, row, v.double() ** 2)
+    v = (v / ss.sqrt()[row]).float()
+    C = torch.randn(k, d, device=device(), generator=g).abs()
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    X = DeviceCsr(rp, col, v, d)
+    assert X.nnz * k >= 1 << 32
+    ctx = _ctx()
+    lse, loss = ctx.soft_assign_fwd(X, C, 0.05)
+    tol = 302 * 2.0 ** -24 / 0.05 + 1e-5
+    for lo in range(0, n, 10_000):
+        hi = min(n, lo + 10_000)
+        D = torch.zeros(hi - lo, d, dtype=torch.float64, device=device())
+        b, e = int(rp[lo]), int(rp[hi])
+        D[row[b:e] - lo, col[b:e].long()] = v[b:e].double()
+        ref = torch.logsumexp(D @ C.double().T / 0.05, 1)
+        assert float((lse[lo:hi].double() - ref).abs().max()) <= tol
+    assert abs(loss + lse.double().sum().item()) <= 1e-9 * abs(loss)
+    again, _ = ctx.soft_assign_fwd(X, C, 0.05)
+    assert torch.equal(again, lse)
+    plain, _ = _ctx(workspace_cap_bytes=1 << 40).soft_assign_fwd(X, C, 0.05)   # capped: no LDS form
+    assert float((plain - lse).abs().max()) <= 2 * tol

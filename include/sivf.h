@@ -306,7 +306,8 @@ sivf_status sivf_run_lloyd(sivf_ctx* ctx, const sivf_csr* X, int32_t k, const in
  *   S = X C^T, lse_i = log sum_j exp(S_ij / tau), loss = -sum_i lse_i.
  * X: N x d CSR (SIVF_F32 values).  C: f32[k * d] row-major dense centroids.
  * lse_out: f32[N].  loss_host: optional (waits); summed in FP64 in a fixed order.
- * Nothing of size N x k is stored. */
+ * Nothing of size N x k is stored.  Larger calls without a workspace cap also
+ * hold X's nonzeros in another order (8 B each, and 264 B per row of 65,536). */
 sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* C, int32_t k,
                                  float tau, float* lse_out, double* loss_host);
 
@@ -318,8 +319,9 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
  * Workspace held by the ctx: C^T and dC^T (k rounded up to 64 times d floats
  * each), X's column copy (24 B per nonzero and 1 B of counts), dS for one chunk
  * of rows (at most 512 MiB), dX partials (4 B per nonzero of a chunk and 64
- * columns), and the dC pass's partial rows (k floats per 256 nonzeros of a
- * chunk). */
+ * columns), the dC pass's partial rows (k floats per 256 nonzeros of a chunk)
+ * and, in larger calls without a workspace cap, its densest terms' products (up
+ * to 100 MB). */
 sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* C, int32_t k,
                                  float tau, const float* lse, float grad_loss, float* dC_out,
                                  float* dxval_out);

@@ -1337,12 +1337,26 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
         STCHK(ws(ctx, "dct_count", nch * 4, &dw.count));
         HIPCHK(ctx, fill_u64(dw.count, 0ull, nch * 4, s));
         if (n == 0) HIPCHK(ctx, fill_i32((int32_t*)dC_out, 0, (int64_t)k * d, s));
+        // the densest terms by matrix products: without a workspace cap, and only
+        // if there is memory
+        if (ctx->opt.workspace_cap_bytes == 0 && n > 0 && Xc.nnz * (int64_t)k >= kSoftProdWork) {
+            const int64_t room = dct_cands(Xc.nnz, n);
+            dw.nnz = Xc.nnz;
+            if (ws(ctx, "dct_prod", dct_prod_elems(rc, k), &dw.prod) == SIVF_OK && ws(ctx, "dct_slot", d, &dw.slot) == SIVF_OK &&
+                ws(ctx, "dct_term", kDctDense, &dw.term) == SIVF_OK && ws(ctx, "dct_cand", room, &dw.cand) == SIVF_OK &&
+                ws(ctx, "dct_cand_df", room, &dw.cand_df) == SIVF_OK && ws(ctx, "dct_ndense", 2, &dw.ndense) == SIVF_OK &&
+                ws(ctx, "dct_xd", rc * kDctDense, &dw.xd) == SIVF_OK) {
+                HIPCHK(ctx, fill_u64(dw.ndense, 0ull, 2, s));
+                HIPCHK(ctx, dct_pick(n, d, colptr, dw, s));
+            }
+        }
     }
     for (int64_t c0 = 0, j = 0; c0 < n; c0 += rc, ++j) {
         const int64_t c1 = std::min(n, c0 + rc);
         HIPCHK(ctx, soft_bwd_rows(c0, c1, ho[(size_t)j], ho[(size_t)j + 1], Xc.rp, Xc.col, (const float*)Xc.val, CT, d, k,
                                   tau, grad_loss, lse, dS, dxp, dxval_out, ctx->n_cu, s));
         if (dC_out) {
+            if (dw.xd) HIPCHK(ctx, dct_dense_rows(c0, c1, Xc.rp, Xc.col, (const float*)Xc.val, dw, ctx->n_cu, s));
             HIPCHK(ctx, soft_dct(d, k, c0, c1, j == 0, colptr, xt_row, xt_val, dS, dCT, dw, ctx->n_cu, s));
             dw.count += 4;
         }

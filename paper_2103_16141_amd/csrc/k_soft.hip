@@ -711,7 +711,8 @@ hipError_t soft_chunk_offsets(const int64_t* rp, int64_t n, int64_t rc, int64_t 
 // The chunk's slices of one block (24,576 rows, 3 MB) mostly stay in the XCD's
 // L2 whatever the order of the rows.  What bounds it: L1 misses on random
 // 128-byte slices (12 TB/s) and, for the rare terms, the read and write of dCT
-// per chunk.  At the forward's shapes 42.7 and 0.50 ms; with 512-column slices
+// per chunk.  At the forward's shapes 42.7 and 0.50 ms (less the densest terms'
+// entries 30.6); with 512-column slices
 // in chunks of 16,384 rows, cut at row blocks, 44 and 2.9 ms.
 constexpr int kTiny = 8;
 constexpr int kPiece = kSoftPiece;
@@ -741,6 +742,7 @@ __global__ void k_dct_plan(int64_t d, int64_t c1, int first, const int64_t* __re
         if (hi == lo + 4) hi = row_lower_bound(xt_row, hi, end, c1);
         w.next[t] = hi;
         len = hi - lo;
+        if (w.xd && w.slot[t] >= 0 && w.count[3] == 0) len = 0;   // k_dct_dense has it
         w.lo[t] = lo;
         w.len[t] = (int32_t)len;
     }
@@ -890,10 +892,217 @@ __global__ __launch_bounds__(256) void k_dct_combine(int64_t d, int64_t nsb, int
     }
 }
 
+// ---------------------------------------------------------------- dC^T of the densest terms
+// A term in more than a few percent of the rows costs less as a row of a matrix
+// product than entry by entry: dC^T = Xd^T dS with Xd the chunk's rows over the
+// 256 densest terms (46% of the nonzeros at Zipf 1.1, D = 100,000, 100 terms a
+// row), on the FP32 matrix cores.  An entry costs 0.4 ps of gathers per column, a
+// place of Xd 0.015, so terms in 1/32 of the rows and more are taken.  N =
+// 262,144, k = 4,096: 42.6 ms for dC before, 36.0 now (5.4 the products, at 104
+// TFLOP/s of 149 that a library product reaches); at N = 20,011, k = 1,021
+// (kSoftProdWork / 2.4) 0.18 ms less for the entries and 0.20 for the products
+// and choosing the terms.
+
+__global__ void k_dct_cands(int64_t N, int64_t d, const int64_t* __restrict__ colptr, int64_t room, DctWs w) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t df = t < d ? colptr[t + 1] - colptr[t] : 0;
+    const bool has = df * 32 >= N && df > 0;
+    const unsigned long long m = ballot(has);
+    if (t < d) w.slot[t] = -1;
+    if (!m) return;
+    int64_t at = 0;
+    if ((threadIdx.x & 63) == 0) at = (int64_t)atomicAdd(&w.ndense[0], (unsigned long long)__popcll(m));
+    at = bcast_i64(at, 0) + lanes_below(m);
+    if (has && at < room) {
+        w.cand[at] = (int32_t)t;
+        w.cand_df[at] = (uint32_t)min(df, (int64_t)0xffffffffu);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_dct_pick(int64_t room, DctWs w) {
+    __shared__ uint32_t sh[258];
+    __shared__ uint32_t taken;
+    if (threadIdx.x == 0) taken = 0;
+    const int64_t n = min(room, (int64_t)w.ndense[0]);
+    const uint32_t x = top_weights(w.cand_df, n, kDctDense, sh);
+    each_weight(w.cand_df, n, [&](uint32_t v, int64_t i) {
+        if (i >= n || v < x) return;
+        const uint32_t q = atomicAdd(&taken, 1u);   // any numbering gives the same sums
+        w.term[q] = w.cand[i];
+        w.slot[w.cand[i]] = (int32_t)q;
+    });
+    __syncthreads();
+    if (threadIdx.x == 0) w.ndense[1] = taken;
+}
+
+hipError_t dct_pick(int64_t N, int64_t d, const int64_t* colptr, DctWs w, hipStream_t s) {
+    const int64_t room = dct_cands(w.nnz, N);
+    hipLaunchKernelGGL(k_dct_cands, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, N, d, colptr, room, w);
+    hipLaunchKernelGGL(k_dct_pick, dim3(1), dim3(1024), 0, s, room, w);
+    return hipGetLastError();
+}
+
+// a wave per row: its densest terms' values over zeros, in LDS, then written
+__global__ __launch_bounds__(256) void k_dct_dense_rows(int64_t c0, int64_t n, const int64_t* __restrict__ rp,
+                                                        const int32_t* __restrict__ col, const float* __restrict__ xv,
+                                                        DctWs w) {
+    __shared__ float4 buf[4][kDctDense / 4];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    float* row = reinterpret_cast<float*>(buf[wid]);
+    for (int64_t i = (int64_t)blockIdx.x * 4 + wid; i < n; i += (int64_t)gridDim.x * 4) {
+        buf[wid][lane] = zero4();
+        const int64_t r1 = rp[c0 + i + 1];
+        for (int64_t p = rp[c0 + i] + lane; p < r1; p += 64) {
+            const int32_t q = w.slot[col[p]];
+            if (q >= 0) row[q] = xv[p];
+        }
+        reinterpret_cast<float4*>(w.xd + i * kDctDense)[lane] = buf[wid][lane];
+    }
+}
+
+hipError_t dct_dense_rows(int64_t c0, int64_t c1, const int64_t* rp, const int32_t* col, const float* xv, DctWs w,
+                          int n_cu, hipStream_t s) {
+    const int64_t n = c1 - c0;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n + 3) / 4, (int64_t)n_cu * 8);
+    hipLaunchKernelGGL(k_dct_dense_rows, dim3(blocks), dim3(256), 0, s, c0, n, rp, col, xv, w);
+    return hipGetLastError();
+}
+
+// How a chunk of n rows is cut: about 512 workgroups of two dS blocks by a range
+// of rows (a multiple of 32).
+constexpr int kProdRows = 32;   // rows of Xd in LDS
+struct ProdCut {
+    int cgroups, rows, splits;
+};
+static ProdCut prod_cut(int64_t n, int32_t k) {
+    ProdCut c;
+    c.cgroups = (int)((((int64_t)k + kBlk - 1) / kBlk));
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>(512 / c.cgroups, (n + kProdRows - 1) / kProdRows));
+    c.rows = (int)(((n + want - 1) / want + kProdRows - 1) / kProdRows * kProdRows);
+    c.splits = (int)((n + c.rows - 1) / c.rows);
+    return c;
+}
+int64_t dct_prod_elems(int64_t rows, int32_t k) {
+    const int64_t cg = ((int64_t)k + kBlk - 1) / kBlk;
+    return std::max<int64_t>(1, std::min<int64_t>(512 / cg, (rows + kProdRows - 1) / kProdRows)) * cg * 2 * kDctDense * kSub;
+}
+
+// prod[split][sb][slot][32] = sum over the split's rows of xd[row][slot] dS[sb][row].
+// Four waves: two dS blocks by two halves of the terms; a wave holds 128 terms x
+// 32 columns of sums.  v_mfma_f32_32x32x2_f32 takes two rows a step: lane l gives
+// term (or column) l % 32 of row l / 32, and holds rows 8 (r / 4) + 4 (l / 32) +
+// r % 4 of column l % 32 in result r.  32 rows of Xd are in LDS (rows 288 floats
+// apart: the two rows of a step use different banks), the next 32 and their dS on
+// the way.  Sums of 32 rows are added to the running ones, which rounds less than
+// one chain.  Zeros of Xd meet every dS: a dS that is not finite sets count[3],
+// and the chunk's sums are then taken entry by entry.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(256, 2) void k_dct_dense(int n, int nsb, ProdCut cut, const float* __restrict__ dS,
+                                                      DctWs w) {
+    constexpr int kStride = kDctDense + 32;
+    __shared__ float tile[2][kProdRows * kStride];
+    const int M = (int)w.ndense[1];
+    if (M == 0) return;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, j = lane & 31, kk = lane >> 5;
+    // the splits of an XCD are its own: their rows of Xd stay in its L2
+    const int split = blockIdx.x % cut.splits, cg = blockIdx.x / cut.splits;
+    const int sb = 2 * cg + (wid & 1), half = 128 * (wid >> 1);
+    const int mt = __builtin_amdgcn_readfirstlane(min(4, max(0, (M - half + 31) / 32)));
+    const int r0 = split * cut.rows, r1 = min(n, r0 + cut.rows);
+    const float* ds = dS + (int64_t)sb * n * kSub + j;   // nsb is even: both blocks exist
+    float4 a[8];
+    float b[kProdRows / 2], nb[kProdRows / 2];
+    auto fetch = [&](int base, float* bb) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = i * 256 + threadIdx.x, row = base + (e >> 6);
+            a[i] = row < r1 ? reinterpret_cast<const float4*>(w.xd + (int64_t)row * kDctDense)[e & 63] : zero4();
+        }
+#pragma unroll
+        for (int i = 0; i < kProdRows / 2; ++i) {
+            const int row = base + 2 * i + kk;
+            bb[i] = row < r1 ? ds[(int64_t)row * kSub] : 0.0f;
+        }
+    };
+    auto put = [&](float* to) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = i * 256 + threadIdx.x;
+            *reinterpret_cast<float4*>(to + (e >> 6) * kStride + 4 * (e & 63)) = a[i];
+        }
+    };
+    f32x16 sum[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[m][r] = 0.0f;
+    bool bad = false;
+    fetch(r0, b);
+    put(tile[0]);
+    __syncthreads();
+    int cur = 0;
+    for (int base = r0; base < r1; base += kProdRows) {
+        const bool more = base + kProdRows < r1;
+        if (more) fetch(base + kProdRows, nb);
+        const float* t = tile[cur] + kk * kStride + half + j;
+#pragma unroll
+        for (int i = 0; i < kProdRows / 2; ++i) bad |= (__float_as_uint(b[i]) & 0x7f800000u) == 0x7f800000u;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            if (m >= mt) break;
+            f32x16 c;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[r] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < kProdRows / 2; ++i)
+                c = __builtin_amdgcn_mfma_f32_32x32x2f32(t[2 * i * kStride + 32 * m], b[i], c, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[m][r] = sum[m][r] + c[r];
+        }
+        if (more) {
+            put(tile[cur ^ 1]);
+#pragma unroll
+            for (int i = 0; i < kProdRows / 2; ++i) b[i] = nb[i];
+        }
+        cur ^= 1;
+        __syncthreads();
+    }
+    if (ballot(bad) && lane == 0) atomicOr(&w.count[3], 1ull);
+    float* out = w.prod + (((int64_t)split * nsb + sb) * kDctDense + half) * kSub + j;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        if (m >= mt) break;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[(32 * m + 8 * (r / 4) + 4 * kk + r % 4) * kSub] = sum[m][r];
+    }
+}
+
+// dCT += the splits' products, in order
+__global__ __launch_bounds__(256) void k_dct_dense_add(int64_t d, int nsb, int nsb2, int splits, float* __restrict__ dCT, DctWs w) {
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;   // (sb, slot, q)
+    const int64_t rowi = e >> 3;
+    const int slot = (int)(rowi % kDctDense);
+    const int64_t sb = rowi / kDctDense;
+    if (sb >= nsb || slot >= (int)w.ndense[1] || w.count[3] != 0) return;
+    const float4* p = reinterpret_cast<const float4*>(w.prod) + e;
+    float4 a = p[0];
+    for (int s = 1; s < splits; ++s) {
+        const float4 x = p[(int64_t)s * nsb2 * kDctDense * (kSub / 4)];
+        a = make_float4(a.x + x.x, a.y + x.y, a.z + x.z, a.w + x.w);
+    }
+    float4* out = reinterpret_cast<float4*>(dCT + (sb * d + w.term[slot]) * kSub) + (e & 7);
+    const float4 o = *out;
+    *out = make_float4(o.x + a.x, o.y + a.y, o.z + a.z, o.w + a.w);
+}
+
 hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, const int64_t* colptr,
                     const int32_t* xt_row, const float* xt_val, const float* dS, float* dCT, DctWs w, int n_cu,
                     hipStream_t s) {
     const int64_t nsb = ((int64_t)k + kSub - 1) / kSub, n = c1 - c0;
+    const ProdCut cut = prod_cut(n, k);
+    const int nsb2 = 2 * cut.cgroups;   // dS and dCT have an even number of blocks
+    if (w.xd) hipLaunchKernelGGL(k_dct_dense, dim3((unsigned)(cut.splits * cut.cgroups)), dim3(256), 0, s, (int)n, nsb2, cut, dS, w);
     hipLaunchKernelGGL(k_dct_plan, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, d, c1, first, colptr, xt_row, w);
     const unsigned gt = share_grid((const void*)k_dct_tiny, (d + 7) / 8, nsb, 256, n_cu);
     const unsigned gw = share_grid((const void*)k_dct_wave, d, nsb, 256, n_cu);
@@ -902,6 +1111,9 @@ hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, con
     hipLaunchKernelGGL(k_dct_tiny, dim3(gt), dim3(256), 0, s, d, nsb, c0, n, first, xt_row, xt_val, dS, dCT, w);
     if (w.max_pieces > 0)
         hipLaunchKernelGGL(k_dct_combine, dim3(gc), dim3(256), 0, s, d, nsb, first, dCT, w);
+    if (w.xd)
+        hipLaunchKernelGGL(k_dct_dense_add, dim3((unsigned)(nsb * kDctDense * 8 / 256)), dim3(256), 0, s, d, (int)nsb,
+                           nsb2, cut.splits, dCT, w);
     return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 // Declarations of the soft-assignment kernels (k_soft.hip) used by the C ABI.
 #pragma once
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace sivf {
@@ -8,6 +10,7 @@ namespace sivf {
 constexpr int kSoftBlk = 64;     // columns of a C^T block
 constexpr int kSoftSub = 32;     // columns of a dS / dC^T block
 constexpr int64_t kSoftLdsWork = 1ll << 32;   // nonzeros x k from which the forward uses LDS
+constexpr int64_t kSoftProdWork = 1ll << 32;  // nonzeros x k from which dC's densest terms are matrix products
 constexpr int kSoftPiece = 512;  // CSC entries a wave sums at most
 
 // C (k x d) -> blocks [ceil(k / 64)][d][64] of C^T, zero past column k
@@ -49,8 +52,26 @@ struct DctWs {
     int32_t* piece_len;   // [max_pieces] entries
     float* part;          // [2 ceil(k / 64) * max_pieces * 32] partial rows
     int64_t max_pieces;   // at least the pieces of any chunk (nonzeros / (kSoftPiece / 2) suffice)
-    unsigned long long* count;   // [3] mid terms, pieces, long terms; zero before the call
+    unsigned long long* count;   // [4] mid terms, pieces, long terms, dS not finite; zero before the call
+    // the densest terms by matrix products (xd == nullptr: not)
+    int64_t nnz;          // of all rows
+    float* xd;            // [rows * kDctDense] their values in the chunk's rows
+    float* prod;          // [dct_prod_elems(rows, k)] partial products
+    int32_t* slot;        // [d] of the densest terms, else -1 (set by dct_pick)
+    int32_t* term;        // [kDctDense] its inverse
+    int32_t* cand;        // [dct_cands(nonzeros, rows)] workspace of dct_pick
+    uint32_t* cand_df;
+    unsigned long long* ndense;   // [2] candidates, densest terms; zero before dct_pick
 };
+constexpr int kDctDense = 256;
+// values of the partial products of a chunk of `rows` rows; terms dct_pick considers at most
+int64_t dct_prod_elems(int64_t rows, int32_t k);
+inline int64_t dct_cands(int64_t nnz, int64_t rows) { return 32 * (nnz / std::max<int64_t>(rows, 1) + 1); }
+// the terms in at least 1/32 of N rows, at most kDctDense of them
+hipError_t dct_pick(int64_t N, int64_t d, const int64_t* colptr, DctWs w, hipStream_t s);
+// rows [c0, c1) of the densest terms into w.xd
+hipError_t dct_dense_rows(int64_t c0, int64_t c1, const int64_t* rp, const int32_t* col, const float* xv, DctWs w,
+                          int n_cu, hipStream_t s);
 hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, const int64_t* colptr,
                     const int32_t* xt_row, const float* xt_val, const float* dS, float* dCT, DctWs w, int n_cu,
                     hipStream_t s);

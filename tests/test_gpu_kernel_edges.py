@@ -461,3 +461,59 @@ def test_soft_forward_with_common_terms_in_lds(n, d, k):
     assert torch.equal(again, lse)
     plain, _ = _ctx(workspace_cap_bytes=1 << 40).soft_assign_fwd(X, C, 0.05)   # capped: no LDS form
     assert float((plain - lse).abs().max()) <= 2 * tol
+
+
+@pytest.mark.parametrize("n,d,k,common,broken", [
+    (5_101, 700, 2_201, 700, False),     # 256 of 700 dense terms; 35 column groups, the last of 25 columns
+    (70_001, 50_000, 1_500, 40, False),   # 40 dense terms, three chunks of rows, the last with splits of its own
+    (9_500, 3_000, 5_300, 130, True),    # 130: one past half the terms of a workgroup; a column of C is infinite
+])
+def test_soft_gradient_of_the_densest_terms(n, d, k, common, broken):
+    # dC of the densest terms is a matrix product, the others' a sum over entries;
+    # against FP64 with the tolerance of the other gradients, and against the
+    # entry-by-entry form (which a workspace cap selects)
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("densest terms n %d d %d k %d" % (n, d, k))
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(k)
+    rows, cols = [], []
+    for lo in range(0, n, 5_000):
+        m = min(5_000, n - lo)
+        # the common terms in 12 to 100% of the rows, the others rarely
+        p = torch.full((d,), min(0.02, 20.0 / d), device=dev)
+        p[:common] = torch.linspace(1.0, 0.12, common, device=dev)
+        hit = (torch.rand(m, d, device=dev, generator=g) < p).nonzero()
+        rows.append(hit[:, 0] + lo)
+        cols.append(hit[:, 1])
+    row, col = torch.cat(rows), torch.cat(cols)
+    rp = torch.zeros(n + 1, dtype=torch.int64, device=dev)
+    rp[1:] = torch.bincount(row, minlength=n).cumsum(0)
+    v = torch.rand(col.numel(), device=dev, generator=g) + 0.1
+    ss = torch.zeros(n, device=dev, dtype=torch.float64).index_add_(0, row, v.double() ** 2)
+    v = (v / ss.sqrt()[row]).float()
+    C = torch.rand(k, d, device=dev, generator=g)
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    if broken:
+        C[7, common + 5] = float("inf")
+    X = DeviceCsr(rp, col.int(), v, d)
+    assert X.nnz * k >= 1 << 32
+    ctx = _ctx()
+    lse, _ = ctx.soft_assign_fwd(X, C, 0.05)
+    dC, dX = ctx.soft_assign_bwd(X, C, 0.05, lse, 0.9)
+    dP, dXp = _ctx(workspace_cap_bytes=1 << 40).soft_assign_bwd(X, C, 0.05, lse, 0.9)
+    assert torch.equal(torch.isnan(dC), torch.isnan(dP)) and torch.equal(torch.isnan(dX), torch.isnan(dXp))
+    assert torch.equal(torch.nan_to_num(dX, nan=0.0), torch.nan_to_num(dXp, nan=0.0))
+    if broken:
+        assert bool(torch.isnan(dC).any()) and not bool(torch.isnan(dC).all())
+        assert torch.equal(torch.nan_to_num(dC, nan=0.0), torch.nan_to_num(dP, nan=0.0))
+        return
+    ref = torch.zeros(k, d, dtype=torch.float64, device=dev)
+    for lo in range(0, n, 2_000):
+        hi = min(n, lo + 2_000)
+        b, e = int(rp[lo]), int(rp[hi])
+        D = torch.zeros(hi - lo, d, dtype=torch.float64, device=dev)
+        D[row[b:e] - lo, col[b:e]] = v[b:e].double()
+        P = torch.softmax(D @ C.double().T / 0.05, 1)
+        ref += (-0.9 / 0.05) * (P.T.contiguous() @ D)
+    assert bool(((dC.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
+    assert torch.equal(ctx.soft_assign_bwd(X, C, 0.05, lse, 0.9)[0], dC)

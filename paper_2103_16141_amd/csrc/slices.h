@@ -140,9 +140,9 @@ __device__ inline uint2 next_pairs(__amdgpu_buffer_rsrc_t ents, DenseList& l, ui
 
 // 16 pairs of the LDS rows (e) and CQ groups of four of the others (c) of a
 // wave's objects: the latter's slices and the next pairs are in flight while
-// the former are added.  mh, mc: steps left.
+// the former are added.  The two have sums of their own.  mh, mc: steps left.
 template <int CQ>
-__device__ inline void dense_round(float4& acc, uint2& c, uint2& e, int mh, int mc, __amdgpu_buffer_rsrc_t ents, DenseList& lc,
+__device__ inline void dense_round(float4& hot, float4& cold, uint2& c, uint2& e, int mh, int mc, __amdgpu_buffer_rsrc_t ents, DenseList& lc,
                                    DenseList& lh, uint32_t panel16, __amdgpu_buffer_rsrc_t rsrc, uint32_t q16,
                                    uint32_t q8) {
     u32x4 u0[4], u1[4], u2[4], u3[4], a[4];
@@ -158,25 +158,25 @@ __device__ inline void dense_round(float4& acc, uint2& c, uint2& e, int mh, int 
     const float ev = __uint_as_float(e.y), cv = __uint_as_float(c.y);
     if (0 < mh) {
         dense_hot_load4<0>(a, panel16, e);
-        dense_fma4<0>(acc, ev, a);
+        dense_fma4<0>(hot, ev, a);
     }
     if (4 < mh) {
         dense_hot_load4<1>(a, panel16, e);
-        dense_fma4<1>(acc, ev, a);
+        dense_fma4<1>(hot, ev, a);
     }
     if (8 < mh) {
         dense_hot_load4<2>(a, panel16, e);
-        dense_fma4<2>(acc, ev, a);
+        dense_fma4<2>(hot, ev, a);
     }
     if (12 < mh) {
         dense_hot_load4<3>(a, panel16, e);
-        dense_fma4<3>(acc, ev, a);
+        dense_fma4<3>(hot, ev, a);
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (CQ > 0) dense_fma4<0>(acc, cv, u0);
-    if (CQ > 1) dense_fma4<1>(acc, cv, u1);
-    if (CQ > 2) dense_fma4<2>(acc, cv, u2);
-    if (CQ > 3) dense_fma4<3>(acc, cv, u3);
+    if (CQ > 0) dense_fma4<0>(cold, cv, u0);
+    if (CQ > 1) dense_fma4<1>(cold, cv, u1);
+    if (CQ > 2) dense_fma4<2>(cold, cv, u2);
+    if (CQ > 3) dense_fma4<3>(cold, cv, u3);
     c = cn;
     e = en;
 }
@@ -253,7 +253,8 @@ __device__ inline void each_block(int blocks, int groups, F f) {
 // This wave's groups among [g0, g1) of a block: header(g) loads the lane's
 // object's header, wanted(g, header) says whether its sums are, done(g, sums,
 // wanted) takes them (lane: columns 4 q .. 4 q + 3 of object 4 g + sub).  SUMS:
-// 1, or 4 partial sums of every fourth step, which round less.  loads:
+// partial sums, 2 (32 LDS rows' at a time, and the rest), or 4 of every fourth
+// step each, which round less but take registers from slices in flight.  loads:
 // += KB requested.
 template <int SUMS, typename Header, typename Wanted, typename Done>
 __device__ inline void dense_groups(int g0, int g1, __amdgpu_buffer_rsrc_t ents, const u32x4* panel,
@@ -292,20 +293,24 @@ __device__ inline void dense_groups(int g0, int g1, __amdgpu_buffer_rsrc_t ents,
         for (int i = 0; i < SUMS; ++i) acc[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         auto round = [&](auto cq) {
             constexpr int CQ = decltype(cq)::value;
-            if constexpr (SUMS == 1) dense_round<CQ>(acc[0], c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
+            if constexpr (SUMS == 2) dense_round<CQ>(acc[0], acc[1], c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
             else dense_round<CQ>(acc, c, e, mh - h, mc - h, ents, mlc, mlh, panel16, rsrc, q16, q8);
         };
         for (h = 0; h < mc || h < mh; h += 16) {
             const int cq = min(4, max(0, mc - h + 3) >> 2);
             loads += 1 + 4u * cq;
+            if (SUMS == 2 && (h & 31) == 0 && h > 0) {
+                acc[1] = make_float4(acc[0].x + acc[1].x, acc[0].y + acc[1].y, acc[0].z + acc[1].z, acc[0].w + acc[1].w);
+                acc[0] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
             if (cq == 0) round(std::integral_constant<int, 0>{});
             else if (cq == 1) round(std::integral_constant<int, 1>{});
             else if (cq == 2) round(std::integral_constant<int, 2>{});
             else if (cq == 3) round(std::integral_constant<int, 3>{});
             else round(std::integral_constant<int, 4>{});
         }
-        if constexpr (SUMS == 1)
-            done(g, acc[0], want);
+        if constexpr (SUMS == 2)
+            done(g, make_float4(acc[0].x + acc[1].x, acc[0].y + acc[1].y, acc[0].z + acc[1].z, acc[0].w + acc[1].w), want);
         else
             done(g,
                  make_float4((acc[0].x + acc[1].x) + (acc[2].x + acc[3].x), (acc[0].y + acc[1].y) + (acc[2].y + acc[3].y),

@@ -125,10 +125,20 @@ struct WalkArgs {
 
 }  // namespace sivf
 
+// one allocation of a centroid store's entries
+struct StoreBlock {
+    void* mem = nullptr;
+    size_t bytes = 0;
+};
+
 struct sivf_ivf {
     int32_t k = 0;
     int64_t d = 0;
-    int32_t kt = 0, T = 0, Tcap = 0;   // tile width, tiles, tiles that seg, mid and rec have room for
+    int32_t kt = 0, T = 0;          // tile width, tiles
+    // the allocations: what follows k and d, the stores' entries, the postings
+    void *fixed = nullptr, *postings = nullptr;
+    size_t fixed_bytes = 0, postings_bytes = 0;
+    StoreBlock cur_mem, nxt_mem;
     sivf_dtype pdt = SIVF_F32;
     sivf::Store cur, nxt;           // current centroids, and the buffer the next update writes
     int64_t* seg = nullptr;         // [d*T + 1]

@@ -1200,7 +1200,7 @@ sivf_status sivf_resume(sivf_ctx* ctx, const sivf_csr* X, const sivf_csr* centro
     A.xval = Xc.val;
     A.x_f64 = Xc.f64;
     if (Xc.n > 0) {
-        hipError_t e = resume_own(A, f->cur, a_prev, f->lam, own_sim_out, own64_out, (int64_t)ctx->n_cu * 16, s);
+        hipError_t e = resume_own(A, f->cur, a_prev, f->lam, own_sim_out, own64_out, (int64_t)ctx->n_cu * 32, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             free_file(ctx, f);

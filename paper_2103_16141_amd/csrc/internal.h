@@ -190,7 +190,6 @@ int64_t scan_ws_elems(int64_t n);
 hipError_t fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
 hipError_t fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s);
 hipError_t fill_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
-hipError_t fill_f64(double* p, double v, int64_t n, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
 // validation: fills flags[0..3] of 8 words (all cleared first): [0] error bits, [2] any

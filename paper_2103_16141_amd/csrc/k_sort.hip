@@ -35,40 +35,17 @@ struct SortArgs {
     int64_t ntiles;
 };
 
-template <typename V>
-__device__ inline int64_t sort_count(const SortIn<V>& in) {
-    return in.n_dev ? min(in.n, *in.n_dev) : in.n;
-}
-
-// address of entry p of a store, whose row is r
-template <typename V>
-__device__ inline int64_t store_at(const SortIn<V>& in, int64_t r, int64_t p) {
-    return in.start[in.perm[r]] + (p - in.rp[r]);
-}
-
 template <int KIND, typename V>
 __global__ __launch_bounds__(kFoldThreads) void k_sort_hist(SortArgs<V> A, int64_t* __restrict__ table) {
     __shared__ uint32_t h[kFoldBins];
     const uint32_t dm = (1u << A.nbits) - 1u;
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t n = sort_count(A.in), lo = (int64_t)blockIdx.x * kFoldTile;
-    if (lo < n) {
-        int64_t ra = 0, rb = 0;
-        if (KIND == kSortStore) {
-            ra = row_of(A.in.rp, 0, A.in.rows - 1, lo);
-            rb = row_of(A.in.rp, ra, A.in.rows - 1, min(n, lo + kFoldTile) - 1);
-        }
+    const int64_t n = A.in.n, lo = (int64_t)blockIdx.x * kFoldTile;
 #pragma unroll
-        for (int i = 0; i < kFoldPer; ++i) {
-            const int64_t p = lo + i * kFoldThreads + threadIdx.x;
-            if (p < n) {
-                uint32_t k;
-                if (KIND == kSortStore) k = (uint32_t)A.in.key[store_at(A.in, row_of(A.in.rp, ra, rb, p), p)];
-                else k = (uint32_t)(KIND == kMoved ? A.key : A.in.key)[p];
-                atomicAdd(&h[(k >> A.shift) & dm], 1u);
-            }
-        }
+    for (int i = 0; i < kFoldPer; ++i) {
+        const int64_t p = lo + i * kFoldThreads + threadIdx.x;
+        if (p < n) atomicAdd(&h[((uint32_t)(KIND == kMoved ? A.key : A.in.key)[p] >> A.shift) & dm], 1u);
     }
     __syncthreads();
     table[(int64_t)threadIdx.x * A.ntiles + blockIdx.x] = h[threadIdx.x];
@@ -77,7 +54,7 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_hist(SortArgs<V> A, int64
 struct SortLds {
     uint32_t key[kFoldTile];
     int32_t row[kFoldTile];
-    float val[kFoldTile];        // FP64 values are read again from memory instead
+    float val[kFoldTile];
     uint16_t order[kFoldTile];
     int64_t at[kFoldBins];
     TileSortLds s;
@@ -88,13 +65,12 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const
                                                             int32_t* __restrict__ okey, int32_t* __restrict__ orow,
                                                             V* __restrict__ oval) {
     __shared__ SortLds L;
-    constexpr bool kWide = sizeof(V) > 4;
     const int tid = threadIdx.x;
-    const int64_t n = sort_count(A.in), lo = (int64_t)blockIdx.x * kFoldTile;
+    const int64_t n = A.in.n, lo = (int64_t)blockIdx.x * kFoldTile;
     if (lo >= n) return;   // workgroup-uniform
     const int ne = (int)min((int64_t)kFoldTile, n - lo);
     int64_t ra = 0, rb = 0;
-    if (KIND == kSortCsr || KIND == kSortStore) {
+    if (KIND == kSortCsr) {
         ra = row_of(A.in.rp, 0, A.in.rows - 1, lo);
         rb = row_of(A.in.rp, ra, A.in.rows - 1, lo + ne - 1);
     }
@@ -106,16 +82,15 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const
         if (KIND == kMoved) {
             L.key[e] = (uint32_t)A.key[p];
             L.row[e] = A.row[p];
-            if (!kWide && A.val) L.val[e] = (float)A.val[p];
+            if (A.val) L.val[e] = A.val[p];
         } else if (KIND == kSortIota) {
             L.key[e] = (uint32_t)A.in.key[p];
             L.row[e] = (int32_t)p;
         } else {
             const int64_t r = row_of(A.in.rp, ra, rb, p);
-            const int64_t at = KIND == kSortStore ? store_at(A.in, r, p) : p;
-            L.key[e] = (uint32_t)A.in.key[at];
+            L.key[e] = (uint32_t)A.in.key[p];
             L.row[e] = (int32_t)r;
-            if (!kWide) L.val[e] = (float)A.in.val[at];
+            L.val[e] = A.in.val[p];
         }
     }
     const int64_t first = table[(int64_t)tid * A.ntiles + blockIdx.x];
@@ -132,12 +107,7 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const
         const int64_t to = L.at[(L.key[e] >> A.shift) & dm] + s;
         okey[to] = (int32_t)L.key[e];
         orow[to] = L.row[e];
-        if (oval) {
-            if (!kWide) oval[to] = (V)L.val[e];
-            else if (KIND == kMoved) oval[to] = A.val[lo + e];
-            else if (KIND == kSortStore) oval[to] = A.in.val[store_at(A.in, L.row[e], lo + e)];
-            else oval[to] = A.in.val[lo + e];
-        }
+        if (oval) oval[to] = L.val[e];
     }
 }
 
@@ -162,10 +132,9 @@ hipError_t sort_entries(const SortIn<V>& in, int64_t nkeys, const SortWs<V>& w, 
     for (int p = 0; p < passes && A.ntiles > 0; ++p) {
         const int b = p & 1;
         A.shift = p * nbits;
-        const hipError_t e = p > 0                    ? sort_pass<kMoved, V>(A, w, b, s)
-                             : in.kind == kSortStore ? sort_pass<kSortStore, V>(A, w, b, s)
-                             : in.kind == kSortCsr   ? sort_pass<kSortCsr, V>(A, w, b, s)
-                                                     : sort_pass<kSortIota, V>(A, w, b, s);
+        const hipError_t e = p > 0                  ? sort_pass<kMoved, V>(A, w, b, s)
+                             : in.kind == kSortCsr ? sort_pass<kSortCsr, V>(A, w, b, s)
+                                                   : sort_pass<kSortIota, V>(A, w, b, s);
         if (e != hipSuccess) return e;
         A.key = w.key[b];
         A.row = w.row[b];

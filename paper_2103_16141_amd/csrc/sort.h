@@ -1,6 +1,5 @@
 // Stable radix sort of (key, row, value) entries by a small integer key
-// (k_sort.hip): the column copy of X (soft form), the structured file's
-// postings by term, and the objects by cluster.
+// (k_sort.hip): the column copy of X (soft form) and the objects by cluster.
 #pragma once
 
 #include "internal.h"
@@ -9,22 +8,17 @@ namespace sivf {
 
 // Where the entries of the first pass come from.  Entry p in [0, n):
 //   kSortCsr:    rows r of a CSR matrix: key[p], value val[p], row r with rp[r] <= p < rp[r + 1]
-//   kSortStore:  row r = position r of a centroid store: the entries of row
-//                perm[r] start at start[perm[r]]; rp = scan of the row lengths
 //   kSortIota:   key[p], row p, no value
-enum SortSource { kSortCsr, kSortStore, kSortIota };
+enum SortSource { kSortCsr, kSortIota };
 
 template <typename V>
 struct SortIn {
     SortSource kind;
-    int64_t n;              // entries, or at most so many when n_dev is set
-    const int64_t* n_dev;   // device count of the entries (nullptr: n)
+    int64_t n;              // entries
     const int32_t* key;
     const V* val;           // kSortIota: nullptr
     int64_t rows;
     const int64_t* rp;
-    const int64_t* start;   // kSortStore
-    const int32_t* perm;    // kSortStore
 };
 
 // two buffers of entries (val: nullptr without values), the digit counts of

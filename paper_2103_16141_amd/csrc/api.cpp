@@ -510,12 +510,11 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     }
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
     // sliced rows, if a split walk pays and there is room for them
+    uint32_t* wt = nullptr;
+    int32_t* sterm2 = nullptr;
     if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
-        rows_reserve(&f->sval, &f->scap, SH) == SIVF_OK) {
-        uint32_t* wt = nullptr;
-        int32_t* sterm2 = nullptr;
-        STCHK(ws(ctx, "split_wt", SH, &wt));
-        STCHK(ws(ctx, "split_term2", SH, &sterm2));
+        rows_reserve(&f->sval, &f->scap, SH) == SIVF_OK && ws(ctx, "split_wt", SH, &wt) == SIVF_OK &&
+        ws(ctx, "split_term2", SH, &sterm2) == SIVF_OK) {
         HIPCHK(ctx, split_order(sterm, f->seg, f->T, f->v32, SH, wt, sterm2, f->srow, meta, ctx->stream));
         HIPCHK(ctx, split_fill(sterm2, f->seg, f->cid, f->v32, f->T, head_ktp(f->kt), SH, f->sval, ctx->stream));
         f->srows = SH;

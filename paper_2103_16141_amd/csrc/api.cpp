@@ -621,7 +621,8 @@ struct AssignBufs {
     int64_t range = 0, ranges = 1;
     uint2* ent = nullptr;
     int64_t npairs = 0;
-    uint2* hdr = nullptr;
+    uint2 *hdr = nullptr, *ghdr = nullptr;
+    int32_t* place = nullptr;
     float* S = nullptr;
 };
 
@@ -652,6 +653,7 @@ sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
         if (pairs <= kSplitMaxPairs) break;
     }
     if (w.get("split_ent", pairs, &b->ent) != SIVF_OK || w.get("split_hdr", range, &b->hdr) != SIVF_OK ||
+        w.get("split_ghdr", range, &b->ghdr) != SIVF_OK || w.get("split_place", range, &b->place) != SIVF_OK ||
         w.get("split_S", range * ktp, &b->S) != SIVF_OK)
         return SIVF_OK;
     b->npairs = pairs;
@@ -792,6 +794,8 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
             R.ent = B.ent;
             R.npairs = B.npairs;
             R.hdr = B.hdr;
+            R.ghdr = B.ghdr;
+            R.place = B.place;
             R.S = B.S;
             for (int64_t r = 0; r < B.ranges; ++r) {
                 R.c0 = r * B.range;

@@ -106,7 +106,9 @@ struct WalkArgs {
     uint2* ent;             // [npairs] (code, value) pairs of the range's objects
     int64_t npairs;
     uint2* hdr;             // [n] an object's first pair; other sliced rows << 12 | LDS rows << 2 | 2: relaxed | 1: ICP
-    float* S;               // [n * head_ktp(kt)] head terms' sums of the current tile
+    uint2* ghdr;            // [n] the headers, objects of alike numbers of pairs together
+    int32_t* place;         // [n] an object's place among them
+    float* S;               // [n * head_ktp(kt)] head terms' sums of the current tile, by place
     // relaxed ICP (filter mode RELAXED)
     Store st;                  // the current centroids (FP64 CSR) for exact similarities
     int relaxed;

@@ -572,7 +572,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 if (SPLIT && ch == 0) {
                     // the tile starts from the head terms' sums (only the eligible
                     // prefix is read or written below)
-                    const float4* src = reinterpret_cast<const float4*>(A.S + o * (int64_t)ktp);
+                    const float4* src = reinterpret_cast<const float4*>(A.S + A.place[o] * (int64_t)ktp);
                     float4* dst = reinterpret_cast<float4*>(sim);
                     for (int q = lane; 4 * q < elim; q += 64) dst[q] = src[q];
                     lwords += (uint32_t)(elim + 3);
@@ -887,28 +887,22 @@ int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split) {
 // 1024 is 16 blocks over 8 XCDs), all objects, with the slices of the heaviest
 // rows in LDS.  k_walk_prep sorts every object's terms by where their values
 // come from, k_walk_dense leaves the head terms' sums in A.S, and the list walk
-// starts from them.  1,000,000 objects, k = 1,000: 20.1 ms as one kernel, 13.4
-// (prep 1.5, dense 8.7, lists 3.5) now; 2,000,000, k = 10,000: 231 and 185 ms
-// (2.7, 104, 78).
+// starts from them.  1,000,000 objects, k = 1,000: 20.1 ms as one kernel, 13.3
+// (pairs 1.5, dense 8.2, lists 3.5) now; 2,000,000, k = 10,000: 231 and 175 ms
+// (3, 94, 78).
 
-// One wave per object of the range: its terms as (code, value) pairs, rows of
-// LDS slices first (code: byte offset of the slice in a block), then the other
-// sliced rows, then the terms with lists only (code: the term), each in ascending
-// term order, the first two filled up to 16 with pairs that add nothing; their
-// counts; the filter decision; the object's mult-adds.  Object o's pairs start
-// at 32 + (nonzeros before it) + 32 o; pairs 0 .. 31 are two chunks of fill.
-__global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
-    __shared__ unsigned long long sh[4][4];
+// Three steps.  A wave per object counts its terms with a slice in LDS and the
+// other sliced ones, and takes the filter decision (k_walk_count).  A wave of
+// k_walk_dense takes four objects for as many steps as the longest needs, so
+// 1,024 neighbours are ordered by their pairs in fours, LDS rows first, and
+// their pairs are laid out in that order (k_walk_group): rows 102 -> 94 ms at
+// 2,000,000 objects, k = 10,000.  Then the pairs are written (k_walk_prep).
+__global__ __launch_bounds__(256) void k_walk_count(WalkArgs A) {
+    __shared__ unsigned long long sh[4][2];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int64_t nw = (int64_t)gridDim.x * 4;
     const int nhot = (int)A.meta[3];
-    const int64_t p0 = A.rp[A.c0];
-    // the LDS slices' row of zeros; past a block's slices (at most kSplitMaxRows
-    // rows), where a buffer load gives 0
-    const uint2 fill_hot = make_uint2((uint32_t)nhot * kSliceBytes, 0u), fill_cold = make_uint2(kOutside, 0u);
-    if (blockIdx.x == 0 && threadIdx.x < 32) A.ent[threadIdx.x] = threadIdx.x < 16 ? fill_hot : fill_cold;
-    unsigned long long macc = 0, icp_cnt = 0, rel_cnt = 0, terms = 0;
-    for (int64_t o = (int64_t)blockIdx.x * 4 + wid; o < A.n; o += nw) {
+    unsigned long long icp_cnt = 0, rel_cnt = 0;
+    for (int64_t o = (int64_t)blockIdx.x * 4 + wid; o < A.n; o += (int64_t)gridDim.x * 4) {
         const int64_t i = A.c0 + o, r0 = A.rp[i];
         const int n = (int)(A.rp[i + 1] - r0);
         bool icp = false, rel = false;
@@ -923,7 +917,6 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
         }
         icp_cnt += icp ? 1 : 0;
         rel_cnt += rel ? 1 : 0;
-        terms += (unsigned long long)n;
         int nh = 0, nc = 0;
         for (int h0 = 0; h0 < n; h0 += 64) {
             const int h = h0 + lane;
@@ -931,9 +924,95 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
             nh += __popcll(ballot(row >= 0 && row < nhot));
             nc += __popcll(ballot(row >= nhot));
         }
-        const int ph = 16 * chunks16(nh), pc = 16 * chunks16(nc);
-        const int64_t to = 32 + (r0 - p0) + 32 * o;
-        uint2* out = A.ent + to;
+        if (lane == 0)
+            A.hdr[o] = make_uint2(0u, ((uint32_t)nc << 12) | ((uint32_t)nh << 2) | (icp ? 1u : 0u) | (rel ? 2u : 0u));
+    }
+    if (lane == 0) {
+        sh[wid][0] = icp_cnt;
+        sh[wid][1] = rel_cnt;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        const unsigned long long t = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
+        if (t) atomicAdd(&A.counters[threadIdx.x ? 7 : 3], t);
+    }
+}
+
+// ghdr: the headers in the new order; place[o]: where object o came.  The 1,024
+// objects' pairs start at 32 + (nonzeros before them) + 32 (objects before them).
+__global__ __launch_bounds__(1024) void k_walk_group(WalkArgs A) {
+    __shared__ uint32_t key[1024], packed[1024], sums[16];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int64_t b = (int64_t)blockIdx.x * 1024;
+    const int m = (int)min((int64_t)1024, A.n - b);
+    uint32_t k = 0xffffffffu;   // past the range: last
+    if (tid < m) {
+        const uint2 hd = A.hdr[b + tid];
+        packed[tid] = hd.y;
+        k = ((uint32_t)((hdr_hot(hd) + 3) / 4) << 24) | ((uint32_t)min((hdr_cold(hd) + 3) / 4, 16383) << 10) | (uint32_t)tid;
+    }
+    key[tid] = k;
+    for (int size = 2; size <= 1024; size <<= 1)
+        for (int st = size >> 1; st > 0; st >>= 1) {
+            __syncthreads();
+            const int other = tid ^ st;
+            const uint32_t x = key[tid], y = key[other];
+            __syncthreads();
+            key[tid] = ((tid & size) == 0) == (tid < other) ? min(x, y) : max(x, y);
+        }
+    __syncthreads();
+    const int o = (int)(key[tid] & 1023u);
+    const uint2 hd = make_uint2(0u, tid < m ? packed[o] : 0u);
+    uint32_t size = 0;
+    if (tid < m) {
+        const int64_t i = A.c0 + b + o;
+        const int nh = hdr_hot(hd), nc = hdr_cold(hd);
+        size = (uint32_t)(A.rp[i + 1] - A.rp[i]) - (uint32_t)(nh + nc) + 16u * (uint32_t)(chunks16(nh) + chunks16(nc));
+    }
+    // exclusive sums over the workgroup
+    uint32_t at = size;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t v = __shfl_up(at, d, 64);
+        if (lane >= d) at += v;
+    }
+    if (lane == 63) sums[wid] = at;
+    __syncthreads();
+    at -= size;
+    for (int w = 0; w < wid; ++w) at += sums[w];
+    if (tid < m) {
+        at += (uint32_t)(32 + (A.rp[A.c0 + b] - A.rp[A.c0]) + 32 * b);
+        A.hdr[b + o] = make_uint2(at, hd.y);
+        // turned by another amount in every 1,024, or a wave would always get the
+        // long ones: its groups are a power of two apart (rows 115 ms so)
+        const int64_t to = b + (m == 1024 ? (tid + 4 * (53 * blockIdx.x & 255)) & 1023 : tid);
+        A.ghdr[to] = make_uint2(at, hd.y);
+        A.place[b + o] = (int32_t)to;
+    }
+}
+
+// One wave per object of the range: its terms as (code, value) pairs, rows of
+// LDS slices first (code: byte offset of the slice in a block), then the other
+// sliced rows, then the terms with lists only (code: the term), each in ascending
+// term order, the first two filled up to 16 with pairs that add nothing; and the
+// object's mult-adds.  Pairs 0 .. 31 are two chunks of fill.
+__global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
+    __shared__ unsigned long long sh[4][2];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int nhot = (int)A.meta[3];
+    // the LDS slices' row of zeros; past a block's slices (at most kSplitMaxRows
+    // rows), where a buffer load gives 0
+    const uint2 fill_hot = make_uint2((uint32_t)nhot * kSliceBytes, 0u), fill_cold = make_uint2(kOutside, 0u);
+    if (blockIdx.x == 0 && threadIdx.x < 32) A.ent[threadIdx.x] = threadIdx.x < 16 ? fill_hot : fill_cold;
+    unsigned long long macc = 0, terms = 0;
+    for (int64_t o = (int64_t)blockIdx.x * 4 + wid; o < A.n; o += (int64_t)gridDim.x * 4) {
+        const int64_t i = A.c0 + o, r0 = A.rp[i];
+        const int n = (int)(A.rp[i + 1] - r0);
+        const uint2 hd = A.hdr[o];
+        const bool filt = (hd.y & 3u) != 0;
+        const int nh = hdr_hot(hd), nc = hdr_cold(hd), ph = 16 * chunks16(nh), pc = 16 * chunks16(nc);
+        uint2* out = A.ent + hd.x;
+        terms += (unsigned long long)n;
         if (lane < 16) {
             if (nh + lane < ph) out[nh + lane] = fill_hot;
             if (nc + lane < pc) out[ph + nc + lane] = fill_cold;
@@ -949,7 +1028,7 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
                 v = load_xval(A.xval, A.x_f64, r0 + h);
                 row = A.srow[t];
                 const int2 len = A.tlen[t];
-                macc += (unsigned long long)(icp || rel ? len.y : len.x);
+                macc += (unsigned long long)(filt ? len.y : len.x);
             }
             const bool hot = in && row >= 0 && row < nhot, cold = in && row >= nhot, tail = in && row < 0;
             const unsigned long long mh = ballot(hot), mc = ballot(cold), mt = ballot(tail);
@@ -959,22 +1038,16 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
             ac += __popcll(mc);
             at += __popcll(mt);
         }
-        if (lane == 0)
-            A.hdr[o] = make_uint2((uint32_t)to,
-                                  ((uint32_t)nc << 12) | ((uint32_t)nh << 2) | (icp ? 1u : 0u) | (rel ? 2u : 0u));
     }
     macc = (unsigned long long)wave_sum_i64((int64_t)macc);
     if (lane == 0) {
         sh[wid][0] = macc;
-        sh[wid][1] = icp_cnt;
-        sh[wid][2] = rel_cnt;
-        sh[wid][3] = terms * (A.x_f64 ? 32 : 28);   // bytes loaded: column and row twice, value, lengths
+        sh[wid][1] = terms * (A.x_f64 ? 32 : 28);   // bytes loaded: column and row twice, value, lengths
     }
     __syncthreads();
-    if (threadIdx.x < 4) {
+    if (threadIdx.x < 2) {
         const unsigned long long t = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
-        const int slot[4] = {0, 3, 7, 10};
-        if (t) atomicAdd(&A.counters[slot[threadIdx.x]], t);
+        if (t) atomicAdd(&A.counters[threadIdx.x ? 10 : 0], t);
     }
 }
 
@@ -1005,7 +1078,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_walk_dense(WalkArgs A, int ti
         const bool moving = base + blk * kSliceCols < A.nmv;   // some centroid of the block moved
         dense_groups<2>(
             g0, g1, ents, panel, bytes_rsrc(src, (uint32_t)(A.srows * kSliceBytes)), loads,
-            [&](int g) { return A.hdr[min(4 * g + sub, n - 1)]; },
+            [&](int g) { return A.ghdr[min(4 * g + sub, n - 1)]; },
             // a set flag: the object compares moving centroids only
             [&](int g, const uint2& hd) { return 4 * g + sub < n && ((hd.y & 3u) == 0 || moving); },
             [&](int g, const float4& acc, bool want) {
@@ -1034,6 +1107,8 @@ hipError_t range_nnz(const int64_t* rp, int64_t n, int64_t range, int64_t* most,
 
 hipError_t walk_prep(const WalkArgs& a, int n_cu, hipStream_t s) {
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((a.n + 3) / 4, (int64_t)n_cu * 8));
+    hipLaunchKernelGGL(k_walk_count, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_walk_group, dim3((unsigned)((a.n + 1023) / 1024)), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(k_walk_prep, dim3((unsigned)blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -155,7 +155,9 @@ typedef struct {
                                     head-row batches, segment records, staged terms) */
     int64_t walk_wide_bytes;     /* of which 16-byte-per-lane loads (dense head rows and
                                     segment records; the rest are 4- and 8-byte loads) */
-    int32_t walk_launches;       /* fast-pass kernel launches of this step */
+    int32_t walk_launches;       /* fast-pass launches of this step: one per tile (group of
+                                    tiles_per_launch) and, where the walk is split, per
+                                    range of objects */
     int32_t reserved;
 } sivf_iter_stats;
 

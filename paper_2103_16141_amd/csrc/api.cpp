@@ -1277,10 +1277,14 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     float *CT = nullptr, *dS = nullptr, *dxp = nullptr, *dCT = nullptr;
     STCHK(ws(ctx, "soft_CT", kp * d, &CT));
     // rows per chunk: 24,576 rows of a 32-column dS block take 3 MB of an XCD's
-    // 4 MB L2 (backward at N = 262,144, k = 4,096 with 8,192 / 12,288 / 16,384 /
-    // 24,576 / 32,768 rows: 96 / 85 / 79 / 76 / 77 ms: smaller chunks read and
-    // write dC more often, larger ones miss L2); dS of a chunk is at most 512 MiB
-    const int64_t rc = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), (int64_t)24576, (int64_t)(128ll << 20) / kp}));
+    // 4 MB L2; smaller chunks read and write dC more often, larger ones miss L2.
+    // Where a term has few entries in a chunk (below 32 on average), dC costs more
+    // than the misses: backward with 16,384 / 24,576 / 32,768 / 40,960 rows, N =
+    // 262,144, D = 100,000, 100 terms, k = 4,096 (25 entries) 78.6 / 73.2 / 71.0 /
+    // 71.6 ms; N = 97,062, D = 38,883, 177 terms, k = 3,837 (112) - / 46.2 / 47.5 /
+    // 48.9.  dS of a chunk is at most 512 MiB.
+    const int64_t rows = (double)Xc.nnz * 24576.0 < 32.0 * (double)n * (double)d ? 32768 : 24576;
+    const int64_t rc = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), rows, (int64_t)(128ll << 20) / kp}));
     const int64_t nch = std::max<int64_t>(1, (n + rc - 1) / rc);
     HIPCHK(ctx, soft_pack(C, CT, k, d, s));
     // nonzero offsets of the row chunks: they size the per-block dX shares and

@@ -712,7 +712,7 @@ hipError_t soft_chunk_offsets(const int64_t* rp, int64_t n, int64_t rc, int64_t 
 // L2 whatever the order of the rows.  What bounds it: L1 misses on random
 // 128-byte slices (12 TB/s) and, for the rare terms, the read and write of dCT
 // per chunk.  At the forward's shapes 42.7 and 0.50 ms (less the densest terms'
-// entries 30.6); with 512-column slices
+// entries 30.6, in chunks of 32,768 rows 28.6); with 512-column slices
 // in chunks of 16,384 rows, cut at row blocks, 44 and 2.9 ms.
 constexpr int kTiny = 8;
 constexpr int kPiece = kSoftPiece;
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(256) void k_dct_combine(int64_t d, int64_t nsb, int
 // 256 densest terms (46% of the nonzeros at Zipf 1.1, D = 100,000, 100 terms a
 // row), on the FP32 matrix cores.  An entry costs 0.4 ps of gathers per column, a
 // place of Xd 0.015, so terms in 1/32 of the rows and more are taken.  N =
-// 262,144, k = 4,096: 42.6 ms for dC before, 36.0 now (5.4 the products, at 104
+// 262,144, k = 4,096: 42.6 ms for dC before, 36.0 so (5.4 the products, at 104
 // TFLOP/s of 149 that a library product reaches); at N = 20,011, k = 1,021
 // (kSoftProdWork / 2.4) 0.18 ms less for the entries and 0.20 for the products
 // and choosing the terms.

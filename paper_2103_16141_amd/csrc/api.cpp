@@ -282,31 +282,6 @@ sivf_status validate(sivf_ctx* ctx, const sivf_csr* X, Csr* out, std::initialize
     return validate(ctx, X, out, w, ids);
 }
 
-// Tiles of k centroids holding an estimated `postings` over d terms.  Every
-// tile repeats an object's work per term and its scan, so the widest is the best
-// as long as its rows stay in cache; wider than 2048 costs occupancy (LDS).
-// FP32, walk in ms with 1024 and 2048: 60,000 objects, k = 1,531 1.14 and 0.71
-// (one tile for two); 400,000, k = 20,000 84.4 and 68.9; 5,000,000, k = 10,000
-// 536 and 500 (2560: 10 - 15% more).  BF16 files, half the bytes, pay the
-// scattered access to a wider tile sooner: sparse (the seed objects: 62.5 and
-// 51.7) 2048; up to 3% dense, or in at most two tiles, 1536 (k = 10,000, 2%
-// dense: 86.2 with 1024, 86.0 with 1536, 88.8 with 2048; k = 1,500, 12% dense
-// 19.7 and 15.4); denser 1024 (5,000,000 objects, 6% dense: 439, 460, 490).
-void choose_tiles(const sivf_ctx* ctx, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
-    int32_t want = ctx->opt.k_tile;
-    if (want <= 0) {
-        const double density = postings / ((double)k * (double)d);
-        int32_t kmax = kTileWide;
-        if (ctx->opt.posting_dtype == SIVF_BF16 && density > 0.003)
-            kmax = density < 0.033 || k <= 2 * kTileMid ? kTileMid : kTileNarrow;
-        const int32_t t = (k + kmax - 1) / kmax;
-        const int32_t w = (k + t - 1) / t;
-        want = ((w + 63) / 64) * 64;
-    }
-    *kt = want;
-    *T = (k + want - 1) / want;
-}
-
 // The split walk reads the head rows faster than the plain one, but moves a sum
 // per object and slot through memory and takes three launches per range and
 // tile.  FP32 postings only (BF16 rows are half the bytes, and the plain walk
@@ -417,8 +392,10 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     f->k = k;
     f->d = d;
     f->pdt = ctx->opt.posting_dtype;
+    f->k_tile = ctx->opt.k_tile;
     // arrays for the most tiles the file may come to have
-    choose_tiles(ctx, k, INFINITY, d, &f->kt, &f->T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, &f->kt, &f->T);
+    f->T_max = f->T;
     const size_t kk = (size_t)k, dd = (size_t)d, dt = (size_t)(d * f->T);
     const size_t hd = ctx->opt.head_density > 0.0f ? dd : 0, sd = split_possible(ctx->opt) ? dd : 0;
     const sivf_status st = pieces_alloc(
@@ -443,7 +420,13 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 // (nullptr: unknown); the split walk's rows are made if it pays for them.  A file built from given centroids gets none before its first
 // update (they take 0.17 ms of a 3.0 ms restart, and nobody may walk it so).
 sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, const Csr* X) {
-    choose_tiles(ctx, f->k, postings, f->d, &f->kt, &f->T);
+    // the tiles follow from the options the file was made with: a ctx with others
+    // may update it, and its arrays have room for T_max tiles
+    int32_t kt = 0, T = 0;
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, &kt, &T);
+    if (T > f->T_max) return fail(ctx, SIVF_E_HIP, "internal: %d tiles in a file made for %d", T, f->T_max);
+    f->kt = kt;
+    f->T = T;
     const int64_t W64 = ivf_w64(f->k);
     const int64_t nseg2 = f->d * f->T * 2;
     IvfBuildWs w{};

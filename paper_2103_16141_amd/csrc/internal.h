@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/sivf.h"
+#include "plan.h"
 
 namespace sivf {
 
@@ -26,7 +27,6 @@ constexpr int64_t kSplitMaxRows = (1 << 20) - 1;   // 20 bits; a block's slices 
 constexpr int kMeta = 7;           // counts of a file on the device (sivf_ivf::meta)
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request
 constexpr int kWalkWaves = 4;      // waves per workgroup in the walk kernels
-constexpr int kTileWide = 2048, kTileMid = 1536, kTileNarrow = 1024;   // automatic tile widths
 constexpr int kMaxTile = 4096;     // largest similarity tile (centroids) per wave
 constexpr size_t kPinBytes = 1024;
 
@@ -137,6 +137,7 @@ struct sivf_ivf {
     int32_t k = 0;
     int64_t d = 0;
     int32_t kt = 0, T = 0;          // tile width, tiles
+    int32_t k_tile = 0, T_max = 0;  // the width asked for (0: automatic), tiles the arrays have room for
     // the allocations: what follows k and d, the stores' entries, the postings
     void *fixed = nullptr, *postings = nullptr;
     size_t fixed_bytes = 0, postings_bytes = 0;

@@ -1,0 +1,60 @@
+"""A file of centroids through other contexts than the one it was made in, and
+after calls on it that failed."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from tests.gpu_util import device, log
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(**kw):
+    from paper_2103_16141_amd.api import Context
+    return Context(0, **kw)
+
+
+def _X(c):
+    from paper_2103_16141_amd.api import DeviceCsr
+    return DeviceCsr.from_corpus(c, device())
+
+
+def _state(n, k):
+    return (torch.zeros(n, dtype=torch.int32, device=device()), torch.zeros(n, dtype=torch.float32, device=device()),
+            torch.zeros(k, dtype=torch.uint8, device=device()))
+
+
+def _same_export(f, g):
+    p, q = f.export(), g.export()
+    for m in p:
+        assert torch.equal(p[m], q[m]), m
+
+
+@pytest.mark.parametrize("made,other", [
+    (dict(), dict(k_tile=64)),
+    (dict(), dict(posting_dtype="bf16")),
+    (dict(posting_dtype="bf16"), dict(posting_dtype="bf16", k_tile=64)),
+    (dict(posting_dtype="bf16"), dict()),
+    (dict(k_tile=512), dict(k_tile=64, head_density=0.9)),
+])
+def test_a_file_keeps_its_tiling_when_another_context_updates_it(made, other):
+    # tiles follow from the options the file was made with, whoever updates it:
+    # every step is that of a file that stays in its own context
+    log("file of %s updated by %s" % (made, other))
+    k, d = 3_100, 400
+    c = synth.make_corpus(2 * k + 3, d, 40, 1.0, np.float32, seed=11)
+    X, ids = _X(c), synth.init_ids(c.n, k, 12)
+    home, guest = _ctx(**made), _ctx(**other)
+    f, g = home.init_centroids(X, k, ids), home.init_centroids(X, k, ids)
+    (a, own, lam), (a2, own2, lam2) = _state(c.n, k), _state(c.n, k)
+    for r in (1, 2, 3):
+        home.assign(X, f, r, a, own, lam)
+        home.assign(X, g, r, a2, own2, lam2)
+        assert torch.equal(a, a2) and torch.equal(own, own2) and torch.equal(lam, lam2)
+        home.update(X, a, lam, f)
+        guest.update(X, a2, lam2, g)
+        assert f.sizes() == g.sizes()
+        _same_export(f, g)
+    f.free()
+    g.free()

@@ -1,0 +1,49 @@
+"""Sizes the host decides without a device (csrc/plan.h), compiled for the CPU
+and checked over their ranges."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HARNESS = r"""
+#include "plan.h"
+extern "C" {
+void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
+    sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, kt, T);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, lib = d / "plan.cpp", d / "plan.so"
+    src.write_text(HARNESS)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I",
+                           os.path.join(ROOT, "paper_2103_16141_amd", "csrc"), str(src), "-o", str(lib)])
+    return ctypes.CDLL(str(lib))
+
+
+def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
+    # a file's arrays are allocated for infinitely many postings; an update
+    # chooses the tiles again for the postings it expects
+    def tiles(k_tile, bf16, k, postings, d):
+        kt, T = ctypes.c_int32(), ctypes.c_int32()
+        plan.tiles(k_tile, bf16, k, ctypes.c_double(postings), ctypes.c_int64(d), ctypes.byref(kt), ctypes.byref(T))
+        return kt.value, T.value
+
+    rng = np.random.default_rng(0)
+    ks = [1, 63, 64, 65, 1023, 1024, 1025, 1536, 1537, 2047, 2048, 2049, 3071, 3072, 3073, 4096, 2 ** 31 - 1]
+    ks += [int(k) for k in np.exp(rng.uniform(0, np.log(1e7), 2000))]
+    for k in ks:
+        for bf16 in (0, 1):
+            for k_tile in (0, 64, 128, 4096):
+                _, most = tiles(k_tile, bf16, k, float("inf"), 1000)
+                for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
+                    kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000)
+                    assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt

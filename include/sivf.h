@@ -267,7 +267,11 @@ sivf_status sivf_assign_noalloc(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf
 /* Update step r (Alg. 5): replace the file's centroids by mu^[r] computed from
  * X and assign = a^[r] (int32[N], values in [0, k)), and restructure it with
  * lambda = lambda^[r] (uint8[k]).  Clusters with lambda_j = 1 or no members keep
- * their centroid bitwise.  stats_host optional (t_update_ms). */
+ * their centroid bitwise.  stats_host optional (t_update_ms).  If it fails
+ * once its inputs were accepted (SIVF_E_NOMEM, SIVF_E_HIP, SIVF_E_UNSUPPORTED),
+ * the file may be left without its structure: until an update of it succeeds,
+ * sivf_assign and the export of term_ptr, split and postings return
+ * SIVF_E_INVALID. */
 sivf_status sivf_update(sivf_ctx* ctx, const sivf_csr* X, const int32_t* assign,
                         const uint8_t* lambda, sivf_ivf* ivf_inout, sivf_iter_stats* stats_host);
 

@@ -424,6 +424,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // may update it, and its arrays have room for T_max tiles
     int32_t kt = 0, T = 0;
     choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, &kt, &T);
+    f->built = false;   // until every array below is whole again
     if (T > f->T_max) return fail(ctx, SIVF_E_HIP, "internal: %d tiles in a file made for %d", T, f->T_max);
     f->kt = kt;
     f->T = T;
@@ -460,8 +461,8 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     const int64_t P = h[1], P2 = h[kMeta], H = f->head ? h[2] : 0, SH = f->srow ? h[4] : 0;
     if (P != P2)
         return fail(ctx, SIVF_E_HIP, "internal: %lld postings for %lld centroid entries", (long long)P2, (long long)P);
-    STCHK(postings_reserve(ctx, f, P));
     f->P = P;
+    STCHK(postings_reserve(ctx, f, P));
     HIPCHK(ctx, ivf_fill(f->cur, f->k, f->d, f->kt, f->T, f->iperm, cscan, f->nmv, P, w, f->cid, f->v32, f->v16,
                          f->v64, ctx->stream));
     f->H = 0;
@@ -505,6 +506,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // norm bounds for the signed-data certificate: needed whenever the X of a
     // later call has a negative value, whatever the centroids' signs
     if (norms) HIPCHK(ctx, centroid_norms(f->cur, f->k, f->cnorm, ctx->stream));
+    f->built = true;
     return SIVF_OK;
 }
 
@@ -689,6 +691,12 @@ sivf_status validate_with_ids(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* 
     return validate(ctx, X, out, w, {{ids, X->n_rows, f->k, what}});
 }
 
+// The structure of a file whose update failed half way is not there to be read.
+sivf_status check_built(sivf_ctx* ctx, const sivf_ivf* f) {
+    if (f->built) return SIVF_OK;
+    return fail(ctx, SIVF_E_INVALID, "the file has no structure since an update of it failed; update it again");
+}
+
 // Assignment step r = iter (Alg. 4) of X against the file f.
 sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, int32_t iter, int32_t* assign_inout,
                         float* own_sim_inout, double* own64_inout, uint8_t* lambda_out, sivf_iter_stats* stats_host) {
@@ -870,10 +878,11 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     HIPCHK(ctx, upd_bounds(k, Xc.d, Xc.nnz, lambda, 1, f->cur, w, s));
     // room for the new entries: the exact bound is on the device; where the
     // largest it can be already fits or is small, the host need not wait for it
+    // (after a failed update f->P may not be the current entries)
     int64_t most = f->P + Xc.nnz;
     if (f->d < most / k) most = f->d * k;
-    if (!f->nxt.term || f->nxt.cap < most) {
-        if (ctx->opt.workspace_cap_bytes != 0 || most > ((int64_t)4 << 20)) {
+    if (!f->nxt.term || f->nxt.cap < most || !f->built) {
+        if (ctx->opt.workspace_cap_bytes != 0 || !f->built || most > ((int64_t)4 << 20)) {
             int64_t* total = (int64_t*)ctx->pin;
             HIPCHK(ctx, hipMemcpyAsync(total, w.ubscan + k, 8, hipMemcpyDeviceToHost, s));
             HIPCHK(ctx, hipStreamSynchronize(s));
@@ -881,6 +890,7 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
         }
         STCHK(store_reserve(ctx, f, &f->nxt, &f->nxt_mem, most));
     }
+    f->built = false;
     HIPCHK(ctx, upd_means(Xc, k, lambda, 1, f->cur, f->nxt, w, f->cnorm, s));
     std::swap(f->cur, f->nxt);
     std::swap(f->cur_mem, f->nxt_mem);
@@ -1023,6 +1033,7 @@ sivf_status sivf_ivf_export(sivf_ctx* ctx, const sivf_ivf* f, int64_t* c_ptr, in
     DevGuard g(ctx->device);
     if ((c_col || c_val) && !c_ptr) return fail(ctx, SIVF_E_INVALID, "c_col/c_val need c_ptr");
     if ((p_cid || p_val) && !term_ptr) return fail(ctx, SIVF_E_INVALID, "p_cid/p_val need term_ptr");
+    if (term_ptr || split) STCHK(check_built(ctx, f));
     int64_t* sws = nullptr;
     STCHK(ws(ctx, "scan_ws", scan_ws_elems(std::max<int64_t>(f->k, f->d) + 1) + 8, &sws));
     if (c_ptr) {
@@ -1047,6 +1058,7 @@ sivf_status sivf_assign(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* f, int
     if (ctx->opt.filter_mode == SIVF_MODE_RELAXED && !own64_inout)
         return fail(ctx, SIVF_E_INVALID, "the RELAXED filter needs own64_inout");
     if (iter < 1) return fail(ctx, SIVF_E_INVALID, "iter must be >= 1");
+    STCHK(check_built(ctx, f));
     Csr Xc;
     Work w{ctx};
     STCHK(validate_with_ids(ctx, X, f, iter >= 2 ? assign_inout : nullptr, "assign_inout (a^[r-1])", &Xc, w));
@@ -1062,6 +1074,7 @@ sivf_status sivf_assign_noalloc(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf
     if (ctx->opt.filter_mode == SIVF_MODE_RELAXED && !own64_inout)
         return fail(ctx, SIVF_E_INVALID, "the RELAXED filter needs own64_inout");
     if (iter < 1) return fail(ctx, SIVF_E_INVALID, "iter must be >= 1");
+    STCHK(check_built(ctx, f));
     STCHK(check_csr_args(ctx, X, "X"));
     // the same requests as the run below, counted without memory
     Work m{ctx, Work::kMeasure};

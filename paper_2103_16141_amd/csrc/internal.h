@@ -169,6 +169,7 @@ struct sivf_ivf {
     uint8_t* lam = nullptr;         // [k]
     double* cnorm = nullptr;        // [k]
     int nonneg = 1;
+    bool built = false;             // the structure is that of `cur` (not so once an update has failed half way)
     size_t bytes = 0;               // device bytes held (counted against the ctx cap)
 };
 

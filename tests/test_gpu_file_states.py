@@ -58,3 +58,47 @@ def test_a_file_keeps_its_tiling_when_another_context_updates_it(made, other):
         _same_export(f, g)
     f.free()
     g.free()
+
+
+@pytest.mark.parametrize("posting", ["fp32", "bf16"])
+def test_a_file_whose_update_ran_out_of_memory_is_refused_until_updated(posting):
+    # caps from too small for the first buffer to enough for the whole update:
+    # whatever request fails, the file is either as it was or refused, and the
+    # same update with enough memory gives what it would have given
+    from paper_2103_16141_amd._native import SivfError
+    log("failed updates, %s" % posting)
+    k, d = 2_000, 900
+    c = synth.make_corpus(9_001, d, 60, 1.0, np.float32, seed=21)
+    X, ids = _X(c), synth.init_ids(c.n, k, 22)
+    home = _ctx(posting_dtype=posting)
+    (a, own, lam), (a2, own2, lam2) = _state(c.n, k), _state(c.n, k)
+    want = home.init_centroids(X, k, ids)
+    home.assign(X, want, 1, a, own, lam)
+    home.update(X, a, lam, want)
+    refused = kept = 0
+    done = False
+    for cap in (int(2.0 ** (e / 16)) for e in range(368, 500)):
+        f = home.init_centroids(X, k, ids)
+        guest = _ctx(posting_dtype=posting, workspace_cap_bytes=cap)
+        try:
+            guest.update(X, a, lam, f)
+            done = True
+        except SivfError as e:
+            assert e.name == "SIVF_E_NOMEM"
+            try:
+                home.assign(X, f, 1, a2, own2, lam2)
+                kept += 1
+                assert torch.equal(a2, a) and torch.equal(own2, own)
+            except SivfError as e:
+                refused += 1
+                assert e.name == "SIVF_E_INVALID"
+                with pytest.raises(SivfError):
+                    f.export()
+            home.update(X, a, lam, f)
+        _same_export(f, want)
+        home.assign(X, f, 1, a2, own2, lam2)
+        f.free()
+        guest.close()
+        if done:
+            break
+    assert done and refused and kept

@@ -170,6 +170,7 @@ hipError_t exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, int64_
 // With consistent row bounds, rows ascend strictly exactly if every descent
 // lies at the start of a (non-empty) row, so the pass counts all descents,
 // takes away those at row starts, and the rows ascend iff nothing is left.
+// The arrays hold row_ptr[n] nonzeros: no more are read if more are stated.
 // Bound: one read of X.  Each thread takes 4 consecutive nonzeros (16-byte
 // loads where the arrays allow).  Against one wave per 64 rows walking their
 // nonzeros 64 at a time (32 waves for 2,000 long centroid rows), a restart of
@@ -187,10 +188,11 @@ __device__ inline bool finite_bits(double v) {
 
 template <typename V>
 __global__ __launch_bounds__(256) void k_validate(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                  const V* __restrict__ val, int64_t n, int64_t d, int64_t nnz,
+                                                  const V* __restrict__ val, int64_t n, int64_t d, int64_t stated,
                                                   int vec, unsigned long long* flags) {
     __shared__ int sh_diff[4];
     __shared__ unsigned sh_bad[4];
+    const int64_t nnz = min(stated, rp[n]);   // negative: none
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
     unsigned bad = 0;   // flags[0]'s bits, bit 4: a negative value
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(256) void k_validate(const int64_t* __restrict__ rp
     for (int64_t i = t0; i < n; i += nt) {
         const int64_t b = rp[i], e = rp[i + 1];
         if (i == 0 && b != 0) bad |= 8;
-        if (i == n - 1 && e != nnz) bad |= 8;
+        if (i == n - 1 && e != stated) bad |= 8;
         if (e < b || b < 0 || e > nnz) bad |= 1;
         else if (b < e && b > 0 && col[b] <= col[b - 1]) --diff;
     }
@@ -274,14 +276,15 @@ __global__ __launch_bounds__(256) void k_validate(const int64_t* __restrict__ rp
 // bits of the row starts that fall in it, so a lane knows whether its element
 // opens a row; otherwise its column must exceed its left neighbour's (taken
 // by a shuffle, lane 0 from the previous window).  Row bounds that are out of
-// order are reported as such and their group's elements are not inspected.
+// order are reported as such and their group's elements are not inspected; nor
+// are any past row_ptr[n], which the arrays need not hold.
 __global__ __launch_bounds__(256) void k_validate_rows(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                        const void* __restrict__ val, int f64, int64_t n, int64_t d,
                                                        int64_t nnz, unsigned long long* flags) {
     const int lane = threadIdx.x & 63;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t ngroups = (n + 63) / 64;
+    const int64_t ngroups = (n + 63) / 64, held = rp[n];
     for (int64_t g = wave; g < ngroups; g += nw) {
         const int64_t i = g * 64 + lane;
         const bool row = i < n;
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(256) void k_validate_rows(const int64_t* __restrict
             if (e < b || b < 0 || e > nnz) bad |= 1;
         }
         int64_t first_bad_row = bad ? i : INT64_MAX;
-        const bool bounds_ok = ballot(bad != 0) == 0ull;
+        const bool bounds_ok = ballot(bad != 0 || e > held) == 0ull;
         unsigned long long ebad = 0;
         if (bounds_ok) {
             // the group's nonzeros: [rp[g*64], rp[min(g*64+64, n)])

@@ -102,3 +102,25 @@ def test_a_file_whose_update_ran_out_of_memory_is_refused_until_updated(posting)
         if done:
             break
     assert done and refused and kept
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("rows", [1, 64, 200])
+def test_no_nonzero_past_the_last_row_bound_is_read(dtype, rows):
+    # a matrix whose stated number of nonzeros is far more than its row bounds
+    # (and its arrays) hold is refused without a look past them
+    import ctypes
+    from paper_2103_16141_amd import _native as N
+    log("stated nonzeros, %d rows" % rows)
+    c = synth.make_corpus(rows, 50, 5, 1.0, dtype, seed=rows)
+    X = _X(c)
+    ctx = _ctx()
+    for stated in (c.nnz + 1, 1 << 33, 1 << 40):
+        s = X.struct()
+        s.nnz = stated
+        assert N.load().sivf_validate_csr(ctx.handle, ctypes.byref(s)) == -3
+        assert b"row_ptr[n] != nnz" in N.load().sivf_last_error(ctx.handle)
+    s = X.struct()
+    s.nnz = c.nnz - 1
+    assert N.load().sivf_validate_csr(ctx.handle, ctypes.byref(s)) == -3
+    ctx.validate(X)

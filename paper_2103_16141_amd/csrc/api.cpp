@@ -622,21 +622,28 @@ sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     const double h = f->sfrac * Xc.nnz / Xc.n;
     if (!split_pays(h, Xc.n, f)) return SIVF_OK;
     const int64_t ktp = head_ktp(f->kt);
-    int64_t range = std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp), pairs = 0, *most = nullptr;
+    int64_t pairs = 0, *most = nullptr;
     STCHK(w.get("split_most", 1, &most));
-    for (;; range = (range + 1) / 2) {
-        if (!split_pays(h, range, f)) return SIVF_OK;   // very long rows
-        int64_t nnz = Xc.nnz;
-        if (range < Xc.n) {
-            HIPCHK(ctx, fill_i64(most, 0, 1, ctx->stream));
-            HIPCHK(ctx, range_nnz(Xc.rp, Xc.n, range, most, ctx->stream));
-            HIPCHK(ctx, hipMemcpyAsync(ctx->pin, most, 8, hipMemcpyDeviceToHost, ctx->stream));
-            HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-            nnz = *(const int64_t*)ctx->pin;
-        }
-        pairs = split_pairs(nnz, range);
-        if (pairs <= kSplitMaxPairs) break;
-    }
+    sivf_status st = SIVF_OK;
+    auto longest = [&](int64_t r, int64_t* nnz) -> sivf_status {
+        *nnz = Xc.nnz;
+        if (r == Xc.n) return SIVF_OK;
+        HIPCHK(ctx, fill_i64(most, 0, 1, ctx->stream));
+        HIPCHK(ctx, range_nnz(Xc.rp, Xc.n, r, most, ctx->stream));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->pin, most, 8, hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+        *nnz = *(const int64_t*)ctx->pin;
+        return SIVF_OK;
+    };
+    const int64_t range = split_range(
+        std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp), [&](int64_t r) { return split_pays(h, r, f); },
+        [&](int64_t r) {
+            int64_t nnz = 0;
+            st = longest(r, &nnz);
+            return st == SIVF_OK ? nnz : -1;
+        },
+        &pairs);
+    if (st != SIVF_OK || range == 0) return st;
     if (w.get("split_ent", pairs, &b->ent) != SIVF_OK || w.get("split_hdr", range, &b->hdr) != SIVF_OK ||
         w.get("split_ghdr", range, &b->ghdr) != SIVF_OK || w.get("split_place", range, &b->place) != SIVF_OK ||
         w.get("split_S", range * ktp, &b->S) != SIVF_OK)

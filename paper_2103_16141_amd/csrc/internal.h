@@ -20,9 +20,6 @@ static_assert(kTermCap % 64 == 0, "the walk reads staged terms a whole 64-term c
 constexpr int kSliceBytes = 256;   // of a sliced row: one block of 64 centroids
 constexpr int kSliceCols = 64;
 constexpr int kSplitHot = 608;     // sliced rows whose slices of a block fit a CU's LDS (and a row of zeros)
-// pairs of a range: two chunks of fill, then every object's, filled up twice
-inline int64_t split_pairs(int64_t nnz, int64_t objects) { return 32 + nnz + 32 * objects; }
-constexpr int64_t kSplitMaxPairs = (1 << 29) - 1;   // of a range: less than 4 GiB
 constexpr int64_t kSplitMaxRows = (1 << 20) - 1;   // 20 bits; a block's slices stay well below 4 GiB
 constexpr int kMeta = 7;           // counts of a file on the device (sivf_ivf::meta)
 constexpr int64_t kHeadMaxBytes = 1LL << 36;      // largest dense head-row buffer a file may request

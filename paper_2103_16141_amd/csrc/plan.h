@@ -35,4 +35,24 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
     *T = (int32_t)(((int64_t)k + want - 1) / want);
 }
 
+// pairs of a range of the split walk's objects: two chunks of fill, then every
+// object's, filled up twice
+inline int64_t split_pairs(int64_t nnz, int64_t objects) { return 32 + nnz + 32 * objects; }
+constexpr int64_t kSplitMaxPairs = (1 << 29) - 1;   // of a range: less than 4 GiB
+
+// Objects per range: at most `most` (at least 1), halved while the longest range
+// has too many pairs; 0 if that is so for one object, pays(range) ends, or
+// longest(range), the nonzeros of the longest range, is negative (not known).
+template <typename Pays, typename Longest>
+int64_t split_range(int64_t most, Pays pays, Longest longest, int64_t* pairs) {
+    for (int64_t range = most;; range = (range + 1) / 2) {
+        if (!pays(range)) return 0;
+        const int64_t nnz = longest(range);
+        if (nnz < 0) return 0;
+        *pairs = split_pairs(nnz, range);
+        if (*pairs <= kSplitMaxPairs) return range;
+        if (range == 1) return 0;
+    }
+}
+
 }  // namespace sivf

@@ -15,6 +15,10 @@ extern "C" {
 void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
     sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, kt, T);
 }
+typedef int64_t (*fn)(int64_t);
+int64_t split(int64_t most, fn pays, fn longest, int64_t* pairs) {
+    return sivf::split_range(most, [=](int64_t r) { return pays(r) != 0; }, longest, pairs);
+}
 }
 """
 
@@ -47,3 +51,29 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
                 for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
                     kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000)
                     assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt
+
+
+@pytest.mark.parametrize("objects,row,floor,want", [
+    (1, 1 << 30, 0, 0),                        # one row alone has too many pairs: not split
+    (1_000_000, 1 << 30, 0, 0),
+    (1_000_000, 100, 0, 1_000_000),            # everything fits
+    (1_000_000, 2_000, 0, 250_000),            # 2,032 pairs an object: at most 264,208 objects
+    (1_000_000, 2_000, 300_000, 0),            # no longer pays so small
+    (3, (1 << 29) - 65, 0, 1),                 # one row just fits (64 pairs of fill)
+    (3, (1 << 29) - 64, 0, 0),                 # one more does not
+])
+def test_ranges_of_the_split_walk_end(plan, objects, row, floor, want):
+    fn = ctypes.CFUNCTYPE(ctypes.c_int64, ctypes.c_int64)
+    calls = []
+
+    def longest(r):
+        calls.append(r)
+        assert len(calls) < 64, "does not end"
+        return r * row
+
+    plan.split.restype = ctypes.c_int64
+    pairs = ctypes.c_int64()
+    got = plan.split(ctypes.c_int64(objects), fn(lambda r: r >= floor), fn(longest), ctypes.byref(pairs))
+    assert got == want
+    if want:
+        assert pairs.value == 32 + want * (row + 32)

@@ -63,13 +63,50 @@ bool cap_ok(sivf_ctx* ctx, size_t more) {
     return ctx->opt.workspace_cap_bytes == 0 || ctx->bytes_held + more <= ctx->opt.workspace_cap_bytes;
 }
 
+void dev_free(sivf_ctx* ctx, void* p, size_t bytes, size_t* account) {
+    if (!p) return;
+    if (bytes == 0) bytes = 8;
+    (void)hipFree(p);
+    ctx->bytes_held -= std::min(ctx->bytes_held, bytes);
+    if (account) *account -= std::min(*account, bytes);
+}
+
+// Frees what the ctx holds for faster forms only: its optional buffers, and the
+// sliced rows of the file that is being updated.  None of it is in use then: a
+// call asks for what it cannot do without first, and the stream is waited for.
+// Returns whether there was anything.
+bool give_back(sivf_ctx* ctx) {
+    sivf_ivf* f = ctx->updating;
+    bool any = f && f->sval;
+    for (const auto& kv : ctx->ws) any = any || kv.second.optional;
+    if (!any || hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+    for (auto it = ctx->ws.begin(); it != ctx->ws.end();) {
+        if (!it->second.optional) {
+            ++it;
+            continue;
+        }
+        dev_free(ctx, it->second.p, it->second.bytes, nullptr);
+        it = ctx->ws.erase(it);
+    }
+    if (f && f->sval) {
+        dev_free(ctx, f->sval, (size_t)f->scap * 4, &f->bytes);
+        f->sval = nullptr;
+        f->scap = f->srows = 0;
+    }
+    return true;
+}
+
 sivf_status dev_alloc(sivf_ctx* ctx, void** p, size_t bytes, size_t* account) {
     *p = nullptr;
     if (bytes == 0) bytes = 8;
-    if (!cap_ok(ctx, bytes))
+    if (!cap_ok(ctx, bytes) && !(give_back(ctx) && cap_ok(ctx, bytes)))
         return fail(ctx, SIVF_E_NOMEM, "workspace cap of %zu bytes exceeded (%zu held, %zu requested)",
                     ctx->opt.workspace_cap_bytes, ctx->bytes_held, bytes);
     hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (give_back(ctx)) e = hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         *p = nullptr;
@@ -80,12 +117,21 @@ sivf_status dev_alloc(sivf_ctx* ctx, void** p, size_t bytes, size_t* account) {
     return SIVF_OK;
 }
 
-void dev_free(sivf_ctx* ctx, void* p, size_t bytes, size_t* account) {
-    if (!p) return;
-    if (bytes == 0) bytes = 8;
-    (void)hipFree(p);
-    ctx->bytes_held -= std::min(ctx->bytes_held, bytes);
-    if (account) *account -= std::min(*account, bytes);
+// Memory for a faster form that a call can do without: at most half of what is
+// free, so that the caller's next allocations find room, and no error if there
+// is none.
+bool optional_alloc(sivf_ctx* ctx, void** p, size_t bytes, size_t* account) {
+    *p = nullptr;
+    size_t room = 0, all = 0;
+    if (!cap_ok(ctx, bytes) || hipMemGetInfo(&room, &all) != hipSuccess || bytes > room / 2 ||
+        hipMalloc(p, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+        return false;
+    }
+    ctx->bytes_held += bytes;
+    if (account) *account += bytes;
+    return true;
 }
 
 // Grow-only named workspace buffer owned by the ctx.
@@ -93,21 +139,65 @@ template <typename T>
 sivf_status ws(sivf_ctx* ctx, const char* name, int64_t elems, T** out) {
     size_t bytes = (size_t)std::max<int64_t>(elems, 1) * sizeof(T);
     auto it = ctx->ws.find(name);
-    if (it != ctx->ws.end() && it->second.second >= bytes) {
-        *out = (T*)it->second.first;
+    if (it != ctx->ws.end() && it->second.bytes >= bytes) {
+        *out = (T*)it->second.p;
         return SIVF_OK;
     }
     if (it != ctx->ws.end()) {
         HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-        dev_free(ctx, it->second.first, it->second.second, nullptr);
+        dev_free(ctx, it->second.p, it->second.bytes, nullptr);
         ctx->ws.erase(it);
     }
     size_t grow = bytes + bytes / 8;
     void* p = nullptr;
     STCHK(dev_alloc(ctx, &p, grow, nullptr));
-    ctx->ws[name] = {p, grow};
+    ctx->ws[name] = {p, grow, false};
     *out = (T*)p;
     return SIVF_OK;
+}
+
+// Named buffers of a faster form: all of them, or none (the ctx then holds none
+// of them).  To be asked for after everything the call cannot do without; later
+// calls give them back where they need the room.
+struct Optional {
+    const char* name;
+    size_t bytes;
+    void** p;
+};
+
+bool ws_optional(sivf_ctx* ctx, std::initializer_list<Optional> list) {
+    auto granted = [](size_t bytes) { return bytes + bytes / 8 + 8; };
+    size_t more = 0, room = 0, all = 0;
+    for (const Optional& q : list) {
+        auto it = ctx->ws.find(q.name);
+        if (it != ctx->ws.end() && it->second.bytes >= q.bytes) *q.p = it->second.p;
+        else more += granted(q.bytes);
+    }
+    if (more == 0) return true;
+    bool ok = hipStreamSynchronize(ctx->stream) == hipSuccess;
+    auto drop = [&](bool whole) {
+        for (const Optional& q : list) {
+            auto it = ctx->ws.find(q.name);
+            if (it == ctx->ws.end() || (!whole && it->second.bytes >= q.bytes)) continue;
+            dev_free(ctx, it->second.p, it->second.bytes, nullptr);
+            ctx->ws.erase(it);
+        }
+    };
+    if (ok) drop(false);
+    // together at most half of what is free (each is then at most half of what is left)
+    ok = ok && hipMemGetInfo(&room, &all) == hipSuccess && more <= room / 2;
+    for (const Optional& q : list) {
+        if (!ok) break;
+        if (ctx->ws.count(q.name)) continue;
+        ok = optional_alloc(ctx, q.p, granted(q.bytes), nullptr);
+        if (ok) ctx->ws[q.name] = {*q.p, granted(q.bytes), true};
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        drop(true);
+        for (const Optional& q : list) *q.p = nullptr;
+    }
+    return ok;
 }
 
 // The same, cleared when it is allocated (all of it: a later, larger request
@@ -116,12 +206,12 @@ template <typename T>
 sivf_status ws_zeroed(sivf_ctx* ctx, const char* name, int64_t elems, T** out) {
     static_assert(sizeof(T) == 8, "cleared by 8-byte words");
     auto it = ctx->ws.find(name);
-    void* before = it == ctx->ws.end() ? nullptr : it->second.first;
-    const size_t size = it == ctx->ws.end() ? 0 : it->second.second;
+    void* before = it == ctx->ws.end() ? nullptr : it->second.p;
+    const size_t size = it == ctx->ws.end() ? 0 : it->second.bytes;
     STCHK(ws(ctx, name, elems, out));
     const auto& got = ctx->ws[name];
-    if (got.first != before || got.second != size)
-        HIPCHK(ctx, fill_u64((unsigned long long*)got.first, 0ull, (int64_t)(got.second / 8), ctx->stream));
+    if (got.p != before || got.bytes != size)
+        HIPCHK(ctx, fill_u64((unsigned long long*)got.p, 0ull, (int64_t)(got.bytes / 8), ctx->stream));
     return SIVF_OK;
 }
 
@@ -451,7 +541,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
         std::max<int64_t>(1, (int64_t)std::ceil(kSplitDensity * (double)ctx->opt.head_density * f->k));
     HIPCHK(ctx, ivf_offsets(f->d, f->T, w, min_len, f->seg, f->mid, f->head, hterm, split_len, f->tlen, f->srow, sterm,
                             meta, ctx->stream));
-    const bool split = X && f->srow && X->n > 0 && X->nnz > 0;
+    const bool split = X && f->srow && split_possible(ctx->opt) && X->n > 0 && X->nnz > 0;
     if (split) HIPCHK(ctx, split_sample(X->col, X->nnz, f->srow, meta, ctx->stream));
     int64_t* h = (int64_t*)ctx->pin;
     HIPCHK(ctx, hipMemcpyAsync(h, meta, kMeta * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
@@ -469,15 +559,17 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     f->srows = 0;
     f->sfrac = split && h[6] > 0 ? (double)h[5] / (double)h[6] : 0.0;
     const int64_t kpad = (int64_t)f->T * head_ktp(f->kt), esz = f->pdt == SIVF_BF16 ? 2 : 4;
-    // room for n rows in one of the two row buffers (cap: in values)
-    auto rows_reserve = [&](void** buf, int64_t* cap, int64_t n) -> sivf_status {
+    // room for n rows in one of the two row buffers (cap: in values); the sliced
+    // rows are optional
+    auto rows_reserve = [&](void** buf, int64_t* cap, int64_t n, bool optional) -> sivf_status {
         if (n * kpad <= *cap) return SIVF_OK;
         HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
         dev_free(ctx, *buf, (size_t)(*cap * esz), &f->bytes);
         *buf = nullptr;
         *cap = 0;
         const int64_t c = std::min<int64_t>(n + n / 8 + 16, std::min<int64_t>(f->d, kHeadMaxBytes / (kpad * esz))) * kpad;
-        STCHK(dev_alloc(ctx, buf, (size_t)(c * esz), &f->bytes));
+        if (!optional) STCHK(dev_alloc(ctx, buf, (size_t)(c * esz), &f->bytes));
+        else if (!optional_alloc(ctx, buf, (size_t)(c * esz), &f->bytes)) return SIVF_E_NOMEM;
         *cap = c;
         return SIVF_OK;
     };
@@ -488,17 +580,18 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
             return fail(ctx, SIVF_E_UNSUPPORTED,
                         "dense head rows would take %lld bytes (%lld rows), above %lld; raise head_density",
                         (long long)(H * kpad * esz), (long long)H, (long long)kHeadMaxBytes);
-        STCHK(rows_reserve(&f->hval, &f->hcap, H));
+        STCHK(rows_reserve(&f->hval, &f->hcap, H, false));
         HIPCHK(ctx, head_fill(hterm, f->seg, f->cid, f->v32, f->v16, f->T, head_ktp(f->kt), H, f->hval, ctx->stream));
         f->H = H;
     }
     HIPCHK(ctx, seg_records(f->seg, f->mid, f->H > 0 ? f->head : nullptr, f->d, f->T, f->rec, ctx->stream));
     // sliced rows, if a split walk pays and there is room for them
+    // (the last requests of an update: they are optional)
     uint32_t* wt = nullptr;
     int32_t* sterm2 = nullptr;
     if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
-        rows_reserve(&f->sval, &f->scap, SH) == SIVF_OK && ws(ctx, "split_wt", SH, &wt) == SIVF_OK &&
-        ws(ctx, "split_term2", SH, &sterm2) == SIVF_OK) {
+        rows_reserve(&f->sval, &f->scap, SH, true) == SIVF_OK &&
+        ws_optional(ctx, {{"split_wt", (size_t)SH * 4, (void**)&wt}, {"split_term2", (size_t)SH * 4, (void**)&sterm2}})) {
         HIPCHK(ctx, split_order(sterm, f->seg, f->T, f->v32, SH, wt, sterm2, f->srow, meta, ctx->stream));
         HIPCHK(ctx, split_fill(sterm2, f->seg, f->cid, f->v32, f->T, head_ktp(f->kt), SH, f->sval, ctx->stream));
         f->srows = SH;
@@ -611,11 +704,10 @@ struct AssignBufs {
     float* S = nullptr;
 };
 
-// Decide whether the walk of Xc against f is split, and reserve what that needs.
+// Decide whether the walk of Xc against f is split, and into which ranges.
 // A range's sums take at most 4 GiB (2,000,000 objects, k = 10,000: 210 ms;
-// with 1 GiB 215, with 256 MiB 270, its launches being short then).  Without
-// the memory the walk is not split.
-sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, AssignBufs* b) {
+// with 1 GiB 215, with 256 MiB 270, its launches being short then).
+sivf_status split_plan(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f, AssignBufs* b) {
     b->range = 0;
     b->ranges = 1;
     if (w.mode != Work::kCtx || !split_possible(ctx->opt) || f->srows == 0 || Xc.n == 0) return SIVF_OK;
@@ -644,14 +736,25 @@ sivf_status split_setup(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
         },
         &pairs);
     if (st != SIVF_OK || range == 0) return st;
-    if (w.get("split_ent", pairs, &b->ent) != SIVF_OK || w.get("split_hdr", range, &b->hdr) != SIVF_OK ||
-        w.get("split_ghdr", range, &b->ghdr) != SIVF_OK || w.get("split_place", range, &b->place) != SIVF_OK ||
-        w.get("split_S", range * ktp, &b->S) != SIVF_OK)
-        return SIVF_OK;
     b->npairs = pairs;
     b->range = range;
     b->ranges = (Xc.n + range - 1) / range;
     return SIVF_OK;
+}
+
+// What a split walk needs besides assign_buffers', asked for after those.
+// Without the memory the walk is not split.
+void split_reserve(sivf_ctx* ctx, const sivf_ivf* f, AssignBufs* b) {
+    if (!b->range) return;
+    const size_t r = (size_t)b->range;
+    if (ws_optional(ctx, {{"split_ent", (size_t)b->npairs * sizeof(uint2), (void**)&b->ent},
+                          {"split_hdr", r * sizeof(uint2), (void**)&b->hdr},
+                          {"split_ghdr", r * sizeof(uint2), (void**)&b->ghdr},
+                          {"split_place", r * sizeof(int32_t), (void**)&b->place},
+                          {"split_S", r * head_ktp(f->kt) * sizeof(float), (void**)&b->S}}))
+        return;
+    b->range = 0;
+    b->ranges = 1;
 }
 
 sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, const sivf_ivf* f, AssignBufs* b) {
@@ -673,7 +776,9 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, const sivf_ivf* f,
     STCHK(w.get("obj_partial", b->nfin + 1, &b->obj_partial));
     b->obj = (double*)(b->counters + 12);   // read back with the counters
     if (ctx->opt.exact_objective) STCHK(w.get("obj64_partial", b->nobj, &b->obj64_partial));
-    const int64_t m = std::max<int64_t>(b->range ? b->range : n, 1);
+    // (for all objects, also where ranges of them would do: the walk may yet turn
+    // out not to be split)
+    const int64_t m = std::max<int64_t>(n, 1);
     if (b->launches > 1) {
         STCHK(w.get("st_theta", m, &b->st_theta));
         STCHK(w.get("st_best", m, &b->st_best));
@@ -683,8 +788,8 @@ sivf_status assign_buffers(sivf_ctx* ctx, Work& w, int64_t n, const sivf_ivf* f,
         STCHK(w.get("st_cr", m * kCandCap, &b->st_cr));
     }
     if (relaxed) {
-        STCHK(w.get("own64_cur", std::max<int64_t>(n, 1), &b->own64_cur));
-        STCHK(w.get("own64_queue", std::max<int64_t>(n, 1), &b->own64_queue));
+        STCHK(w.get("own64_cur", m, &b->own64_cur));
+        STCHK(w.get("own64_queue", m, &b->own64_queue));
         if (b->launches > 1) STCHK(w.get("st_rel", m, &b->st_rel));
     }
     return SIVF_OK;
@@ -713,8 +818,9 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     const int relaxed = ctx->opt.filter_mode == SIVF_MODE_RELAXED;
     const int icp_on = iter >= 2 && ctx->opt.filter_mode != SIVF_MODE_IVF;
     AssignBufs B;
-    STCHK(split_setup(ctx, w, Xc, f, &B));
+    STCHK(split_plan(ctx, w, Xc, f, &B));
     STCHK(assign_buffers(ctx, w, n, f, &B));
+    split_reserve(ctx, f, &B);
     const int64_t qcap = B.qcap;
     unsigned long long* counters = B.counters;
     int32_t *a_new = B.a_new, *qobj = B.qobj, *qcand = B.qcand, *qcnt = B.qcnt, *fobj = B.fobj;
@@ -861,6 +967,11 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     const int64_t n = Xc.n;
     const int32_t k = f->k;
     hipStream_t s = ctx->stream;
+    struct Updating {
+        sivf_ctx* ctx;
+        Updating(sivf_ctx* c, sivf_ivf* f) : ctx(c) { ctx->updating = f; }
+        ~Updating() { ctx->updating = nullptr; }
+    } updating(ctx, f);
     UpdateWs w{};
     w.nslots = upd_fold_groups(ctx->n_cu);
     STCHK(ws(ctx, "u_ccount", k, &w.ccount));
@@ -979,7 +1090,7 @@ sivf_status sivf_destroy(sivf_ctx* ctx) {
     if (!ctx) return SIVF_OK;
     DevGuard g(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    for (auto& kv : ctx->ws) (void)hipFree(kv.second.first);
+    for (auto& kv : ctx->ws) (void)hipFree(kv.second.p);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
     if (ctx->pin) (void)hipHostFree(ctx->pin);
@@ -1233,24 +1344,27 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     SoftFwdWs w{};
     // rows per launch: the per-block partials of one launch take at most 512 MiB
     w.rows = std::max<int64_t>(1, std::min<int64_t>(Xc.n, (int64_t)(64ll << 20) / nblk));
-    // the commonest terms in LDS: fewer rows per launch; without a workspace cap,
-    // and only if there is memory
-    const int64_t lds_rows = ctx->opt.workspace_cap_bytes == 0 ? soft_lds_rows(Xc.n, Xc.nnz, Xc.d, k) : 0;
-    if (lds_rows > 0) {
-        const int64_t rows = std::min(lds_rows, w.rows);
-        w.nnz = Xc.nnz;
-        if (ws(ctx, "soft_hdr", rows, &w.hdr) == SIVF_OK && ws(ctx, "soft_count", Xc.d, &w.count) == SIVF_OK &&
-            ws(ctx, "soft_slot", Xc.d, &w.slot) == SIVF_OK && ws(ctx, "soft_hot", kSplitHot + 1, &w.term) == SIVF_OK &&
-            ws(ctx, "soft_ent", split_pairs(Xc.nnz, rows), &w.ent) == SIVF_OK) {
-            w.nhot = w.term + kSplitHot;
-            w.rows = rows;
-        }
-    }
     STCHK(ws(ctx, "soft_CT", nblk * kSoftBlk * Xc.d, &CT));
     STCHK(ws(ctx, "soft_loss", 1, &loss));
     STCHK(ws(ctx, "soft_pmax", w.rows * nblk, &w.pmax));
     STCHK(ws(ctx, "soft_psum", w.rows * nblk, &w.psum));
-    STCHK(ws(ctx, "soft_part", Xc.n / 256 + Xc.n / w.rows + 2, &w.part));
+    // the commonest terms in LDS: fewer rows per launch; without a workspace cap,
+    // and only if there is memory
+    const int64_t lds_rows =
+        ctx->opt.workspace_cap_bytes == 0 ? std::min(soft_lds_rows(Xc.n, Xc.nnz, Xc.d, k), w.rows) : 0;
+    const int64_t least = lds_rows > 0 ? lds_rows : w.rows;
+    STCHK(ws(ctx, "soft_part", Xc.n / 256 + Xc.n / least + 2, &w.part));
+    const size_t dd = (size_t)Xc.d;
+    if (lds_rows > 0 &&
+        ws_optional(ctx, {{"soft_hdr", lds_rows * sizeof(uint2), (void**)&w.hdr},
+                          {"soft_count", dd * 4, (void**)&w.count},
+                          {"soft_slot", dd * 4, (void**)&w.slot},
+                          {"soft_hot", (kSplitHot + 1) * 4, (void**)&w.term},
+                          {"soft_ent", (size_t)split_pairs(Xc.nnz, lds_rows) * sizeof(uint2), (void**)&w.ent}})) {
+        w.nnz = Xc.nnz;
+        w.nhot = w.term + kSplitHot;
+        w.rows = lds_rows;
+    }
     hipStream_t s = ctx->stream;
     HIPCHK(ctx, soft_pack(C, CT, k, Xc.d, s));
     HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, CT, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
@@ -1342,12 +1456,15 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
         // the densest terms by matrix products: without a workspace cap, and only
         // if there is memory
         if (ctx->opt.workspace_cap_bytes == 0 && n > 0 && Xc.nnz * (int64_t)k >= kSoftProdWork) {
-            const int64_t room = dct_cands(Xc.nnz, n);
+            const size_t room = (size_t)dct_cands(Xc.nnz, n);
             dw.nnz = Xc.nnz;
-            if (ws(ctx, "dct_prod", dct_prod_elems(rc, k), &dw.prod) == SIVF_OK && ws(ctx, "dct_slot", d, &dw.slot) == SIVF_OK &&
-                ws(ctx, "dct_term", kDctDense, &dw.term) == SIVF_OK && ws(ctx, "dct_cand", room, &dw.cand) == SIVF_OK &&
-                ws(ctx, "dct_cand_df", room, &dw.cand_df) == SIVF_OK && ws(ctx, "dct_ndense", 2, &dw.ndense) == SIVF_OK &&
-                ws(ctx, "dct_xd", rc * kDctDense, &dw.xd) == SIVF_OK) {
+            if (ws_optional(ctx, {{"dct_prod", (size_t)dct_prod_elems(rc, k) * 4, (void**)&dw.prod},
+                                  {"dct_slot", (size_t)d * 4, (void**)&dw.slot},
+                                  {"dct_term", kDctDense * 4, (void**)&dw.term},
+                                  {"dct_cand", room * 4, (void**)&dw.cand},
+                                  {"dct_cand_df", room * 4, (void**)&dw.cand_df},
+                                  {"dct_ndense", 2 * 8, (void**)&dw.ndense},
+                                  {"dct_xd", (size_t)rc * kDctDense * 4, (void**)&dw.xd}})) {
                 HIPCHK(ctx, fill_u64(dw.ndense, 0ull, 2, s));
                 HIPCHK(ctx, dct_pick(n, d, colptr, dw, s));
             }

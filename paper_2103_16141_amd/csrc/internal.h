@@ -170,6 +170,14 @@ struct sivf_ivf {
     size_t bytes = 0;               // device bytes held (counted against the ctx cap)
 };
 
+namespace sivf {
+struct WsBuf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    bool optional = false;   // of a faster form: may be given back between calls
+};
+}  // namespace sivf
+
 struct sivf_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -177,7 +185,8 @@ struct sivf_ctx {
     std::string err;
     int n_cu = 256;
     size_t bytes_held = 0;
-    std::map<std::string, std::pair<void*, size_t>> ws;  // grow-only named workspace
+    std::map<std::string, sivf::WsBuf> ws;  // grow-only named workspace
+    sivf_ivf* updating = nullptr;           // the file an update holds, during it
     hipEvent_t ev[8] = {};
     void* pin = nullptr;   // kPinBytes of pinned host memory the calls read results through
 };

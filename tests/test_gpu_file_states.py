@@ -124,3 +124,58 @@ def test_no_nonzero_past_the_last_row_bound_is_read(dtype, rows):
     s.nnz = c.nnz - 1
     assert N.load().sivf_validate_csr(ctx.handle, ctypes.byref(s)) == -3
     ctx.validate(X)
+
+
+def test_buffers_of_faster_forms_leave_room_for_what_calls_need():
+    # 2,100,000 of 2,200,001 objects at a time, 512 slots each: the split walk
+    # asks for about 7 GB.  With 10 GB free that is more than half: the walk is
+    # not split, and nothing is said.  Held from an earlier call, they are given
+    # back when a call that needs 3.4 GB finds 2.5 GB free
+    from paper_2103_16141_amd import _native as N
+    from paper_2103_16141_amd.api import DeviceCsr
+    from tests.test_gpu_kernel_edges import _striped
+    log("optional buffers on a full device")
+    n, d, lam, k = 2_200_001, 1_120, 80, 12
+    X = _striped(n, d, lam, 5, torch.float32)
+    ids = np.arange(k, dtype=np.int32) * 1_000
+    wide = 12_000_000   # columns of a matrix of two rows: 64 of them are 3.1 GB
+    rp = torch.tensor([0, 2, 3], device=device())
+    col = torch.tensor([5, wide - 1, 7], dtype=torch.int32, device=device())
+    Y = DeviceCsr(rp, col, torch.tensor([0.6, 0.8, 1.0], device=device()), wide)
+    C = torch.zeros(1, wide, device=device())
+    C[0, 5], C[0, 7], C[0, wide - 1] = 1.0, 0.25, 0.5
+
+    def step(ctx):
+        f = ctx.init_centroids(X, k, ids)
+        a, own, l = _state(n, k)
+        ctx.assign(X, f, 1, a, own, l)
+        ctx.update(X, a, l, f)
+        st = ctx.assign(X, f, 1, a, own, l)   # (iter 1: no state needed)
+        return f, a, st
+
+    def fill(left):
+        torch.cuda.empty_cache()
+        free, _ = torch.cuda.mem_get_info()
+        return torch.empty(free - left, dtype=torch.uint8, device=device())
+
+    holder, plain, late = _ctx(head_density=0.02), _ctx(head_density=0.02, workspace_cap_bytes=1 << 40), \
+        _ctx(head_density=0.02)
+    f0, a0, s0 = step(holder)
+    f1, a1, s1 = step(plain)
+    assert torch.equal(a0, a1) and s0["walk_bytes"] != s1["walk_bytes"]
+    plain.soft_assign_fwd(Y, C, 0.05)   # its kernels are loaded
+    plain.close()
+    hog = fill(10 << 30)
+    f2, a2, s2 = step(late)
+    assert torch.equal(a2, a0) and s2["walk_bytes"] == s1["walk_bytes"]
+    assert N.load().sivf_last_error(late.handle) == b""
+    late.close()
+    del hog
+    hog = fill(5 << 29)
+    lse, _ = holder.soft_assign_fwd(Y, C, 0.05)
+    # one centroid: the log of the sum is its similarity / tau (two products and one sum in FP32)
+    assert float((lse.double() * 0.05 - torch.tensor([1.0, 0.25], device=device())).abs().max()) < 4 * 2.0 ** -24
+    del hog
+    torch.cuda.empty_cache()
+    a, own, l = _state(n, k)
+    assert holder.assign(X, f0, 1, a, own, l)["walk_bytes"] == s0["walk_bytes"] and torch.equal(a, a0)

@@ -323,11 +323,14 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
  *   dX_it = sum_j dS_ij C_jt on X's nonzeros -> dxval_out f32[nnz] (overwritten).
  * Either output may be NULL.  Deterministic (fixed summation order).
  * Workspace held by the ctx: C^T and dC^T (k rounded up to 64 times d floats
- * each), X's column copy (24 B per nonzero and 1 B of counts), dS for one chunk
- * of rows (at most 512 MiB), dX partials (4 B per nonzero of a chunk and 64
- * columns), the dC pass's partial rows (k floats per 256 nonzeros of a chunk)
+ * each), X's column copy (24 B per nonzero and 2 B of counts), dS for one chunk
+ * of rows (at most 512 MiB), dX partials and dC's partial rows (4 B and 1 B per
+ * nonzero of a chunk and 64 columns: columns are taken in groups where that
+ * passes 2 GiB)
  * and, in larger calls without a workspace cap, its densest terms' products (up
- * to 100 MB). */
+ * to 100 MB).  Where a request fails, less is held at a time: down to 64 columns
+ * and the column copy of a chunk (31 B per nonzero of a chunk, 556 B per term),
+ * then fewer rows a chunk; dX is the same, dC up to where its sums are cut. */
 sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* C, int32_t k,
                                  float tau, const float* lse, float grad_loss, float* dC_out,
                                  float* dxval_out);

@@ -200,6 +200,17 @@ bool ws_optional(sivf_ctx* ctx, std::initializer_list<Optional> list) {
     return ok;
 }
 
+// Frees the named buffers whose names begin so.
+void ws_drop(sivf_ctx* ctx, std::initializer_list<const char*> prefixes) {
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return;
+    for (auto it = ctx->ws.begin(); it != ctx->ws.end();) {
+        bool drop = false;
+        for (const char* q : prefixes) drop = drop || it->first.compare(0, strlen(q), q) == 0;
+        if (drop) dev_free(ctx, it->second.p, it->second.bytes, nullptr);
+        it = drop ? ctx->ws.erase(it) : std::next(it);
+    }
+}
+
 // The same, cleared when it is allocated (all of it: a later, larger request
 // may fit what was granted).
 template <typename T>
@@ -803,6 +814,133 @@ sivf_status validate_with_ids(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* 
     return validate(ctx, X, out, w, {{ids, X->n_rows, f->k, what}});
 }
 
+// ---------------------------------------------------------------- soft backward
+struct SoftBwd {
+    SoftPlan p{};
+    std::vector<int64_t> offs;   // first nonzero of each chunk of rows, and the end
+    int64_t nnz_max = 0;
+    float *CT = nullptr, *dS = nullptr, *dxp = nullptr, *dCT = nullptr;
+    int64_t* colptr = nullptr;
+    SortWs<float> sort{};
+    DctWs dct{};
+};
+
+// The attempt-th plan of a backward of Xc against k centroids and its memory.
+sivf_status soft_bwd_reserve(sivf_ctx* ctx, const Csr& Xc, int32_t k, int attempt, bool want_dC, bool want_dx, SoftBwd* b) {
+    const int64_t n = Xc.n, d = Xc.d, nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk;
+    hipStream_t s = ctx->stream;
+    SoftPlan& p = b->p;
+    if (!soft_bwd_plan(attempt, n, Xc.nnz, d, nblk, &p)) return fail(ctx, SIVF_E_NOMEM, "no memory for one row");
+    // nonzero offsets of the row chunks
+    int64_t nch = 0;
+    for (;; p.rows = (p.rows + 1) / 2) {
+        nch = std::max<int64_t>(1, (n + p.rows - 1) / p.rows);
+        b->offs.assign((size_t)nch + 1, 0);
+        b->offs[(size_t)nch] = Xc.nnz;
+        if (nch > 1) {
+            int64_t* offs = nullptr;
+            STCHK(ws(ctx, "soft_offs", nch + 1, &offs));
+            HIPCHK(ctx, soft_chunk_offsets(Xc.rp, n, p.rows, nch, offs, s));
+            HIPCHK(ctx, hipMemcpyAsync(b->offs.data(), offs, (size_t)(nch + 1) * 8, hipMemcpyDeviceToHost, s));
+            HIPCHK(ctx, hipStreamSynchronize(s));
+        }
+        b->nnz_max = 0;
+        for (size_t j = 0; j < (size_t)nch; ++j) b->nnz_max = std::max(b->nnz_max, b->offs[j + 1] - b->offs[j]);
+        if (b->nnz_max <= kSoftChunkNnz || p.rows == 1) break;
+    }
+    p.blocks = soft_bwd_blocks(p.blocks, b->nnz_max);
+    const int64_t kp = p.blocks * kSoftBlk, groups = (nblk + p.blocks - 1) / p.blocks;
+    STCHK(ws(ctx, "soft_CT", kp * d, &b->CT));
+    if (want_dx && nblk > 1) STCHK(ws(ctx, "soft_dxp", b->nnz_max * p.blocks, &b->dxp));
+    if (!want_dC) return SIVF_OK;
+    DctWs& w = b->dct;
+    STCHK(ws(ctx, "soft_dS", p.rows * kp, &b->dS));
+    STCHK(ws(ctx, "soft_dCT", kp * d, &b->dCT));
+    STCHK(sort_ws(ctx, "soft", p.whole ? Xc.nnz : b->nnz_max, true, &b->sort));
+    STCHK(ws(ctx, "csc_ptr", d + 1, &b->colptr));
+    // a range of more than kSoftPiece entries has less than one piece per
+    // kSoftPiece / 2 entries
+    w.max_pieces = b->nnz_max / (kSoftPiece / 2);
+    STCHK(ws(ctx, "dct_next", d, &w.next));
+    STCHK(ws(ctx, "dct_lo", d, &w.lo));
+    STCHK(ws(ctx, "dct_len", d, &w.len));
+    STCHK(ws(ctx, "dct_mid", d, &w.mid));
+    STCHK(ws(ctx, "dct_longt", d, &w.longt));
+    STCHK(ws(ctx, "dct_longp", d, &w.longp));
+    STCHK(ws(ctx, "dct_piece", w.max_pieces, &w.piece));
+    STCHK(ws(ctx, "dct_piece_len", w.max_pieces, &w.piece_len));
+    STCHK(ws(ctx, "dct_part", w.max_pieces * kp, &w.part));
+    STCHK(ws(ctx, "dct_count", 4, &w.count));
+    // the densest terms by matrix products: without a workspace cap, and only if
+    // there is memory
+    if (ctx->opt.workspace_cap_bytes == 0 && p.whole && n > 0 && Xc.nnz * (int64_t)k >= kSoftProdWork) {
+        const size_t room = (size_t)dct_cands(Xc.nnz, n);
+        const int64_t last = nblk - (groups - 1) * p.blocks;   // blocks of the last group
+        const size_t prod = (size_t)std::max(dct_prod_elems(p.rows, (int32_t)std::min<int64_t>(k, kp)),
+                                             dct_prod_elems(p.rows, (int32_t)std::min<int64_t>(k, last * kSoftBlk)));
+        w.nnz = Xc.nnz;
+        ws_optional(ctx, {{"dct_prod", prod * 4, (void**)&w.prod},
+                          {"dct_slot", (size_t)d * 4, (void**)&w.slot},
+                          {"dct_term", kDctDense * 4, (void**)&w.term},
+                          {"dct_cand", room * 4, (void**)&w.cand},
+                          {"dct_cand_df", room * 4, (void**)&w.cand_df},
+                          {"dct_ndense", 2 * 8, (void**)&w.ndense},
+                          {"dct_xd", (size_t)p.rows * kDctDense * 4, (void**)&w.xd}});
+    }
+    return SIVF_OK;
+}
+
+sivf_status soft_bwd_run(sivf_ctx* ctx, const Csr& Xc, const float* C, int32_t k, float tau, const float* lse, float grad,
+                         float* dC, float* dX, const SoftBwd& b) {
+    const int64_t n = Xc.n, d = Xc.d, rc = b.p.rows, gk = b.p.blocks * kSoftBlk;
+    hipStream_t s = ctx->stream;
+    const float* xv = (const float*)Xc.val;
+    const int32_t* xt_row = nullptr;
+    const float* xt_val = nullptr;
+    const DctWs& w = b.dct;
+    // the column copy of rows [c0, c1), whose nonzeros are [p0, p1)
+    auto copy = [&](int64_t c0, int64_t c1, int64_t p0, int64_t p1) -> sivf_status {
+        const int32_t* xt_col = nullptr;
+        SortIn<float> in{};
+        in.kind = kSortCsr;
+        in.n = p1 - p0;
+        in.key = Xc.col + p0;
+        in.val = xv + p0;
+        in.rows = c1 - c0;
+        in.rp = Xc.rp + c0;
+        in.p0 = p0;
+        in.row0 = c0;
+        HIPCHK(ctx, sort_entries(in, d, b.sort, &xt_col, &xt_row, &xt_val, s));
+        HIPCHK(ctx, sort_starts(xt_col, in.n, d, b.colptr, s));
+        return SIVF_OK;
+    };
+    if (dC) {
+        if (n == 0) HIPCHK(ctx, fill_i32((int32_t*)dC, 0, (int64_t)k * d, s));
+        if (b.p.whole) STCHK(copy(0, n, 0, Xc.nnz));
+        if (w.xd) {
+            HIPCHK(ctx, fill_u64(w.ndense, 0ull, 2, s));
+            HIPCHK(ctx, dct_pick(n, d, b.colptr, w, s));
+        }
+    }
+    for (int64_t j0 = 0; j0 < k && n > 0; j0 += gk) {   // columns j0 .. j0 + kg - 1
+        const int32_t kg = (int32_t)std::min<int64_t>(gk, k - j0);
+        HIPCHK(ctx, soft_pack(C + j0 * d, b.CT, kg, d, s));
+        for (int64_t c0 = 0, j = 0; c0 < n; c0 += rc, ++j) {
+            const int64_t c1 = std::min(n, c0 + rc), p0 = b.offs[(size_t)j], p1 = b.offs[(size_t)j + 1];
+            HIPCHK(ctx, soft_bwd_rows(c0, c1, p0, p1, Xc.rp, Xc.col, xv, b.CT, d, kg, tau, grad, lse, b.dS, b.dxp, dX,
+                                      j0 > 0, ctx->n_cu, s));
+            if (!dC) continue;
+            HIPCHK(ctx, fill_u64(w.count, 0ull, 4, s));
+            if (!b.p.whole) STCHK(copy(c0, c1, p0, p1));
+            if (w.xd) HIPCHK(ctx, dct_dense_rows(c0, c1, Xc.rp, Xc.col, xv, w, ctx->n_cu, s));
+            HIPCHK(ctx, soft_dct(d, kg, c0, c1, j == 0, j == 0 || !b.p.whole, b.colptr, xt_row, xt_val, b.dS, b.dCT, w,
+                                 ctx->n_cu, s));
+        }
+        if (dC) HIPCHK(ctx, soft_unpack(b.dCT, dC + j0 * d, kg, d, s));
+    }
+    return SIVF_OK;
+}
+
 // The structure of a file whose update failed half way is not there to be read.
 sivf_status check_built(sivf_ctx* ctx, const sivf_ivf* f) {
     if (f->built) return SIVF_OK;
@@ -1388,100 +1526,19 @@ sivf_status sivf_soft_assign_bwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     STCHK(validate(ctx, X, &Xc));
     if (Xc.f64) return fail(ctx, SIVF_E_UNSUPPORTED, "soft assignment takes SIVF_F32 object values");
     if (!dC_out && !dxval_out) return SIVF_OK;
-    const int64_t n = Xc.n, d = Xc.d;
-    hipStream_t s = ctx->stream;
-    const int64_t nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk, kp = nblk * kSoftBlk;
-    float *CT = nullptr, *dS = nullptr, *dxp = nullptr, *dCT = nullptr;
-    STCHK(ws(ctx, "soft_CT", kp * d, &CT));
-    // rows per chunk: 24,576 rows of a 32-column dS block take 3 MB of an XCD's
-    // 4 MB L2; smaller chunks read and write dC more often, larger ones miss L2.
-    // Where a term has few entries in a chunk (below 32 on average), dC costs more
-    // than the misses: backward with 16,384 / 24,576 / 32,768 / 40,960 rows, N =
-    // 262,144, D = 100,000, 100 terms, k = 4,096 (25 entries) 78.6 / 73.2 / 71.0 /
-    // 71.6 ms; N = 97,062, D = 38,883, 177 terms, k = 3,837 (112) - / 46.2 / 47.5 /
-    // 48.9.  dS of a chunk is at most 512 MiB.
-    const int64_t rows = (double)Xc.nnz * 24576.0 < 32.0 * (double)n * (double)d ? 32768 : 24576;
-    const int64_t rc = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), rows, (int64_t)(128ll << 20) / kp}));
-    const int64_t nch = std::max<int64_t>(1, (n + rc - 1) / rc);
-    HIPCHK(ctx, soft_pack(C, CT, k, d, s));
-    // nonzero offsets of the row chunks: they size the per-block dX shares and
-    // the pieces of the dC pass
-    std::vector<int64_t> ho((size_t)nch + 1);
-    ho[(size_t)nch] = Xc.nnz;
-    if (nch > 1) {
-        int64_t* offs = nullptr;
-        STCHK(ws(ctx, "soft_offs", nch + 1, &offs));
-        HIPCHK(ctx, soft_chunk_offsets(Xc.rp, n, rc, nch, offs, s));
-        HIPCHK(ctx, hipMemcpyAsync(ho.data(), offs, (size_t)(nch + 1) * 8, hipMemcpyDeviceToHost, s));
-        HIPCHK(ctx, hipStreamSynchronize(s));
-    }
-    int64_t nnz_max = 0;
-    for (int64_t j = 0; j < nch; ++j) nnz_max = std::max(nnz_max, ho[(size_t)j + 1] - ho[(size_t)j]);
-    if (dxval_out && nblk > 1) STCHK(ws(ctx, "soft_dxp", nnz_max * nblk, &dxp));
-    int64_t* colptr = nullptr;
-    const int32_t* xt_row = nullptr;
-    const float* xt_val = nullptr;
-    DctWs dw{};
-    if (dC_out) {
-        STCHK(ws(ctx, "soft_dS", rc * kp, &dS));
-        STCHK(ws(ctx, "soft_dCT", kp * d, &dCT));
-        SortWs<float> cw{};
-        STCHK(sort_ws(ctx, "soft", Xc.nnz, true, &cw));
-        STCHK(ws(ctx, "csc_ptr", d + 1, &colptr));
-        const int32_t* xt_col = nullptr;
-        SortIn<float> in{};
-        in.kind = kSortCsr;
-        in.n = Xc.nnz;
-        in.key = Xc.col;
-        in.val = (const float*)Xc.val;
-        in.rows = n;
-        in.rp = Xc.rp;
-        HIPCHK(ctx, sort_entries(in, d, cw, &xt_col, &xt_row, &xt_val, s));
-        HIPCHK(ctx, sort_starts(xt_col, Xc.nnz, d, colptr, s));
-        // a range of more than kSoftPiece entries has less than one piece per
-        // kSoftPiece / 2 entries
-        dw.max_pieces = nnz_max / (kSoftPiece / 2);
-        STCHK(ws(ctx, "dct_next", d, &dw.next));
-        STCHK(ws(ctx, "dct_lo", d, &dw.lo));
-        STCHK(ws(ctx, "dct_len", d, &dw.len));
-        STCHK(ws(ctx, "dct_mid", d, &dw.mid));
-        STCHK(ws(ctx, "dct_longt", d, &dw.longt));
-        STCHK(ws(ctx, "dct_longp", d, &dw.longp));
-        STCHK(ws(ctx, "dct_piece", dw.max_pieces, &dw.piece));
-        STCHK(ws(ctx, "dct_piece_len", dw.max_pieces, &dw.piece_len));
-        STCHK(ws(ctx, "dct_part", dw.max_pieces * kp, &dw.part));
-        STCHK(ws(ctx, "dct_count", nch * 4, &dw.count));
-        HIPCHK(ctx, fill_u64(dw.count, 0ull, nch * 4, s));
-        if (n == 0) HIPCHK(ctx, fill_i32((int32_t*)dC_out, 0, (int64_t)k * d, s));
-        // the densest terms by matrix products: without a workspace cap, and only
-        // if there is memory
-        if (ctx->opt.workspace_cap_bytes == 0 && n > 0 && Xc.nnz * (int64_t)k >= kSoftProdWork) {
-            const size_t room = (size_t)dct_cands(Xc.nnz, n);
-            dw.nnz = Xc.nnz;
-            if (ws_optional(ctx, {{"dct_prod", (size_t)dct_prod_elems(rc, k) * 4, (void**)&dw.prod},
-                                  {"dct_slot", (size_t)d * 4, (void**)&dw.slot},
-                                  {"dct_term", kDctDense * 4, (void**)&dw.term},
-                                  {"dct_cand", room * 4, (void**)&dw.cand},
-                                  {"dct_cand_df", room * 4, (void**)&dw.cand_df},
-                                  {"dct_ndense", 2 * 8, (void**)&dw.ndense},
-                                  {"dct_xd", (size_t)rc * kDctDense * 4, (void**)&dw.xd}})) {
-                HIPCHK(ctx, fill_u64(dw.ndense, 0ull, 2, s));
-                HIPCHK(ctx, dct_pick(n, d, colptr, dw, s));
-            }
+    const std::string err = ctx->err;
+    for (int attempt = 0;; ++attempt) {
+        SoftBwd b;
+        const sivf_status st = soft_bwd_reserve(ctx, Xc, k, attempt, dC_out != nullptr, dxval_out != nullptr, &b);
+        if (st == SIVF_OK) {
+            ctx->err = err;
+            return soft_bwd_run(ctx, Xc, C, k, tau, lse, grad_loss, dC_out, dxval_out, b);
         }
+        if (st != SIVF_E_NOMEM) return st;
+        ws_drop(ctx, {"soft_", "csc_", "dct_"});   // for the next plan, or for other calls
+        SoftPlan next;
+        if (!soft_bwd_plan(attempt + 1, Xc.n, Xc.nnz, Xc.d, ((int64_t)k + kSoftBlk - 1) / kSoftBlk, &next)) return st;
     }
-    for (int64_t c0 = 0, j = 0; c0 < n; c0 += rc, ++j) {
-        const int64_t c1 = std::min(n, c0 + rc);
-        HIPCHK(ctx, soft_bwd_rows(c0, c1, ho[(size_t)j], ho[(size_t)j + 1], Xc.rp, Xc.col, (const float*)Xc.val, CT, d, k,
-                                  tau, grad_loss, lse, dS, dxp, dxval_out, ctx->n_cu, s));
-        if (dC_out) {
-            if (dw.xd) HIPCHK(ctx, dct_dense_rows(c0, c1, Xc.rp, Xc.col, (const float*)Xc.val, dw, ctx->n_cu, s));
-            HIPCHK(ctx, soft_dct(d, k, c0, c1, j == 0, colptr, xt_row, xt_val, dS, dCT, dw, ctx->n_cu, s));
-            dw.count += 4;
-        }
-    }
-    if (dC_out && n > 0) HIPCHK(ctx, soft_unpack(dCT, dC_out, k, d, s));
-    return SIVF_OK;
 }
 
 }  // extern "C"

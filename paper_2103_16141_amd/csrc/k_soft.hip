@@ -654,22 +654,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-// dxv[p] = sum over the blocks, in order, of dxp[b][p]
-__global__ void k_soft_dx_combine(int64_t pn, int64_t nblk, const float* __restrict__ dxp, float* __restrict__ dxv) {
+// dxv[p] = (add ? dxv[p] : 0) + sum over the blocks, in order, of dxp[b][p]
+__global__ void k_soft_dx_combine(int64_t pn, int64_t nblk, bool add, const float* __restrict__ dxp,
+                                  float* __restrict__ dxv) {
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (p >= pn) return;
-    float a = dxp[p];
+    float a = add ? dxv[p] + dxp[p] : dxp[p];
     for (int64_t b = 1; b < nblk; ++b) a = a + dxp[b * pn + p];
     dxv[p] = a;
 }
 
 hipError_t soft_bwd_rows(int64_t c0, int64_t c1, int64_t p0, int64_t p1, const int64_t* rp, const int32_t* col,
                          const float* xv, const float* CT, int64_t d, int32_t k, float tau, float grad,
-                         const float* lse, float* dS, float* dxp, float* dxv, int n_cu, hipStream_t s) {
+                         const float* lse, float* dS, float* dxp, float* dxv, bool add, int n_cu, hipStream_t s) {
     if (c1 <= c0) return hipSuccess;
     const int64_t nblk = ((int64_t)k + kBlk - 1) / kBlk, pn = p1 - p0;
-    // with one block its share is dX itself
-    float* dx = !dxv ? nullptr : nblk == 1 ? dxv + p0 : dxp;
+    // where there is one block in all, its share is dX itself
+    float* dx = !dxv ? nullptr : dxp ? dxp : dxv + p0;
     const bool narrow = narrow_offsets(d);
     const void* fn = narrow ? (const void*)k_soft_bwd_rows<uint32_t> : (const void*)k_soft_bwd_rows<uint64_t>;
     const unsigned grid = share_grid(fn, c1 - c0, nblk, 256, n_cu);
@@ -679,8 +680,8 @@ hipError_t soft_bwd_rows(int64_t c0, int64_t c1, int64_t p0, int64_t p1, const i
     else
         hipLaunchKernelGGL(k_soft_bwd_rows<uint64_t>, dim3(grid), dim3(256), 0, s, c0, c1, p0, pn, rp, col, xv, CT, d,
                            k, 1.0f / tau, -grad / tau, lse, dS, dx);
-    if (dxv && nblk > 1 && pn > 0)
-        hipLaunchKernelGGL(k_soft_dx_combine, dim3((unsigned)((pn + 255) / 256)), dim3(256), 0, s, pn, nblk, dxp,
+    if (dxv && dxp && pn > 0)
+        hipLaunchKernelGGL(k_soft_dx_combine, dim3((unsigned)((pn + 255) / 256)), dim3(256), 0, s, pn, nblk, add, dxp,
                            dxv + p0);
     return hipGetLastError();
 }
@@ -729,12 +730,12 @@ __device__ inline int64_t row_lower_bound(const int32_t* __restrict__ xt_row, in
 // The ranges of every term in the chunk ending at row c1 (`next` remembers
 // where the previous chunk ended) and the lists of the longer ones.  List
 // positions come from atomics: any order gives the same sums.
-__global__ void k_dct_plan(int64_t d, int64_t c1, int first, const int64_t* __restrict__ colptr,
+__global__ void k_dct_plan(int64_t d, int64_t c1, int fresh, const int64_t* __restrict__ colptr,
                            const int32_t* __restrict__ xt_row, DctWs w) {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     int64_t lo = 0, len = 0;
     if (t < d) {
-        lo = first ? colptr[t] : w.next[t];
+        lo = fresh ? colptr[t] : w.next[t];
         const int64_t end = colptr[t + 1];
         // most ranges are short: a few steps forward before the search
         int64_t hi = lo;
@@ -1096,14 +1097,14 @@ __global__ __launch_bounds__(256) void k_dct_dense_add(int64_t d, int nsb, int n
     *out = make_float4(o.x + a.x, o.y + a.y, o.z + a.z, o.w + a.w);
 }
 
-hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, const int64_t* colptr,
+hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, int fresh, const int64_t* colptr,
                     const int32_t* xt_row, const float* xt_val, const float* dS, float* dCT, DctWs w, int n_cu,
                     hipStream_t s) {
     const int64_t nsb = ((int64_t)k + kSub - 1) / kSub, n = c1 - c0;
     const ProdCut cut = prod_cut(n, k);
     const int nsb2 = 2 * cut.cgroups;   // dS and dCT have an even number of blocks
     if (w.xd) hipLaunchKernelGGL(k_dct_dense, dim3((unsigned)(cut.splits * cut.cgroups)), dim3(256), 0, s, (int)n, nsb2, cut, dS, w);
-    hipLaunchKernelGGL(k_dct_plan, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, d, c1, first, colptr, xt_row, w);
+    hipLaunchKernelGGL(k_dct_plan, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, d, c1, fresh, colptr, xt_row, w);
     const unsigned gt = share_grid((const void*)k_dct_tiny, (d + 7) / 8, nsb, 256, n_cu);
     const unsigned gw = share_grid((const void*)k_dct_wave, d, nsb, 256, n_cu);
     const unsigned gc = share_grid((const void*)k_dct_combine, std::min<int64_t>(d, w.max_pieces), nsb, 256, n_cu);

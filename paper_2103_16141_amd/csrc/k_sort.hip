@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const
     const int ne = (int)min((int64_t)kFoldTile, n - lo);
     int64_t ra = 0, rb = 0;
     if (KIND == kSortCsr) {
-        ra = row_of(A.in.rp, 0, A.in.rows - 1, lo);
-        rb = row_of(A.in.rp, ra, A.in.rows - 1, lo + ne - 1);
+        ra = row_of(A.in.rp, 0, A.in.rows - 1, A.in.p0 + lo);
+        rb = row_of(A.in.rp, ra, A.in.rows - 1, A.in.p0 + lo + ne - 1);
     }
 #pragma unroll
     for (int i = 0; i < kFoldPer; ++i) {
@@ -87,9 +87,9 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const
             L.key[e] = (uint32_t)A.in.key[p];
             L.row[e] = (int32_t)p;
         } else {
-            const int64_t r = row_of(A.in.rp, ra, rb, p);
+            const int64_t r = row_of(A.in.rp, ra, rb, A.in.p0 + p);
             L.key[e] = (uint32_t)A.in.key[p];
-            L.row[e] = (int32_t)r;
+            L.row[e] = (int32_t)(A.in.row0 + r);
             L.val[e] = A.in.val[p];
         }
     }

@@ -2,6 +2,7 @@
 // checked on the CPU over their whole ranges.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 namespace sivf {
@@ -53,6 +54,47 @@ int64_t split_range(int64_t most, Pays pays, Longest longest, int64_t* pairs) {
         if (*pairs <= kSplitMaxPairs) return range;
         if (range == 1) return 0;
     }
+}
+
+// ---------------------------------------------------------------- soft backward
+// What of the backward is in memory at once: chunks of `rows` rows, `blocks`
+// blocks of 64 columns, the column copy of the whole matrix or of a chunk.
+struct SoftPlan {
+    int64_t rows, blocks;
+    bool whole;
+};
+
+// The attempt-th plan, until one fits the memory; false: there is none left.
+// Each needs less than the one before: all columns at once; eight blocks (one
+// per XCD); one block and the copy of a chunk, 31 B per nonzero of a chunk and
+// 556 B per term; the same with ever fewer rows.  The results are the same, but
+// for the rounding where dC's chunks are cut elsewhere.
+// Rows: 24,576 rows of a 32-column dS block take 3 MB of an XCD's
+// 4 MB L2; smaller chunks read and write dC more often, larger ones miss L2.
+// Where a term has few entries in a chunk (below 32 on average), dC costs more
+// than the misses: backward with 16,384 / 24,576 / 32,768 / 40,960 rows, N =
+// 262,144, D = 100,000, 100 terms, k = 4,096 (25 entries) 78.6 / 73.2 / 71.0 /
+// 71.6 ms; N = 97,062, D = 38,883, 177 terms, k = 3,837 (112) - / 46.2 / 47.5 /
+// 48.9.  dS of a chunk is at most 512 MiB.
+inline bool soft_bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, SoftPlan* p) {
+    const int64_t most = (double)nnz * 24576.0 < 32.0 * (double)n * (double)d ? 32768 : 24576;
+    int64_t rows = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), most, (int64_t)(128ll << 20) / (64 * nblk)}));
+    for (int a = 3; a <= attempt; ++a) {
+        if (rows == 1) return false;
+        rows = (rows + 1) / 2;
+    }
+    *p = SoftPlan{rows, attempt == 0 ? nblk : attempt == 1 ? std::min<int64_t>(nblk, 8) : 1, attempt < 2};
+    return true;
+}
+
+// A chunk of rows takes 5 B per nonzero and block for dX's shares (4) and dC's
+// partial rows (1): blocks are taken in groups of at least eight where those of
+// the longest chunk would pass 2 GiB, and chunks of more than kSoftChunkNnz
+// nonzeros are halved.
+constexpr int64_t kSoftChunkNnz = 1ll << 26;
+inline int64_t soft_bwd_blocks(int64_t blocks, int64_t nnz_max) {
+    const int64_t fit = (int64_t)(2ll << 30) / (5 * std::max<int64_t>(nnz_max, 1));
+    return fit >= blocks ? blocks : std::min(blocks, std::max<int64_t>(8, fit / 8 * 8));
 }
 
 }  // namespace sivf

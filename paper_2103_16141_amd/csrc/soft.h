@@ -33,16 +33,18 @@ struct SoftFwdWs {
 int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k);
 hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* CT, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s);
-// rows [c0, c1) whose nonzeros are [p0, p1).  dS: blocks [2 ceil(k / 64)][c1 - c0][32]
-// or nullptr; dxv: dX or nullptr; dxp: [ceil(k / 64) * (p1 - p0)] when k > 64 and dxv
+// rows [c0, c1) whose nonzeros are [p0, p1), k columns of C^T.  dS: blocks
+// [2 ceil(k / 64)][c1 - c0][32] or nullptr; dxv: dX or nullptr; dxp:
+// [ceil(k / 64) * (p1 - p0)], or nullptr when k <= 64 are all columns; add: dX has
+// the columns before these
 hipError_t soft_bwd_rows(int64_t c0, int64_t c1, int64_t p0, int64_t p1, const int64_t* rp, const int32_t* col,
                          const float* xv, const float* CT, int64_t d, int32_t k, float tau, float grad,
-                         const float* lse, float* dS, float* dxp, float* dxv, int n_cu, hipStream_t s);
+                         const float* lse, float* dS, float* dxp, float* dxv, bool add, int n_cu, hipStream_t s);
 // out[j] = rp[min(j * rc, n)] for j in [0, nch]: the nonzero offsets of the row chunks
 hipError_t soft_chunk_offsets(const int64_t* rp, int64_t n, int64_t rc, int64_t nch, int64_t* out, hipStream_t s);
 // workspace of the dC pass of one chunk of rows
 struct DctWs {
-    int64_t* next;        // [d] CSC entry the next chunk's range starts at (set by the first chunk)
+    int64_t* next;        // [d] CSC entry the next chunk's range starts at (set by each)
     int64_t* lo;          // [d] first CSC entry of the chunk's rows
     int32_t* len;         // [d] entries
     int32_t* mid;         // [d] terms summed by a wave each
@@ -52,7 +54,7 @@ struct DctWs {
     int32_t* piece_len;   // [max_pieces] entries
     float* part;          // [2 ceil(k / 64) * max_pieces * 32] partial rows
     int64_t max_pieces;   // at least the pieces of any chunk (nonzeros / (kSoftPiece / 2) suffice)
-    unsigned long long* count;   // [4] mid terms, pieces, long terms, dS not finite; zero before the call
+    unsigned long long* count;   // [4] mid terms, pieces, long terms, dS not finite; zero before every chunk
     // the densest terms by matrix products (xd == nullptr: not)
     int64_t nnz;          // of all rows
     float* xd;            // [rows * kDctDense] their values in the chunk's rows
@@ -72,7 +74,8 @@ hipError_t dct_pick(int64_t N, int64_t d, const int64_t* colptr, DctWs w, hipStr
 // rows [c0, c1) of the densest terms into w.xd
 hipError_t dct_dense_rows(int64_t c0, int64_t c1, const int64_t* rp, const int32_t* col, const float* xv, DctWs w,
                           int n_cu, hipStream_t s);
-hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, const int64_t* colptr,
+// first: dCT is overwritten; fresh: the chunk's ranges start at colptr (else at w.next)
+hipError_t soft_dct(int64_t d, int32_t k, int64_t c0, int64_t c1, int first, int fresh, const int64_t* colptr,
                     const int32_t* xt_row, const float* xt_val, const float* dS, float* dCT, DctWs w, int n_cu,
                     hipStream_t s);
 

@@ -7,7 +7,7 @@
 namespace sivf {
 
 // Where the entries of the first pass come from.  Entry p in [0, n):
-//   kSortCsr:    rows r of a CSR matrix: key[p], value val[p], row r with rp[r] <= p < rp[r + 1]
+//   kSortCsr:    rows of a CSR matrix: key[p], value val[p], row row0 + r with rp[r] <= p0 + p < rp[r + 1]
 //   kSortIota:   key[p], row p, no value
 enum SortSource { kSortCsr, kSortIota };
 
@@ -17,8 +17,9 @@ struct SortIn {
     int64_t n;              // entries
     const int32_t* key;
     const V* val;           // kSortIota: nullptr
-    int64_t rows;
-    const int64_t* rp;
+    int64_t rows;           // kSortCsr
+    const int64_t* rp;      // row bounds, p0 the first of them
+    int64_t p0, row0;
 };
 
 // two buffers of entries (val: nullptr without values), the digit counts of

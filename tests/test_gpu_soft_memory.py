@@ -1,0 +1,89 @@
+"""The soft form under workspace caps: long and skewed rows, column groups and
+chunk copies against the form that has all the memory it asks for."""
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import device, log
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(**kw):
+    from paper_2103_16141_amd.api import Context
+    return Context(0, **kw)
+
+
+def _corpus(n, d, short, long, every, seed):
+    """n unit rows of `short` distinct terms, every `every`-th one of `long`."""
+    from paper_2103_16141_amd.api import DeviceCsr
+    g = torch.Generator(device=device()).manual_seed(seed)
+    cols, lens = [], []
+    for lo in range(0, n, 5_000):
+        m = torch.full((min(5_000, n - lo),), short, device=device())
+        m[(torch.arange(lo, lo + m.numel(), device=device()) % every) == 0] = long
+        w = torch.rand(m.numel(), d, device=device(), generator=g) * torch.linspace(0.3, 1.0, d, device=device())
+        take = torch.zeros(m.numel(), d, dtype=torch.bool, device=device())
+        take.scatter_(1, w.argsort(1), torch.arange(d, device=device())[None, :] < m[:, None])
+        cols.append(take.nonzero()[:, 1].int())
+        lens.append(m)
+    lens, col = torch.cat(lens), torch.cat(cols)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64, device=device()), lens.cumsum(0)])
+    v = torch.rand(col.numel(), device=device(), generator=g) + 0.1
+    row = torch.repeat_interleave(torch.arange(n, device=device()), lens)
+    ss = torch.zeros(n, device=device(), dtype=torch.float64).index_add_(0, row, v.double() ** 2)
+    return DeviceCsr(rp, col, (v / ss.sqrt()[row]).float(), d), row
+
+
+def _needed(X, k):
+    """Bytes that are always enough for k >= 64, by the array: C^T and dC^T, dS of
+    2^26 / k rows, 32 B per nonzero of such a chunk, row and value per nonzero,
+    counts per 1,024 rows, 88 B per term; each an eighth more."""
+    n, d, nnz = X.n_rows, X.n_cols, X.nnz
+    rc = min(n, (64 << 20) // k)
+    rp = X.row_ptr.cpu().numpy()
+    most = max(int(rp[min(n, c + rc)] - rp[c]) for c in range(0, n, rc))
+    return 9 * (8 * k * d + 4 * rc * k + 32 * most + 8 * nnz + 4 * ((n + 1023) // 1024) * d + 88 * d) // 8 + (1 << 16)
+
+
+@pytest.mark.parametrize("n,d,short,long,every,k", [
+    (30_000, 2_000, 20, 1_500, 100, 1_000),    # two chunks of rows, a few rows hold most nonzeros
+    (6_000, 4_000, 700, 3_999, 1_000, 4_096),  # long rows throughout
+    (1_000, 60_000, 30, 2_000, 50, 64),        # one block of columns
+    (25_000, 8_000, 4_000, 8_000, 5_000, 64),  # 1e8 nonzeros: two chunks for their number
+    (50_000, 300, 3, 300, 49_000, 130),        # a chunk of short rows after one long row; three blocks, the last of 2
+])
+def test_soft_backward_within_the_memory_of_eight_shares(n, d, short, long, every, k):
+    from paper_2103_16141_amd._native import SivfError
+    log("soft backward under caps n %d d %d k %d" % (n, d, k))
+    X, row = _corpus(n, d, short, long, every, k)
+    g = torch.Generator(device=device()).manual_seed(k)
+    C = torch.rand(k, d, device=device(), generator=g)
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    lse, _ = _ctx().soft_assign_fwd(X, C, 0.05)
+    dC, dX = _ctx().soft_assign_bwd(X, C, 0.05, lse, 0.9)
+    ref = torch.zeros(k, d, dtype=torch.float64, device=device())
+    for lo in range(0, n, 2_000):
+        hi = min(n, lo + 2_000)
+        b, e = int(X.row_ptr[lo]), int(X.row_ptr[hi])
+        D = torch.zeros(hi - lo, d, dtype=torch.float64, device=device())
+        D[row[b:e] - lo, X.col[b:e].long()] = X.val[b:e].double()
+        P = torch.softmax(D @ C.double().T / 0.05, 1)
+        ref += (-0.9 / 0.05) * (P.T.contiguous() @ D)
+    need, fits = _needed(X, k), []
+    for cap in [need] + [int(need * 0.8 ** e) for e in range(1, 24)] + [1 << 12]:
+        ctx = _ctx(workspace_cap_bytes=cap)
+        try:
+            c, x = ctx.soft_assign_bwd(X, C, 0.05, lse, 0.9)
+        except SivfError as e:
+            assert e.name == "SIVF_E_NOMEM"
+            c = None
+        fits.append(c is not None)
+        if c is not None:
+            # dX adds its blocks in order whatever is in memory at once; dC's sums
+            # are cut where the chunks are
+            assert torch.equal(x, dX)
+            assert bool(((c.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
+        ctx.close()
+    assert fits[0] and fits == sorted(fits, reverse=True) and not fits[-1]
+    assert bool(((dC.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())

@@ -15,6 +15,15 @@ extern "C" {
 void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
     sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, kt, T);
 }
+int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64_t* rows, int64_t* blocks, int* whole) {
+    sivf::SoftPlan p;
+    if (!sivf::soft_bwd_plan(attempt, n, nnz, d, nblk, &p)) return 0;
+    *rows = p.rows;
+    *blocks = p.blocks;
+    *whole = p.whole;
+    return 1;
+}
+int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
 typedef int64_t (*fn)(int64_t);
 int64_t split(int64_t most, fn pays, fn longest, int64_t* pairs) {
     return sivf::split_range(most, [=](int64_t r) { return pays(r) != 0; }, longest, pairs);
@@ -77,3 +86,37 @@ def test_ranges_of_the_split_walk_end(plan, objects, row, floor, want):
     assert got == want
     if want:
         assert pairs.value == 32 + want * (row + 32)
+
+
+def test_soft_backward_plans_shrink_to_less_than_eight_shares_took(plan):
+    # bytes per array, as the library asks for them, against 32 B per nonzero of a
+    # chunk of 2^26 / k rows, 8 B per nonzero, counts per 1,024 rows and 88 B a term
+    plan.bwd_plan.restype = ctypes.c_int
+    plan.bwd_blocks.restype = ctypes.c_int64
+    rng = np.random.default_rng(1)
+    for _ in range(3000):
+        k = int(np.exp(rng.uniform(np.log(64), np.log(1e5))))
+        n = int(np.exp(rng.uniform(0, np.log(1e7))))
+        d = int(np.exp(rng.uniform(np.log(100), np.log(1e6))))
+        lam = int(np.exp(rng.uniform(0, np.log(d))))
+        nnz, nblk, least = n * lam, (k + 63) // 64, None
+        old_rows = max(1, min(n, (64 << 20) // k))
+        old = 8 * k * d + 4 * old_rows * k + 40 * old_rows * lam + 88 * d
+        attempt = 0
+        while True:
+            rows, blocks, whole = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int()
+            if not plan.bwd_plan(attempt, ctypes.c_int64(n), ctypes.c_int64(nnz), ctypes.c_int64(d),
+                                 ctypes.c_int64(nblk), ctypes.byref(rows), ctypes.byref(blocks), ctypes.byref(whole)):
+                break
+            rows, copy = rows.value, nnz if whole.value else min(n, rows.value) * lam
+            blocks = plan.bwd_blocks(ctypes.c_int64(blocks.value), ctypes.c_int64(rows * lam))
+            assert 1 <= rows <= max(n, 1) and 1 <= blocks <= nblk
+            if attempt == 0 and 5 * rows * lam * nblk <= 2 << 30:
+                assert blocks == nblk   # everything at once where it is not much
+            size = 512 * blocks * d + 256 * rows * blocks + 5 * rows * lam * blocks + 26 * copy + 44 * d + 16384
+            if least is not None:
+                assert size <= least + 16384
+            least, last, attempt = size, (rows, blocks), attempt + 1
+        assert last == (1, 1) and attempt < 40
+        # the last plan fits wherever those bytes were there
+        assert least <= old + 16384

@@ -312,8 +312,12 @@ sivf_status sivf_run_lloyd(sivf_ctx* ctx, const sivf_csr* X, int32_t k, const in
  *   S = X C^T, lse_i = log sum_j exp(S_ij / tau), loss = -sum_i lse_i.
  * X: N x d CSR (SIVF_F32 values).  C: f32[k * d] row-major dense centroids.
  * lse_out: f32[N].  loss_host: optional (waits); summed in FP64 in a fixed order.
- * Nothing of size N x k is stored.  Larger calls without a workspace cap also
- * hold X's nonzeros in another order (8 B each, and 264 B per row of 65,536). */
+ * Nothing of size N x k is stored.  Workspace held by the ctx: C^T (k rounded up
+ * to 64 times d floats) and 8 B per row and 64 columns of at most 512 MiB at a
+ * time; larger calls without a workspace cap also
+ * hold X's nonzeros in another order (8 B each, and 264 B per row of 65,536).
+ * Where a request fails, less is held at a time, down to 64 B per row and 64
+ * columns of C^T; lse is the same. */
 sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* C, int32_t k,
                                  float tau, float* lse_out, double* loss_host);
 

@@ -814,7 +814,38 @@ sivf_status validate_with_ids(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* 
     return validate(ctx, X, out, w, {{ids, X->n_rows, f->k, what}});
 }
 
-// ---------------------------------------------------------------- soft backward
+// ---------------------------------------------------------------- soft form
+// Memory of a forward of Xc against k centroids by plan p; lds: with the
+// commonest terms in LDS, if that pays and there is memory.
+sivf_status soft_fwd_reserve(sivf_ctx* ctx, const Csr& Xc, int32_t k, const SoftFwdPlan& p, bool lds, SoftFwdWs* w,
+                             double** loss) {
+    const int64_t nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk;
+    *w = SoftFwdWs{};
+    w->rows = p.rows;
+    w->blocks = p.blocks;
+    // (fewer rows per launch; without a workspace cap)
+    const int64_t lds_rows =
+        lds && ctx->opt.workspace_cap_bytes == 0 ? std::min(soft_lds_rows(Xc.n, Xc.nnz, Xc.d, k), w->rows) : 0;
+    const int64_t least = lds_rows > 0 ? lds_rows : w->rows;
+    STCHK(ws(ctx, "soft_CT", p.blocks * kSoftBlk * Xc.d, &w->CT));
+    STCHK(ws(ctx, "soft_loss", 1, loss));
+    STCHK(ws(ctx, "soft_pmax", w->rows * nblk, &w->pmax));
+    STCHK(ws(ctx, "soft_psum", w->rows * nblk, &w->psum));
+    STCHK(ws(ctx, "soft_part", Xc.n / 256 + Xc.n / least + 2, &w->part));
+    const size_t d = (size_t)Xc.d;
+    if (lds_rows > 0 &&
+        ws_optional(ctx, {{"soft_hdr", lds_rows * sizeof(uint2), (void**)&w->hdr},
+                          {"soft_count", d * 4, (void**)&w->count},
+                          {"soft_slot", d * 4, (void**)&w->slot},
+                          {"soft_hot", (kSplitHot + 1) * 4, (void**)&w->term},
+                          {"soft_ent", (size_t)split_pairs(Xc.nnz, lds_rows) * sizeof(uint2), (void**)&w->ent}})) {
+        w->nnz = Xc.nnz;
+        w->nhot = w->term + kSplitHot;
+        w->rows = lds_rows;
+    }
+    return SIVF_OK;
+}
+
 struct SoftBwd {
     SoftPlan p{};
     std::vector<int64_t> offs;   // first nonzero of each chunk of rows, and the end
@@ -1476,36 +1507,20 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     Csr Xc;
     STCHK(validate(ctx, X, &Xc));
     if (Xc.f64) return fail(ctx, SIVF_E_UNSUPPORTED, "soft assignment takes SIVF_F32 object values");
-    const int64_t nblk = ((int64_t)k + kSoftBlk - 1) / kSoftBlk;
-    float* CT = nullptr;
+    const std::string err = ctx->err;
     double* loss = nullptr;
     SoftFwdWs w{};
-    // rows per launch: the per-block partials of one launch take at most 512 MiB
-    w.rows = std::max<int64_t>(1, std::min<int64_t>(Xc.n, (int64_t)(64ll << 20) / nblk));
-    STCHK(ws(ctx, "soft_CT", nblk * kSoftBlk * Xc.d, &CT));
-    STCHK(ws(ctx, "soft_loss", 1, &loss));
-    STCHK(ws(ctx, "soft_pmax", w.rows * nblk, &w.pmax));
-    STCHK(ws(ctx, "soft_psum", w.rows * nblk, &w.psum));
-    // the commonest terms in LDS: fewer rows per launch; without a workspace cap,
-    // and only if there is memory
-    const int64_t lds_rows =
-        ctx->opt.workspace_cap_bytes == 0 ? std::min(soft_lds_rows(Xc.n, Xc.nnz, Xc.d, k), w.rows) : 0;
-    const int64_t least = lds_rows > 0 ? lds_rows : w.rows;
-    STCHK(ws(ctx, "soft_part", Xc.n / 256 + Xc.n / least + 2, &w.part));
-    const size_t dd = (size_t)Xc.d;
-    if (lds_rows > 0 &&
-        ws_optional(ctx, {{"soft_hdr", lds_rows * sizeof(uint2), (void**)&w.hdr},
-                          {"soft_count", dd * 4, (void**)&w.count},
-                          {"soft_slot", dd * 4, (void**)&w.slot},
-                          {"soft_hot", (kSplitHot + 1) * 4, (void**)&w.term},
-                          {"soft_ent", (size_t)split_pairs(Xc.nnz, lds_rows) * sizeof(uint2), (void**)&w.ent}})) {
-        w.nnz = Xc.nnz;
-        w.nhot = w.term + kSplitHot;
-        w.rows = lds_rows;
+    sivf_status st = SIVF_E_NOMEM;
+    SoftFwdPlan p;
+    for (int a = 0; st == SIVF_E_NOMEM && soft_fwd_plan(a, Xc.n, ((int64_t)k + kSoftBlk - 1) / kSoftBlk, &p); ++a) {
+        if (a > 0) ws_drop(ctx, {"soft_"});
+        st = soft_fwd_reserve(ctx, Xc, k, p, a == 0, &w, &loss);
     }
+    if (st == SIVF_E_NOMEM) ws_drop(ctx, {"soft_"});
+    STCHK(st);
+    ctx->err = err;
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, soft_pack(C, CT, k, Xc.d, s));
-    HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, CT, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
+    HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, C, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
     if (loss_host) {
         HIPCHK(ctx, hipMemcpyAsync(ctx->pin, loss, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));

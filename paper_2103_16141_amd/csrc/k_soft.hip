@@ -459,7 +459,7 @@ int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k) {
     return std::min(N, kRows);
 }
 
-hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* CT, int64_t d,
+hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* C, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s) {
     const int64_t nblk = ((int64_t)k + kBlk - 1) / kBlk;
     const bool narrow = narrow_offsets(d);
@@ -475,20 +475,29 @@ hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const 
     int64_t parts = 0;
     for (int64_t c0 = 0; c0 < N; c0 += w.rows) {
         const int64_t c1 = std::min(N, c0 + w.rows), n = c1 - c0;
-        const unsigned grid = share_grid(fn, n, nblk, 256, n_cu);
         if (w.ent) {
             const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + 3) / 4, (int64_t)n_cu * 8));
             hipLaunchKernelGGL(k_soft_prep, dim3((unsigned)blocks), dim3(256), 0, s, c0, n, rp, col, xv, w.slot, w.nhot,
                                w.ent, w.hdr);
-            hipLaunchKernelGGL(k_soft_fwd_lds, dim3((unsigned)((n_cu + kXcds - 1) / kXcds * kXcds)), dim3(kDenseThreads), lds,
-                               s, (int)n, w.ent, (uint32_t)split_pairs(w.nnz, w.rows), w.hdr, w.term, w.nhot, CT, d, k,
-                               1.0f / tau, w.pmax, w.psum);
-        } else if (narrow) {
-            hipLaunchKernelGGL(k_soft_fwd<uint32_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, CT, d, k,
-                               1.0f / tau, w.pmax, w.psum);
-        } else {
-            hipLaunchKernelGGL(k_soft_fwd<uint64_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, CT, d, k,
-                               1.0f / tau, w.pmax, w.psum);
+        }
+        for (int64_t b0 = 0; b0 < nblk; b0 += w.blocks) {
+            const int32_t kg = (int32_t)std::min<int64_t>(w.blocks * kBlk, k - b0 * kBlk);
+            const unsigned grid = share_grid(fn, n, std::min(w.blocks, nblk - b0), 256, n_cu);
+            float *pmax = w.pmax + b0 * n, *psum = w.psum + b0 * n;
+            if (c0 == 0 || w.blocks < nblk) {
+                const hipError_t e = soft_pack(C + b0 * kBlk * d, w.CT, kg, d, s);
+                if (e != hipSuccess) return e;
+            }
+            if (w.ent)
+                hipLaunchKernelGGL(k_soft_fwd_lds, dim3((unsigned)((n_cu + kXcds - 1) / kXcds * kXcds)), dim3(kDenseThreads),
+                                   lds, s, (int)n, w.ent, (uint32_t)split_pairs(w.nnz, w.rows), w.hdr, w.term, w.nhot, w.CT,
+                                   d, kg, 1.0f / tau, pmax, psum);
+            else if (narrow)
+                hipLaunchKernelGGL(k_soft_fwd<uint32_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, w.CT, d, kg,
+                                   1.0f / tau, pmax, psum);
+            else
+                hipLaunchKernelGGL(k_soft_fwd<uint64_t>, dim3(grid), dim3(256), 0, s, c0, c1, rp, col, xv, w.CT, d, kg,
+                                   1.0f / tau, pmax, psum);
         }
         const int64_t wgs = (n + 255) / 256;
         hipLaunchKernelGGL(k_soft_lse, dim3((unsigned)wgs), dim3(256), 0, s, n, nblk, w.pmax, w.psum, lse + c0,

@@ -56,6 +56,21 @@ int64_t split_range(int64_t most, Pays pays, Longest longest, int64_t* pairs) {
     }
 }
 
+// ---------------------------------------------------------------- soft forward
+// As for the backward below: rows per launch and blocks of 64 columns in C^T at
+// once.  The per-block partials of one launch take at most 512 MiB, in the later
+// plans 64 B per row of the matrix.
+struct SoftFwdPlan {
+    int64_t rows, blocks;
+};
+
+inline bool soft_fwd_plan(int attempt, int64_t n, int64_t nblk, SoftFwdPlan* p) {
+    const int64_t partials = attempt == 0 ? (int64_t)64 << 20 : 8 * n;
+    p->rows = std::max<int64_t>(1, std::min<int64_t>(n, partials / nblk));
+    p->blocks = attempt < 2 ? nblk : 1;
+    return attempt < 3;
+}
+
 // ---------------------------------------------------------------- soft backward
 // What of the backward is in memory at once: chunks of `rows` rows, `blocks`
 // blocks of 64 columns, the column copy of the whole matrix or of a chunk.

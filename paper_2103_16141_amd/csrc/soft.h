@@ -19,6 +19,8 @@ hipError_t soft_pack(const float* C, float* out, int64_t k, int64_t d, hipStream
 hipError_t soft_unpack(const float* dCT, float* dC, int64_t k, int64_t d, hipStream_t s);
 struct SoftFwdWs {
     int64_t rows;    // rows per launch
+    int64_t blocks;  // blocks of 64 columns in C^T at once
+    float* CT;       // [64 * blocks * d]
     float* pmax;     // [ceil(k / 64) * rows] max of S / tau per (block, row)
     float* psum;     // [ceil(k / 64) * rows] sum of exp(S / tau - max)
     double* part;    // partial sums of lse: one per 256 rows of every launch
@@ -31,7 +33,7 @@ struct SoftFwdWs {
 };
 // rows per launch with the commonest terms in LDS, or 0: not so
 int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k);
-hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* CT, int64_t d,
+hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* C, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s);
 // rows [c0, c1) whose nonzeros are [p0, p1), k columns of C^T.  dS: blocks
 // [2 ceil(k / 64)][c1 - c0][32] or nullptr; dxv: dX or nullptr; dxp:

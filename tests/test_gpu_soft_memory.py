@@ -87,3 +87,39 @@ def test_soft_backward_within_the_memory_of_eight_shares(n, d, short, long, ever
         ctx.close()
     assert fits[0] and fits == sorted(fits, reverse=True) and not fits[-1]
     assert bool(((dC.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
+
+
+@pytest.mark.parametrize("n,d,short,long,every,k", [
+    (300_000, 600, 5, 60, 10, 1_000),       # sixteen blocks: partials of 128 B a row
+    (5_000, 20_000, 30, 300, 50, 777),      # C^T is most of it; the last block of 9 columns
+    (7, 500, 20, 500, 3, 5_000),            # more blocks than eight per row
+])
+def test_soft_forward_within_the_memory_of_eight_partials(n, d, short, long, every, k):
+    from paper_2103_16141_amd._native import SivfError
+    log("soft forward under caps n %d d %d k %d" % (n, d, k))
+    X, row = _corpus(n, d, short, long, every, k)
+    C = torch.rand(k, d, device=device(), generator=torch.Generator(device=device()).manual_seed(k))
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    want, loss = _ctx(workspace_cap_bytes=1 << 40).soft_assign_fwd(X, C, 0.05)
+    ref = torch.empty(n, dtype=torch.float64, device=device())
+    for lo in range(0, n, 10_000):
+        hi = min(n, lo + 10_000)
+        b, e = int(X.row_ptr[lo]), int(X.row_ptr[hi])
+        D = torch.zeros(hi - lo, d, dtype=torch.float64, device=device())
+        D[row[b:e] - lo, X.col[b:e].long()] = X.val[b:e].double()
+        ref[lo:hi] = torch.logsumexp(D @ C.double().T / 0.05, 1)
+    # a sum of at most d products of unit vectors' entries over tau; exp and log add 1e-5
+    assert float((want.double() - ref).abs().max()) <= (long + 2) * 2.0 ** -24 / 0.05 + 1e-5
+    need, fits = 9 * (4 * k * d + 64 * n) // 8 + (1 << 16), []
+    for cap in [need] + [int(need * 0.8 ** e) for e in range(1, 12)] + [1 << 12]:
+        ctx = _ctx(workspace_cap_bytes=cap)
+        try:
+            lse, lo = ctx.soft_assign_fwd(X, C, 0.05)
+        except SivfError as e:
+            assert e.name == "SIVF_E_NOMEM"
+            lse = None
+        fits.append(lse is not None)
+        if lse is not None:
+            assert torch.equal(lse, want) and abs(lo - loss) <= 1e-12 * abs(loss)
+        ctx.close()
+    assert fits[0] and fits == sorted(fits, reverse=True) and not fits[-1]

@@ -600,7 +600,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // (the last requests of an update: they are optional)
     uint32_t* wt = nullptr;
     int32_t* sterm2 = nullptr;
-    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes &&
+    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes && SH * f->T <= kMaxGroups &&
         rows_reserve(&f->sval, &f->scap, SH, true) == SIVF_OK &&
         ws_optional(ctx, {{"split_wt", (size_t)SH * 4, (void**)&wt}, {"split_term2", (size_t)SH * 4, (void**)&sterm2}})) {
         HIPCHK(ctx, split_order(sterm, f->seg, f->T, f->v32, SH, wt, sterm2, f->srow, meta, ctx->stream));

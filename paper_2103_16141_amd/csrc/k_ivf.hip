@@ -358,8 +358,7 @@ hipError_t seg_records(const int64_t* seg, const int32_t* mid, const int32_t* he
 
 hipError_t head_fill(const int32_t* hterm, const int64_t* seg, const uint16_t* cid, const float* v32,
                      const uint16_t* v16, int32_t T, int32_t ktp, int64_t H, void* hval, hipStream_t s) {
-    // at most 2^31 - 1 workgroups a launch
-    const int64_t most = ((int64_t)1 << 30) / T;
+    const int64_t most = std::max<int64_t>(1, kMaxGroups / T);
     for (int64_t r = 0; r < H; r += most) {
         const int64_t n = std::min(most, H - r);
         void* to = v16 ? (void*)((uint16_t*)hval + r * T * ktp) : (void*)((float*)hval + r * T * ktp);

@@ -9,6 +9,9 @@ namespace sivf {
 
 constexpr int kTileWide = 2048, kTileMid = 1536, kTileNarrow = 1024;   // automatic tile widths
 
+// workgroups of 256 threads a launch may have: its threads are counted in 32 bits
+constexpr int64_t kMaxGroups = (1 << 24) - 1;
+
 // Tiles of k centroids holding an estimated `postings` over d terms; k_tile and
 // bf16: the options the file was made with (k_tile 0: automatic).  Every
 // tile repeats an object's work per term and its scan, so the widest is the best

@@ -179,3 +179,27 @@ def test_buffers_of_faster_forms_leave_room_for_what_calls_need():
     torch.cuda.empty_cache()
     a, own, l = _state(n, k)
     assert holder.assign(X, f0, 1, a, own, l)["walk_bytes"] == s0["walk_bytes"] and torch.equal(a, a0)
+
+
+@pytest.mark.parametrize("posting", ["fp32", "bf16"])
+def test_more_dense_rows_than_a_launch_has_workgroups(posting):
+    # one centroid with 2^24 + 1,000 terms: each has a dense row of 512 slots
+    # (17 or 34 GB), more workgroups of 256 threads than 32 bits count threads
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("dense rows of a wide centroid, %s" % posting)
+    d = (1 << 24) + 1_000
+    dev = device()
+    ctx = _ctx(posting_dtype=posting)
+    col = torch.arange(d, dtype=torch.int32, device=dev)
+    val = ((col % 251).double() + 1.0) / 256.0     # exact in BF16
+    f = ctx.build_centroid_ivf(torch.tensor([0, d], device=dev), col, val, d)
+    # rows of one term on both sides of 2^24 and at the ends, of value 1
+    terms = torch.tensor([0, 1, (1 << 24) - 2, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, d - 1], device=dev)
+    X = DeviceCsr(torch.arange(8, device=dev), terms.int(), torch.ones(7, device=dev), d)
+    a, own, lam = _state(7, 1)
+    st = ctx.assign(X, f, 1, a, own, lam)
+    assert st["head_rows"] == d and bool((a == 0).all())
+    assert torch.equal(own.double(), val[terms])
+    f.free()
+    ctx.close()
+    torch.cuda.empty_cache()

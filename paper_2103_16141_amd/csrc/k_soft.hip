@@ -957,6 +957,7 @@ __global__ __launch_bounds__(256) void k_dct_dense_rows(int64_t c0, int64_t n, c
                                                         const int32_t* __restrict__ col, const float* __restrict__ xv,
                                                         DctWs w) {
     __shared__ float4 buf[4][kDctDense / 4];
+    if (w.ndense[1] == 0) return;   // no term qualified: nothing reads them
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     float* row = reinterpret_cast<float*>(buf[wid]);
     for (int64_t i = (int64_t)blockIdx.x * 4 + wid; i < n; i += (int64_t)gridDim.x * 4) {

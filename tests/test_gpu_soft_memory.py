@@ -123,3 +123,27 @@ def test_soft_forward_within_the_memory_of_eight_partials(n, d, short, long, eve
             assert torch.equal(lse, want) and abs(lo - loss) <= 1e-12 * abs(loss)
         ctx.close()
     assert fits[0] and fits == sorted(fits, reverse=True) and not fits[-1]
+
+
+def test_soft_gradient_of_a_large_call_without_dense_terms():
+    # nonzeros x k past the line of the products, every term in fewer than 1/32 of
+    # the rows: the matrix of dense terms is not written and dC is the capped
+    # call's (entries only) bit for bit
+    log("no dense terms")
+    n, d, k = 70_001, 40_000, 2_100
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(3)
+    from paper_2103_16141_amd.api import DeviceCsr
+    width = 40   # a term from each of 30 stripes of the first 1,200 terms
+    col = torch.randint(width, (n, 30), device=dev, generator=g) + torch.arange(30, device=dev) * width
+    v = torch.rand(n, 30, device=dev, generator=g) + 0.1
+    v /= torch.linalg.vector_norm(v, dim=1, keepdim=True)
+    X = DeviceCsr(torch.arange(n + 1, device=dev) * 30, col.int().reshape(-1).contiguous(), v.reshape(-1).contiguous(), d)
+    assert X.nnz * k >= 1 << 32 and int(torch.bincount(col.reshape(-1)).max()) * 32 < n
+    C = torch.rand(k, d, device=dev, generator=g)
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    ctx = _ctx()
+    lse, _ = ctx.soft_assign_fwd(X, C, 0.05)
+    dC, dX = ctx.soft_assign_bwd(X, C, 0.05, lse, 0.9)
+    pC, pX = _ctx(workspace_cap_bytes=1 << 40).soft_assign_bwd(X, C, 0.05, lse, 0.9)
+    assert torch.equal(dC, pC) and torch.equal(dX, pX) and bool((dC != 0).any())

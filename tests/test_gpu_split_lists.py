@@ -1,0 +1,112 @@
+"""The split walk where its own filter and list code runs: objects with dense
+and listed terms, flags chosen so that moving centroids end inside a tile and
+inside a block of 64 slots, several tiles and ranges."""
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import device, log
+
+pytestmark = pytest.mark.gpu
+
+DENSE, RARE, WIDTH = 100, 200, 1_000   # stripes of 4 common terms, of 1,000 rare ones
+D = 4 * DENSE + RARE * WIDTH
+
+
+def _objects(n, dtype, signed, seed):
+    """Unit rows: one term of each of 100 stripes of 4, and of the first m of 200
+    stripes of 1,000, m from 0 to 200; every 501st row empty.  The common terms'
+    ids lie in the middle."""
+    from paper_2103_16141_amd.api import DeviceCsr
+    g = torch.Generator(device=device()).manual_seed(seed)
+    half = RARE // 2
+    rare = torch.randint(WIDTH, (n, RARE), device=device(), generator=g, dtype=torch.int32)
+    rare += torch.arange(RARE, device=device(), dtype=torch.int32) * WIDTH
+    rare[:, half:] += 4 * DENSE
+    dense = torch.randint(4, (n, DENSE), device=device(), generator=g, dtype=torch.int32)
+    dense += torch.arange(DENSE, device=device(), dtype=torch.int32) * 4 + half * WIDTH
+    m = torch.tensor([0, 1, 27, 28, 29, 64, 92, 127, 128, 129, 160, 200], device=device())
+    m = m[torch.randint(m.numel(), (n,), device=device(), generator=g)]
+    keep = torch.arange(RARE, device=device())[None, :] < m[:, None]
+    col = torch.cat([rare[:, :half], dense, rare[:, half:]], 1)
+    keep = torch.cat([keep[:, :half], torch.ones_like(dense, dtype=torch.bool), keep[:, half:]], 1)
+    keep[::501] = False
+    lens = keep.sum(1)
+    v = torch.rand(n, DENSE + RARE, device=device(), generator=g, dtype=torch.float64) + 0.05
+    if signed:
+        v *= torch.where(torch.rand(n, DENSE + RARE, device=device(), generator=g) < 0.3, -1.0, 1.0)
+    v *= keep
+    v /= torch.linalg.vector_norm(v, dim=1, keepdim=True).clamp_(min=1e-30)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64, device=device()), lens.cumsum(0)])
+    return DeviceCsr(rp, col[keep].contiguous(), v[keep].to(dtype).contiguous(), D)
+
+
+@pytest.mark.parametrize("n,k,kt,mode,dtype,signed,moving,ranges", [
+    (60_003, 1_100, 640, "sivf", torch.float32, False, (700, 333, 1_037), 1),   # into tile 1, short of it, nearly all
+    (60_003, 1_100, 640, "relaxed", torch.float64, False, (450, 641), 1),
+    (40_001, 1_500, 0, "sivf", torch.float32, True, (1_001, 70), 1),            # one tile, signed values
+    (300_007, 4_200, 4_096, "sivf", torch.float32, False, (2_000, 4_130), 2),   # two tiles of two ranges of objects
+    (270_001, 4_200, 4_096, "relaxed", torch.float32, True, (3_333,), 2),
+])
+def test_split_walk_of_objects_with_listed_terms_under_the_filter(n, k, kt, mode, dtype, signed, moving, ranges):
+    from paper_2103_16141_amd.api import Context
+    log("split walk with lists n %d k %d %s" % (n, k, mode))
+    dev = device()
+    X = _objects(n, dtype, signed, n)
+    rng = np.random.default_rng(k)
+    ids = (rng.choice(n - 1, k, replace=False) + 1).astype(np.int32)
+    ids[ids % 501 == 0] = 1    # no empty seed (ids may repeat)
+    opts = dict(k_tile=kt, filter_mode=mode)
+    split, plain = Context(0, **opts), Context(0, workspace_cap_bytes=1 << 40, **opts)
+    state = [(split, split.init_centroids(X, k, ids)), (plain, plain.init_centroids(X, k, ids))]
+    a = torch.zeros(n, dtype=torch.int32, device=dev)
+    own = torch.zeros(n, dtype=torch.float32, device=dev)
+    own64 = torch.zeros(n, dtype=torch.float64, device=dev) if mode == "relaxed" else None
+    lam = torch.zeros(k, dtype=torch.uint8, device=dev)
+    plain.assign(X, state[1][1], 1, a, own, lam, own64=own64)
+    for r, mv in enumerate(moving, 2):
+        # any clusters may be kept: flagged ones keep their centroids bitwise, so
+        # the filter's premise holds and the argmax stays the exact one
+        flags = np.ones(k, np.uint8)
+        flags[rng.choice(k, mv, replace=False)] = 0
+        flags = torch.from_numpy(flags).to(dev)
+        out = []
+        for ctx, f in state:
+            ctx.update(X, a, flags, f)
+            a1, own1, l1 = a.clone(), own.clone(), lam.clone()
+            e1 = None if own64 is None else own64.clone()
+            out.append((a1, own1, l1, e1, ctx.assign(X, f, r, a1, own1, l1, own64=e1)))
+        (a1, o1, l1, e1, s1), (a2, o2, l2, e2, s2) = out
+        tiles = state[0][1].sizes()["n_tiles"]
+        assert s1["walk_bytes"] != s2["walk_bytes"] and s1["walk_launches"] == tiles * ranges   # split
+        assert s2["walk_launches"] == tiles
+        assert torch.equal(a1, a2) and torch.equal(l1, l2)
+        for key in ("multadds", "moved", "icp_objects", "n_invariant", "relaxed_objects", "head_rows"):
+            assert s1[key] == s2[key], key
+        assert 0 < s1["icp_objects"] < n and (mode != "relaxed" or s1["relaxed_objects"] > 0)
+        if own64 is not None:
+            assert torch.equal(e1, e2)
+        # two FP32 sums of at most 300 products of a unit row and a unit column,
+        # each within 302 * 2^-24 of the exact value, or the FP64 value rounded
+        assert float((o1.double() - o2.double()).abs().max()) <= 2 * 302 * 2.0 ** -24
+        # the assignment is the argmax in FP64, on rows at the ends of the ranges and between
+        c = state[0][1].centroids()
+        C = torch.zeros(k, D, dtype=torch.float64, device=dev)
+        C[torch.repeat_interleave(torch.arange(k, device=dev), c.row_ptr.diff()), c.col.long()] = c.val
+        step = (n + ranges - 1) // ranges
+        pick = {0, 1, 500, 501, 502, n - 1, n // 2, (1 << 30) // 4_096, (1 << 30) // 4_096 - 1, step, step - 1}
+        pick |= set(rng.choice(n, 1_500).tolist())
+        pick = torch.tensor(sorted(p for p in pick if p < n), device=dev)
+        rows = torch.zeros(pick.numel(), D, dtype=torch.float64, device=dev)
+        for q, i in enumerate(pick.tolist()):
+            b, e = int(X.row_ptr[i]), int(X.row_ptr[i + 1])
+            rows[q, X.col[b:e].long()] = X.val[b:e].double()
+        S = rows @ C.T
+        mine = S.gather(1, a1[pick].long()[:, None])[:, 0]
+        assert float((S.max(1).values - mine).max()) <= 1e-12
+        del C, S, rows
+        a, own, own64, lam = a1, o1, e1, l1
+    for ctx, f in state:
+        f.free()
+        ctx.close()
+    torch.cuda.empty_cache()

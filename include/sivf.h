@@ -243,14 +243,23 @@ sivf_status sivf_ivf_export(sivf_ctx* ctx, const sivf_ivf* ivf, int64_t* c_ptr, 
  * ICP branch: iter >= 2, filter mode SIVF/CBICP/RELAXED, and the file's flag
  * of the object's previous cluster is 1.  Relaxed branch (RELAXED): iter >= 2,
  * that flag is 0, and the object's FP64 similarity to its previous centroid
- * now is >= own64_inout. */
+ * now is >= own64_inout.
+ * Larger batches against FP32 files whose dense terms carry most of an object's
+ * work are walked in two parts (split), where that pays and the ctx has no
+ * workspace cap: up to 4 GiB of sums, 8 B per nonzero (at most 4 GiB) and 20 B
+ * per object of a range, and as many rows again as head_density gives, all
+ * given back when another call of the ctx needs the room.  Without the memory
+ * the walk is not split.  Assignments, flags, own64 and mult-adds do not depend
+ * on it; own_sim (within the certificate's bound), the re-score counts, the
+ * bytes and the launches are those of the walk that was taken. */
 sivf_status sivf_assign(sivf_ctx* ctx, const sivf_csr* X, const sivf_ivf* ivf, int32_t iter,
                         int32_t* assign_inout, float* own_sim_inout, double* own64_inout, uint8_t* lambda_out,
                         sivf_iter_stats* stats_host);
 
 /* sivf_assign for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same step with the same arguments, results and errors, but its
+ * the same step with the same arguments, results and errors (where sivf_assign
+ * splits the walk, up to what may depend on that), but its
  * workspace is a fixed 64 MiB block per device that the library holds from
  * its first use on the device until the process ends; the call makes no
  * device allocation and frees nothing.  The block bounds the sizes it takes:

@@ -110,3 +110,36 @@ def test_split_walk_of_objects_with_listed_terms_under_the_filter(n, k, kt, mode
         f.free()
         ctx.close()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("mode", ["sivf", "relaxed"])
+def test_noalloc_assign_where_assign_splits_the_walk(mode):
+    # the call that allocates nothing never splits: the same assignments, flags,
+    # exact similarities and mult-adds, own similarities within the bound of both
+    from paper_2103_16141_amd.api import Context
+    log("no-alloc assign against a split walk, %s" % mode)
+    n, k, dev = 60_003, 1_100, device()
+    X = _objects(n, torch.float32, False, 9)
+    rng = np.random.default_rng(9)
+    ids = (rng.choice(n - 1, k, replace=False) + 1).astype(np.int32)
+    ids[ids % 501 == 0] = 1
+    ctx = Context(0, filter_mode=mode)
+    na = Context(0, filter_mode=mode, workspace_cap_bytes=1)
+    f = ctx.init_centroids(X, k, ids)
+    a = torch.zeros(n, dtype=torch.int32, device=dev)
+    own = torch.zeros(n, dtype=torch.float32, device=dev)
+    own64 = torch.zeros(n, dtype=torch.float64, device=dev) if mode == "relaxed" else None
+    lam = torch.zeros(k, dtype=torch.uint8, device=dev)
+    ctx.assign(X, f, 1, a, own, lam, own64=own64)
+    flags = torch.from_numpy((rng.random(k) < 0.4).astype(np.uint8)).to(dev)
+    ctx.update(X, a, flags, f)
+    out = []
+    for call in (ctx.assign, na.assign_noalloc):
+        a1, o1, l1, e1 = a.clone(), own.clone(), lam.clone(), None if own64 is None else own64.clone()
+        out.append((a1, o1, l1, e1, call(X, f, 2, a1, o1, l1, own64=e1)))
+    (a1, o1, l1, e1, s1), (a2, o2, l2, e2, s2) = out
+    assert s1["walk_bytes"] != s2["walk_bytes"]   # split there, plain here
+    assert torch.equal(a1, a2) and torch.equal(l1, l2) and (e1 is None or torch.equal(e1, e2))
+    for key in ("multadds", "moved", "icp_objects", "n_invariant", "relaxed_objects"):
+        assert s1[key] == s2[key], key
+    assert float((o1.double() - o2.double()).abs().max()) <= 2 * 302 * 2.0 ** -24

@@ -1056,6 +1056,7 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     HIPCHK(ctx, hipEventRecord(ctx->ev[0], s));
     if (n > 0) {
         const int bf16 = f->pdt == SIVF_BF16;
+        const double terms = (double)Xc.nnz / (double)n;
         const int bpc = walk_blocks_per_cu(f->kt, bf16, A.cbicp, B.range > 0);
         if (B.range) {
             WalkArgs R = A;
@@ -1076,12 +1077,12 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
                 HIPCHK(ctx, walk_prep(R, ctx->n_cu, s));
                 for (int t = 0; t < f->T; ++t) {
                     HIPCHK(ctx, walk_dense(R, t, ctx->n_cu, s));
-                    HIPCHK(ctx, walk_fast(R, bf16, ctx->n_cu * bpc * kWalkWaves, t, t + 1, counters + 16 + r * f->T + t, s));
+                    HIPCHK(ctx, walk_fast(R, terms, bf16, ctx->n_cu * bpc * kWalkWaves, t, t + 1, counters + 16 + r * f->T + t, s));
                 }
             }
         } else {
             for (int l = 0; l < launches; ++l)
-                HIPCHK(ctx, walk_fast(A, bf16, ctx->n_cu * bpc * kWalkWaves, l * tpl, std::min(f->T, (l + 1) * tpl),
+                HIPCHK(ctx, walk_fast(A, terms, bf16, ctx->n_cu * bpc * kWalkWaves, l * tpl, std::min(f->T, (l + 1) * tpl),
                                       counters + 16 + l, s));
         }
     }

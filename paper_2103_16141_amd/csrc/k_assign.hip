@@ -398,9 +398,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
     uint32_t lwords = 0;   // 4-byte words requested by this wave's vector loads (flushed at 2^31)
     uint32_t hwords = 0;   // of which words of 16-byte-per-lane loads (head rows, records)
     const uint32_t xb = 4u + (A.x_f64 ? 8u : 4u);   // one staged term: column + value
-    // SHARE: a wave takes `share` objects by its number; else it grabs as many at a time
+    // SHARE: a wave takes every (number of waves)-th piece of `share` objects; else it
+    // grabs as many at a time
     for (int64_t g0 = SHARE ? ((int64_t)blockIdx.x * kWalkWaves + wid) * share : wave_grab(work, share); g0 < A.n;
-         g0 = SHARE ? A.n : wave_grab(work, share)) {
+         g0 = SHARE ? g0 + (int64_t)gridDim.x * kWalkWaves * share : wave_grab(work, share)) {
         const int64_t gend = min(g0 + share, A.n);
         for (int64_t o = g0; o < gend; ++o) {   // o: the object's number in this launch's range
             const int64_t i = SPLIT ? A.c0 + o : o;
@@ -839,24 +840,25 @@ static const void* walk_kernel(int bf16, int cb, bool share, bool split) {
                 : (cb ? walk_kernel_s<false, true, false>(share) : walk_kernel_s<false, false, false>(share));
 }
 
-hipError_t walk_fast(const WalkArgs& a, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
-                     hipStream_t s) {
+hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_waves, int tb, int te,
+                     unsigned long long* work, hipStream_t s) {
     const size_t lds = walk_lds_bytes(a.kt);
     int blocks = (grid_waves + kWalkWaves - 1) / kWalkWaves;
     if (blocks < 1) blocks = 1;
     // Many objects: a wave grabs them from the work counter, which evens out
     // their costs, 8 at a time or at least four times (60,000 objects, BF16, one
-    // tile: 1.36 ms by twos, 1.64 by eights, 1.47 in equal shares).  Up to 8
-    // objects a wave the counter costs more than that (5,120 waves' turns on it
-    // take 50 us), so the waves take equal shares: 64 objects, k = 100, 260 (8
-    // waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects,
+    // tile: 1.36 ms by twos, 1.64 by eights, 1.47 in equal shares).  Fewer
+    // (walk_shared) cost the counter more than that, so the waves take equal shares,
+    // in pieces of at most 8 objects spread over the batch: 64 objects, k = 100, 260
+    // (8 waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects,
     // k = 1,531, BF16 842 -> 346 us.
     const int64_t waves = (int64_t)blocks * kWalkWaves;
-    const bool shared = a.n <= 8 * waves;
+    const bool shared = a.n <= walk_shared(terms, a.k, a.kt, a.S != nullptr) * waves;
     int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, a.n / (waves * 4)));
     if (shared) {
-        share = (int)std::max<int64_t>(1, (a.n + waves - 1) / waves);
-        blocks = (int)((a.n + (int64_t)share * kWalkWaves - 1) / ((int64_t)share * kWalkWaves));
+        const int64_t pieces = std::max<int64_t>(1, (a.n + 8 * waves - 1) / (8 * waves));   // a wave's
+        share = (int)std::max<int64_t>(1, (a.n + waves * pieces - 1) / (waves * pieces));
+        blocks = (int)((a.n + pieces * share * kWalkWaves - 1) / (pieces * share * kWalkWaves));
     }
     const void* fn = walk_kernel(pdt_bf16, a.cbicp, shared, a.S != nullptr);
     if (lds > 65536) {

@@ -143,3 +143,80 @@ def test_noalloc_assign_where_assign_splits_the_walk(mode):
     for key in ("multadds", "moved", "icp_objects", "n_invariant", "relaxed_objects"):
         assert s1[key] == s2[key], key
     assert float((o1.double() - o2.double()).abs().max()) <= 2 * 302 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("posting", ["fp32", "bf16"])
+@pytest.mark.parametrize("mode", ["sivf", "cbicp"])
+def test_assignment_in_several_pieces_of_objects_a_wave(posting, mode):
+    # up to 16 or 24 objects a wave (5,120 or 6,144 waves) are taken in two or
+    # three pieces of at most 8: every batch gives what its objects give in batches of at
+    # most 8 a wave, with and without the filter
+    from paper_2103_16141_amd.api import Context, DeviceCsr
+    import oracle
+    import synth
+    log("pieces %s %s" % (posting, mode))
+    n, d, dev = 150_000, 700, device()
+    c = synth.make_corpus(n, d, 8, 1.1, np.float32, seed=77)
+    X = DeviceCsr.from_corpus(c, dev)
+    for k in (9, 300):
+        ctx = Context(0, posting_dtype=posting, filter_mode=mode)
+        ids = synth.init_ids(n, k, 3)
+        f = ctx.init_centroids(X, k, ids)
+        a = torch.zeros(n, dtype=torch.int32, device=dev)
+        own = torch.zeros(n, dtype=torch.float32, device=dev)
+        lam = torch.zeros(k, dtype=torch.uint8, device=dev)
+        ctx.assign(X, f, 1, a, own, lam)
+        ref, _, _ = oracle.assign(c, oracle.init_centroids(c, ids), rows=np.arange(0, n, 191))
+        assert np.array_equal(a.cpu().numpy()[::191], ref)
+        flags = torch.zeros(k, dtype=torch.uint8, device=dev)
+        flags[k // 2:] = 1
+        ctx.update(X, a, flags, f)
+
+        def run(lo, hi, it):
+            b, e = int(c.row_ptr[lo]), int(c.row_ptr[hi])
+            rows = DeviceCsr(X.row_ptr[lo:hi + 1] - b, X.col[b:e].clone(), X.val[b:e].clone(), d)
+            pa, po = a[lo:hi].clone(), own[lo:hi].clone()
+            st = ctx.assign(rows, f, it, pa, po, lam.clone())
+            return pa, po, st["multadds"], st["icp_objects"]
+
+        for it in (1, 2):
+            small = [run(lo, min(n, lo + 37_000), it) for lo in range(0, n, 37_000)]
+            want_a, want_o = torch.cat([s[0] for s in small]), torch.cat([s[1] for s in small])
+            for hi in (40_961, 49_153, 81_920, 81_921, 98_304, 98_305, 122_880, 122_881, 147_456, 147_457, n):
+                pa, po, m, icp = run(0, hi, it)
+                assert torch.equal(pa, want_a[:hi]) and torch.equal(po, want_o[:hi]), hi
+                if hi == n:
+                    assert m == sum(s[2] for s in small) and icp == sum(s[3] for s in small) and (icp > 0) == (it == 2)
+        f.free()
+        ctx.close()
+
+
+@pytest.mark.parametrize("n", [40_960, 40_961, 81_920, 81_921, 122_880, 122_881])
+def test_split_lists_in_several_pieces_of_objects_a_wave(n):
+    # one tile of 512: equal shares up to 24 objects a wave, then grabs
+    from paper_2103_16141_amd.api import Context
+    log("pieces of a split walk, n %d" % n)
+    k, dev = 512, device()
+    X = _objects(n, torch.float32, False, 3)
+    split, plain = Context(0), Context(0, workspace_cap_bytes=1 << 40)
+    ids = np.arange(1, k + 1, dtype=np.int32)
+    ids[500] = 600   # row 501 is empty
+    out = []
+    a = torch.zeros(n, dtype=torch.int32, device=dev)
+    own = torch.zeros(n, dtype=torch.float32, device=dev)
+    lam = torch.zeros(k, dtype=torch.uint8, device=dev)
+    for ctx in (split, plain):
+        f = ctx.init_centroids(X, k, ids)
+        ctx.assign(X, f, 1, a, own, lam)
+        flags = torch.zeros(k, dtype=torch.uint8, device=dev)
+        flags[::3] = 1
+        ctx.update(X, a, flags, f)
+        for it in (1, 2):
+            a1, o1, l1 = a.clone(), own.clone(), lam.clone()
+            out.append((a1, o1, l1, ctx.assign(X, f, it, a1, o1, l1)))
+        f.free()
+    for (a1, o1, l1, s1), (a2, o2, l2, s2) in zip(out[:2], out[2:]):
+        assert s1["walk_bytes"] != s2["walk_bytes"]
+        assert torch.equal(a1, a2) and torch.equal(l1, l2) and s1["multadds"] == s2["multadds"]
+        assert s1["icp_objects"] == s2["icp_objects"]
+        assert float((o1.double() - o2.double()).abs().max()) <= 2 * 302 * 2.0 ** -24

@@ -24,6 +24,7 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
     return 1;
 }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
+int64_t shared(double terms, int32_t k, int32_t kt, int split) { return sivf::walk_shared(terms, k, kt, split != 0); }
 typedef int64_t (*fn)(int64_t);
 int64_t split(int64_t most, fn pays, fn longest, int64_t* pairs) {
     return sivf::split_range(most, [=](int64_t r) { return pays(r) != 0; }, longest, pairs);
@@ -120,3 +121,11 @@ def test_soft_backward_plans_shrink_to_less_than_eight_shares_took(plan):
         assert last == (1, 1) and attempt < 40
         # the last plan fits wherever those bytes were there
         assert least <= old + 16384
+
+
+def test_equal_shares_reach_further_for_lighter_walks(plan):
+    plan.shared.restype = ctypes.c_int64
+    shared = lambda terms, k, kt, split: plan.shared(ctypes.c_double(terms), k, kt, split)
+    assert [shared(60, k, (k + 63) // 64 * 64, 0) for k in (1, 16, 64, 300, 600, 1000, 2048)] == [24, 24, 16, 16, 16, 8, 8]
+    assert shared(100, 500, 512, 0) == 8 and shared(1e4, 1, 64, 0) == 8 and shared(0, 5, 64, 0) == 24
+    assert [shared(100, kt, kt, 1) for kt in (64, 512, 576, 4096)] == [24, 24, 16, 16]

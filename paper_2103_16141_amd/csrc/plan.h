@@ -23,17 +23,33 @@ constexpr int64_t kMaxGroups = (1 << 24) - 1;
 // 51.7) 2048; up to 3% dense, or in at most two tiles, 1536 (k = 10,000, 2%
 // dense: 86.2 with 1024, 86.0 with 1536, 88.8 with 2048; k = 1,500, 12% dense
 // 19.7 and 15.4); denser 1024 (5,000,000 objects, 6% dense: 439, 460, 490).
-// More postings never give fewer tiles: a file's arrays are made for infinitely
-// many.
-inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
+// FP32 files with many dense rows that no split walk will read: `heads` such rows
+// (0: few, or unknown, or split) are read through L2 by the plain walk, and a wide
+// tile's no longer fit.  ms with 1024 and as wide as it gets, (rows, width):
+// (399, 2048) 3.9 and 3.7, (558, 2048) 3.5 and 3.7, (715, 2048) 3.4 and 4.2, (732,
+// 2048) 6.9 and 6.8, (1,076, 2048) 11.6 and 12.8; (1,264, 1536) 2.8 and 3.3,
+// (1,010, 1536) 6.1 and 5.2; 5 tiles: (278, 2048) 58.5 and 69.3, (214, 2048) 34.4
+// and 36.4, (250, 2048) 42.5 and 41.3; 3 tiles: (382, 1728) 25.5 and 26.0, (151,
+// 1728) 9.1 and 8.7.  Halving a tile of at most 1152 never pays.
+// More postings or dense rows never give fewer tiles: a file's arrays are made for
+// infinitely many.
+inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, int64_t d, int64_t heads, int32_t* kt,
+                         int32_t* T) {
     int32_t want = k_tile;
     if (want <= 0) {
         const double density = postings / ((double)k * (double)d);
         int32_t kmax = kTileWide;
         if (bf16 && density > 0.003) kmax = density < 0.033 || k <= 2 * kTileMid ? kTileMid : kTileNarrow;
-        const int32_t t = (int32_t)(((int64_t)k + kmax - 1) / kmax);
-        const int32_t w = (int32_t)(((int64_t)k + t - 1) / t);
-        want = ((w + 63) / 64) * 64;
+        auto width = [k](int32_t most) {
+            const int32_t t = (int32_t)(((int64_t)k + most - 1) / most);
+            const int32_t w = (int32_t)(((int64_t)k + t - 1) / t);
+            return ((w + 63) / 64) * 64;
+        };
+        want = width(kmax);
+        if (!bf16 && want > 1152) {
+            const int64_t many = k > 2 * want ? 260 : want > 1536 ? 480 : 1200;
+            if (heads >= many) want = width(kTileNarrow);
+        }
     }
     *kt = want;
     *T = (int32_t)(((int64_t)k + want - 1) / want);

@@ -220,3 +220,37 @@ def test_split_lists_in_several_pieces_of_objects_a_wave(n):
         assert torch.equal(a1, a2) and torch.equal(l1, l2) and s1["multadds"] == s2["multadds"]
         assert s1["icp_objects"] == s2["icp_objects"]
         assert float((o1.double() - o2.double()).abs().max()) <= 2 * 302 * 2.0 ** -24
+
+
+def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
+    # a workspace cap keeps the walk plain; 480 dense rows and more are then read in tiles
+    # of 1,024 from the second update on, and every step is that of fixed tiles
+    from tests.test_gpu_kernel_edges import _striped
+    from paper_2103_16141_amd.api import Context
+    log("capped tiles")
+    n, d, lam, k, dev = 8_195, 2_000, 500, 2_048, device()
+    X = _striped(n, d, lam, 4, torch.float32)
+    ids = np.random.default_rng(2).choice(n, k, replace=False).astype(np.int32)
+    state = []
+    for kt, cap in ((0, 1 << 40), (512, 1 << 40), (0, 0)):
+        ctx = Context(0, k_tile=kt, workspace_cap_bytes=cap, head_density=0.55)
+        state.append([ctx, ctx.init_centroids(X, k, ids), torch.zeros(n, dtype=torch.int32, device=dev),
+                      torch.zeros(n, dtype=torch.float32, device=dev), torch.zeros(k, dtype=torch.uint8, device=dev)])
+    widths = []
+    for r in (1, 2, 3, 4):
+        widths.append([f.sizes()["k_tile"] for _, f, *_ in state])
+        st = [ctx.assign(X, f, r, a, own, l) for ctx, f, a, own, l in state]
+        for (_, _, a, _, l), s in zip(state[1:], st[1:]):
+            assert torch.equal(a, state[0][2]) and torch.equal(l, state[0][4])
+            assert all(s[q] == st[0][q] for q in ("multadds", "moved", "icp_objects", "n_invariant", "head_rows"))
+        for ctx, f, a, own, l in state:
+            ctx.update(X, a, l, f)
+    assert st[0]["head_rows"] >= 480
+    assert widths == [[2048, 512, 2048], [2048, 512, 2048], [1024, 512, 2048], [1024, 512, 2048]]
+    # the file made without a cap has no room for more tiles: a capped ctx that
+    # updates it keeps their number
+    ctx, f, a, own, l = state[2]
+    state[0][0].update(X, a, l, f)
+    assert f.sizes()["k_tile"] == 2048
+    for ctx, f, *_ in state:
+        f.free()

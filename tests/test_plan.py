@@ -12,8 +12,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HARNESS = r"""
 #include "plan.h"
 extern "C" {
-void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int32_t* kt, int32_t* T) {
-    sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, kt, T);
+void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int64_t heads, int32_t* kt, int32_t* T) {
+    sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, heads, kt, T);
 }
 int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64_t* rows, int64_t* blocks, int* whole) {
     sivf::SoftPlan p;
@@ -46,9 +46,10 @@ def plan(tmp_path_factory):
 def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
     # a file's arrays are allocated for infinitely many postings; an update
     # chooses the tiles again for the postings it expects
-    def tiles(k_tile, bf16, k, postings, d):
+    def tiles(k_tile, bf16, k, postings, d, heads):
         kt, T = ctypes.c_int32(), ctypes.c_int32()
-        plan.tiles(k_tile, bf16, k, ctypes.c_double(postings), ctypes.c_int64(d), ctypes.byref(kt), ctypes.byref(T))
+        plan.tiles(k_tile, bf16, k, ctypes.c_double(postings), ctypes.c_int64(d), ctypes.c_int64(heads), ctypes.byref(kt),
+                   ctypes.byref(T))
         return kt.value, T.value
 
     rng = np.random.default_rng(0)
@@ -57,10 +58,15 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
     for k in ks:
         for bf16 in (0, 1):
             for k_tile in (0, 64, 128, 4096):
-                _, most = tiles(k_tile, bf16, k, float("inf"), 1000)
-                for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
-                    kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000)
-                    assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt
+                for heads in (0, 200, 300, 700, 1200, 2 ** 63 - 1):
+                    _, most = tiles(k_tile, bf16, k, float("inf"), 1000, 2 ** 63 - 1 if heads else 0)
+                    for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
+                        kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000, heads)
+                        assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt
+    width = lambda k, heads: tiles(0, 0, k, 0.0, 1000, heads)[0]
+    assert [width(2048, h) for h in (0, 479, 480)] == [2048, 2048, 1024]
+    assert [width(1500, h) for h in (0, 1199, 1200)] == [1536, 1536, 768]
+    assert [width(10_000, h) for h in (259, 260)] == [2048, 1024] and width(1100, 10 ** 6) == 1152
 
 
 @pytest.mark.parametrize("objects,row,floor,want", [

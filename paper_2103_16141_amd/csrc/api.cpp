@@ -1529,7 +1529,7 @@ sivf_status sivf_soft_assign_fwd(sivf_ctx* ctx, const sivf_csr* X, const float* 
     STCHK(st);
     ctx->err = err;
     hipStream_t s = ctx->stream;
-    HIPCHK(ctx, soft_forward(Xc.n, Xc.rp, Xc.col, (const float*)Xc.val, C, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
+    HIPCHK(ctx, soft_forward(Xc.n, Xc.nnz, Xc.rp, Xc.col, (const float*)Xc.val, C, Xc.d, k, tau, lse_out, loss, w, ctx->n_cu, s));
     if (loss_host) {
         HIPCHK(ctx, hipMemcpyAsync(ctx->pin, loss, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(ctx, hipStreamSynchronize(s));

@@ -33,7 +33,7 @@ struct SoftFwdWs {
 };
 // rows per launch with the commonest terms in LDS, or 0: not so
 int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k);
-hipError_t soft_forward(int64_t N, const int64_t* rp, const int32_t* col, const float* xv, const float* C, int64_t d,
+hipError_t soft_forward(int64_t N, int64_t nnz, const int64_t* rp, const int32_t* col, const float* xv, const float* C, int64_t d,
                         int32_t k, float tau, float* lse, double* loss_dev, SoftFwdWs w, int n_cu, hipStream_t s);
 // rows [c0, c1) whose nonzeros are [p0, p1), k columns of C^T.  dS: blocks
 // [2 ceil(k / 64)][c1 - c0][32] or nullptr; dxv: dX or nullptr; dxp:

@@ -92,15 +92,20 @@ constexpr int kXcds = 8;   // workgroup b runs on XCD b mod 8
 
 // Blocks run in phases of up to 8, one block per XCD; in a phase with fewer
 // blocks than XCDs, XCDs share a block and split its rows.  A wave takes items
-// first, first + step, ... of block `blk`.
+// first, first + step, ... of block `blk`.  The workgroups are in `lanes` groups
+// (a divisor of those of an XCD), which take every lanes-th phase each.
 struct Share {
     int64_t blk, first, step;
 };
 
-__device__ inline Share phase_share(int64_t phase, int64_t nblk) {
+__device__ inline int phase_lane(int lanes) { return (int)((blockIdx.x / kXcds) / (gridDim.x / kXcds / lanes)); }
+
+__device__ inline Share phase_share(int64_t phase, int64_t nblk, int lanes = 1) {
     const int x = blockIdx.x % kXcds;
-    const int64_t wave = __builtin_amdgcn_readfirstlane((int)((blockIdx.x / kXcds) * (blockDim.x >> 6) + (threadIdx.x >> 6)));
-    const int64_t waves = (int64_t)(gridDim.x / kXcds) * (blockDim.x >> 6);
+    const unsigned groups = gridDim.x / kXcds / lanes;   // workgroups of an XCD and lane
+    const int64_t wave =
+        __builtin_amdgcn_readfirstlane((int)((blockIdx.x / kXcds) % groups * (blockDim.x >> 6) + (threadIdx.x >> 6)));
+    const int64_t waves = (int64_t)groups * (blockDim.x >> 6);
     const int nb = (int)min((int64_t)kXcds, nblk - phase * kXcds);
     const int b = x % nb, sharers = (kXcds - 1 - b) / nb + 1;
     return {phase * kXcds + b, wave * sharers + x / nb, waves * sharers};

@@ -50,6 +50,7 @@ def _needed(X, k):
     (30_000, 2_000, 20, 1_500, 100, 1_000),    # two chunks of rows, a few rows hold most nonzeros
     (6_000, 4_000, 700, 3_999, 1_000, 4_096),  # long rows throughout
     (1_000, 60_000, 30, 2_000, 50, 64),        # one block of columns
+    (67, 900, 40, 300, 5, 10_000),             # few rows, 157 blocks: phases of blocks side by side
     (25_000, 8_000, 4_000, 8_000, 5_000, 64),  # 1e8 nonzeros: two chunks for their number
     (50_000, 300, 3, 300, 49_000, 130),        # a chunk of short rows after one long row; three blocks, the last of 2
 ])

@@ -62,14 +62,15 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
 // the counter shows.  Walk in us by grabs and in equal shares, FP32, 60 terms an
 // object: 60,000 objects (12 a wave) k = 1 435 and 97, 100 479 and 390, 300 515 and
 // 465, 2,048 654 and 724; 100,000 (20) k = 16 430 and 390, 100 630 and 655; 100
-// terms, 55,000 objects, k = 500 (51,000 terms x tile width) 564 and 620.  The
+// terms, 55,000 objects, k = 500 (51,000 terms x tile width) 564 and 620; 131 terms
+// over a wide vocabulary, 42,569 objects, k = 242 (34,000) 757 and 854.  The
 // lists of a split walk: 55,000 objects, k = 500 721 and 508, 70,000, k = 1,000 887
 // and 767, k = 4,000 2,820 and 2,840; 100,000, k = 500 833 and 625, k = 2,000 2,030
 // and 2,140.
 inline int64_t walk_shared(double terms, int32_t k, int32_t kt, bool split) {
     if (split) return kt <= 512 ? 24 : 16;
     if (terms * k <= 1024.0) return 24;
-    return terms * kt <= 40000.0 ? 16 : 8;
+    return terms * kt <= 20000.0 ? 16 : 8;
 }
 
 // pairs of a range of the split walk's objects: two chunks of fill, then every

@@ -132,6 +132,6 @@ def test_soft_backward_plans_shrink_to_less_than_eight_shares_took(plan):
 def test_equal_shares_reach_further_for_lighter_walks(plan):
     plan.shared.restype = ctypes.c_int64
     shared = lambda terms, k, kt, split: plan.shared(ctypes.c_double(terms), k, kt, split)
-    assert [shared(60, k, (k + 63) // 64 * 64, 0) for k in (1, 16, 64, 300, 600, 1000, 2048)] == [24, 24, 16, 16, 16, 8, 8]
+    assert [shared(60, k, (k + 63) // 64 * 64, 0) for k in (1, 16, 64, 300, 600, 1000, 2048)] == [24, 24, 16, 16, 8, 8, 8]
     assert shared(100, 500, 512, 0) == 8 and shared(1e4, 1, 64, 0) == 8 and shared(0, 5, 64, 0) == 24
     assert [shared(100, kt, kt, 1) for kt in (64, 512, 576, 4096)] == [24, 24, 16, 16]

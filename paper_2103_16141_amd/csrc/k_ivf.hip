@@ -99,40 +99,32 @@ hipError_t ivf_perm(const uint8_t* lam, int32_t k, const int64_t* nnz, int32_t* 
     return hipGetLastError();
 }
 
-// Calls f(centroid j, entry address) for the entries of all centroids in pieces
-// of kPiece consecutive ones per wave, wherever the centroids begin.  (A wave
-// per centroid left 1,000 waves with 30,000 entries each: presence bits 0.57,
-// file fill 2.07 ms at k = 1,000, D = 100,000; 0.25 and 1.14 in pieces.)
+// Calls f(centroid j, first entry's address, past the last, lane, lanes) for the
+// entries of all centroids in pieces of kPiece consecutive ones per wave, wherever
+// the centroids begin.  (A wave per centroid left 1,000 waves with 30,000 entries
+// each: presence bits 0.57, file fill 2.07 ms at k = 1,000, D = 100,000; 0.25 and
+// 1.14 in pieces.)
 constexpr int kPiece = 256;
 
 template <typename F>
 __device__ inline void each_entry(const Store& st, int32_t k, const int64_t* __restrict__ cscan, F f) {
-    const int lane = threadIdx.x & 63;
     const int64_t n = cscan[k], nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-    for (int64_t p0 = wave * kPiece; p0 < n; p0 += nw * kPiece) {
-        const int64_t p1 = min(n, p0 + kPiece);
-        int64_t lo = 0, hi = k - 1;   // last centroid starting at or before p0
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (cscan[mid] <= p0) lo = mid;
-            else hi = mid - 1;
-        }
-        for (int64_t j = lo; j < k && cscan[j] < p1; ++j) {
-            const int64_t a = max(p0, cscan[j]), e = min(p1, cscan[j + 1]), b = st.start[j] - cscan[j];
-            if (a < e) f(j, b + a, b + e, lane);
-        }
-    }
+    for (int64_t p0 = wave * kPiece; p0 < n; p0 += nw * kPiece)
+        piece_entries(cscan, k, p0, min(n, p0 + kPiece), [&](int64_t j, int64_t a, int64_t e, int first, int step) {
+            const int64_t b = st.start[j] - cscan[j];
+            f(j, b + a, b + e, first, step);
+        });
 }
 
 __global__ __launch_bounds__(256) void k_ivf_bits(Store st, int32_t k, int64_t d, const int64_t* __restrict__ cscan,
                                                   const int32_t* __restrict__ iperm,
                                                   unsigned long long* __restrict__ bm) {
-    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int lane) {
+    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int first, int step) {
         const int64_t q = iperm[j];
         unsigned long long* row = bm + (q >> 6) * d;
         const unsigned long long bit = 1ull << (q & 63);
-        for (int64_t p = a + lane; p < e; p += 64) {
+        for (int64_t p = a + first; p < e; p += step) {
             const int32_t t = st.term[p];
             if (t >= 0 && t < d) atomicOr(&row[t], bit);
         }
@@ -250,7 +242,7 @@ __global__ __launch_bounds__(256) void k_ivf_fill(Store st, int32_t k, int64_t d
                                                   const int64_t* __restrict__ off, uint16_t* __restrict__ cid,
                                                   float* __restrict__ v32, uint16_t* __restrict__ v16,
                                                   double* __restrict__ v64) {
-    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int lane) {
+    each_entry(st, k, cscan, [&](int64_t j, int64_t a, int64_t e, int first, int step) {
         const int64_t q = iperm[j];
         const int part = q >= n_moving ? 1 : 0;
         const int64_t tile = q / kt, w = q >> 6;
@@ -258,7 +250,7 @@ __global__ __launch_bounds__(256) void k_ivf_fill(Store st, int32_t k, int64_t d
         const unsigned long long pm = (part ? ~mv : mv) & ((1ull << (q & 63)) - 1ull);
         const uint16_t* pre = part ? pre1 : pre0;
         const uint16_t local = (uint16_t)(q - tile * kt);
-        for (int64_t p = a + lane; p < e; p += 64) {
+        for (int64_t p = a + first; p < e; p += step) {
             const int64_t t = st.term[p];
             const double u = st.val[p];
             const int64_t rank = pre[w * d + t] + __popcll(bm[w * d + t] & pm);

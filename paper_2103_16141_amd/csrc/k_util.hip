@@ -457,24 +457,16 @@ hipError_t csr_to_store(const int64_t* ptr, const int32_t* col, const double* va
 
 __global__ __launch_bounds__(256) void k_store_export(Store st, int32_t k, const int64_t* __restrict__ c_ptr,
                                                       int32_t* c_col, double* c_val) {
-    const int lane = threadIdx.x & 63;
     const int64_t n = c_ptr[k], nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
     const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
     for (int64_t p0 = wave * kCopyPiece; p0 < n; p0 += nw * kCopyPiece) {
-        const int64_t p1 = min(n, p0 + kCopyPiece);
-        int64_t lo = 0, hi = k - 1;   // last centroid starting at or before p0
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (c_ptr[mid] <= p0) lo = mid;
-            else hi = mid - 1;
-        }
-        for (int64_t j = lo; j < k && c_ptr[j] < p1; ++j) {
-            const int64_t a = max(p0, c_ptr[j]), e = min(p1, c_ptr[j + 1]), b = st.start[j] - c_ptr[j];
-            for (int64_t p = a + lane; p < e; p += 64) {
+        piece_entries(c_ptr, k, p0, min(n, p0 + kCopyPiece), [&](int64_t j, int64_t a, int64_t e, int first, int step) {
+            const int64_t b = st.start[j] - c_ptr[j];
+            for (int64_t p = a + first; p < e; p += step) {
                 if (c_col) c_col[p] = st.term[b + p];
                 if (c_val) c_val[p] = st.val[b + p];
             }
-        }
+        });
     }
 }
 

@@ -88,6 +88,35 @@ __device__ inline int32_t wave_min_i32(int32_t v) {
 // error <= nnz * 2^-53): square root, then a 2^-30 relative margin.
 __device__ inline double centroid_norm_bound(double acc) { return sqrt(acc) * (1.0 + 0x1p-30) + 0x1p-1000; }
 
+// last centroid in [lo, hi] whose entries start at or before p (start ascends;
+// empty ones share their successor's)
+__device__ inline int64_t start_before(const int64_t* __restrict__ start, int64_t lo, int64_t hi, int64_t p) {
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (start[mid] <= p) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Calls f(centroid j, first entry, past the last, lane, lanes) for the entries
+// [p0, p1) of k centroids starting at start[j], by one wave: centroid by centroid
+// with all lanes, or, where the piece holds many short ones, an entry per lane
+// (600 centroids of one entry: export 385 -> 150 us).
+template <typename F>
+__device__ inline void piece_entries(const int64_t* __restrict__ start, int64_t k, int64_t p0, int64_t p1, F f) {
+    const int lane = lane_id();
+    const int64_t lo = start_before(start, 0, k - 1, p0), hi = start_before(start, lo, k - 1, p1 - 1);
+    if (hi - lo >= 16) {
+        for (int64_t p = p0 + lane; p < p1; p += 64) f(start_before(start, lo, hi, p), p, p + 1, 0, 1);
+        return;
+    }
+    for (int64_t j = lo; j <= hi; ++j) {
+        const int64_t a = max(p0, start[j]), e = min(p1, start[j + 1]);
+        if (a < e) f(j, a, e, lane, 64);
+    }
+}
+
 constexpr int kXcds = 8;   // workgroup b runs on XCD b mod 8
 
 // Blocks run in phases of up to 8, one block per XCD; in a phase with fewer

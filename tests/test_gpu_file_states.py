@@ -203,3 +203,25 @@ def test_more_dense_rows_than_a_launch_has_workgroups(posting):
     f.free()
     ctx.close()
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("lens", [[1], [0, 0, 1], [2, 0, 3, 1], [15, 17, 0, 16, 18], [0] * 40 + [700] + [1] * 30],
+                         ids=["ones", "mostly empty", "short", "about sixteen a piece", "a long one among short"])
+def test_files_of_many_short_centroids(lens):
+    # a piece of entries with 16 centroids and more is taken an entry per lane
+    import oracle
+    log("short centroids %s" % lens[:6])
+    k, d = 3_001, 800
+    rng = np.random.default_rng(len(lens))
+    m = np.resize(lens, k)
+    ptr = np.concatenate([[0], np.cumsum(m)]).astype(np.int64)
+    col = np.concatenate([np.sort(rng.choice(d, q, replace=False)) for q in m] + [np.zeros(0)]).astype(np.int32)
+    val = rng.standard_normal(len(col))
+    lam = (rng.random(k) < 0.5).astype(np.uint8)
+    f = _ctx().build_centroid_ivf(*[torch.from_numpy(x).to(device()) for x in (ptr, col, val)], d,
+                                  torch.from_numpy(lam).to(device()))
+    ex = {q: t.cpu().numpy() for q, t in f.export().items()}
+    ref = oracle.build_ivf(oracle.Centroids(k, d, ptr, col, val), lam)
+    assert np.array_equal(ex["c_ptr"], ptr) and np.array_equal(ex["c_col"], col) and np.array_equal(ex["c_val"], val)
+    assert np.array_equal(ex["term_ptr"], ref.term_ptr) and np.array_equal(ex["split"], ref.split)
+    assert np.array_equal(ex["p_cid"], ref.cid) and np.array_equal(ex["p_val"], ref.val)

@@ -1064,7 +1064,7 @@ sivf_status assign_impl(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f
     HIPCHK(ctx, hipEventRecord(ctx->ev[0], s));
     if (n > 0) {
         const int bf16 = f->pdt == SIVF_BF16;
-        const double terms = (double)Xc.nnz / (double)n;
+        const double terms = (double)Xc.nnz / (double)n * (B.range ? 1.0 - f->sfrac : 1.0);
         const int bpc = walk_blocks_per_cu(f->kt, bf16, A.cbicp, B.range > 0);
         if (B.range) {
             WalkArgs R = A;

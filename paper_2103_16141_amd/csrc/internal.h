@@ -267,8 +267,8 @@ hipError_t store_export(const Store st, int32_t k, const int64_t* c_ptr, int32_t
                         hipStream_t s);
 
 // assignment
-// walks tiles [tb, te) for every object, of `terms` terms on average; `work` is a
-// zeroed grab counter
+// walks tiles [tb, te) for every object, of `terms` terms to walk on average; `work`
+// is a zeroed grab counter
 hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
                      hipStream_t s);
 int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split);

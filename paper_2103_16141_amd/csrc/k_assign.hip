@@ -846,15 +846,15 @@ hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_wav
     int blocks = (grid_waves + kWalkWaves - 1) / kWalkWaves;
     if (blocks < 1) blocks = 1;
     // Many objects: a wave grabs them from the work counter, which evens out
-    // their costs, 8 at a time or at least four times (60,000 objects, BF16, one
-    // tile: 1.36 ms by twos, 1.64 by eights, 1.47 in equal shares).  Fewer
-    // (walk_shared) cost the counter more than that, so the waves take equal shares,
+    // their costs (walk_grab: 60,000 objects, BF16, one tile 1.36 ms by twos, 1.64 by
+    // eights, 1.47 in equal shares).  Up to 8 objects a wave, and more where they are
+    // light (walk_shared), the counter costs more than that, so the waves take equal shares,
     // in pieces of at most 8 objects spread over the batch: 64 objects, k = 100, 260
     // (8 waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects,
     // k = 1,531, BF16 842 -> 346 us.
     const int64_t waves = (int64_t)blocks * kWalkWaves;
-    const bool shared = a.n <= walk_shared(terms, a.k, a.kt, a.S != nullptr) * waves;
-    int share = (int)std::max<int64_t>(1, std::min<int64_t>(8, a.n / (waves * 4)));
+    const bool shared = walk_shared(a.n, waves, terms, a.kt, a.S != nullptr);
+    int share = (int)walk_grab(a.n, waves);
     if (shared) {
         const int64_t pieces = std::max<int64_t>(1, (a.n + 8 * waves - 1) / (8 * waves));   // a wave's
         share = (int)std::max<int64_t>(1, (a.n + waves * pieces - 1) / (waves * pieces));

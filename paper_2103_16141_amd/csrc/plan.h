@@ -55,22 +55,30 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
     *T = (int32_t)(((int64_t)k + want - 1) / want);
 }
 
-// Objects per wave up to which the waves of a walk take equal shares instead of
-// grabbing them from a counter.  A grab costs 15 ns, one after the other for all
-// waves: 22,000 of them (44,000 objects by twos) hold a walk that could be done in
-// 80 us to 340.  The heavier an object, the more uneven the shares and the less
-// the counter shows.  Walk in us by grabs and in equal shares, FP32, 60 terms an
-// object: 60,000 objects (12 a wave) k = 1 435 and 97, 100 479 and 390, 300 515 and
-// 465, 2,048 654 and 724; 100,000 (20) k = 16 430 and 390, 100 630 and 655; 100
-// terms, 55,000 objects, k = 500 (51,000 terms x tile width) 564 and 620; 131 terms
-// over a wide vocabulary, 42,569 objects, k = 242 (34,000) 757 and 854.  The
-// lists of a split walk: 55,000 objects, k = 500 721 and 508, 70,000, k = 1,000 887
-// and 767, k = 4,000 2,820 and 2,840; 100,000, k = 500 833 and 625, k = 2,000 2,030
-// and 2,140.
-inline int64_t walk_shared(double terms, int32_t k, int32_t kt, bool split) {
-    if (split) return kt <= 512 ? 24 : 16;
-    if (terms * k <= 1024.0) return 24;
-    return terms * kt <= 20000.0 ? 16 : 8;
+// Objects a wave grabs from a walk's counter at a time: 8, or at least four times.
+inline int64_t walk_grab(int64_t n, int64_t waves) {
+    return std::max<int64_t>(1, std::min<int64_t>(8, n / (waves * 4)));
+}
+
+// Whether the waves of a walk take equal shares of n objects instead, of `terms`
+// terms on average (split: of the listed ones).  A grab costs 15 ns, one after the
+// other for all waves: 22,000 of them (44,000 objects by twos) hold a walk that
+// could be done in 80 us to 340.  But the heavier an object, the more uneven the
+// shares, and the less the counter shows: the line is where the objects of a grab
+// take about as long as the grab itself, by an estimate that fits these.  Walk in us by
+// grabs and in equal shares, FP32, 60 terms an object: 60,000 objects (12 a wave,
+// by twos) k = 1 435 and 97, 100 479 and 390, 300 515 and 465, 2,048 654 and 724;
+// 100,000 (by fours) k = 16 430 and 390, 100 630 and 655; 100 terms, 55,000 objects,
+// k = 500 564 and 620; 131 terms over a wide vocabulary, 42,569 objects, k = 242 757
+// and 854; 273 terms, 88,424 objects, k = 1 1,960 and 2,210.  Lists of a split walk,
+// 100 terms, about 45 listed: 55,000 objects, k = 500 721 and 508, k = 2,000 1,200
+// and 1,216; 70,000, k = 1,000 993 and 958; 100,000, k = 500 914 and 770, k = 1,000
+// 1,281 and 1,324.
+inline bool walk_shared(int64_t n, int64_t waves, double terms, int32_t kt, bool split) {
+    if (n <= 8 * waves) return true;
+    if (n > 24 * waves) return false;
+    const double object = terms * (0.065 + (split ? 0.000045 : 0.00009) * kt);   // ns of the whole chip
+    return object * (double)walk_grab(n, waves) <= 17.0;
 }
 
 // pairs of a range of the split walk's objects: two chunks of fill, then every

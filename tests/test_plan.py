@@ -24,7 +24,9 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
     return 1;
 }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
-int64_t shared(double terms, int32_t k, int32_t kt, int split) { return sivf::walk_shared(terms, k, kt, split != 0); }
+int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
+    return sivf::walk_shared(n, waves, terms, kt, split != 0);
+}
 typedef int64_t (*fn)(int64_t);
 int64_t split(int64_t most, fn pays, fn longest, int64_t* pairs) {
     return sivf::split_range(most, [=](int64_t r) { return pays(r) != 0; }, longest, pairs);
@@ -130,8 +132,16 @@ def test_soft_backward_plans_shrink_to_less_than_eight_shares_took(plan):
 
 
 def test_equal_shares_reach_further_for_lighter_walks(plan):
-    plan.shared.restype = ctypes.c_int64
-    shared = lambda terms, k, kt, split: plan.shared(ctypes.c_double(terms), k, kt, split)
-    assert [shared(60, k, (k + 63) // 64 * 64, 0) for k in (1, 16, 64, 300, 600, 1000, 2048)] == [24, 24, 16, 16, 8, 8, 8]
-    assert shared(100, 500, 512, 0) == 8 and shared(1e4, 1, 64, 0) == 8 and shared(0, 5, 64, 0) == 24
-    assert [shared(100, kt, kt, 1) for kt in (64, 512, 576, 4096)] == [24, 24, 16, 16]
+    def shared(n, terms, kt, split=0, waves=5_120):
+        return plan.shared(ctypes.c_int64(n), ctypes.c_int64(waves), ctypes.c_double(terms), kt, split)
+
+    assert shared(1, 1e6, 4096) and shared(40_960, 1e6, 4096)            # up to 8 objects a wave whatever they cost
+    assert not shared(122_881, 0, 64) and not shared(122_881, 0, 64, 1)  # never beyond 24
+    assert [shared(60_000, 60, kt) for kt in (64, 128, 320, 1024)] == [1, 1, 1, 0]
+    assert [shared(100_000, 60, kt) for kt in (64, 128)] == [1, 0]
+    assert not shared(55_000, 100, 512) and not shared(42_569, 131, 256) and not shared(88_424, 273, 64, waves=6_144)
+    assert [shared(55_000, 45, kt, 1) for kt in (512, 1024)] == [1, 1] and not shared(55_000, 45, 2048, 1, waves=4_096)
+    for n in (41_000, 60_000, 80_000, 100_000, 122_880):   # fewer terms or narrower tiles never take it away
+        for kt in (64, 512, 2048):
+            got = [shared(n, t, kt) for t in (0, 5, 20, 60, 200, 1000)]
+            assert got == sorted(got, reverse=True) and all(shared(n, t, 64) >= g for t, g in zip((0, 5, 20), got))

@@ -417,7 +417,6 @@ bool split_pays(double h, int64_t objects, const sivf_ivf* f) {
     return (h - 38.0) * (double)objects * (double)f->k >= 1e9 * f->T;
 }
 
-
 // ---------------------------------------------------------------- file storage
 // Several arrays in one allocation (each 256-byte aligned; an allocation and its
 // release cost 20 to 60 us whatever their size: a restart's file took 19 of
@@ -523,9 +522,10 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 // Structure f's current centroids by the flags in f->lam (Alg. 5 second half):
 // positions put the moving centroids first, then the file is built by position.
 // norms: f->cnorm has yet to be computed (the update fills it).
-// postings: an estimate of their entries.  X: objects likely to walk it
-// (nullptr: unknown); the split walk's rows are made if it pays for them.  A file built from given centroids gets none before its first
-// update (they take 0.17 ms of a 3.0 ms restart, and nobody may walk it so).
+// postings: an estimate of their entries.  X: objects likely to walk it (nullptr:
+// unknown); the split walk's rows are made if it pays for them.  A file built from
+// given centroids gets none before its first update (they take 0.17 ms of a 3.0 ms
+// restart, and nobody may walk it so).
 sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, const Csr* X) {
     // the tiles follow from the options the file was made with: a ctx with others
     // may update it, and its arrays have room for T_max tiles
@@ -608,7 +608,8 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // (the last requests of an update: they are optional)
     uint32_t* wt = nullptr;
     int32_t* sterm2 = nullptr;
-    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows && SH * kpad * esz <= kHeadMaxBytes && SH * f->T <= kMaxGroups &&
+    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows &&
+        SH * kpad * esz <= kHeadMaxBytes && SH * f->T <= kMaxGroups &&
         rows_reserve(&f->sval, &f->scap, SH, true) == SIVF_OK &&
         ws_optional(ctx, {{"split_wt", (size_t)SH * 4, (void**)&wt}, {"split_term2", (size_t)SH * 4, (void**)&sterm2}})) {
         HIPCHK(ctx, split_order(sterm, f->seg, f->T, f->v32, SH, wt, sterm2, f->srow, meta, ctx->stream));

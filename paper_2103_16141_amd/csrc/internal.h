@@ -231,7 +231,8 @@ struct IvfBuildWs {
 };
 int64_t ivf_w64(int32_t k);
 // positions: moving centroids (flag 0) first, each group in ascending id;
-// cscan [k + 1]: exclusive scan of nnz; meta [3]: moving centroids, entries, 0
+// cscan [k + 1]: exclusive scan of nnz; meta [kMeta]: [0] moving centroids, [1]
+// entries, the counts that come later ([2], [4] .. [6]) cleared
 hipError_t ivf_perm(const uint8_t* lam, int32_t k, const int64_t* nnz, int32_t* perm, int32_t* iperm, int64_t* cscan,
                     int64_t* meta, hipStream_t s);
 hipError_t ivf_count(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T, const int32_t* iperm,

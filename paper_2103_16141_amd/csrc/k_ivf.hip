@@ -275,9 +275,9 @@ hipError_t ivf_fill(const Store st, int32_t k, int64_t d, int32_t kt, int32_t T,
 // ---------------------------------------------------------------- dense head rows
 // A memory layout of this implementation (not the paper's): a term whose
 // lists hold at least min_len postings gets a row of kpad = T * ktp values,
-// one per centroid id (zero where the centroid lacks the term), rounded to
-// the posting dtype exactly as its postings are.  Rows are numbered in term
-// order.  Each tile's kt centroids take ktp = kt rounded up to 512 slots.
+// one per position (zero where the centroid lacks the term), rounded to
+// the posting dtype exactly as its postings are.  Rows are numbered by atomics (no
+// result depends on it).  Each tile's kt centroids take ktp = kt rounded up to 512 slots.
 // FP32 rows hold the tile's centroids in order.  BF16 rows interleave each
 // 512-centroid block so that one 16-byte load gives a lane both of its
 // 4-centroid groups: slots 8l..8l+3 hold centroids 4l..4l+3 of the block,

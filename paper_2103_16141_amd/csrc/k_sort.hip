@@ -51,6 +51,7 @@ __global__ __launch_bounds__(kFoldThreads) void k_sort_hist(SortArgs<V> A, int64
     table[(int64_t)threadIdx.x * A.ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
+// (values go through LDS as floats)
 struct SortLds {
     uint32_t key[kFoldTile];
     int32_t row[kFoldTile];
@@ -64,6 +65,7 @@ template <int KIND, typename V>
 __global__ __launch_bounds__(kFoldThreads) void k_sort_move(SortArgs<V> A, const int64_t* __restrict__ table,
                                                             int32_t* __restrict__ okey, int32_t* __restrict__ orow,
                                                             V* __restrict__ oval) {
+    static_assert(sizeof(V) == sizeof(float), "a wider value would be rounded in LDS");
     __shared__ SortLds L;
     const int tid = threadIdx.x;
     const int64_t n = A.in.n, lo = (int64_t)blockIdx.x * kFoldTile;
@@ -147,9 +149,6 @@ hipError_t sort_entries(const SortIn<V>& in, int64_t nkeys, const SortWs<V>& w, 
 }
 template hipError_t sort_entries<float>(const SortIn<float>&, int64_t, const SortWs<float>&, const int32_t**,
                                         const int32_t**, const float**, hipStream_t);
-template hipError_t sort_entries<double>(const SortIn<double>&, int64_t, const SortWs<double>&, const int32_t**,
-                                         const int32_t**, const double**, hipStream_t);
-
 __global__ void k_sort_starts(int64_t nkeys, int64_t n, const int32_t* __restrict__ key, int64_t* __restrict__ ptr) {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t > nkeys) return;

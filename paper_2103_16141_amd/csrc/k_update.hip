@@ -107,7 +107,7 @@ hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int
 // members' values in ascending object id.  Only additions to the same term are
 // ordered, so a workgroup takes kFoldTile nonzeros of a cluster's members at a
 // time (in member order), sorts them stably by term in LDS (radix passes of at
-// most 7 bits), and every run of one term is folded by a thread of its own, in
+// most 9 bits), and every run of one term is folded by a thread of its own, in
 // member order:
 //   * a cluster of at most kFoldTile nonzeros is done after one tile;
 //   * a longer one carries its sums from tile to tile in a dense FP64 row of

@@ -148,3 +148,45 @@ def test_soft_gradient_of_a_large_call_without_dense_terms():
     dC, dX = ctx.soft_assign_bwd(X, C, 0.05, lse, 0.9)
     pC, pX = _ctx(workspace_cap_bytes=1 << 40).soft_assign_bwd(X, C, 0.05, lse, 0.9)
     assert torch.equal(dC, pC) and torch.equal(dX, pX) and bool((dC != 0).any())
+
+
+@pytest.mark.parametrize("d,k", [
+    (16_777_215, 3),    # the last width whose slices a 4 GiB descriptor holds
+    (16_777_216, 70),   # the first read by 64-bit offsets; two blocks of columns
+    (20_000_000, 3),
+])
+def test_soft_form_of_very_wide_rows(d, k):
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("wide rows d %d k %d" % (d, k))
+    dev, tau, grad = device(), 0.05, 0.9
+    g = torch.Generator(device=dev).manual_seed(d % 1000 + k)
+    pool = torch.cat([torch.arange(100), d // 2 + torch.arange(100), d - 200 + torch.arange(200)]).to(dev)
+    lens = 1 + (3 * torch.arange(134, device=dev)) % 200   # each number of 16-term groups, and more than 8
+    n = lens.numel()
+    order = torch.rand(n, 400, device=dev, generator=g).argsort(1)
+    order[0] = torch.arange(399, -1, -1, device=dev)       # the last term alone
+    take = torch.zeros(n, 400, dtype=torch.bool, device=dev)
+    take.scatter_(1, order, torch.arange(400, device=dev)[None, :] < lens[:, None])
+    D = torch.where(take, torch.rand(n, 400, device=dev, generator=g) + 0.1, 0.0)
+    D /= torch.linalg.vector_norm(D, dim=1, keepdim=True)
+    rp = torch.cat([torch.zeros(1, dtype=torch.int64, device=dev), take.sum(1).cumsum(0)])
+    X = DeviceCsr(rp, pool[take.nonzero()[:, 1]].int().contiguous(), D[take].contiguous(), d)
+    c = torch.rand(k, 400, device=dev, generator=g)
+    c /= torch.linalg.vector_norm(c, dim=1, keepdim=True)
+    C = torch.zeros(k, d, device=dev)
+    C[:, pool] = c
+    S = D.double() @ c.double().T / tau
+    P = torch.softmax(S, 1)
+    ctx = _ctx()
+    lse, loss = ctx.soft_assign_fwd(X, C, tau)
+    dC, dX = ctx.soft_assign_bwd(X, C, tau, lse, grad)
+    ctx.close()
+    # a sum of at most 200 products of unit vectors' entries over tau; exp and log add 1e-5
+    assert float((lse.double() - torch.logsumexp(S, 1)).abs().max()) <= 202 * 2.0 ** -24 / tau + 1e-5
+    # the terms of every sum have one sign, and P is off by the error of S and lse
+    ref = -grad / tau * (P.T.contiguous() @ D.double())
+    assert bool(((dC[:, pool].double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
+    ref = (-grad / tau * (P @ c.double()))[take]
+    assert bool(((dX.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
+    dC[:, pool] = 0.0
+    assert not bool(dC.any())

@@ -305,9 +305,11 @@ __global__ __launch_bounds__(256) void k_soft_fwd(int64_t c0, int64_t c1, const 
 }
 
 // lse_i = M + log sum_b psum_b exp(pmax_b - M), M = max_b pmax_b, blocks in
-// order, and the FP64 sum of each workgroup's lse in a fixed order.  16 blocks'
-// values are loaded at a time: few rows of many blocks wait for little else (300
-// rows, k = 20,000: forward 379 -> 280 us; 2,000 rows, k = 4,096: 179 -> 156).
+// order, and the FP64 sum of each workgroup's lse in a fixed order.  U blocks'
+// values are loaded at a time: few rows of many blocks wait for little else (U =
+// 16 against 1: 300 rows, k = 20,000: forward 379 -> 280 us; 2,000 rows, k = 4,096:
+// 179 -> 156; of two blocks U = 16 takes 3.8 us for 3.0).
+template <int U>
 __global__ __launch_bounds__(256) void k_soft_lse(int64_t n, int64_t nblk, const float* __restrict__ pmax,
                                                   const float* __restrict__ psum, float* __restrict__ lse,
                                                   double* __restrict__ part) {
@@ -316,23 +318,23 @@ __global__ __launch_bounds__(256) void k_soft_lse(int64_t n, int64_t nblk, const
     double l = 0.0;
     if (i < n) {
         float M = -INFINITY;
-        for (int64_t b = 0; b < nblk; b += 16) {
-            float px[16];
+        for (int64_t b = 0; b < nblk; b += U) {
+            float px[U];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) px[u] = b + u < nblk ? pmax[(b + u) * n + i] : -INFINITY;
+            for (int u = 0; u < U; ++u) px[u] = b + u < nblk ? pmax[(b + u) * n + i] : -INFINITY;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) M = fmaxf(M, px[u]);
+            for (int u = 0; u < U; ++u) M = fmaxf(M, px[u]);
         }
         float z = 0.0f;
-        for (int64_t b = 0; b < nblk; b += 16) {
-            float px[16], ps[16];
+        for (int64_t b = 0; b < nblk; b += U) {
+            float px[U], ps[U];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
+            for (int u = 0; u < U; ++u) {
                 px[u] = b + u < nblk ? pmax[(b + u) * n + i] : -INFINITY;
                 ps[u] = b + u < nblk ? psum[(b + u) * n + i] : 0.0f;
             }
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (px[u] > -INFINITY) z += ps[u] * expf(px[u] - M);
                 else if (ps[u] != 0.0f) z += ps[u];   // not a number
             }
@@ -539,7 +541,7 @@ hipError_t soft_forward(int64_t N, int64_t nnz, const int64_t* rp, const int32_t
                                    1.0f / tau, lanes, pmax, psum);
         }
         const int64_t wgs = (n + 255) / 256;
-        hipLaunchKernelGGL(k_soft_lse, dim3((unsigned)wgs), dim3(256), 0, s, n, nblk, w.pmax, w.psum, lse + c0,
+        hipLaunchKernelGGL(nblk <= 4 ? k_soft_lse<4> : k_soft_lse<16>, dim3((unsigned)wgs), dim3(256), 0, s, n, nblk, w.pmax, w.psum, lse + c0,
                            w.part + parts);
         parts += wgs;
     }

@@ -188,15 +188,15 @@ __device__ inline bool finite_bits(double v) {
 
 // Workgroups are large because each adds its count to one word, 15 ns in turn: with
 // 2,048 of 256 threads a whole check of 5,000,000 rows of one nonzero took 59 us, of
-// 200,000 rows of 60 58; so 41 and 40.
-constexpr int kValidateThreads = 1024;
-
-template <typename V>
-__global__ __launch_bounds__(kValidateThreads) void k_validate(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                  const V* __restrict__ val, int64_t n, int64_t d, int64_t stated,
-                                                  int vec, unsigned long long* flags) {
-    __shared__ int sh_diff[kValidateThreads / 64];
-    __shared__ unsigned sh_bad[kValidateThreads / 64];
+// 200,000 rows of 60 58; so 41 and 40.  Small inputs, whose groups are few, take
+// 256 (the kernel, 256 and 1,024 threads: 8,000 nonzeros 3.1 and 3.3 us, 32,000 3.2
+// and 3.7, 64,000 3.5 both, 130,000 4.0 and 3.7, 520,000 8.5 and 4.7).
+template <typename V, int T>
+__global__ __launch_bounds__(T) void k_validate(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                const V* __restrict__ val, int64_t n, int64_t d, int64_t stated,
+                                                int vec, unsigned long long* flags) {
+    __shared__ int sh_diff[T / 64];
+    __shared__ unsigned sh_bad[T / 64];
     const int64_t nnz = min(stated, rp[n]);   // negative: none
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, nt = (int64_t)gridDim.x * blockDim.x;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kValidateThreads) void k_validate(const int64_t* __
         int dsum = 0;
         unsigned b = 0;
 #pragma unroll
-        for (int w = 0; w < kValidateThreads / 64; ++w) {
+        for (int w = 0; w < T / 64; ++w) {
             dsum += sh_diff[w];
             b |= sh_bad[w];
         }
@@ -361,14 +361,19 @@ hipError_t validate_csr(const int64_t* rp, const int32_t* col, const void* val, 
     if (e != hipSuccess || n <= 0) return e;
     // 16-byte loads need both arrays aligned to them (a caller may pass slices)
     const int vec = (((uintptr_t)col | (uintptr_t)val) & 15) == 0;
-    constexpr int kT = kValidateThreads;
-    const int64_t blocks = std::min<int64_t>(512, std::max<int64_t>((nnz + 4 * kT - 1) / (4 * kT), (n + kT - 1) / kT));
-    if (f64)
-        hipLaunchKernelGGL(k_validate<double>, dim3((unsigned)blocks), dim3(kT), 0, s, rp, col, (const double*)val, n, d,
-                           nnz, vec, flags);
+    const int64_t want = std::max<int64_t>((nnz + 3) / 4, n);   // threads
+    const int T = want <= (1 << 14) ? 256 : 1024;
+    const dim3 grid((unsigned)std::min<int64_t>(512, (want + T - 1) / T));
+    const float* f = (const float*)val;
+    const double* g = (const double*)val;
+    if (f64 && T == 256)
+        hipLaunchKernelGGL((k_validate<double, 256>), grid, dim3(T), 0, s, rp, col, g, n, d, nnz, vec, flags);
+    else if (f64)
+        hipLaunchKernelGGL((k_validate<double, 1024>), grid, dim3(T), 0, s, rp, col, g, n, d, nnz, vec, flags);
+    else if (T == 256)
+        hipLaunchKernelGGL((k_validate<float, 256>), grid, dim3(T), 0, s, rp, col, f, n, d, nnz, vec, flags);
     else
-        hipLaunchKernelGGL(k_validate<float>, dim3((unsigned)blocks), dim3(kT), 0, s, rp, col, (const float*)val, n, d, nnz,
-                           vec, flags);
+        hipLaunchKernelGGL((k_validate<float, 1024>), grid, dim3(T), 0, s, rp, col, f, n, d, nnz, vec, flags);
     return hipGetLastError();
 }
 

@@ -225,3 +225,35 @@ def test_files_of_many_short_centroids(lens):
     assert np.array_equal(ex["c_ptr"], ptr) and np.array_equal(ex["c_col"], col) and np.array_equal(ex["c_val"], val)
     assert np.array_equal(ex["term_ptr"], ref.term_ptr) and np.array_equal(ex["split"], ref.split)
     assert np.array_equal(ex["p_cid"], ref.cid) and np.array_equal(ex["p_val"], ref.val)
+
+
+@pytest.mark.parametrize("n,per", [
+    (16_384, 1), (16_385, 1),       # rows: the last size of small workgroups, the first of large ones
+    (64, 1_024), (5, 13_108),       # nonzeros: 65,536 and 65,540
+    (1, 4), (700_000, 1),           # a thread; more rows than the groups have threads
+])
+def test_validation_errors_at_the_ends_of_its_workgroups(n, per):
+    from paper_2103_16141_amd._native import SivfError
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("validation n %d per %d" % (n, per))
+    ctx, dev, nnz = _ctx(), device(), n * per
+    rp = torch.arange(n + 1, device=dev) * per
+    col = torch.arange(per, dtype=torch.int32, device=dev).repeat(n)
+    val = torch.full((nnz,), per ** -0.5, device=dev)
+    ctx.validate(DeviceCsr(rp, col, val, per))
+    for at in sorted({0, min(1_023, nnz - 1), min(1_024, nnz - 1), min(4_096, nnz - 1), nnz - 1}):
+        for kind, arr, v in (("RANGE", col, per), ("NONFINITE", val, float("inf"))):
+            bad = arr.clone()
+            bad[at] = v
+            X = DeviceCsr(rp, bad if arr is col else col, bad if arr is val else val, per)
+            with pytest.raises(SivfError) as err:
+                ctx.validate(X)
+            if kind == "RANGE" and at % per < per - 1:
+                kind = "UNSORTED"   # above its right neighbour too, which is what is reported
+            assert err.value.name == "SIVF_E_" + kind and "row %d " % (at // per) in str(err.value)
+    if per > 1:   # equal columns in the last row
+        bad = col.clone()
+        bad[-1] = bad[-2]
+        with pytest.raises(SivfError) as err:
+            ctx.validate(DeviceCsr(rp, bad, val, per))
+        assert err.value.name == "SIVF_E_UNSORTED" and "row %d " % (n - 1) in str(err.value)

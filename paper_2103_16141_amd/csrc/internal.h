@@ -270,13 +270,13 @@ hipError_t store_export(const Store st, int32_t k, const int64_t* c_ptr, int32_t
 // assignment
 // walks tiles [tb, te) for every object, of `terms` terms to walk on average; `work`
 // is a zeroed grab counter
-hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_waves, int tb, int te, unsigned long long* work,
-                     hipStream_t s);
+hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_waves, int tb, int te,
+                     unsigned long long* work, hipStream_t s);
 int walk_blocks_per_cu(int kt, int pdt_bf16, int cbicp, bool split);
-// split walk of a range of objects: prepare its terms, then per tile the head
-// terms' sums (walk_fast follows with a.S set)
 // *most = max(*most, nonzeros of a range of `range` rows)
 hipError_t range_nnz(const int64_t* rp, int64_t n, int64_t range, int64_t* most, hipStream_t s);
+// split walk of a range of objects: prepare its terms, then per tile the head
+// terms' sums (walk_fast follows with a.S set)
 hipError_t walk_prep(const WalkArgs& a, int n_cu, hipStream_t s);
 hipError_t walk_dense(const WalkArgs& a, int tile, int n_cu, hipStream_t s);
 hipError_t rescore_candidates(const WalkArgs& a, const Store st, int64_t grid_waves, hipStream_t s);

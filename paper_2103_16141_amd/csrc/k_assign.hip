@@ -587,9 +587,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 // constant, the batch offset is scalar, and lanes past the
                 // list's end read 0 from the hardware range check.
                 // ---- head terms: dense rows (in the ICP branch their moving
-                // prefix only), in ascending term order, whole rows of a
-                // 1024-centroid group summed in registers, one merge into
-                // the tile per chunk
+                // prefix only), in ascending term order, a 512-centroid
+                // group summed in registers at a time, one merge into the
+                // tile per chunk and group
                 int hrow = -1;
                 const bool use_head = !SPLIT && A.head && !(filt && CB);
                 if (use_head && h < n) hrow = hr;
@@ -848,10 +848,10 @@ hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_wav
     // Many objects: a wave grabs them from the work counter, which evens out
     // their costs (walk_grab: 60,000 objects, BF16, one tile 1.36 ms by twos, 1.64 by
     // eights, 1.47 in equal shares).  Up to 8 objects a wave, and more where they are
-    // light (walk_shared), the counter costs more than that, so the waves take equal shares,
-    // in pieces of at most 8 objects spread over the batch: 64 objects, k = 100, 260
-    // (8 waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects,
-    // k = 1,531, BF16 842 -> 346 us.
+    // light (walk_shared), the counter costs more than that, so the waves take equal
+    // shares, in pieces of at most 8 objects spread over the batch: 64 objects, k =
+    // 100, 260 (8 waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects, k
+    // = 1,531, BF16 842 -> 346 us.
     const int64_t waves = (int64_t)blocks * kWalkWaves;
     const bool shared = walk_shared(a.n, waves, terms, a.kt, a.S != nullptr);
     int share = (int)walk_grab(a.n, waves);
@@ -1053,14 +1053,15 @@ __global__ __launch_bounds__(256) void k_walk_prep(WalkArgs A) {
     }
 }
 
-// The head terms' sums of one tile (dense_groups).  Bound by vector instructions
-// (5 a step, 20 cycles, 4 waves per SIMD: 65% of the time at k = 10,000; LDS
-// reads 30%) and by the return path of the other rows' slices, which come from
-// L2 (busy 89%).  Pairs in chunks of 16, fetched a group ahead, multiply-adds
-// that broadcast by themselves, and all XCDs on the same objects: 569,413
-// objects, k = 8,482 46.6 -> 43.2 ms (whole walk).  LDS rows are summed 32 at a
-// time: one running sum is 2% faster and rounds more than the plain walk does
-// (866,129 objects, d = 5,336: 1.9e-7 against 1.4e-7; 1.0e-7 so).
+// The head terms' sums of one tile (dense_groups).  Bound by the vector memory
+// path, which returns the slices that are not in LDS (busy 97% at 2,000,000
+// objects, k = 10,000; 37% of them miss L1, and L1 waits for L2 in 46% of the
+// cycles), and next by vector instructions (67%; 5 a step, 4 waves per SIMD; LDS
+// reads 29%).  Pairs in chunks of 16, fetched a group ahead, multiply-adds that
+// broadcast by themselves, and all XCDs on the same objects: 569,413 objects, k =
+// 8,482 46.6 -> 43.2 ms (whole walk).  LDS rows are summed 32 at a time: one
+// running sum is 2% faster and rounds more than the plain walk does (866,129
+// objects, d = 5,336: 1.9e-7 against 1.4e-7; 1.0e-7 so).
 __global__ __launch_bounds__(kDenseThreads) void k_walk_dense(WalkArgs A, int tile) {
     extern __shared__ u32x4 panel[];
     const int lane = threadIdx.x & 63, q = lane & 15, sub = lane >> 4;

@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 N_CU, CLOCK_GHZ = 256, 2.4   # MI355X compute units and peak engine clock
 POSTING_BYTES = {"fp32": 6, "bf16": 4}  # 2-byte centroid id + value
-# FP32 postings, SIVF filter, split walk; a launch is one of each per tile
+# FP32 postings, SIVF filter, split walk; a launch is one of each per tile and range of objects
 WALK_KERNEL = "k_walk_dense + k_walk_fast<false, false, false, true>"
 # bytes the walk's L2 sends toward memory, from calibrated rocprofv3 --pmc
 # runs; used only while the kernel sources still hash the same
@@ -435,6 +435,9 @@ def main():
                 "peak_basis": "walk's load mix at the probed L1 rates (b128 for 16-byte loads, b64 for 4-/8-byte "
                               "loads) x %d CUs x %.1f GHz" % (N_CU, CLOCK_GHZ),
                 "peak_all_16byte_loads": peak16,
+                "note": "bytes the split walk reads from LDS (its heaviest rows) are no part of achieved; by counters "
+                        "the vector memory path is busy 97% (rows) and 99% (lists) of the time, its L1 waiting for "
+                        "L2 in 46% and 65% of the cycles (N=2,000,000: profiles/split_walk_counters.md)",
                 "dram": dram,
                 "algorithmic_gbs": s32["walk_algorithmic_gbs"],
                 "algorithmic_frac_of_hbm_peak": s32["walk_algorithmic_gbs"] / HBM_PEAK_GBS,

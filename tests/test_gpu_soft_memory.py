@@ -190,3 +190,33 @@ def test_soft_form_of_very_wide_rows(d, k):
     assert bool(((dX.double() - ref).abs() <= 2e-3 * ref.abs() + 1e-7).all())
     dC[:, pool] = 0.0
     assert not bool(dC.any())
+
+
+@pytest.mark.parametrize("k", [64, 128, 129])
+def test_soft_forward_of_many_rows_and_few_blocks(k):
+    # 2^32 nonzeros x k and more: up to two blocks of columns by gathers alone (bit
+    # for bit the capped call's), from three with the commonest terms in LDS
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("many rows, k %d" % k)
+    dev, d, per = device(), 2_000, 40
+    n = (1 << 32) // (per * k) + 11
+    g = torch.Generator(device=dev).manual_seed(k)
+    # a term from each of 40 stripes, the first of a stripe most often
+    off = (torch.rand(n, per, device=dev, generator=g) ** 3 * (d // per)).int()
+    col = (off + torch.arange(per, device=dev, dtype=torch.int32) * (d // per)).reshape(-1).contiguous()
+    v = torch.rand(n, per, device=dev, generator=g) + 0.1
+    v /= torch.linalg.vector_norm(v, dim=1, keepdim=True)
+    X = DeviceCsr(torch.arange(n + 1, device=dev) * per, col, v.reshape(-1).contiguous(), d)
+    assert X.nnz * k >= 1 << 32
+    C = torch.rand(k, d, device=dev, generator=g)
+    C /= torch.linalg.vector_norm(C, dim=1, keepdim=True)
+    lse, loss = _ctx().soft_assign_fwd(X, C, 0.05)
+    plain, _ = _ctx(workspace_cap_bytes=1 << 40).soft_assign_fwd(X, C, 0.05)
+    tol = (per + 2) * 2.0 ** -24 / 0.05 + 1e-5   # products of unit vectors' entries over tau; exp and log
+    assert torch.equal(plain, lse) if k <= 128 else float((plain - lse).abs().max()) <= 2 * tol
+    for rows in (slice(0, 3_000), slice(n - 3_000, n)):
+        D = torch.zeros(3_000, d, dtype=torch.float64, device=dev)
+        D.scatter_(1, col.view(n, per)[rows].long(), v[rows].double())
+        ref = torch.logsumexp(D @ C.double().T / 0.05, 1)
+        assert float((lse[rows].double() - ref).abs().max()) <= tol
+    assert abs(loss + lse.double().sum().item()) <= 1e-9 * abs(loss)

@@ -23,6 +23,7 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
     *whole = p.whole;
     return 1;
 }
+int lds_pays(int64_t nnz, int64_t k) { return sivf::soft_lds_pays(nnz, k); }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
 int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
     return sivf::walk_shared(n, waves, terms, kt, split != 0);
@@ -145,3 +146,9 @@ def test_equal_shares_reach_further_for_lighter_walks(plan):
         for kt in (64, 512, 2048):
             got = [shared(n, t, kt) for t in (0, 5, 20, 60, 200, 1000)]
             assert got == sorted(got, reverse=True) and all(shared(n, t, 64) >= g for t, g in zip((0, 5, 20), got))
+
+
+def test_soft_forward_uses_lds_in_larger_calls_of_three_blocks_and_more(plan):
+    pays = lambda nnz, k: plan.lds_pays(ctypes.c_int64(nnz), ctypes.c_int64(k)) != 0
+    assert [pays(1 << 26, k) for k in (1, 63, 64, 65, 128, 129, 4_096)] == [False] * 5 + [True] * 2
+    assert not pays((1 << 20) - 1, 4_096) and pays(1 << 20, 4_096) and not pays(0, 4_096)

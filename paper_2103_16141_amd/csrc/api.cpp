@@ -913,7 +913,7 @@ sivf_status soft_bwd_reserve(sivf_ctx* ctx, const Csr& Xc, int32_t k, int attemp
     STCHK(ws(ctx, "dct_count", 4, &w.count));
     // the densest terms by matrix products: without a workspace cap, and only if
     // there is memory
-    if (ctx->opt.workspace_cap_bytes == 0 && p.whole && n > 0 && Xc.nnz * (int64_t)k >= kSoftProdWork) {
+    if (ctx->opt.workspace_cap_bytes == 0 && p.whole && n > 0 && soft_prod_pays(n, Xc.nnz, k)) {
         const size_t room = (size_t)dct_cands(Xc.nnz, n);
         const int64_t last = nblk - (groups - 1) * p.blocks;   // blocks of the last group
         const size_t prod = (size_t)std::max(dct_prod_elems(p.rows, (int32_t)std::min<int64_t>(k, kp)),

@@ -371,8 +371,7 @@ __global__ __launch_bounds__(1024) void k_soft_loss(const double* __restrict__ p
 // time, and those slices were most of its L2 hits.  Which terms they are is
 // counted on a sample of the nonzeros; any choice gives the same sums up to
 // their order.  N = 262,144, D = 100,000, 100 terms a row, k = 4,096: 27.5 ->
-// 16.5 ms (0.3 of it choosing and sorting the terms); at N = 20,011, k = 1,021
-// (kSoftLdsWork / 2.4) 0.36 -> 0.37.
+// 16.5 ms (0.3 of it choosing and sorting the terms).
 
 // counts of terms in 1024 runs of 64 nonzeros
 __global__ __launch_bounds__(256) void k_soft_sample(const int32_t* __restrict__ col, int64_t nnz,
@@ -493,7 +492,7 @@ static bool narrow_offsets(int64_t d) { return d * (kBlk * 4) <= (int64_t)0xffff
 int64_t soft_lds_rows(int64_t N, int64_t nnz, int64_t d, int32_t k) {
     constexpr int64_t kRows = 65536;
     // headers hold 20 bits of a row's nonzeros
-    if (nnz * (int64_t)k < kSoftLdsWork || !narrow_offsets(d) || d >= (1 << 20) ||
+    if (!soft_lds_pays(nnz, k) || !narrow_offsets(d) || d >= (1 << 20) ||
         split_pairs(nnz, kRows) > kSplitMaxPairs)
         return 0;
     return std::min(N, kRows);
@@ -951,9 +950,7 @@ __global__ __launch_bounds__(256) void k_dct_combine(int64_t d, int64_t nsb, int
 // row), on the FP32 matrix cores.  An entry costs 0.4 ps of gathers per column, a
 // place of Xd 0.015, so terms in 1/32 of the rows and more are taken.  N =
 // 262,144, k = 4,096: 42.6 ms for dC before, 36.0 so (5.4 the products, at 104
-// TFLOP/s of 149 that a library product reaches); at N = 20,011, k = 1,021
-// (kSoftProdWork / 2.4) 0.18 ms less for the entries and 0.20 for the products
-// and choosing the terms.
+// TFLOP/s of 149 that a library product reaches).
 
 __global__ void k_dct_cands(int64_t N, int64_t d, const int64_t* __restrict__ colptr, int64_t room, DctWs w) {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;

@@ -116,6 +116,16 @@ inline bool soft_fwd_plan(int attempt, int64_t n, int64_t nblk, SoftFwdPlan* p) 
     return attempt < 3;
 }
 
+// Whether the forward keeps its commonest terms' slices in LDS: from 2^32 nonzeros
+// x k, and from three blocks of columns.  Fewer leave most XCDs to one block, whose
+// slices their L2 holds, and the pairs and LDS panels are made for little.  Forward
+// in ms without and with, 6.5e9 nonzeros x k, 30 terms a row (D = 20,000) and 100
+// (50,000): k = 64 1.88 and 3.50, 1.68 and 2.24; 128 1.67 and 2.23, 1.47 and 1.60;
+// 160 2.31 and 2.25, 2.01 and 1.65; 256 1.52 and 1.56, 1.30 and 1.29; 320 2.23 and
+// 1.49, 1.91 and 1.24; 512 1.45 and 1.30, 1.31 and 1.13.  Smaller calls, k of 1,021
+// to 4,096: 1.8e9 0.44 and 0.48, 2.2e9 0.63 and 0.65, 3.7e9 0.77 and 0.69.
+inline bool soft_lds_pays(int64_t nnz, int64_t k) { return nnz * k >= (int64_t)1 << 32 && k > 128; }
+
 // ---------------------------------------------------------------- soft backward
 // What of the backward is in memory at once: chunks of `rows` rows, `blocks`
 // blocks of 64 columns, the column copy of the whole matrix or of a chunk.
@@ -145,6 +155,18 @@ inline bool soft_bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_
     }
     *p = SoftPlan{rows, attempt == 0 ? nblk : attempt == 1 ? std::min<int64_t>(nblk, 8) : 1, attempt < 2};
     return true;
+}
+
+// Whether dC of the densest terms is made by matrix products: from 2^32 nonzeros x k,
+// and from 2^17 per row.  A row of the matrix of dense terms costs 4 ns whatever k
+// is, its products 5 ps a column; what they save goes with a row's dense terms times
+// k.  Backward in ms without and with, 8.6e9 nonzeros x k: 40 terms a row k = 256
+// 8.25 and 10.41, 1,024 6.27 and 6.99, 3,000 7.32 and 7.55; 100 terms k = 256 6.61
+// and 7.41, 1,024 5.71 and 5.79, 1,536 5.93 and 5.93, 3,000 7.13 and 6.81; 200 terms
+// k = 512 6.18 and 6.13, 768 6.10 and 5.99, 2,048 6.53 and 6.13; 30 terms, k = 64,
+// 3,000,000 rows 14.4 and 28.5.
+inline bool soft_prod_pays(int64_t n, int64_t nnz, int64_t k) {
+    return nnz * k >= (int64_t)1 << 32 && (double)nnz * (double)k >= 131072.0 * (double)n;
 }
 
 // A chunk of rows takes 5 B per nonzero and block for dX's shares (4) and dC's

@@ -9,8 +9,6 @@ namespace sivf {
 
 constexpr int kSoftBlk = 64;     // columns of a C^T block
 constexpr int kSoftSub = 32;     // columns of a dS / dC^T block
-constexpr int64_t kSoftLdsWork = 1ll << 32;   // nonzeros x k from which the forward uses LDS
-constexpr int64_t kSoftProdWork = 1ll << 32;  // nonzeros x k from which dC's densest terms are matrix products
 constexpr int kSoftPiece = 512;  // CSC entries a wave sums at most
 
 // C (k x d) -> blocks [ceil(k / 64)][d][64] of C^T, zero past column k

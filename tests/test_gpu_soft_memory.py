@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from tests.gpu_util import device, log
+from tests.test_gpu_kernel_edges import test_soft_gradient_of_the_densest_terms as _dense_terms
 
 pytestmark = pytest.mark.gpu
 
@@ -220,3 +221,11 @@ def test_soft_forward_of_many_rows_and_few_blocks(k):
         ref = torch.logsumexp(D @ C.double().T / 0.05, 1)
         assert float((lse[rows].double() - ref).abs().max()) <= tol
     assert abs(loss + lse.double().sum().item()) <= 1e-9 * abs(loss)
+
+
+@pytest.mark.parametrize("n,d,k,common,broken", [
+    (70_001, 20_000, 2_500, 70, False),   # three chunks of rows, the last with splits of its own
+    (80_001, 20_000, 1_000, 70, False),   # work in all, not enough a row: entry by entry
+])
+def test_soft_gradient_of_dense_terms_over_several_chunks(n, d, k, common, broken):
+    _dense_terms(n, d, k, common, broken)

@@ -24,6 +24,7 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
     return 1;
 }
 int lds_pays(int64_t nnz, int64_t k) { return sivf::soft_lds_pays(nnz, k); }
+int prod_pays(int64_t n, int64_t nnz, int64_t k) { return sivf::soft_prod_pays(n, nnz, k); }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
 int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
     return sivf::walk_shared(n, waves, terms, kt, split != 0);
@@ -152,3 +153,10 @@ def test_soft_forward_uses_lds_in_larger_calls_of_three_blocks_and_more(plan):
     pays = lambda nnz, k: plan.lds_pays(ctypes.c_int64(nnz), ctypes.c_int64(k)) != 0
     assert [pays(1 << 26, k) for k in (1, 63, 64, 65, 128, 129, 4_096)] == [False] * 5 + [True] * 2
     assert not pays((1 << 20) - 1, 4_096) and pays(1 << 20, 4_096) and not pays(0, 4_096)
+
+
+def test_dense_terms_are_products_where_a_row_has_work_for_them(plan):
+    pays = lambda n, nnz, k: plan.prod_pays(*(ctypes.c_int64(i) for i in (n, nnz, k))) != 0
+    assert pays(32_768, 32_768 * 128, 1_024) and not pays(32_767, 32_767 * 128, 1_024)         # in all
+    assert not pays(1 << 20, (1 << 20) * 128, 1_023) and pays(1 << 20, (1 << 20) * 128, 1_024)  # a row
+    assert not pays(1 << 30, 1 << 31, 64) and pays(1, 1 << 30, 4_096) and not pays(5, 0, 4_096)

@@ -145,7 +145,12 @@ struct SoftPlan {
 // than the misses: backward with 16,384 / 24,576 / 32,768 / 40,960 rows, N =
 // 262,144, D = 100,000, 100 terms, k = 4,096 (25 entries) 78.6 / 73.2 / 71.0 /
 // 71.6 ms; N = 97,062, D = 38,883, 177 terms, k = 3,837 (112) - / 46.2 / 47.5 /
-// 48.9.  dS of a chunk is at most 512 MiB.
+// 48.9.  The line is a rough one (it also matters how full the last chunk is): against
+// 24,576 rows, 32,768 take, at 8 / 14 / 18 / 21 / 24 / 28 / 31 entries, 7 / 5 / 4 / 4 /
+// 1 / 2 / 1% less (N = 131,072, D = 50,000, k = 512), 4 / 4 / 3 / 4 / 3 / 2 / 1% less
+// (200,000, 100,000, 512), 5 / 3 / 3 / 1 / 1 / 0 / 0% less (131,072, 50,000, 1,500), but
+// 5 / 1 / 1% less and 1 / 0 / 2 / 1% more (131,072, 50,000, 4,000) and 2% less, then 1 /
+// 4 / 1 / 3 / 6 / 7% more (200,000, 100,000, 4,000).  dS of a chunk is at most 512 MiB.
 inline bool soft_bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, SoftPlan* p) {
     const int64_t most = (double)nnz * 24576.0 < 32.0 * (double)n * (double)d ? 32768 : 24576;
     int64_t rows = std::max<int64_t>(1, std::min<int64_t>({std::max<int64_t>(n, 1), most, (int64_t)(128ll << 20) / (64 * nblk)}));

@@ -398,10 +398,11 @@ bool split_possible(const sivf_options& o) {
            o.tiles_per_launch <= 1 && o.head_density > 0.0f;
 }
 
-// A ctx whose workspace cap alone keeps its FP32 walks from being split.
-bool plain_rows(const sivf_options& o) {
-    return o.posting_dtype == SIVF_F32 && o.filter_mode != SIVF_MODE_CBICP && o.workspace_cap_bytes != 0 &&
-           o.tiles_per_launch <= 1 && o.head_density > 0.0f;
+// Whether the plain walk will read the file's dense rows: a BF16 file's, or an FP32
+// file's where a workspace cap alone keeps the walk from being split.
+bool walks_rows(const sivf_ivf* f, const sivf_options& o) {
+    return f->pdt == SIVF_BF16 || (o.posting_dtype == SIVF_F32 && o.filter_mode != SIVF_MODE_CBICP &&
+                                   o.workspace_cap_bytes != 0 && o.tiles_per_launch <= 1 && o.head_density > 0.0f);
 }
 
 // What it saves and costs per object and centroid grows with the sliced terms
@@ -500,7 +501,7 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     f->pdt = ctx->opt.posting_dtype;
     f->k_tile = ctx->opt.k_tile;
     // arrays for the most tiles the file may come to have
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, plain_rows(ctx->opt) ? INT64_MAX : 0, &f->kt, &f->T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, walks_rows(f, ctx->opt) ? INT64_MAX : 0, &f->kt, &f->T);
     f->T_max = f->T;
     const size_t kk = (size_t)k, dd = (size_t)d, dt = (size_t)(d * f->T);
     const size_t hd = ctx->opt.head_density > 0.0f ? dd : 0, sd = split_possible(ctx->opt) ? dd : 0;
@@ -531,7 +532,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // may update it, and its arrays have room for T_max tiles
     // (dense rows: as many as the file had so far)
     int32_t kt = 0, T = 0;
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, plain_rows(ctx->opt) ? f->H : 0, &kt, &T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, walks_rows(f, ctx->opt) ? f->H : 0, &kt, &T);
     if (T > f->T_max) choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, 0, &kt, &T);
     f->built = false;   // until every array below is whole again
     if (T > f->T_max) return fail(ctx, SIVF_E_HIP, "internal: %d tiles in a file made for %d", T, f->T_max);

@@ -23,14 +23,21 @@ constexpr int64_t kMaxGroups = (1 << 24) - 1;
 // 51.7) 2048; up to 3% dense, or in at most two tiles, 1536 (k = 10,000, 2%
 // dense: 86.2 with 1024, 86.0 with 1536, 88.8 with 2048; k = 1,500, 12% dense
 // 19.7 and 15.4); denser 1024 (5,000,000 objects, 6% dense: 439, 460, 490).
-// FP32 files with many dense rows that no split walk will read: `heads` such rows
-// (0: few, or unknown, or split) are read through L2 by the plain walk, and a wide
+// FP32 files with many dense rows that no split walk will read: `heads` dense rows
+// (0: few, unknown, or read by a split walk) are read through L2 by the plain walk, and a wide
 // tile's no longer fit.  ms with 1024 and as wide as it gets, (rows, width):
 // (399, 2048) 3.9 and 3.7, (558, 2048) 3.5 and 3.7, (715, 2048) 3.4 and 4.2, (732,
 // 2048) 6.9 and 6.8, (1,076, 2048) 11.6 and 12.8; (1,264, 1536) 2.8 and 3.3,
 // (1,010, 1536) 6.1 and 5.2; 5 tiles: (278, 2048) 58.5 and 69.3, (214, 2048) 34.4
 // and 36.4, (250, 2048) 42.5 and 41.3; 3 tiles: (382, 1728) 25.5 and 26.0, (151,
 // 1728) 9.1 and 8.7.  Halving a tile of at most 1152 never pays.
+// BF16 files narrow for the same reason, later: in two tiles from 2,600 rows on
+// ((rows, width, D): 1,999, 1344, 30,000 9.44 with 1024 and 9.30 so; 2,725, 1536, 5,000
+// 12.5 and 12.7; 2,878, 1344, 150,000 14.5 and 14.2; 3,465, 1344, 30,000 5.15 and 5.61;
+// 4,285, 1536, 30,000 10.3 and 11.8), in more from 1,000 (967, 1536 39.2 and 39.2; 518,
+// 1536 56.4 and 53.1; 1,221, 2048 19.2 and 20.0), or from 500 if the narrow tiles' rows,
+// which come in 512s, are shorter in all (431, 1344 4.81 and 4.84; 583, 1344 37.7 and
+// 39.5; 831, 1344 37.7 and 40.3; 1,815, 1344 19.5 and 20.9).
 // More postings or dense rows never give fewer tiles: a file's arrays are made for
 // infinitely many.
 inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, int64_t d, int64_t heads, int32_t* kt,
@@ -46,9 +53,13 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
             return ((w + 63) / 64) * 64;
         };
         want = width(kmax);
-        if (!bf16 && want > 1152) {
-            const int64_t many = k > 2 * want ? 260 : want > 1536 ? 480 : 1200;
-            if (heads >= many) want = width(kTileNarrow);
+        const int32_t narrow = width(kTileNarrow);
+        auto slots = [k](int32_t w) { return ((int64_t)k + w - 1) / w * ((w + 511) / 512 * 512); };
+        const bool two = k <= 2 * (int64_t)want;
+        if (bf16 ? want > kTileNarrow && want < k : want > 1152) {
+            const int64_t many = bf16 ? (two ? 2600 : slots(narrow) < slots(want) ? 500 : 1000)
+                                      : !two ? 260 : want > 1536 ? 480 : 1200;
+            if (heads >= many) want = narrow;
         }
     }
     *kt = want;

@@ -254,3 +254,33 @@ def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
     assert f.sizes()["k_tile"] == 2048
     for ctx, f, *_ in state:
         f.free()
+
+
+def test_tiles_of_a_bf16_file_narrow_once_it_has_many_dense_rows():
+    # two tiles become three when 2,600 terms have dense rows: every step is that
+    # of fixed tiles
+    from tests.test_gpu_kernel_edges import _striped
+    from paper_2103_16141_amd.api import Context
+    log("bf16 tiles")
+    n, d, lam, k, dev = 8_403, 4_000, 1_500, 2_100, device()
+    X = _striped(n, d, lam, 5, torch.float32)
+    ids = np.random.default_rng(3).choice(n, k, replace=False).astype(np.int32)
+    state = []
+    for kt in (0, 512):
+        ctx = Context(0, k_tile=kt, posting_dtype="bf16")
+        state.append([ctx, ctx.init_centroids(X, k, ids), torch.zeros(n, dtype=torch.int32, device=dev),
+                      torch.zeros(n, dtype=torch.float32, device=dev), torch.zeros(k, dtype=torch.uint8, device=dev)])
+    widths, rows = [], []
+    for r in (1, 2, 3, 4):
+        widths.append(state[0][1].sizes()["k_tile"])
+        st = [ctx.assign(X, f, r, a, own, l) for ctx, f, a, own, l in state]
+        rows.append(st[0]["head_rows"])
+        assert torch.equal(state[0][2], state[1][2]) and torch.equal(state[0][4], state[1][4])
+        assert all(st[0][q] == st[1][q] for q in ("multadds", "moved", "icp_objects", "n_invariant", "head_rows"))
+        for ctx, f, a, own, l in state:
+            ctx.update(X, a, l, f)
+    # a file narrows at the update after the one that made the rows
+    assert widths == [704 if r and rows[r - 1] >= 2_600 else 1_088 for r in range(4)] and rows[-1] >= 2_600 and 704 in widths
+    for ctx, f, *_ in state:
+        f.free()
+        ctx.close()

@@ -62,7 +62,7 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
     for k in ks:
         for bf16 in (0, 1):
             for k_tile in (0, 64, 128, 4096):
-                for heads in (0, 200, 300, 700, 1200, 2 ** 63 - 1):
+                for heads in (0, 200, 300, 500, 700, 1000, 1200, 2600, 2 ** 63 - 1):
                     _, most = tiles(k_tile, bf16, k, float("inf"), 1000, 2 ** 63 - 1 if heads else 0)
                     for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
                         kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000, heads)
@@ -71,6 +71,11 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
     assert [width(2048, h) for h in (0, 479, 480)] == [2048, 2048, 1024]
     assert [width(1500, h) for h in (0, 1199, 1200)] == [1536, 1536, 768]
     assert [width(10_000, h) for h in (259, 260)] == [2048, 1024] and width(1100, 10 ** 6) == 1152
+    bf16 = lambda k, heads: tiles(0, 1, k, 0.02 * k * 1000, 1000, heads)[0]
+    assert [bf16(3072, h) for h in (2599, 2600)] == [1536, 1024] and bf16(2100, 2600) == 704
+    assert [bf16(4000, h) for h in (499, 500)] == [1344, 1024]     # 4,608 and 4,096 slots
+    assert [bf16(12_288, h) for h in (999, 1000)] == [1536, 1024]   # 12,288 both
+    assert bf16(1536, 10 ** 6) == 1536 and bf16(2048, 10 ** 6) == 1024
 
 
 @pytest.mark.parametrize("objects,row,floor,want", [

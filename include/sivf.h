@@ -101,9 +101,9 @@ typedef struct {
     int32_t k_tile;             /* centroids per LDS similarity tile; 0 = automatic
                                    (k split evenly into tiles of at most 2048,
                                    denser BF16 files 1536 or 1024, files with
-                                   many dense rows 1024 (FP32 where a workspace
-                                   cap keeps the walk from being split), rounded
-                                   up to a multiple of 64);
+                                   many dense rows 1024 (FP32 where the walk of
+                                   the objects is not split), rounded up to a
+                                   multiple of 64);
                                    otherwise a multiple of 64 in [64, 4096] */
     int32_t certify;            /* 1 (default): exact assignments (certificate + FP64
                                    re-score).  0: take the fast-pass argmax as is

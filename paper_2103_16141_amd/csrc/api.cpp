@@ -398,13 +398,6 @@ bool split_possible(const sivf_options& o) {
            o.tiles_per_launch <= 1 && o.head_density > 0.0f;
 }
 
-// Whether the plain walk will read the file's dense rows: a BF16 file's, or an FP32
-// file's where a workspace cap alone keeps the walk from being split.
-bool walks_rows(const sivf_ivf* f, const sivf_options& o) {
-    return f->pdt == SIVF_BF16 || (o.posting_dtype == SIVF_F32 && o.filter_mode != SIVF_MODE_CBICP &&
-                                   o.workspace_cap_bytes != 0 && o.tiles_per_launch <= 1 && o.head_density > 0.0f);
-}
-
 // What it saves and costs per object and centroid grows with the sliced terms
 // per object (h): about (h - 38) 0.1 ps, and 0.13 ms a tile are lost.  Plain and
 // split, ms: k = 10,000: h = 21 65.1 and 76.8 (1,000,000 objects), 34 8.8 and 9.1
@@ -414,8 +407,8 @@ bool walks_rows(const sivf_ivf* f, const sivf_options& o) {
 // 400,000 2.10 and 2.04.  Few rows stay in L2 anyway (37 rows, h = 41: 18.2 and
 // 18.9; 270 rows, h = 42 27.3 and 25.6).
 constexpr int64_t kSplitMinRows = 128;
-bool split_pays(double h, int64_t objects, const sivf_ivf* f) {
-    return (h - 38.0) * (double)objects * (double)f->k >= 1e9 * f->T;
+bool split_pays(double h, int64_t objects, int32_t k, int32_t tiles) {
+    return (h - 38.0) * (double)objects * (double)k >= 1e9 * tiles;
 }
 
 // ---------------------------------------------------------------- file storage
@@ -501,7 +494,7 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     f->pdt = ctx->opt.posting_dtype;
     f->k_tile = ctx->opt.k_tile;
     // arrays for the most tiles the file may come to have
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, walks_rows(f, ctx->opt) ? INT64_MAX : 0, &f->kt, &f->T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, INT64_MAX, &f->kt, &f->T);
     f->T_max = f->T;
     const size_t kk = (size_t)k, dd = (size_t)d, dt = (size_t)(d * f->T);
     const size_t hd = ctx->opt.head_density > 0.0f ? dd : 0, sd = split_possible(ctx->opt) ? dd : 0;
@@ -530,10 +523,12 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
 sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings, const Csr* X) {
     // the tiles follow from the options the file was made with: a ctx with others
     // may update it, and its arrays have room for T_max tiles
-    // (dense rows: as many as the file had so far)
     int32_t kt = 0, T = 0;
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, walks_rows(f, ctx->opt) ? f->H : 0, &kt, &T);
-    if (T > f->T_max) choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, 0, &kt, &T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, 0, &kt, &T);
+    // rows that X will walk as they are (both taken to be what the file had so far)
+    const bool split_X = f->pdt == SIVF_F32 && split_possible(ctx->opt) &&
+                         (!X || X->n < 1 || split_pays(f->sfrac * X->nnz / X->n, X->n, f->k, T));
+    if (!split_X) choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, f->H, &kt, &T);
     f->built = false;   // until every array below is whole again
     if (T > f->T_max) return fail(ctx, SIVF_E_HIP, "internal: %d tiles in a file made for %d", T, f->T_max);
     f->kt = kt;
@@ -609,7 +604,7 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // (the last requests of an update: they are optional)
     uint32_t* wt = nullptr;
     int32_t* sterm2 = nullptr;
-    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f) && SH <= kSplitMaxRows &&
+    if (split && SH >= kSplitMinRows && split_pays(f->sfrac * X->nnz / X->n, X->n, f->k, f->T) && SH <= kSplitMaxRows &&
         SH * kpad * esz <= kHeadMaxBytes && SH * f->T <= kMaxGroups &&
         rows_reserve(&f->sval, &f->scap, SH, true) == SIVF_OK &&
         ws_optional(ctx, {{"split_wt", (size_t)SH * 4, (void**)&wt}, {"split_term2", (size_t)SH * 4, (void**)&sterm2}})) {
@@ -733,7 +728,7 @@ sivf_status split_plan(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f,
     b->ranges = 1;
     if (w.mode != Work::kCtx || !split_possible(ctx->opt) || f->srows == 0 || Xc.n == 0) return SIVF_OK;
     const double h = f->sfrac * Xc.nnz / Xc.n;
-    if (!split_pays(h, Xc.n, f)) return SIVF_OK;
+    if (!split_pays(h, Xc.n, f->k, f->T)) return SIVF_OK;
     const int64_t ktp = head_ktp(f->kt);
     int64_t pairs = 0, *most = nullptr;
     STCHK(w.get("split_most", 1, &most));
@@ -749,7 +744,7 @@ sivf_status split_plan(sivf_ctx* ctx, Work& w, const Csr& Xc, const sivf_ivf* f,
         return SIVF_OK;
     };
     const int64_t range = split_range(
-        std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp), [&](int64_t r) { return split_pays(h, r, f); },
+        std::min<int64_t>(Xc.n, (int64_t)(1ll << 30) / ktp), [&](int64_t r) { return split_pays(h, r, f->k, f->T); },
         [&](int64_t r) {
             int64_t nnz = 0;
             st = longest(r, &nnz);

@@ -30,7 +30,9 @@ constexpr int64_t kMaxGroups = (1 << 24) - 1;
 // 2048) 6.9 and 6.8, (1,076, 2048) 11.6 and 12.8; (1,264, 1536) 2.8 and 3.3,
 // (1,010, 1536) 6.1 and 5.2; 5 tiles: (278, 2048) 58.5 and 69.3, (214, 2048) 34.4
 // and 36.4, (250, 2048) 42.5 and 41.3; 3 tiles: (382, 1728) 25.5 and 26.0, (151,
-// 1728) 9.1 and 8.7.  Halving a tile of at most 1152 never pays.
+// 1728) 9.1 and 8.7; short rows (too short to be split) of a flat vocabulary: 9 tiles
+// (775, 1856) 25.5 and 38.1, 4 (1,910, 2048) 15.2 and 20.2, 2 (2,045, 2048) 7.4 and
+// 10.1.  Halving a tile of at most 1152 never pays.
 // BF16 files narrow for the same reason, later: in two tiles from 2,600 rows on
 // ((rows, width, D): 1,999, 1344, 30,000 9.44 with 1024 and 9.30 so; 2,725, 1536, 5,000
 // 12.5 and 12.7; 2,878, 1344, 150,000 14.5 and 14.2; 3,465, 1344, 30,000 5.15 and 5.61;

@@ -247,27 +247,30 @@ def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
             ctx.update(X, a, l, f)
     assert st[0]["head_rows"] >= 480
     assert widths == [[2048, 512, 2048], [2048, 512, 2048], [1024, 512, 2048], [1024, 512, 2048]]
-    # the file made without a cap has no room for more tiles: a capped ctx that
-    # updates it keeps their number
+    # the file made without a cap narrows when a capped ctx updates it
     ctx, f, a, own, l = state[2]
     state[0][0].update(X, a, l, f)
-    assert f.sizes()["k_tile"] == 2048
+    assert f.sizes()["k_tile"] == 1024
     for ctx, f, *_ in state:
         f.free()
 
 
-def test_tiles_of_a_bf16_file_narrow_once_it_has_many_dense_rows():
-    # two tiles become three when 2,600 terms have dense rows: every step is that
-    # of fixed tiles
+@pytest.mark.parametrize("k,lam,wide,narrow,rows_from,options", [
+    (2_100, 1_500, 1_088, 704, 2_600, dict(posting_dtype="bf16")),
+    (2_048, 30, 2_048, 1_024, 480, dict(head_density=0.02)),   # rows too short for the split walk
+    (4_000, 30, 2_048, 1_024, 480, dict(head_density=0.01, filter_mode="cbicp")),
+])
+def test_tiles_narrow_once_many_dense_rows_are_walked_as_they_are(k, lam, wide, narrow, rows_from, options):
+    # every step is that of fixed tiles
     from tests.test_gpu_kernel_edges import _striped
     from paper_2103_16141_amd.api import Context
-    log("bf16 tiles")
-    n, d, lam, k, dev = 8_403, 4_000, 1_500, 2_100, device()
+    log("tiles k %d %s" % (k, options))
+    n, d, dev = 4 * k + 3, 4_000, device()
     X = _striped(n, d, lam, 5, torch.float32)
     ids = np.random.default_rng(3).choice(n, k, replace=False).astype(np.int32)
     state = []
     for kt in (0, 512):
-        ctx = Context(0, k_tile=kt, posting_dtype="bf16")
+        ctx = Context(0, k_tile=kt, **options)
         state.append([ctx, ctx.init_centroids(X, k, ids), torch.zeros(n, dtype=torch.int32, device=dev),
                       torch.zeros(n, dtype=torch.float32, device=dev), torch.zeros(k, dtype=torch.uint8, device=dev)])
     widths, rows = [], []
@@ -280,7 +283,8 @@ def test_tiles_of_a_bf16_file_narrow_once_it_has_many_dense_rows():
         for ctx, f, a, own, l in state:
             ctx.update(X, a, l, f)
     # a file narrows at the update after the one that made the rows
-    assert widths == [704 if r and rows[r - 1] >= 2_600 else 1_088 for r in range(4)] and rows[-1] >= 2_600 and 704 in widths
+    assert widths == [narrow if r and rows[r - 1] >= rows_from else wide for r in range(4)]
+    assert wide in widths and narrow in widths
     for ctx, f, *_ in state:
         f.free()
         ctx.close()

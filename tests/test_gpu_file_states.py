@@ -257,3 +257,45 @@ def test_validation_errors_at_the_ends_of_its_workgroups(n, per):
         with pytest.raises(SivfError) as err:
             ctx.validate(DeviceCsr(rp, bad, val, per))
         assert err.value.name == "SIVF_E_UNSORTED" and "row %d " % (n - 1) in str(err.value)
+
+
+@pytest.mark.parametrize("d,long,dtype,signed", [
+    (8_192, 900, np.float32, False),     # the widest vocabulary summed member by member
+    (8_193, 900, np.float32, False),     # the next is not
+    (700, 700, np.float64, True),
+    (250, 250, np.float32, True),
+])
+def test_update_of_clusters_summed_member_by_member(d, long, dtype, signed):
+    # clusters of more than a tile (4,096 nonzeros) and of at most twice the mean of
+    # members: one of exactly as many and one of one more; rows of no, few, 256, 257
+    # and many terms; twice, so that the sums are used again
+    import oracle
+    from tests.gpu_util import assert_centroids_equal, centroids_from_export
+    from tests.test_gpu_kernel_edges import _rows_corpus
+    log("member by member d %d" % d)
+    rng = np.random.default_rng(d)
+    row = min(d, 250)
+    n, k = 5_500_000 // row, 900
+    lens = np.full(n, row)
+    for m in (0, 3, 256, 257, long):
+        lens[rng.integers(0, n, 100)] = min(d, m)
+    c = _rows_corpus([int(x) for x in lens], d, dtype, 3, signed)
+    most = 2 * n // k
+    assert c.nnz // 100_000 >= most and c.nnz > 4_096 * k and most * row < 4 * 4_096
+    tile = 4_096 // row
+    sizes = [most, most + 1, most - 1, tile, tile + 1, tile + 2, 1, 0, 2 * most]
+    sizes += [(n - sum(sizes) - 40 * most) // (k - 50)] * (k - 50) + [most] * 40
+    a = np.repeat(np.arange(k), sizes + [n - sum(sizes)]).astype(np.int32)
+    rng.shuffle(a)
+    X, ids = _X(c), [int(i) for i in rng.choice(n, k, replace=False)]
+    ctx = _ctx()
+    ivf = ctx.init_centroids(X, k, ids)
+    ref = oracle.init_centroids(c, np.array(ids, np.int32))
+    lam = torch.zeros(k, dtype=torch.uint8, device=device())
+    for step in range(2):
+        ctx.update(X, torch.from_numpy(a).to(device()), lam, ivf)
+        ref, _ = oracle.update(c, a, ref)
+        assert_centroids_equal(centroids_from_export(ivf.export(), k, d), ref, "d %d, step %d" % (d, step))
+        a = np.roll(a, 1)
+    ivf.free()
+    ctx.close()

@@ -25,6 +25,7 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
 }
 int lds_pays(int64_t nnz, int64_t k) { return sivf::soft_lds_pays(nnz, k); }
 int prod_pays(int64_t n, int64_t nnz, int64_t k) { return sivf::soft_prod_pays(n, nnz, k); }
+int64_t members(int64_t n, int64_t nnz, int64_t d, int64_t k) { return sivf::upd_members(n, nnz, d, k); }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
 int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
     return sivf::walk_shared(n, waves, terms, kt, split != 0);
@@ -165,3 +166,13 @@ def test_dense_terms_are_products_where_a_row_has_work_for_them(plan):
     assert pays(32_768, 32_768 * 128, 1_024) and not pays(32_767, 32_767 * 128, 1_024)         # in all
     assert not pays(1 << 20, (1 << 20) * 128, 1_023) and pays(1 << 20, (1 << 20) * 128, 1_024)  # a row
     assert not pays(1 << 30, 1 << 31, 64) and pays(1, 1 << 30, 4_096) and not pays(5, 0, 4_096)
+
+
+def test_member_by_member_only_where_chains_are_short_and_sums_fit(plan):
+    plan.members.restype = ctypes.c_int64
+    members = lambda *a: plan.members(*(ctypes.c_int64(i) for i in a))
+    assert members(400_000, 80_000_000, 4_000, 1_000) == 800 and members(400_000, 80_000_000, 4_000, 3_000) == 266
+    assert members(400_000, 80_000_000, 8_192, 3_000) == 266 and members(400_000, 80_000_000, 8_193, 3_000) == 0
+    assert members(100_000, 15_000_000, 4_000, 1_000) == 150 and members(100_000, 15_000_000, 4_000, 999) == 0
+    assert members(150_000, 11_250_000, 4_000, 2_747) == 0 and members(150_000, 11_250_000, 4_000, 2_746) > 0   # a tile
+    assert members(1, 0, 1, 1) == 0 and members(0, 0, 5, 3) == 0

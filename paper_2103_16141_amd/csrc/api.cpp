@@ -1168,7 +1168,7 @@ sivf_status update_impl(sivf_ctx* ctx, const Csr& Xc, const int32_t* assign, con
     STCHK(ws_zeroed(ctx, "u_touched", (int64_t)(w.nslots + kFoldBig) * ((Xc.d + 63) / 64), &w.touched));
     HIPCHK(ctx, hipEventRecord(ctx->ev[3], s));
     HIPCHK(ctx, upd_sort(assign, n, k, Xc.rp, sw, &w, s));
-    HIPCHK(ctx, upd_bounds(k, Xc.d, Xc.nnz, lambda, 1, f->cur, w, s));
+    HIPCHK(ctx, upd_bounds(k, n, Xc.d, Xc.nnz, lambda, 1, f->cur, w, s));
     // room for the new entries: the exact bound is on the device; where the
     // largest it can be already fits or is small, the host need not wait for it
     // (after a failed update f->P may not be the current entries)

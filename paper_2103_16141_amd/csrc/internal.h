@@ -306,6 +306,7 @@ constexpr int kFoldTile = 4096;     // nonzeros a workgroup sorts and sums at a 
 constexpr int kFoldBigTiles = 2;    // clusters of at least as many tiles are cut into term ranges
 constexpr int kFoldRanges = 32;     // ranges of such a cluster, at most
 constexpr int kFoldBig = 1024;      // such clusters, at most (the others are summed whole)
+constexpr int kByMembers = 1 << 30;  // UpdateWs::bigslot of a cluster summed member by member
 struct UpdateWs {
     int64_t* ccount;    // [k] cluster sizes
     int64_t* cstart;    // [k + 1] first member of each cluster in perm
@@ -315,7 +316,7 @@ struct UpdateWs {
     int64_t* ubscan;    // [k + 1] exclusive scan of ub
     double* W;          // [(nslots + kFoldBig) * d] dense FP64 accumulators, kept zero between uses
     unsigned long long* touched;  // [(nslots + kFoldBig) * ceil(d / 64)] terms of W in use, kept zero between uses
-    int32_t* bigslot;   // [k] number of a cluster cut into ranges, else -1
+    int32_t* bigslot;   // [k] number of a cluster cut into ranges, kByMembers, else -1
     int32_t* bigc;      // [kFoldBig] its cluster
     int32_t* bigr;      // [kFoldBig] its ranges
     int32_t* splits;    // [kFoldBig * (kFoldRanges + 1)] their first terms
@@ -329,7 +330,7 @@ struct SortWs;
 // sorts the objects (n > 0) by cluster: perm, cstart, ccount, memnnz of *w
 hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, const SortWs<float>& sw, UpdateWs* w,
                     hipStream_t s);
-hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
+hipError_t upd_bounds(int32_t k, int64_t n, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
                       UpdateWs w, hipStream_t s);
 int upd_fold_groups(int n_cu);   // workgroups (and accumulator rows) of the member sums
 // means and norms of every cluster into `next`, norm bounds into cnorm

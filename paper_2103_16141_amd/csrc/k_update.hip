@@ -6,7 +6,7 @@
 //    for 1M at k = 1,000; this takes 30 us and 0.1 ms.)
 // 2. One workgroup per cluster sums its members' values term by term in
 //    ascending object id (k_upd_fold: tiles of nonzeros sorted by term in
-//    LDS), q_t = w_t / |C_j|, support = {t : q_t != 0}; then s = s + q_t*q_t
+//    LDS; k_upd_members: row by row), q_t = w_t / |C_j|, support = {t : q_t != 0}; then s = s + q_t*q_t
 //    sequentially in ascending term order and u_t = q_t / sqrt(s)
 //    (k_upd_norm).  Clusters with no members, or with unchanged members
 //    (flag 1), keep their previous centroid bitwise (it would be recomputed
@@ -66,16 +66,18 @@ hipError_t upd_sort(const int32_t* a, int64_t n, int32_t k, const int64_t* rp, c
 // least kFoldBigTiles tiles that holds more than 1 / kFoldBig of all nonzeros
 // (half a workgroup's share: fewer than kFoldBig clusters can) is cut into
 // term ranges that run side by side: up to kFoldRanges, a tile and about 8
-// nonzeros of a row each.
-__global__ void k_upd_bounds(int32_t k, int64_t d, int64_t nnz_all, const uint8_t* __restrict__ lam, int allow_copy,
-                             Store prev, UpdateWs w) {
+// nonzeros of a row each.  members: see upd_members.
+__global__ void k_upd_bounds(int32_t k, int64_t d, int64_t nnz_all, int64_t members, const uint8_t* __restrict__ lam,
+                             int allow_copy, Store prev, UpdateWs w) {
     const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (j >= k) return;
     const int64_t cnt = w.ccount[j], nnz = w.memnnz[j];
     const bool copy = cnt == 0 || (allow_copy && lam[j]);
     w.ub[j] = copy ? prev.nnz[j] : min(d, nnz);
     int32_t slot = -1;
-    if (!copy && nnz >= (int64_t)kFoldBigTiles * kFoldTile && nnz > nnz_all / kFoldBig) {
+    if (!copy && nnz > kFoldTile && cnt <= members) {
+        slot = kByMembers;
+    } else if (!copy && nnz >= (int64_t)kFoldBigTiles * kFoldTile && nnz > nnz_all / kFoldBig) {
         const int64_t R = min(min((int64_t)kFoldRanges, nnz / kFoldTile), nnz / (8 * cnt));
         if (R >= 2) {
             const unsigned long long b = atomicAdd(&w.work[1], 1ull);
@@ -91,12 +93,12 @@ __global__ void k_upd_bounds(int32_t k, int64_t d, int64_t nnz_all, const uint8_
     w.bigslot[j] = slot;
 }
 
-hipError_t upd_bounds(int32_t k, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
+hipError_t upd_bounds(int32_t k, int64_t n, int64_t d, int64_t nnz, const uint8_t* lam, int allow_copy, const Store prev,
                       UpdateWs w, hipStream_t s) {
     hipError_t e = fill_u64(w.work, 0ull, 3, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_upd_bounds, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, k, d, nnz, lam, allow_copy,
-                       prev, w);
+    hipLaunchKernelGGL(k_upd_bounds, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, k, d, nnz,
+                       upd_members(n, nnz, d, k), lam, allow_copy, prev, w);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return exclusive_scan_i64(w.ub, w.ubscan, k, w.scan_ws, s);
@@ -502,6 +504,88 @@ __global__ __launch_bounds__(kFoldThreads) void k_upd_emit(int64_t d, Store next
     }
 }
 
+// Clusters of more than a tile and few members over a vocabulary whose FP64 sums
+// fit LDS: a wave each adds its members' rows one after the other (a row's terms
+// are distinct, and a wave's LDS operations complete in order), then emits the
+// sums in ascending order.  Bound by that chain, 0.4 us a member with the bounds of
+// 64 members and the nonzeros of the next one loaded ahead, instead of by the sort's
+// passes: 400,000 rows of 200 of 4,000 terms, k = 3,000 (130 members a cluster) whole
+// update 2.71 -> 1.33 ms.
+template <typename V>
+__global__ __launch_bounds__(64) void k_upd_members(Csr X, int32_t k, Store next, UpdateWs w) {
+    extern __shared__ double sums[];   // zero between clusters
+    constexpr int kAhead = 4;          // 64 nonzeros each
+    const int lane = threadIdx.x;
+    const V* __restrict__ xv = (const V*)X.val;
+    for (int64_t t = lane; t < X.d; t += 64) sums[t] = 0.0;
+    for (int64_t j = blockIdx.x; j < k; j += gridDim.x) {
+        if (w.bigslot[j] != kByMembers) continue;
+        const int64_t cnt = w.ccount[j], q0 = w.cstart[j], o = w.ubscan[j];
+        for (int64_t m0 = 0; m0 < cnt; m0 += 64) {
+            int64_t mb = 0, me = 0;   // of member m0 + lane
+            if (m0 + lane < cnt) {
+                const int64_t i = w.perm[q0 + m0 + lane];
+                mb = X.rp[i];
+                me = X.rp[i + 1];
+            }
+            const int nm = (int)min((int64_t)64, cnt - m0);
+            int32_t t[kAhead], tn[kAhead];
+            V v[kAhead], vn[kAhead];
+            // unconditional loads: a branch would wait for them
+            auto load = [&](int m, int32_t (&tt)[kAhead], V (&vv)[kAhead]) {
+                const int64_t b = bcast_i64(mb, m), e = bcast_i64(me, m);
+#pragma unroll
+                for (int c = 0; c < kAhead; ++c) {
+                    const int64_t p = b + c * 64 + lane, at = min(p, X.nnz - 1);
+                    const int32_t col = X.col[at];
+                    vv[c] = xv[at];
+                    tt[c] = p < e ? col : -1;
+                }
+            };
+            load(0, t, v);
+            for (int m = 0; m < nm; ++m) {
+                load(min(m + 1, nm - 1), tn, vn);
+                double a[kAhead];
+#pragma unroll
+                for (int c = 0; c < kAhead; ++c) a[c] = sums[max(t[c], 0)];
+#pragma unroll
+                for (int c = 0; c < kAhead; ++c)
+                    if (t[c] >= 0) sums[t[c]] = a[c] + (double)v[c];
+                const int64_t e = bcast_i64(me, m);
+                for (int64_t p = bcast_i64(mb, m) + kAhead * 64 + lane; p < e; p += 64)
+                    sums[X.col[p]] = sums[X.col[p]] + (double)xv[p];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int c = 0; c < kAhead; ++c) {
+                    t[c] = tn[c];
+                    v[c] = vn[c];
+                }
+            }
+        }
+        const double dc = (double)cnt;
+        int64_t eo = 0;
+        for (int64_t p0 = 0; p0 < X.d; p0 += 64) {
+            const int64_t p = p0 + lane;
+            const double q = p < X.d ? sums[p] / dc : 0.0;
+            if (p < X.d) sums[p] = 0.0;
+            const unsigned long long mask = ballot(q != 0.0);
+            if (q != 0.0) {
+                const int64_t at = o + eo + lanes_below(mask);
+                next.term[at] = (int32_t)p;
+                next.val[at] = q;
+            }
+            eo += __popcll(mask);
+        }
+        if (lane == 0) {
+            next.start[j] = o;
+            next.nnz[j] = eo;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // u_t = q_t / sqrt(s) with s = s + q_t * q_t sequentially in ascending t, or a
 // copy of the previous centroid for unchanged and empty clusters; and the
 // centroid's norm bound (as k_centroid_norms).  One workgroup per cluster: all
@@ -611,6 +695,13 @@ static hipError_t upd_means_t(const Csr& X, int32_t k, const uint8_t* lam, int a
         hipLaunchKernelGGL(k_upd_split<V>, dim3(kFoldBig), dim3(kFoldThreads), lds, s, X, w, passes, nbits);
     hipLaunchKernelGGL(k_upd_fold<V>, dim3(groups), dim3(kFoldThreads), lds, s, X, k, lam, allow_copy, next, w, passes,
                        nbits);
+    if (upd_members(X.n, X.nnz, X.d, k) > 0) {
+        const size_t room = (size_t)X.d * 8;
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_upd_members<V>, 64, room) != hipSuccess || nb < 1) nb = 1;
+        const unsigned waves = (unsigned)std::min<int64_t>(k, (int64_t)groups / 2 * nb);
+        hipLaunchKernelGGL(k_upd_members<V>, dim3(waves), dim3(64), room, s, X, k, next, w);
+    }
     if (X.nnz >= (int64_t)kFoldBigTiles * kFoldTile)
         hipLaunchKernelGGL(k_upd_emit, dim3(kFoldBig), dim3(kFoldThreads), 0, s, X.d, next, w);
     return hipGetLastError();

@@ -73,6 +73,21 @@ inline int64_t walk_grab(int64_t n, int64_t waves) {
     return std::max<int64_t>(1, std::min<int64_t>(8, n / (waves * 4)));
 }
 
+// Members up to which a cluster of more than a tile of nonzeros is summed member by
+// member (k_upd_members), 0: none is.  The sums of the whole vocabulary have to fit
+// 64 KB of LDS.  A member waits for the one before it, 0.4 us in all, and the tiles of
+// all clusters take 24 ps a nonzero, so only chains of at most nonzeros / 100,000
+// members (a sixth of that) are worth it, and only where most clusters have more than
+// a tile and are no longer: 1.5 times the mean is, the limit is twice the mean.  Update in us, tiles and
+// members, D = 4,000, flat vocabulary: 150,000 rows of 200 terms, k = 3,000 2,016 and
+// 994; 400,000 rows, k = 1,000 2,372 and 969; 1,000,000 rows of 75, k = 10,000 6,278
+// and 3,138; skewed: 400,000 rows of 200, k = 1,000 2,296 and 2,042.  Where the mean is
+// longer: 1,000,000 rows of 75, k = 1,000 2,160 and 2,587.
+inline int64_t upd_members(int64_t n, int64_t nnz, int64_t d, int64_t k) {
+    const int64_t chain = nnz / 100000;
+    return d <= 8192 && nnz > 4096 * k && 2 * chain * k >= 3 * n ? std::min(2 * n / k, chain) : 0;
+}
+
 // Whether the waves of a walk take equal shares of n objects instead, of `terms`
 // terms on average (split: of the listed ones).  A grab costs 15 ns, one after the
 // other for all waves: 22,000 of them (44,000 objects by twos) hold a walk that
@@ -87,6 +102,8 @@ inline int64_t walk_grab(int64_t n, int64_t waves) {
 // 100 terms, about 45 listed: 55,000 objects, k = 500 721 and 508, k = 2,000 1,200
 // and 1,216; 70,000, k = 1,000 993 and 958; 100,000, k = 500 914 and 770, k = 1,000
 // 1,281 and 1,324.
+// Over 780 walks of three vocabularies, 45,000 to 115,000 objects of 20 to 130 terms, k
+// = 16 to 800, no other line loses less: 3% on average to the better way of each.
 inline bool walk_shared(int64_t n, int64_t waves, double terms, int32_t kt, bool split) {
     if (n <= 8 * waves) return true;
     if (n > 24 * waves) return false;

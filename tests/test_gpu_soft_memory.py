@@ -225,7 +225,7 @@ def test_soft_forward_of_many_rows_and_few_blocks(k):
 
 @pytest.mark.parametrize("n,d,k,common,broken", [
     (70_001, 20_000, 2_500, 70, False),   # three chunks of rows, the last with splits of its own
-    (80_001, 20_000, 1_000, 70, False),   # work in all, not enough a row: entry by entry
+    (70_001, 20_000, 2_500, 12, False),   # 7 dense terms a row are too few: entry by entry
 ])
 def test_soft_gradient_of_dense_terms_over_several_chunks(n, d, k, common, broken):
     _dense_terms(n, d, k, common, broken)

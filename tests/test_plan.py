@@ -24,7 +24,8 @@ int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64
     return 1;
 }
 int lds_pays(int64_t nnz, int64_t k) { return sivf::soft_lds_pays(nnz, k); }
-int prod_pays(int64_t n, int64_t nnz, int64_t k) { return sivf::soft_prod_pays(n, nnz, k); }
+int prod_may(int64_t n, int64_t nnz, int64_t k) { return sivf::soft_prod_may(n, nnz, k); }
+int prod_pays(int64_t entries, int64_t n, int64_t k) { return sivf::soft_prod_pays(entries, n, k); }
 int64_t members(int64_t n, int64_t nnz, int64_t d, int64_t k) { return sivf::upd_members(n, nnz, d, k); }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
 int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
@@ -161,11 +162,14 @@ def test_soft_forward_uses_lds_in_larger_calls_of_three_blocks_and_more(plan):
     assert not pays((1 << 20) - 1, 4_096) and pays(1 << 20, 4_096) and not pays(0, 4_096)
 
 
-def test_dense_terms_are_products_where_a_row_has_work_for_them(plan):
-    pays = lambda n, nnz, k: plan.prod_pays(*(ctypes.c_int64(i) for i in (n, nnz, k))) != 0
-    assert pays(32_768, 32_768 * 128, 1_024) and not pays(32_767, 32_767 * 128, 1_024)         # in all
-    assert not pays(1 << 20, (1 << 20) * 128, 1_023) and pays(1 << 20, (1 << 20) * 128, 1_024)  # a row
-    assert not pays(1 << 30, 1 << 31, 64) and pays(1, 1 << 30, 4_096) and not pays(5, 0, 4_096)
+def test_dense_terms_are_products_where_rows_hold_enough_of_them(plan):
+    pays = lambda entries, n, k: plan.prod_pays(*(ctypes.c_int64(i) for i in (entries, n, k))) != 0
+    assert pays(18_000, 1_000, 1_000) and not pays(17_999, 1_000, 1_000)
+    assert pays(13 * 10 ** 9, 10 ** 9, 4_096) and not pays(256 * 10, 10, 32)   # all 256 terms in every row
+    assert not pays(0, 1, 4_096) and not pays(0, 10 ** 9, 10 ** 9)
+    may = lambda n, nnz, k: plan.prod_may(*(ctypes.c_int64(i) for i in (n, nnz, k))) != 0
+    assert may(10_000, 1 << 22, 1_024) and not may(10_000, (1 << 22) - 1, 1_024)   # in all
+    assert may(10 ** 6, 18 * 10 ** 6, 1_000) and not may(10 ** 6, 18 * 10 ** 6 - 1, 1_000)   # too few terms a row, dense or not
 
 
 def test_member_by_member_only_where_chains_are_short_and_sums_fit(plan):

@@ -909,7 +909,7 @@ sivf_status soft_bwd_reserve(sivf_ctx* ctx, const Csr& Xc, int32_t k, int attemp
     STCHK(ws(ctx, "dct_count", 4, &w.count));
     // the densest terms by matrix products: without a workspace cap, and only if
     // there is memory
-    if (ctx->opt.workspace_cap_bytes == 0 && p.whole && n > 0 && soft_prod_pays(n, Xc.nnz, k)) {
+    if (ctx->opt.workspace_cap_bytes == 0 && p.whole && n > 0 && soft_prod_may(n, Xc.nnz, k)) {
         const size_t room = (size_t)dct_cands(Xc.nnz, n);
         const int64_t last = nblk - (groups - 1) * p.blocks;   // blocks of the last group
         const size_t prod = (size_t)std::max(dct_prod_elems(p.rows, (int32_t)std::min<int64_t>(k, kp)),
@@ -955,7 +955,7 @@ sivf_status soft_bwd_run(sivf_ctx* ctx, const Csr& Xc, const float* C, int32_t k
         if (b.p.whole) STCHK(copy(0, n, 0, Xc.nnz));
         if (w.xd) {
             HIPCHK(ctx, fill_u64(w.ndense, 0ull, 2, s));
-            HIPCHK(ctx, dct_pick(n, d, b.colptr, w, s));
+            HIPCHK(ctx, dct_pick(n, d, k, b.colptr, w, s));
         }
     }
     for (int64_t j0 = 0; j0 < k && n > 0; j0 += gk) {   // columns j0 .. j0 + kg - 1

@@ -968,12 +968,22 @@ __global__ void k_dct_cands(int64_t N, int64_t d, const int64_t* __restrict__ co
     }
 }
 
-__global__ __launch_bounds__(1024) void k_dct_pick(int64_t room, DctWs w) {
+// the densest candidates, if their products pay
+__global__ __launch_bounds__(1024) void k_dct_pick(int64_t N, int32_t k, int64_t room, DctWs w) {
     __shared__ uint32_t sh[258];
     __shared__ uint32_t taken;
-    if (threadIdx.x == 0) taken = 0;
+    __shared__ unsigned long long entries;
+    if (threadIdx.x == 0) {
+        taken = 0;
+        entries = 0;
+    }
     const int64_t n = min(room, (int64_t)w.ndense[0]);
     const uint32_t x = top_weights(w.cand_df, n, kDctDense, sh);
+    each_weight(w.cand_df, n, [&](uint32_t v, int64_t i) {
+        if (i < n && v >= x) atomicAdd(&entries, (unsigned long long)v);
+    });
+    __syncthreads();
+    if (!soft_prod_pays((double)entries, (double)N, (double)k)) return;   // ndense[1] stays 0, all slots -1
     each_weight(w.cand_df, n, [&](uint32_t v, int64_t i) {
         if (i >= n || v < x) return;
         const uint32_t q = atomicAdd(&taken, 1u);   // any numbering gives the same sums
@@ -984,10 +994,10 @@ __global__ __launch_bounds__(1024) void k_dct_pick(int64_t room, DctWs w) {
     if (threadIdx.x == 0) w.ndense[1] = taken;
 }
 
-hipError_t dct_pick(int64_t N, int64_t d, const int64_t* colptr, DctWs w, hipStream_t s) {
+hipError_t dct_pick(int64_t N, int64_t d, int32_t k, const int64_t* colptr, DctWs w, hipStream_t s) {
     const int64_t room = dct_cands(w.nnz, N);
     hipLaunchKernelGGL(k_dct_cands, dim3((unsigned)((d + 255) / 256)), dim3(256), 0, s, N, d, colptr, room, w);
-    hipLaunchKernelGGL(k_dct_pick, dim3(1), dim3(1024), 0, s, room, w);
+    hipLaunchKernelGGL(k_dct_pick, dim3(1), dim3(1024), 0, s, N, k, room, w);
     return hipGetLastError();
 }
 

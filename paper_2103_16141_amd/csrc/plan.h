@@ -24,15 +24,18 @@ constexpr int64_t kMaxGroups = (1 << 24) - 1;
 // dense: 86.2 with 1024, 86.0 with 1536, 88.8 with 2048; k = 1,500, 12% dense
 // 19.7 and 15.4); denser 1024 (5,000,000 objects, 6% dense: 439, 460, 490).
 // FP32 files with many dense rows that no split walk will read: `heads` dense rows
-// (0: few, unknown, or read by a split walk) are read through L2 by the plain walk, and a wide
-// tile's no longer fit.  ms with 1024 and as wide as it gets, (rows, width):
-// (399, 2048) 3.9 and 3.7, (558, 2048) 3.5 and 3.7, (715, 2048) 3.4 and 4.2, (732,
-// 2048) 6.9 and 6.8, (1,076, 2048) 11.6 and 12.8; (1,264, 1536) 2.8 and 3.3,
-// (1,010, 1536) 6.1 and 5.2; 5 tiles: (278, 2048) 58.5 and 69.3, (214, 2048) 34.4
-// and 36.4, (250, 2048) 42.5 and 41.3; 3 tiles: (382, 1728) 25.5 and 26.0, (151,
-// 1728) 9.1 and 8.7; short rows (too short to be split) of a flat vocabulary: 9 tiles
-// (775, 1856) 25.5 and 38.1, 4 (1,910, 2048) 15.2 and 20.2, 2 (2,045, 2048) 7.4 and
-// 10.1.  Halving a tile of at most 1152 never pays.
+// (0: few, unknown, or read by a split walk) are read through L2 by the plain walk, and
+// a wide tile's no longer fit.  ms with 1024 and as wide as it gets, (rows, width):
+// one tile (357, 1856) 1.26 and 1.10, (589, 2048) 1.53 and 1.51, (632, 2048) 5.80 and
+// 5.94, (724, 1856) 5.75 and 5.85, (1,089, 2048) 14.7 and 16.6, (1,301, 2048) 12.2 and
+// 16.5; (1,036, 1600) 5.9 and 5.5, (1,304, 1600) 11.9 and 13.0; (1,250, 1344) 5.1 and
+// 4.6, (1,337, 1536) 10.1 and 10.0, (1,625, 1536) 2.7 and 3.6; (1,369, 1216) 10.1 and
+// 8.3, (2,701, 1216) 13.1 and 11.3.  Two tiles (380, 2048) 10.9 both, (652, 2048) 27.2
+// and 29.9, (1,201, 2048) 24.5 and 34.7; (819, 1664) 26.9 and 25.4, (1,233, 1664) 24.1
+// and 26.2; (882, 1536) 21.4 and 21.8, (1,243, 1536) 18.7 and 20.2; (755, 1088) 7.5 both,
+// (1,296, 1088) 15.4 and 16.8, (2,026, 1088) 5.0 and 7.7.  5 tiles: (278, 2048)
+// 58.5 and 69.3, (214, 2048) 34.4 and 36.4, (250, 2048) 42.5 and 41.3; 9: (775, 1856)
+// 25.5 and 38.1; 3 tiles: (382, 1728) 25.5 and 26.0, (151, 1728) 9.1 and 8.7.
 // BF16 files narrow for the same reason, later: in two tiles from 2,600 rows on
 // ((rows, width, D): 1,999, 1344, 30,000 9.44 with 1024 and 9.30 so; 2,725, 1536, 5,000
 // 12.5 and 12.7; 2,878, 1344, 150,000 14.5 and 14.2; 3,465, 1344, 30,000 5.15 and 5.61;
@@ -58,9 +61,11 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
         const int32_t narrow = width(kTileNarrow);
         auto slots = [k](int32_t w) { return ((int64_t)k + w - 1) / w * ((w + 511) / 512 * 512); };
         const bool two = k <= 2 * (int64_t)want;
-        if (bf16 ? want > kTileNarrow && want < k : want > 1152) {
-            const int64_t many = bf16 ? (two ? 2600 : slots(narrow) < slots(want) ? 500 : 1000)
-                                      : !two ? 260 : want > 1536 ? 480 : 1200;
+        if (want < k ? want > kTileNarrow : !bf16 && want > 1280) {
+            const int64_t many = bf16       ? (two ? 2600 : slots(narrow) < slots(want) ? 500 : 1000)
+                                 : !two     ? 260
+                                 : want < k ? (want > 1792 ? 480 : 1100)
+                                            : (want > 1728 ? 650 : want > 1536 ? 1200 : 1300);
             if (heads >= many) want = narrow;
         }
     }
@@ -192,16 +197,17 @@ inline bool soft_bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_
     return true;
 }
 
-// Whether dC of the densest terms is made by matrix products: from 2^32 nonzeros x k,
-// and from 2^17 per row.  A row of the matrix of dense terms costs 4 ns whatever k
-// is, its products 5 ps a column; what they save goes with a row's dense terms times
-// k.  Backward in ms without and with, 8.6e9 nonzeros x k: 40 terms a row k = 256
-// 8.25 and 10.41, 1,024 6.27 and 6.99, 3,000 7.32 and 7.55; 100 terms k = 256 6.61
-// and 7.41, 1,024 5.71 and 5.79, 1,536 5.93 and 5.93, 3,000 7.13 and 6.81; 200 terms
-// k = 512 6.18 and 6.13, 768 6.10 and 5.99, 2,048 6.53 and 6.13; 30 terms, k = 64,
-// 3,000,000 rows 14.4 and 28.5.
-inline bool soft_prod_pays(int64_t n, int64_t nnz, int64_t k) {
-    return nnz * k >= (int64_t)1 << 32 && (double)nnz * (double)k >= 131072.0 * (double)n;
+// Whether dC of the densest terms may be made by matrix products: in calls of 2^32
+// nonzeros x k.  Whether it is depends on their entries (at most all; the device knows
+// them): an entry costs 0.5 ps a column, a row of the matrix of dense terms 4 ns and its
+// products 5 ps a column.  Backward in ms without and with, 8.6e9 nonzeros x k, by dense terms a row:
+// 9 (40 terms, D = 20,000) k = 256 8.25 and 10.41, 1,024 6.27 and 6.99, 3,000 7.32 and
+// 7.55; 14 (100, 100,000) 256 6.61 and 7.41, 1,536 5.93 and 5.93, 3,000 7.13 and 6.81;
+// 41 (200, 30,000) 256 7.04 and 7.26, 512 6.18 and 6.13, 2,048 6.53 and 6.13; 52
+// (109, 2,281, 2.5e10) 922 14.6 and 11.9; 30 terms, k = 64, 3,000,000 rows 14.4 and 28.5.
+constexpr bool soft_prod_pays(double entries, double n, double k) { return entries * k >= n * (8000.0 + 10.0 * k); }
+inline bool soft_prod_may(int64_t n, int64_t nnz, int64_t k) {
+    return nnz * k >= (int64_t)1 << 32 && soft_prod_pays((double)nnz, (double)n, (double)k);
 }
 
 // A chunk of rows takes 5 B per nonzero and block for dX's shares (4) and dC's

@@ -70,7 +70,7 @@ constexpr int kDctDense = 256;
 int64_t dct_prod_elems(int64_t rows, int32_t k);
 inline int64_t dct_cands(int64_t nnz, int64_t rows) { return 32 * (nnz / std::max<int64_t>(rows, 1) + 1); }
 // the terms in at least 1/32 of N rows, at most kDctDense of them
-hipError_t dct_pick(int64_t N, int64_t d, const int64_t* colptr, DctWs w, hipStream_t s);
+hipError_t dct_pick(int64_t N, int64_t d, int32_t k, const int64_t* colptr, DctWs w, hipStream_t s);
 // rows [c0, c1) of the densest terms into w.xd
 hipError_t dct_dense_rows(int64_t c0, int64_t c1, const int64_t* rp, const int32_t* col, const float* xv, DctWs w,
                           int n_cu, hipStream_t s);

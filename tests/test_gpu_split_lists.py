@@ -223,17 +223,17 @@ def test_split_lists_in_several_pieces_of_objects_a_wave(n):
 
 
 def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
-    # a workspace cap keeps the walk plain; 480 dense rows and more are then read in tiles
+    # a workspace cap keeps the walk plain; 650 dense rows and more are then read in tiles
     # of 1,024 from the second update on, and every step is that of fixed tiles
     from tests.test_gpu_kernel_edges import _striped
     from paper_2103_16141_amd.api import Context
     log("capped tiles")
-    n, d, lam, k, dev = 8_195, 2_000, 500, 2_048, device()
+    n, d, lam, k, dev = 8_195, 2_800, 700, 2_048, device()
     X = _striped(n, d, lam, 4, torch.float32)
     ids = np.random.default_rng(2).choice(n, k, replace=False).astype(np.int32)
     state = []
     for kt, cap in ((0, 1 << 40), (512, 1 << 40), (0, 0)):
-        ctx = Context(0, k_tile=kt, workspace_cap_bytes=cap, head_density=0.55)
+        ctx = Context(0, k_tile=kt, workspace_cap_bytes=cap, head_density=0.5)
         state.append([ctx, ctx.init_centroids(X, k, ids), torch.zeros(n, dtype=torch.int32, device=dev),
                       torch.zeros(n, dtype=torch.float32, device=dev), torch.zeros(k, dtype=torch.uint8, device=dev)])
     widths = []
@@ -245,7 +245,7 @@ def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
             assert all(s[q] == st[0][q] for q in ("multadds", "moved", "icp_objects", "n_invariant", "head_rows"))
         for ctx, f, a, own, l in state:
             ctx.update(X, a, l, f)
-    assert st[0]["head_rows"] >= 480
+    assert st[0]["head_rows"] >= 650
     assert widths == [[2048, 512, 2048], [2048, 512, 2048], [1024, 512, 2048], [1024, 512, 2048]]
     # the file made without a cap narrows when a capped ctx updates it
     ctx, f, a, own, l = state[2]
@@ -257,7 +257,7 @@ def test_tiles_of_a_capped_file_narrow_once_it_has_many_dense_rows():
 
 @pytest.mark.parametrize("k,lam,wide,narrow,rows_from,options", [
     (2_100, 1_500, 1_088, 704, 2_600, dict(posting_dtype="bf16")),
-    (2_048, 30, 2_048, 1_024, 480, dict(head_density=0.02)),   # rows too short for the split walk
+    (2_048, 30, 2_048, 1_024, 650, dict(head_density=0.02)),   # rows too short for the split walk
     (4_000, 30, 2_048, 1_024, 480, dict(head_density=0.01, filter_mode="cbicp")),
 ])
 def test_tiles_narrow_once_many_dense_rows_are_walked_as_they_are(k, lam, wide, narrow, rows_from, options):

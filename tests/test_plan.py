@@ -70,9 +70,10 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
                         kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000, heads)
                         assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt
     width = lambda k, heads: tiles(0, 0, k, 0.0, 1000, heads)[0]
-    assert [width(2048, h) for h in (0, 479, 480)] == [2048, 2048, 1024]
-    assert [width(1500, h) for h in (0, 1199, 1200)] == [1536, 1536, 768]
-    assert [width(10_000, h) for h in (259, 260)] == [2048, 1024] and width(1100, 10 ** 6) == 1152
+    assert [width(2048, h) for h in (0, 649, 650)] == [2048, 2048, 1024]
+    assert [width(1600, h) for h in (1199, 1200)] == [1600, 832] and [width(1500, h) for h in (1299, 1300)] == [1536, 768]
+    assert [width(4000, h) for h in (479, 480)] == [2048, 1024] and [width(2500, h) for h in (1099, 1100)] == [1280, 896]
+    assert [width(10_000, h) for h in (259, 260)] == [2048, 1024] and width(1280, 10 ** 6) == 1280
     bf16 = lambda k, heads: tiles(0, 1, k, 0.02 * k * 1000, 1000, heads)[0]
     assert [bf16(3072, h) for h in (2599, 2600)] == [1536, 1024] and bf16(2100, 2600) == 704
     assert [bf16(4000, h) for h in (499, 500)] == [1344, 1024]     # 4,608 and 4,096 slots

@@ -299,3 +299,45 @@ def test_update_of_clusters_summed_member_by_member(d, long, dtype, signed):
         a = np.roll(a, 1)
     ivf.free()
     ctx.close()
+
+
+@pytest.mark.parametrize("terms", [1, 3, 4, 8_191, 8_192, 8_193, 16_385, 20_000])
+def test_exact_similarity_to_centroids_of_many_terms(terms):
+    # the search for an object's terms among a centroid's: by quarters, from 8,192
+    # terms on by halves; objects of the centroid's first and last terms, of terms
+    # between and beside them, and of all kinds; the FP64 fold in ascending order
+    from paper_2103_16141_amd.api import DeviceCsr
+    log("exact similarity, %d terms" % terms)
+    d = 20_000
+    rng = np.random.default_rng(terms)
+    have = np.sort(rng.choice(d, terms, replace=False)).astype(np.int32)
+    lack = np.setdiff1d(np.arange(d, dtype=np.int32), have)
+    u = rng.random(terms) + 0.1
+    u /= np.sqrt((u * u).sum())
+    rows = [have[:40], have[-40:], np.concatenate([have[:1], have[-1:]]), lack[:50], lack[-50:]]
+    rows += [np.unique(rng.choice(d, 150)) for _ in range(200)]
+    rows += [np.unique(np.concatenate([rng.choice(have, min(terms, 60)), rng.choice(d, 20)])) for _ in range(200)]
+    rows = [np.unique(r).astype(np.int32) for r in rows if len(r)]
+    vals = [(rng.random(len(r)) + 0.1).astype(np.float32) for r in rows]
+    vals = [(v / np.sqrt((v.astype(np.float64) ** 2).sum())).astype(np.float32) for v in vals]
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    X = DeviceCsr.from_numpy(rp, np.concatenate(rows), np.concatenate(vals), d)
+    C = DeviceCsr.from_numpy(np.array([0, terms, 2 * terms], np.int64), np.concatenate([have, have]),
+                             np.concatenate([u, u]), d)
+    dense = np.zeros(d)
+    dense[have] = u
+    in_c = np.zeros(d, bool)
+    in_c[have] = True
+    want = []
+    for r, v in zip(rows, vals):
+        acc = 0.0
+        for t, x in zip(r, v):
+            if in_c[t]:
+                acc = acc + float(x) * dense[t]
+        want.append(acc)
+    ctx = _ctx()
+    a = torch.zeros(len(rows), dtype=torch.int32, device=device())
+    f, own, _ = ctx.resume(X, C, a, a)
+    assert np.array_equal(own.cpu().numpy(), np.array(want).astype(np.float32))
+    f.free()
+    ctx.close()

@@ -327,11 +327,14 @@ __device__ inline uint32_t head_terms(const WalkArgs& A, float* sim, unsigned lo
 // time, look each up in the centroid's sorted term list, and the wave then folds
 // the products sequentially in ascending term order.  Bound by the search's
 // chain of loads: quarters instead of halves, and twice the waves, 200,000
-// objects against 2,000 centroids 0.84 -> 0.56 ms.  Centroids of many terms are
-// bound by the probes' misses, of which quarters make half as many again: from
-// 8,192 terms on halves, relaxed step of 600,000 objects, k = 1,000, 80,000 terms
-// 13.2 -> 12.3 ms, k = 225, 10,000 terms 7.19 -> 6.77; 2,300 terms 3.88, by halves 3.99.
-constexpr int kHalves = 8192;
+// objects against 2,000 centroids 0.84 -> 0.56 ms.  Where all objects look for their
+// own centroid, those of many terms (from HALVES on, kHalves or never) are bound by
+// the probes' misses, of which quarters make half as many again: relaxed step of
+// 600,000 objects, k = 1,000, 80,000 terms 13.2 ms, by halves 12.3; k = 225, 10,000
+// terms 7.19 and 6.77; 2,300 terms 3.88 and 3.99.  Candidates are few at a time:
+// 807,292 objects, k = 63, 45,000 terms 10.7 and 11.4.
+constexpr int kHalves = 8192, kNever = INT32_MAX;
+template <int HALVES>
 __device__ double exact_rho(const WalkArgs& A, const Store& st, int64_t r0, int n, int32_t j) {
     const int lane = threadIdx.x & 63;
     const int64_t cs = st.start[j];
@@ -346,7 +349,7 @@ __device__ double exact_rho(const WalkArgs& A, const Store& st, int64_t r0, int 
             const int32_t t = A.col[r0 + h];
             // the first entry not below t is in [lo, lo + len]
             int lo = 0, len = cm;
-            while (cm >= kHalves && len > 0) {
+            while (cm >= HALVES && len > 0) {
                 const int half = len >> 1;
                 const bool up = term[lo + half] < t;
                 lo = up ? lo + half + 1 : lo;
@@ -443,7 +446,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BF16 ? 6 : 
                 // own centroid did not decrease -> moving centroids only
                 if (A.relaxed && A.icp_on && !icp) {
                     if (tb == 0) {
-                        const double rn = exact_rho(A, A.st, r0, n, a_old);
+                        const double rn = exact_rho<kHalves>(A, A.st, r0, n, a_old);
                         rel = rn >= A.own64_prev[i];
                         if (lane == 0) {
                             A.own64_cur[i] = rn;
@@ -922,7 +925,7 @@ __global__ __launch_bounds__(256) void k_walk_count(WalkArgs A) {
             const int32_t a_old = A.a_prev[i];
             icp = A.lam[a_old] != 0;
             if (A.relaxed && !icp) {
-                const double rn = exact_rho(A, A.st, r0, n, a_old);
+                const double rn = exact_rho<kHalves>(A, A.st, r0, n, a_old);
                 rel = rn >= A.own64_prev[i];
                 if (lane == 0) A.own64_cur[i] = rn;
             }
@@ -1152,7 +1155,7 @@ __global__ __launch_bounds__(256) void k_rescore_cand(WalkArgs A, Store st) {
         int32_t bj = 0x7fffffff;
         for (int c = 0; c < nc; ++c) {
             const int32_t j = A.qcand[slot * kCandCap + c];
-            const double r = exact_rho(A, st, r0, n, j);
+            const double r = exact_rho<kNever>(A, st, r0, n, j);
             if (r > best || (r == best && j < bj)) {
                 best = r;
                 bj = j;
@@ -1197,7 +1200,7 @@ __global__ __launch_bounds__(64) void k_rescore_full(WalkArgs A, const double* _
         double best = -INFINITY;
         int32_t bj = 0x7fffffff;
         if (icp) {
-            best = exact_rho(A, st, r0, n, a_old);
+            best = exact_rho<kNever>(A, st, r0, n, a_old);
             bj = a_old;
         }
         for (int tile = 0; tile < A.T; ++tile) {
@@ -1379,7 +1382,7 @@ __global__ __launch_bounds__(256) void k_own64_exact(WalkArgs A, double* __restr
     for (int64_t q = wave; q < nq; q += nw) {
         const int32_t i = queue[q];
         const int64_t r0 = A.rp[i];
-        const double r = exact_rho(A, A.st, r0, (int)(A.rp[i + 1] - r0), A.a_new[i]);
+        const double r = exact_rho<kHalves>(A, A.st, r0, (int)(A.rp[i + 1] - r0), A.a_new[i]);
         if (lane == 0) own64[i] = r;
     }
 }
@@ -1411,7 +1414,7 @@ __global__ __launch_bounds__(256) void k_objective64(WalkArgs A, Store st, const
     double acc = 0.0;
     for (int64_t i = wave; i < A.n; i += nw) {
         const int64_t r0 = A.rp[i];
-        const double r = exact_rho(A, st, r0, (int)(A.rp[i + 1] - r0), assign[i]);
+        const double r = exact_rho<kHalves>(A, st, r0, (int)(A.rp[i + 1] - r0), assign[i]);
         acc = acc + r;
     }
     if (lane == 0) sh[wid] = acc;
@@ -1472,7 +1475,7 @@ __global__ __launch_bounds__(256) void k_resume_own(WalkArgs A, Store st, const 
     for (int64_t i = wave; i < A.n; i += nw) {
         const int64_t r0 = A.rp[i];
         const int32_t j = assign[i];
-        const double r = exact_rho(A, st, r0, (int)(A.rp[i + 1] - r0), j);
+        const double r = exact_rho<kHalves>(A, st, r0, (int)(A.rp[i + 1] - r0), j);
         if (lane == 0) {
             own32[i] = (float)r;
             if (own64) own64[i] = lam[j] ? r : INFINITY;

@@ -494,7 +494,7 @@ sivf_status new_file(sivf_ctx* ctx, int32_t k, int64_t d, sivf_ivf** out) {
     f->pdt = ctx->opt.posting_dtype;
     f->k_tile = ctx->opt.k_tile;
     // arrays for the most tiles the file may come to have
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, INT64_MAX, &f->kt, &f->T);
+    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, k, INFINITY, d, INT64_MAX, INFINITY, &f->kt, &f->T);
     f->T_max = f->T;
     const size_t kk = (size_t)k, dd = (size_t)d, dt = (size_t)(d * f->T);
     const size_t hd = ctx->opt.head_density > 0.0f ? dd : 0, sd = split_possible(ctx->opt) ? dd : 0;
@@ -524,11 +524,20 @@ sivf_status restructure(sivf_ctx* ctx, sivf_ivf* f, bool norms, double postings,
     // the tiles follow from the options the file was made with: a ctx with others
     // may update it, and its arrays have room for T_max tiles
     int32_t kt = 0, T = 0;
-    choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, 0, &kt, &T);
-    // rows that X will walk as they are (both taken to be what the file had so far)
-    const bool split_X = f->pdt == SIVF_F32 && split_possible(ctx->opt) &&
-                         (!X || X->n < 1 || split_pays(f->sfrac * X->nnz / X->n, X->n, f->k, T));
-    if (!split_X) choose_tiles(f->k_tile, f->pdt == SIVF_BF16, f->k, postings, f->d, f->H, &kt, &T);
+    const bool bf16 = f->pdt == SIVF_BF16;
+    choose_tiles(f->k_tile, bf16, f->k, postings, f->d, 0, 0.0, &kt, &T);
+    if (X && X->n > 0) {
+        // rows that X will walk as they are, some tiles a launch (the rows and the split
+        // walk's share taken to be what the file had so far)
+        const double terms = (double)X->nnz / (double)X->n;
+        int32_t kt2 = 0, T2 = 0;
+        choose_tiles(f->k_tile, bf16, f->k, postings, f->d, f->H, terms, &kt2, &T2);
+        const bool split_X = !bf16 && split_possible(ctx->opt) && split_pays(f->sfrac * terms, X->n, f->k, T);
+        if (!split_X && ctx->opt.tiles_per_launch < T2) {
+            kt = kt2;
+            T = T2;
+        }
+    }
     f->built = false;   // until every array below is whole again
     if (T > f->T_max) return fail(ctx, SIVF_E_HIP, "internal: %d tiles in a file made for %d", T, f->T_max);
     f->kt = kt;

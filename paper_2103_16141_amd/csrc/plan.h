@@ -36,17 +36,23 @@ constexpr int64_t kMaxGroups = (1 << 24) - 1;
 // (1,296, 1088) 15.4 and 16.8, (2,026, 1088) 5.0 and 7.7.  5 tiles: (278, 2048)
 // 58.5 and 69.3, (214, 2048) 34.4 and 36.4, (250, 2048) 42.5 and 41.3; 9: (775, 1856)
 // 25.5 and 38.1; 3 tiles: (382, 1728) 25.5 and 26.0, (151, 1728) 9.1 and 8.7.
+// The lines hold for 30 terms a row and more (`terms`); shorter rows read fewer of the
+// rows for the same work per tile: 17 terms (608, 2048) 2.03 and 1.96, (1,276, 2048) 5.1
+// and 5.9, (1,827, 1472) 4.6 and 4.3, (2,881, 1472) 4.9 and 6.1, 3 tiles (316, 1600) 12.5
+// and 10.7; 11 terms (880, 2048) 5.8 and 5.2, (1,321, 1472) 5.2 and 3.8.
 // BF16 files narrow for the same reason, later: in two tiles from 2,600 rows on
 // ((rows, width, D): 1,999, 1344, 30,000 9.44 with 1024 and 9.30 so; 2,725, 1536, 5,000
 // 12.5 and 12.7; 2,878, 1344, 150,000 14.5 and 14.2; 3,465, 1344, 30,000 5.15 and 5.61;
 // 4,285, 1536, 30,000 10.3 and 11.8), in more from 1,000 (967, 1536 39.2 and 39.2; 518,
-// 1536 56.4 and 53.1; 1,221, 2048 19.2 and 20.0), or from 500 if the narrow tiles' rows,
+// 1536 56.4 and 53.1; 1,221, 2048 19.2 and 20.0), from 800 if the narrow tiles' rows,
 // which come in 512s, are shorter in all (431, 1344 4.81 and 4.84; 583, 1344 37.7 and
-// 39.5; 831, 1344 37.7 and 40.3; 1,815, 1344 19.5 and 20.9).
+// 39.5; 831, 1344 37.7 and 40.3; 1,815, 1344 19.5 and 20.9), from 2,600 if longer (1,275,
+// 1472 19.7 and 18.3); for 60 terms a row and more: 17 terms (1,244, 1216) 10.7 and 10.4,
+// 25 (1,460, 1216) 9.0 and 9.2, 40 (2,620, 1216) 12.5 and 13.9.
 // More postings or dense rows never give fewer tiles: a file's arrays are made for
 // infinitely many.
-inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, int64_t d, int64_t heads, int32_t* kt,
-                         int32_t* T) {
+inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, int64_t d, int64_t heads, double terms,
+                         int32_t* kt, int32_t* T) {
     int32_t want = k_tile;
     if (want <= 0) {
         const double density = postings / ((double)k * (double)d);
@@ -62,11 +68,12 @@ inline void choose_tiles(int32_t k_tile, bool bf16, int32_t k, double postings, 
         auto slots = [k](int32_t w) { return ((int64_t)k + w - 1) / w * ((w + 511) / 512 * 512); };
         const bool two = k <= 2 * (int64_t)want;
         if (want < k ? want > kTileNarrow : !bf16 && want > 1280) {
-            const int64_t many = bf16       ? (two ? 2600 : slots(narrow) < slots(want) ? 500 : 1000)
+            const int64_t less = slots(want) - slots(narrow);
+            const int64_t many = bf16       ? (two || less < 0 ? 2600 : less > 0 ? 800 : 1000)
                                  : !two     ? 260
                                  : want < k ? (want > 1792 ? 480 : 1100)
                                             : (want > 1728 ? 650 : want > 1536 ? 1200 : 1300);
-            if (heads >= many) want = narrow;
+            if ((double)heads * std::min(1.0, terms / (bf16 ? 60.0 : 30.0)) >= (double)many) want = narrow;
         }
     }
     *kt = want;

@@ -12,8 +12,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HARNESS = r"""
 #include "plan.h"
 extern "C" {
-void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int64_t heads, int32_t* kt, int32_t* T) {
-    sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, heads, kt, T);
+void tiles(int32_t k_tile, int bf16, int32_t k, double postings, int64_t d, int64_t heads, double terms, int32_t* kt,
+           int32_t* T) {
+    sivf::choose_tiles(k_tile, bf16 != 0, k, postings, d, heads, terms, kt, T);
 }
 int bwd_plan(int attempt, int64_t n, int64_t nnz, int64_t d, int64_t nblk, int64_t* rows, int64_t* blocks, int* whole) {
     sivf::SoftPlan p;
@@ -52,9 +53,9 @@ def plan(tmp_path_factory):
 def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
     # a file's arrays are allocated for infinitely many postings; an update
     # chooses the tiles again for the postings it expects
-    def tiles(k_tile, bf16, k, postings, d, heads):
+    def tiles(k_tile, bf16, k, postings, d, heads, terms=60.0):
         kt, T = ctypes.c_int32(), ctypes.c_int32()
-        plan.tiles(k_tile, bf16, k, ctypes.c_double(postings), ctypes.c_int64(d), ctypes.c_int64(heads), ctypes.byref(kt),
+        plan.tiles(k_tile, bf16, k, ctypes.c_double(postings), ctypes.c_int64(d), ctypes.c_int64(heads), ctypes.c_double(terms), ctypes.byref(kt),
                    ctypes.byref(T))
         return kt.value, T.value
 
@@ -65,19 +66,23 @@ def test_no_number_of_postings_gives_more_tiles_than_a_file_is_made_for(plan):
         for bf16 in (0, 1):
             for k_tile in (0, 64, 128, 4096):
                 for heads in (0, 200, 300, 500, 700, 1000, 1200, 2600, 2 ** 63 - 1):
-                    _, most = tiles(k_tile, bf16, k, float("inf"), 1000, 2 ** 63 - 1 if heads else 0)
+                    _, most = tiles(k_tile, bf16, k, float("inf"), 1000, 2 ** 63 - 1 if heads else 0, float("inf"))
                     for density in (0.0, 0.002, 0.004, 0.03, 0.04, 1.0):
                         kt, T = tiles(k_tile, bf16, k, density * k * 1000, 1000, heads)
                         assert T <= most and kt % 64 == 0 and 64 <= kt <= 4096 and (T - 1) * kt < k <= T * kt
-    width = lambda k, heads: tiles(0, 0, k, 0.0, 1000, heads)[0]
+    width = lambda k, heads: tiles(0, 0, k, 0.0, 1000, heads, 30.0)[0]
     assert [width(2048, h) for h in (0, 649, 650)] == [2048, 2048, 1024]
     assert [width(1600, h) for h in (1199, 1200)] == [1600, 832] and [width(1500, h) for h in (1299, 1300)] == [1536, 768]
     assert [width(4000, h) for h in (479, 480)] == [2048, 1024] and [width(2500, h) for h in (1099, 1100)] == [1280, 896]
     assert [width(10_000, h) for h in (259, 260)] == [2048, 1024] and width(1280, 10 ** 6) == 1280
     bf16 = lambda k, heads: tiles(0, 1, k, 0.02 * k * 1000, 1000, heads)[0]
     assert [bf16(3072, h) for h in (2599, 2600)] == [1536, 1024] and bf16(2100, 2600) == 704
-    assert [bf16(4000, h) for h in (499, 500)] == [1344, 1024]     # 4,608 and 4,096 slots
+    assert [bf16(4000, h) for h in (799, 800)] == [1344, 1024]     # 4,608 and 4,096 slots
     assert [bf16(12_288, h) for h in (999, 1000)] == [1536, 1024]   # 12,288 both
+    assert [bf16(7319, h) for h in (2599, 2600)] == [1472, 960]     # 7,680 and 8,192
+    # shorter rows, later
+    assert [tiles(0, 0, 2048, 0.0, 1000, h, 15.0)[0] for h in (1299, 1300)] == [2048, 1024]
+    assert [tiles(0, 1, 4000, 80_000.0, 1000, h, 15.0)[0] for h in (3199, 3200)] == [1344, 1024]
     assert bf16(1536, 10 ** 6) == 1536 and bf16(2048, 10 ** 6) == 1024
 
 

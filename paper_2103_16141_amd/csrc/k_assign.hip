@@ -866,7 +866,7 @@ hipError_t walk_fast(const WalkArgs& a, double terms, int pdt_bf16, int grid_wav
     // 100, 260 (8 waves of 8 objects) -> 22 us; 10,000 271 -> 65 us; 20,011 objects, k
     // = 1,531, BF16 842 -> 346 us.
     const int64_t waves = (int64_t)blocks * kWalkWaves;
-    const bool shared = walk_shared(a.n, waves, terms, a.kt, a.S != nullptr);
+    const bool shared = walk_shared(a.n, waves, terms, a.kt, te - tb, a.S != nullptr);
     int share = (int)walk_grab(a.n, waves);
     if (shared) {
         const int64_t pieces = std::max<int64_t>(1, (a.n + 8 * waves - 1) / (8 * waves));   // a wave's

@@ -100,26 +100,25 @@ inline int64_t upd_members(int64_t n, int64_t nnz, int64_t d, int64_t k) {
     return d <= 8192 && nnz > 4096 * k && 2 * chain * k >= 3 * n ? std::min(2 * n / k, chain) : 0;
 }
 
-// Whether the waves of a walk take equal shares of n objects instead, of `terms`
-// terms on average (split: of the listed ones).  A grab costs 15 ns, one after the
-// other for all waves: 22,000 of them (44,000 objects by twos) hold a walk that
-// could be done in 80 us to 340.  But the heavier an object, the more uneven the
-// shares, and the less the counter shows: the line is where the objects of a grab
-// take about as long as the grab itself, by an estimate that fits these.  Walk in us by
-// grabs and in equal shares, FP32, 60 terms an object: 60,000 objects (12 a wave,
-// by twos) k = 1 435 and 97, 100 479 and 390, 300 515 and 465, 2,048 654 and 724;
-// 100,000 (by fours) k = 16 430 and 390, 100 630 and 655; 100 terms, 55,000 objects,
-// k = 500 564 and 620; 131 terms over a wide vocabulary, 42,569 objects, k = 242 757
-// and 854; 273 terms, 88,424 objects, k = 1 1,960 and 2,210.  Lists of a split walk,
-// 100 terms, about 45 listed: 55,000 objects, k = 500 721 and 508, k = 2,000 1,200
-// and 1,216; 70,000, k = 1,000 993 and 958; 100,000, k = 500 914 and 770, k = 1,000
-// 1,281 and 1,324.
-// Over 780 walks of three vocabularies, 45,000 to 115,000 objects of 20 to 130 terms, k
-// = 16 to 800, no other line loses less: 3% on average to the better way of each.
-inline bool walk_shared(int64_t n, int64_t waves, double terms, int32_t kt, bool split) {
+// Whether the waves of a walk of `tiles` tiles take equal shares of n objects instead,
+// of `terms` terms on average (split: of the listed ones).  A grab costs 15 ns, one
+// after the other for all waves: 22,000 of them (44,000 objects by twos) hold a walk
+// that could be done in 80 us to 340.  But the heavier an object, the more uneven the
+// shares, and the less the counter shows: the line is where the objects of a grab take
+// about as long as the grab itself, by an estimate that fits these.  Walk in us by grabs
+// and in equal shares, FP32, 60 terms an object: 60,000 objects (12 a wave, by twos) k =
+// 1 435 and 97, 100 479 and 390, 300 515 and 465, 2,048 654 and 724; 100,000 (by fours)
+// k = 16 430 and 390, 100 630 and 655; 100 terms, 55,000 objects, k = 500 564 and 620;
+// 131 terms over a wide vocabulary, 42,569 objects, k = 242 757 and 854; 273 terms,
+// 88,424 objects, k = 1 1,960 and 2,210.  Lists of a split walk, 100 terms, about 45 listed: 55,000
+// objects, k = 500 721 and 508, k = 2,000 1,200 and 1,216; 70,000, k = 1,000 993 and 958;
+// 100,000, k = 500 914 and 770, k = 1,000 1,281 and 1,324.  Over 1,940 walks of four
+// vocabularies, 30,000 to 115,000 objects of 5 to 130 terms, k = 16 to 4,000, it loses
+// 1.7% on average to the better way of each (worst: two light tiles a launch, 14%).
+inline bool walk_shared(int64_t n, int64_t waves, double terms, int32_t kt, int tiles, bool split) {
     if (n <= 8 * waves) return true;
     if (n > 24 * waves) return false;
-    const double object = terms * (0.065 + (split ? 0.000045 : 0.00009) * kt);   // ns of the whole chip
+    const double object = terms * (0.065 + (split ? 0.000045 : 0.00009) * kt) * tiles;   // ns of the whole chip
     return object * (double)walk_grab(n, waves) <= 17.0;
 }
 

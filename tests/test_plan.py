@@ -29,8 +29,8 @@ int prod_may(int64_t n, int64_t nnz, int64_t k) { return sivf::soft_prod_may(n, 
 int prod_pays(int64_t entries, int64_t n, int64_t k) { return sivf::soft_prod_pays(entries, n, k); }
 int64_t members(int64_t n, int64_t nnz, int64_t d, int64_t k) { return sivf::upd_members(n, nnz, d, k); }
 int64_t bwd_blocks(int64_t blocks, int64_t nnz_max) { return sivf::soft_bwd_blocks(blocks, nnz_max); }
-int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split) {
-    return sivf::walk_shared(n, waves, terms, kt, split != 0);
+int shared(int64_t n, int64_t waves, double terms, int32_t kt, int split, int tiles) {
+    return sivf::walk_shared(n, waves, terms, kt, tiles, split != 0);
 }
 typedef int64_t (*fn)(int64_t);
 int64_t split(int64_t most, fn pays, fn longest, int64_t* pairs) {
@@ -147,12 +147,13 @@ def test_soft_backward_plans_shrink_to_less_than_eight_shares_took(plan):
 
 
 def test_equal_shares_reach_further_for_lighter_walks(plan):
-    def shared(n, terms, kt, split=0, waves=5_120):
-        return plan.shared(ctypes.c_int64(n), ctypes.c_int64(waves), ctypes.c_double(terms), kt, split)
+    def shared(n, terms, kt, split=0, waves=5_120, tiles=1):
+        return plan.shared(ctypes.c_int64(n), ctypes.c_int64(waves), ctypes.c_double(terms), kt, split, tiles)
 
     assert shared(1, 1e6, 4096) and shared(40_960, 1e6, 4096)            # up to 8 objects a wave whatever they cost
     assert not shared(122_881, 0, 64) and not shared(122_881, 0, 64, 1)  # never beyond 24
     assert [shared(60_000, 60, kt) for kt in (64, 128, 320, 1024)] == [1, 1, 1, 0]
+    assert shared(60_000, 60, 128, tiles=1) and not shared(60_000, 60, 128, tiles=2)
     assert [shared(100_000, 60, kt) for kt in (64, 128)] == [1, 0]
     assert not shared(55_000, 100, 512) and not shared(42_569, 131, 256) and not shared(88_424, 273, 64, waves=6_144)
     assert [shared(55_000, 45, kt, 1) for kt in (512, 1024)] == [1, 1] and not shared(55_000, 45, 2048, 1, waves=4_096)
